@@ -50,14 +50,14 @@ def gemv_traffic_key(cfg, elem):
 # algorithmic flops per quadrature-point pair of the regular tiles, counting
 # add/mul/rsqrt/exp as 1 and FMA as 2: Laplace V and K 37, Yukawa 46
 FLOPS_QP = {"laplace": 37, "yukawa": 46}
-# the same for the matrix-free apply's k_mf_pot (one potential pair per
-# quadrature pair): 3 sub, 5 for r^2, rsqrt, 2 mul r^-3, 2 FMA for the two
-# strength sums = 15, plus the per-target-point normal distance and FP64
-# accumulation (11 flops over the 6 source points) = 17; Yukawa forms the
-# double-layer factor as e r^-1 r^-1 (r^-1 + kappa) instead of r^-3: r = r^2
-# r^-1, the exponent (2 mul), exp, e r^-1, then add + 2 mul, in place of the
-# 2 mul of r^-3 = +6
-MF_FLOPS_QP = {"laplace": 17, "yukawa": 23}
+# the same for the matrix-free apply's k_mf_tile, which evaluates each
+# unordered quadrature pair once for both directions: 3 sub, 5 for r^2, rsqrt,
+# 2 mul r^-3, 4 FMA for the strength sums of both directions = 19, plus the
+# normal distances and the accumulation over triangles (120 flops per 36
+# pairs) = 22; Yukawa forms the double-layer factor as e r^-1 r^-1
+# (r^-1 + kappa) instead of r^-3: r, the exponent, exp, e r^-1, then add and
+# 2 mul in place of the 2 mul of r^-3 = +5
+MF_FLOPS_QP = {"laplace": 22, "yukawa": 27}
 FP64_PEAK_TFLOPS = 78.6
 FP32_PEAK_TFLOPS = 157.3
 
@@ -689,8 +689,8 @@ def side_legs(pb, torch, pbgen, args, out):
         side["omega_root_finders_fp64"] = om
     if not args.no_matrix_free:
         # nothing dense stored: every coupled apply evaluates the regular
-        # quadrature-point pairs of both interfaces again (k_mf_pot)
-        mf_flops = 36 * (MF_FLOPS_QP["laplace"] * regular_pairs(prob.tri_m) +
+        # quadrature-point pairs of both interfaces again, each unordered pair once (k_mf_tile)
+        mf_flops = 18 * (MF_FLOPS_QP["laplace"] * regular_pairs(prob.tri_m) +
                          MF_FLOPS_QP["yukawa" if prob.kappa > 0 else "laplace"] * regular_pairs(prob.tri_s))
         mf = {}
         for name, prec, peak in (("fp64", pb.FP64, FP64_PEAK_TFLOPS), ("mixed_fp32_eval", pb.MIXED, FP32_PEAK_TFLOPS)):
