@@ -12,14 +12,26 @@
 //
 // Per-instance state machine (P^-1 the right preconditioner):
 //   INIT  -> w = b, V_0 = b/|b|, target = tol |b|              -> ARN (or DONE if b = 0)
-//   ARN   -> z = P^-1 V_j, w = J z, CGS2, V_{j+1}, Givens       -> UPD at convergence/restart/limit
-//   UPD   -> y = H^{-1} g, t = V y                               -> RES
+//   ARN   -> z = P^-1 V_j, w = J z, CGS2, V_{j+1}, Givens       -> ARN; at convergence, restart
+//            or limit y = H^{-1} g, t = V y                     -> RES (FIN: see GSt)
 //   RES   -> x += P^-1 t, w = b - J x, beta = |w|: beta <= target -> DONE, else V_0 = w/beta -> ARN
+//   FIN   -> x += P^-1 t                                        -> DONE
 // which is the restarted GMRES of the oracle (true residual at every restart).
 // P^-1 is either the inverse diagonal of J or the block preconditioner:
 // Jacobi-scaled Chebyshev terms on the FEM block (one SpMV launch per term
-// after the first) and a sparse approximate inverse on each single-layer
+// after the first two) and a sparse approximate inverse on each single-layer
 // block.
+//
+// One Krylov step of the batch is k_bfirst (approximate inverse, the first
+// two Chebyshev terms), k_bcheb per further term, k_bgemv, k_btail (second
+// stage of the dense product and the FEM SpMV), k_bmdot, k_bmid, k_bend (the
+// two Gram-Schmidt passes), k_bcontrol and k_bnext: 8 + (terms - 2) launches.
+// A launch of a few hundred workgroups takes 2-4 us however little it does,
+// so below about 20k triangles a step's time is its launch count; every
+// kernel here therefore takes the neighbouring small passes in (the packing
+// of the dense input into the last Chebyshev term, the coefficient sums into
+// the pass that uses them, the norm into control, the scaling and t = V y
+// into one).
 //
 // Mixed precision may store the basis in FP32 (products, projections, norms,
 // Hessenberg, rotations, w and x stay FP64).  A restart cycle is then an
@@ -28,6 +40,9 @@
 // iterative refinement: the tolerance is always decided on that residual.
 #include <algorithm>
 #include <cmath>
+#include <cstring>
+#include <initializer_list>
+#include <thread>
 
 #include "gemv_rows.hpp"
 #include "pbfb_internal.hpp"
@@ -48,9 +63,11 @@ struct GDesc {
     void *symP[2]; // FP64 column partials
     const int32_t *dl_ptr[2], *dl_col[2];
     const double *dl_val[2];
-    // packing maps: operator index -> FEM node, and -> surface vertex (Morton
-    // vertex order of the stored operators; matrix-free: ascending, mv null)
-    const int32_t *gm, *gs, *mvm, *mvs;
+    // operator index -> surface vertex (Morton vertex order of the stored
+    // operators; matrix-free: ascending, null)
+    const int32_t *mvm, *mvs;
+    // FEM node -> surface vertex and surface vertex -> operator index (null: the same), per surface
+    const int32_t *nvert[2], *minv[2];
     const int32_t *sptr, *col; // FEM rows, sliced ELL
     const void *val;
     int64_t nn, n;
@@ -58,9 +75,8 @@ struct GDesc {
     void *V; // (m + 1) x n basis, FP64 or FP32 (vf32)
     double *w, *xm, *xs, *x;
     const double *b;
-    double *H, *cs, *sn, *g, *y, *h1, *h2, *part, *npart, *nrm;
-    int *cnt; // completion counter of the x update (index 257)
-    int64_t nch, nchb;
+    double *H, *cs, *sn, *g, *y, *h1, *h2, *part, *part2, *npart, *nrm;
+    int64_t chb, nchb; // rows per Gram-Schmidt chunk, chunks
     double tol;
     int m, maxit;
     // preconditioner
@@ -74,7 +90,7 @@ struct GDesc {
 };
 
 struct GState {
-    int st, j, total, code, napply, fin; // fin: the cycle ended on the residual estimate
+    int st, j, total, code, napply;
     double beta, target, hn;
 };
 
@@ -100,50 +116,17 @@ template <typename VT> __device__ inline const VT *vcol(const GDesc &d, int64_t 
 }
 
 // ---------------------------------------------------------------------------
-// apply: pack, dense GEMV, sliced-ELL SpMV on the current input of each instance
-// (ARN: D^{-1} V_j, RES: x)
+// start of a batched solve: x = 0, the padding of the packed inputs, the
+// Chebyshev coefficients from the bound lmax (grid: blocks x instances)
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_bpack(const WItem *__restrict__ wl, const GDesc *__restrict__ D,
-                                               const GState *__restrict__ S)
+__global__ void __launch_bounds__(256) k_binit(const GDesc *__restrict__ D)
 {
-    const WItem it = wl[blockIdx.x];
-    const GState s = S[it.inst];
-    if (!applies(s.st)) return;
-    const GDesc &d = D[it.inst];
-    const double *in0 = s.st == G_ARN ? d.z : d.x; // ARN: P^-1 V_j, RES: x
-    auto in = [&](int64_t r) { return in0[r]; };
-    for (int64_t k = it.b + threadIdx.x; k < it.b + CH; k += 256) {
-        if (d.two_field) {
-            if (k < d.nm) d.w[d.nn + k] = in(d.nn + k); // identity row of lambda_m
-        } else if (k < d.ldm) {
-            double v = 0.0;
-            if (k < d.nm) v = in(d.gm[k]);
-            else if (k < 2 * d.nm) v = in(d.nn + (d.mvm ? d.mvm[k - d.nm] : k - d.nm));
-            d.xm[k] = v;
-        }
-        if (k < d.lds) {
-            double v = 0.0;
-            if (k < d.ns) v = in(d.gs[k]);
-            else if (k < 2 * d.ns) v = in(d.nn + d.nm + (d.mvs ? d.mvs[k - d.ns] : k - d.ns));
-            d.xs[k] = v;
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// preconditioner stage: z = P^-1 src with src = V_j (ARN) or t = V y (RES,
-// which also adds the result to x).  Chebyshev term s (0-based) of the FEM
-// block is written to z when k - 1 - s is even and to zb otherwise, so the
-// last term always lands in z.
-// ---------------------------------------------------------------------------
-// the Chebyshev coefficients of every instance, from its bound lmax (one
-// thread per instance, once per batched solve)
-__global__ void k_cheb_coef(const GDesc *__restrict__ D, int nb)
-{
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= nb) return;
-    const GDesc &d = D[q];
-    if (d.pc != PBFB_PC_CHEB_SPAI) return;
+    const GDesc &d = D[blockIdx.y];
+    const int64_t i0 = blockIdx.x * int64_t(256) + threadIdx.x, step = gridDim.x * int64_t(256);
+    for (int64_t k = i0; k < d.n; k += step) d.x[k] = 0.0;
+    for (int64_t k = 2 * d.nm + i0; k < d.ldm; k += step) d.xm[k] = 0.0;
+    for (int64_t k = 2 * d.ns + i0; k < d.lds; k += step) d.xs[k] = 0.0;
+    if (i0 != 0 || d.pc != PBFB_PC_CHEB_SPAI) return;
     const double hi = *d.lmax, lo = hi / d.cheb_ratio;
     const double theta = 0.5 * (hi + lo), delta = 0.5 * (hi - lo), sigma = theta / delta;
     double rho = 1.0 / sigma;
@@ -157,51 +140,99 @@ __global__ void k_cheb_coef(const GDesc *__restrict__ D, int nb)
     }
 }
 
+// ---------------------------------------------------------------------------
+// preconditioner stage: z = P^-1 src with src = V_j (ARN) or t = V y (RES and
+// FIN, which also add the result to x).  Chebyshev term s (0-based) of the
+// FEM block is written to z when k - 1 - s is even and to zb otherwise, so
+// the last term always lands in z.
+// ---------------------------------------------------------------------------
+__device__ inline bool prec_active(int st) { return st == G_ARN || st == G_RES || st == G_FIN; }
 __device__ inline double pc_src(const GDesc &d, const GState &s, int64_t r)
 {
-    return (s.st == G_RES || s.st == G_FIN) ? d.t[r] : vget(d, s.j, r);
+    return s.st == G_ARN ? vget(d, s.j, r) : d.t[r];
 }
 
-// first term (FEM rows), the approximate inverse (surface rows) or the diagonal
-__global__ void __launch_bounds__(256) k_bprec0(const WItem *__restrict__ wl, const GDesc *__restrict__ D,
+// the final value z_k of P^-1 src: x += z at the end of a cycle, and the
+// entry of the apply's input (ARN: z, RES: x) into the packed surface
+// vectors x_w = [u on the surface | lambda] (operator order)
+__device__ inline void prec_final(const GDesc &d, const GState &s, int64_t k, double zv)
+{
+    d.z[k] = zv;
+    double in = zv;
+    if (s.st != G_ARN) d.x[k] = in = d.x[k] + zv;
+    if (s.st == G_FIN) return;
+    if (k < d.nn) {
+        const int32_t v0 = d.nvert[0][k], v1 = d.nvert[1][k];
+        if (v0 >= 0) d.xm[d.minv[0] ? d.minv[0][v0] : v0] = in;
+        if (v1 >= 0) d.xs[d.minv[1] ? d.minv[1][v1] : v1] = in;
+    } else if (k < d.nn + d.nm) {
+        const int64_t i = k - d.nn;
+        if (d.two_field) d.w[k] = in; // identity row of lambda_m
+        else d.xm[d.nm + (d.minv[0] ? d.minv[0][i] : i)] = in;
+    } else {
+        const int64_t i = k - d.nn - d.nm;
+        d.xs[d.ns + (d.minv[1] ? d.minv[1][i] : i)] = in;
+    }
+}
+
+// Work items: a = 0: the 64 FEM rows from b, a = 1: the 256 surface rows from
+// nn + b.  Surface rows: the approximate inverse.  FEM rows: the first two
+// Chebyshev terms in one pass -- the first, z_0 = D^-1 src / theta, is
+// pointwise, so the second's SpMV forms it at the gathered columns.  Without
+// the block preconditioner every row is the inverse diagonal.
+__global__ void __launch_bounds__(256) k_bfirst(const WItem *__restrict__ wl, const GDesc *__restrict__ D,
                                                 const GState *__restrict__ S)
 {
     const WItem it = wl[blockIdx.x];
     const GState s = S[it.inst];
-    if (s.st != G_ARN && s.st != G_RES && s.st != G_FIN) return;
+    if (!prec_active(s.st)) return;
     const GDesc &d = D[it.inst];
-    const int64_t k = it.b + threadIdx.x;
-    if (k >= d.n) return;
-    double zv;
-    bool last = true;
-    if (d.pc == PBFB_PC_DIAG) {
-        zv = d.dinv[k] * pc_src(d, s, k);
-        d.z[k] = zv;
-    } else if (k < d.nn) {
-        zv = d.dinv[k] * pc_src(d, s, k) / d.coef[0];
-        d.dk[k] = zv;
-        ((d.cheb_k - 1) % 2 == 0 ? d.z : d.zb)[k] = zv;
-        last = d.cheb_k == 1;
-    } else {
-        const int w = k < d.nn + d.nm ? 0 : 1;
-        const int64_t off = d.nn + (w == 0 ? 0 : d.nm), i = k - off;
-        double acc = 0.0;
-        for (int32_t e = d.sp_ptr[w][i]; e < d.sp_ptr[w][i + 1]; ++e)
-            acc = fma(d.sp_val[w][e], pc_src(d, s, off + d.sp_col[w][e]), acc);
-        zv = acc;
-        d.z[k] = zv;
+    const bool cheb = d.pc == PBFB_PC_CHEB_SPAI;
+    if (it.a) {
+        const int64_t k = d.nn + it.b + threadIdx.x;
+        if (k >= d.n) return;
+        double zv = 0.0;
+        if (cheb) {
+            const int w = k < d.nn + d.nm ? 0 : 1;
+            const int64_t off = d.nn + (w == 0 ? 0 : d.nm), i = k - off;
+            for (int32_t e = d.sp_ptr[w][i]; e < d.sp_ptr[w][i + 1]; ++e)
+                zv = fma(d.sp_val[w][e], pc_src(d, s, off + d.sp_col[w][e]), zv);
+        } else {
+            zv = d.dinv[k] * pc_src(d, s, k);
+        }
+        prec_final(d, s, k, zv);
+        return;
     }
-    if (last && (s.st == G_RES || s.st == G_FIN)) d.x[k] += zv;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t row = it.b + lane;
+    if (!cheb || d.cheb_k == 1) {
+        if (wv == 0 && row < d.nn)
+            prec_final(d, s, row, d.dinv[row] * pc_src(d, s, row) / (cheb ? d.coef[0] : 1.0));
+        return;
+    }
+    const double theta = d.coef[0];
+    auto z0 = [&](int64_t c) { return d.dinv[c] * pc_src(d, s, c) / theta; };
+    const double part = d.f32 ? sell_part_of<float, true>(d.sptr, d.col, static_cast<const float *>(d.val), z0,
+                                                          it.b / SLICE, lane, wv, d.nn)
+                              : sell_part_of<double, true>(d.sptr, d.col, static_cast<const double *>(d.val), z0,
+                                                           it.b / SLICE, lane, wv, d.nn);
+    const double acc = sell_reduce(part, lane, wv);
+    if (wv != 0 || row >= d.nn) return;
+    const double zp = z0(row);
+    const double dv = d.coef[2] * zp + d.coef[3] * d.dinv[row] * (pc_src(d, s, row) - acc);
+    d.dk[row] = dv;
+    if (d.cheb_k == 2) prec_final(d, s, row, zp + dv);
+    else ((d.cheb_k - 2) % 2 == 0 ? d.z : d.zb)[row] = zp + dv;
 }
 
-// Chebyshev term `step` >= 1 of the FEM block: one workgroup per 64-row
+// Chebyshev term `step` >= 2 of the FEM block: one workgroup per 64-row
 // slice (work item: inst, b = first row of the slice)
 __global__ void __launch_bounds__(256) k_bcheb(const WItem *__restrict__ wl, const GDesc *__restrict__ D,
                                                const GState *__restrict__ S, int step)
 {
     const WItem it = wl[blockIdx.x];
     const GState s = S[it.inst];
-    if (s.st != G_ARN && s.st != G_RES && s.st != G_FIN) return;
+    if (!prec_active(s.st)) return;
     const GDesc &d = D[it.inst];
     if (d.pc != PBFB_PC_CHEB_SPAI || step >= d.cheb_k) return;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -217,8 +248,8 @@ __global__ void __launch_bounds__(256) k_bcheb(const WItem *__restrict__ wl, con
     const double dv = d.coef[2 * step] * d.dk[row] + d.coef[2 * step + 1] * d.dinv[row] * (pc_src(d, s, row) - acc);
     d.dk[row] = dv;
     const double zv = zp[row] + dv;
-    zn[row] = zv;
-    if (step == d.cheb_k - 1 && (s.st == G_RES || s.st == G_FIN)) d.x[row] += zv;
+    if (step == d.cheb_k - 1) prec_final(d, s, row, zv);
+    else zn[row] = zv;
 }
 
 // work item: inst, a = interface (0/1), b = first row of the workgroup.  One
@@ -250,32 +281,30 @@ __global__ void __launch_bounds__(GEMV_THREADS, gemv_occupancy<MT>()) k_bgemv(co
     }
 }
 
-// second stage of the symmetric use (work item: inst, a = surface, b = first of GFIN_ROWS rows)
-__global__ void __launch_bounds__(256) k_bgemv_fin(const WItem *__restrict__ wl, const GDesc *__restrict__ D,
-                                                   const GState *__restrict__ S)
+// The rest of the apply after k_bgemv, item first + blockIdx: the first nfin
+// items are the second stage of the symmetric use (inst, a = surface, b =
+// first of GFIN_ROWS rows), the others FEM SpMV slices (b = first row), which
+// do not depend on the dense product.
+__global__ void __launch_bounds__(256) k_btail(const WItem *__restrict__ wl, unsigned first, unsigned nfin,
+                                               const GDesc *__restrict__ D, const GState *__restrict__ S)
 {
-    const WItem it = wl[blockIdx.x];
-    if (!applies(S[it.inst].st)) return;
+    const unsigned bi = first + blockIdx.x;
+    const WItem it = wl[bi];
+    const int st = S[it.inst].st;
+    if (!applies(st)) return;
     const GDesc &d = D[it.inst];
-    if (d.mf || !d.symm[it.a]) return;
-    const int64_t n = it.a == 0 ? d.nm : d.ns;
-    const double *x = it.a == 0 ? d.xm : d.xs;
-    double *y = d.w + d.nn + (it.a == 0 ? 0 : d.nm);
-    gemv_sym_finish(n, static_cast<const double *>(d.symP[it.a]), d.dl_ptr[it.a], d.dl_col[it.a], d.dl_val[it.a], x, y,
-                    it.a == 0 ? d.mvm : d.mvs,
-                    it.b, threadIdx.x);
-}
-
-__global__ void __launch_bounds__(256) k_bspmv(const WItem *__restrict__ wl, const GDesc *__restrict__ D,
-                                               const GState *__restrict__ S)
-{
-    const WItem it = wl[blockIdx.x];
-    const GState s = S[it.inst];
-    if (!applies(s.st)) return;
-    const GDesc &d = D[it.inst];
+    if (bi < nfin) {
+        if (d.mf || !d.symm[it.a]) return;
+        const int64_t n = it.a == 0 ? d.nm : d.ns;
+        const double *x = it.a == 0 ? d.xm : d.xs;
+        double *y = d.w + d.nn + (it.a == 0 ? 0 : d.nm);
+        gemv_sym_finish(n, static_cast<const double *>(d.symP[it.a]), d.dl_ptr[it.a], d.dl_col[it.a], d.dl_val[it.a],
+                        x, y, it.a == 0 ? d.mvm : d.mvs, it.b, threadIdx.x);
+        return;
+    }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t q = it.b / SLICE, row = it.b + lane;
-    const double *in = s.st == G_ARN ? d.z : d.x;
+    const double *in = st == G_ARN ? d.z : d.x;
     const double part = d.f32 ? sell_part<float, false>(d.sptr, d.col, static_cast<const float *>(d.val), in, q,
                                                         lane, wv, d.nn)
                               : sell_part<double, false>(d.sptr, d.col, static_cast<const double *>(d.val), in, q,
@@ -285,157 +314,200 @@ __global__ void __launch_bounds__(256) k_bspmv(const WItem *__restrict__ wl, con
 }
 
 // ---------------------------------------------------------------------------
-// classical Gram-Schmidt pass: partial dot products V_i . w over 2048-row
-// chunks (work item: inst, a = chunk, b = first row; blockIdx.y = group of 8
-// coefficients), then one workgroup per (instance, group) sums the chunk
-// partials in chunk order, so every coefficient is deterministic.  Kernel
-// boundaries order the passes (no device-scope fences).
+// classical Gram-Schmidt, two passes over row chunks (work item: inst, a =
+// chunk, b = first row): k_bmdot leaves the chunk's partial dot products
+// V_i . w; k_bmid adds every chunk's (each workgroup for itself, in chunk
+// order), subtracts and leaves the partials of the second pass from the rows
+// it still holds; k_bend adds those, subtracts and leaves the chunk's |w|^2.
+// Kernel boundaries order the passes, every sum has a fixed order.
 // ---------------------------------------------------------------------------
-constexpr int CHB = 2048; // rows per dot-product chunk (8 per thread)
+// Rows per chunk: about 96 chunks (the sum over chunks that every workgroup
+// of the next pass repeats stays a few loads per thread) of at most 2048 rows
+// (so that large instances still fill the chip)
+constexpr int CHB_MAX = 8; // x 256 rows
+static int64_t chunk_rows(int64_t n)
+{
+    return 256 * std::min<int64_t>(CHB_MAX, std::max<int64_t>(1, (n + 256 * 96 - 1) / (256 * 96)));
+}
 
+// sums over the workgroup of 256 threads of eight values; valid in threads 0..7 (value = thread id)
+__device__ inline double block_sum8(const double (&acc)[8], double (&red)[4][8])
+{
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        double v = acc[q];
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+        if (lane == 0) red[wv][q] = v;
+    }
+    __syncthreads();
+    double r = 0.0;
+    if (threadIdx.x < 8) r = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+    __syncthreads();
+    return r;
+}
+
+// hs[i] = sum over chunks of part[c][i], i < jj: 8 x 32 threads, each 32
+// coefficients at a time over every eighth chunk
+__device__ inline void chunk_sums(const GDesc &d, const double *__restrict__ part, int jj, double *hs,
+                                  double (&red)[8][33])
+{
+    const int g = threadIdx.x >> 5, l = threadIdx.x & 31;
+    for (int i0 = 0; i0 < jj; i0 += 32) {
+        const int i = i0 + l;
+        double t = 0.0;
+        if (i < jj) {
+#pragma unroll 4
+            for (int64_t c = g; c < d.nchb; c += 8) t += part[c * (d.m + 1) + i];
+        }
+        red[g][l] = t;
+        __syncthreads();
+        if (g == 0 && i < jj) {
+            double v = red[0][l];
+#pragma unroll
+            for (int k = 1; k < 8; ++k) v += red[k][l];
+            hs[i] = v;
+        }
+        __syncthreads();
+    }
+}
+
+constexpr int DOT_GROUPS = 4; // groups of eight coefficients in flight per chunk
 __global__ void __launch_bounds__(256) k_bmdot(const WItem *__restrict__ wl, const GDesc *__restrict__ D,
                                                const GState *__restrict__ S)
 {
-    __shared__ double red[8][256];
+    __shared__ double red[4][8];
     const WItem it = wl[blockIdx.x];
     const GState s = S[it.inst];
     if (s.st != G_ARN) return;
-    const int i0 = blockIdx.y * 8;
-    if (i0 > s.j) return;
     const GDesc &d = D[it.inst];
-    const int kk = min(8, s.j + 1 - i0);
-    double acc[8];
+    for (int i0 = blockIdx.y * 8; i0 <= s.j; i0 += 8 * DOT_GROUPS) {
+        const int kk = min(8, s.j + 1 - i0);
+        double acc[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) acc[q] = 0.0;
-    auto body = [&](auto *V0) {
-        for (int64_t k = it.b + threadIdx.x; k < it.b + CHB && k < d.n; k += 256) {
-            const double wk = d.w[k];
+        for (int q = 0; q < 8; ++q) acc[q] = 0.0;
+        auto body = [&](auto *V0) {
+            for (int64_t k = it.b + threadIdx.x; k < it.b + d.chb && k < d.n; k += 256) {
+                const double wk = d.w[k];
 #pragma unroll
-            for (int q = 0; q < 8; ++q)
-                if (q < kk) acc[q] = fma(double(V0[int64_t(q) * d.n + k]), wk, acc[q]);
-        }
-    };
-    if (d.vf32) body(vcol<float>(d, i0));
-    else body(vcol<double>(d, i0));
-#pragma unroll
-    for (int q = 0; q < 8; ++q) red[q][threadIdx.x] = acc[q];
-    __syncthreads();
-    for (int wd = 128; wd > 0; wd >>= 1) {
-        if (threadIdx.x < wd)
-#pragma unroll
-            for (int q = 0; q < 8; ++q) red[q][threadIdx.x] += red[q][threadIdx.x + wd];
-        __syncthreads();
+                for (int q = 0; q < 8; ++q)
+                    if (q < kk) acc[q] = fma(double(V0[int64_t(q) * d.n + k]), wk, acc[q]);
+            }
+        };
+        if (d.vf32) body(vcol<float>(d, i0));
+        else body(vcol<double>(d, i0));
+        const double r = block_sum8(acc, red);
+        if (threadIdx.x < kk) d.part[int64_t(it.a) * (d.m + 1) + i0 + threadIdx.x] = r;
     }
-    if (threadIdx.x < kk) d.part[int64_t(it.a) * (d.m + 1) + i0 + threadIdx.x] = red[threadIdx.x][0];
 }
 
-// h[i] = sum over chunks of part[c][i]; grid (instances, groups of 8)
-__global__ void __launch_bounds__(256) k_breduce(const GDesc *__restrict__ D, const GState *__restrict__ S, int pass)
-{
-    const int q = blockIdx.x;
-    const GState s = S[q];
-    if (s.st != G_ARN) return;
-    const int i0 = blockIdx.y * 8;
-    if (i0 > s.j) return;
-    const GDesc &d = D[q];
-    const int kk = min(8, s.j + 1 - i0);
-    const int g = threadIdx.x >> 5, lane = threadIdx.x & 31;
-    if (g >= kk) return;
-    double t = 0.0;
-    for (int64_t c = lane; c < d.nchb; c += 32) t += d.part[c * (d.m + 1) + i0 + g];
-    for (int off = 16; off > 0; off >>= 1) t += __shfl_xor(t, off, 32);
-    if (lane == 0) (pass == 0 ? d.h1 : d.h2)[i0 + g] = t;
-}
-
-// First pass (second = 0): w -= sum_i h1_i V_i for ARN.
-// Second pass (second = 1): ARN: w -= sum_i h2_i V_i;  RES: w = b - w;
-// INIT: w = b; then |w|^2 per 256-row chunk into npart.
-__global__ void __launch_bounds__(256) k_bmsub(const WItem *__restrict__ wl, const GDesc *__restrict__ D,
-                                               const GState *__restrict__ S, int second)
+// w -= sum_i h1_i V_i; partial dot products of the second pass
+__global__ void __launch_bounds__(256) k_bmid(const WItem *__restrict__ wl, const GDesc *__restrict__ D,
+                                              const GState *__restrict__ S)
 {
     __shared__ double hs[1024];
-    __shared__ double red[256];
+    __shared__ double red[4][8], redc[8][33];
     const WItem it = wl[blockIdx.x];
     const GState s = S[it.inst];
+    if (s.st != G_ARN) return;
     const GDesc &d = D[it.inst];
-    const bool arn = s.st == G_ARN;
-    if (!arn && !(second && (s.st == G_RES || s.st == G_INIT))) return;
-    const int jj = arn ? s.j + 1 : 0;
-    const double *h = second ? d.h2 : d.h1;
-    for (int i = threadIdx.x; i < jj; i += 256) hs[i] = h[i];
-    __syncthreads();
-    const int64_t k = it.b + threadIdx.x;
-    double v = 0.0;
-    if (k < d.n) {
-        if (s.st == G_INIT) v = d.b[k];
-        else if (s.st == G_RES) v = d.b[k] - d.w[k];
-        else {
-            v = d.w[k];
-            if (d.vf32) {
-                const float *V0 = vcol<float>(d, 0);
-                for (int i = 0; i < jj; ++i) v = fma(-hs[i], double(V0[int64_t(i) * d.n + k]), v);
-            } else {
-                const double *V0 = vcol<double>(d, 0);
-                for (int i = 0; i < jj; ++i) v = fma(-hs[i], V0[int64_t(i) * d.n + k], v);
-            }
+    const int jj = s.j + 1;
+    chunk_sums(d, d.part, jj, hs, redc);
+    if (it.a == 0)
+        for (int i = threadIdx.x; i < jj; i += 256) d.h1[i] = hs[i];
+    const int64_t kend = std::min(it.b + d.chb, d.n);
+    double v[CHB_MAX]; // this thread's rows
+    auto body = [&](auto *V0) {
+#pragma unroll
+        for (int r = 0; r < CHB_MAX; ++r) {
+            const int64_t k = it.b + 256 * r + threadIdx.x;
+            v[r] = 0.0;
+            if (k >= kend) continue;
+            double t = d.w[k];
+#pragma unroll 8
+            for (int i = 0; i < jj; ++i) t = fma(-hs[i], double(V0[int64_t(i) * d.n + k]), t);
+            d.w[k] = v[r] = t;
         }
-        d.w[k] = v;
-    }
-    if (!second) return;
-    red[threadIdx.x] = v * v;
-    __syncthreads();
-    for (int wd = 128; wd > 0; wd >>= 1) {
-        if (threadIdx.x < wd) red[threadIdx.x] += red[threadIdx.x + wd];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) d.npart[it.a] = red[0];
+        for (int i0 = 0; i0 < jj; i0 += 8) {
+            double acc[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) acc[q] = 0.0;
+#pragma unroll
+            for (int r = 0; r < CHB_MAX; ++r) {
+                const int64_t k = it.b + 256 * r + threadIdx.x;
+                if (k >= kend) continue;
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    if (i0 + q < jj) acc[q] = fma(double(V0[int64_t(i0 + q) * d.n + k]), v[r], acc[q]);
+            }
+            const double r = block_sum8(acc, red);
+            if (threadIdx.x < 8 && i0 + int(threadIdx.x) < jj)
+                d.part2[int64_t(it.a) * (d.m + 1) + i0 + threadIdx.x] = r;
+        }
+    };
+    if (d.vf32) body(vcol<float>(d, 0));
+    else body(vcol<double>(d, 0));
 }
 
-// |w|^2 = sum of the chunk partials, one workgroup per instance
-__global__ void __launch_bounds__(256) k_bnorm(const GDesc *__restrict__ D, const GState *__restrict__ S)
+// ARN: w -= sum_i h2_i V_i;  RES: w = b - w;  INIT: w = b; the chunk's |w|^2
+__global__ void __launch_bounds__(256) k_bend(const WItem *__restrict__ wl, const GDesc *__restrict__ D,
+                                              const GState *__restrict__ S)
 {
-    __shared__ double red[256];
-    const int q = blockIdx.x;
-    const int st = S[q].st;
-    if (st != G_ARN && st != G_RES && st != G_INIT) return;
-    const GDesc &d = D[q];
-    double t = 0.0;
-    for (int64_t c = threadIdx.x; c < d.nch; c += 256) t += d.npart[c];
-    red[threadIdx.x] = t;
-    __syncthreads();
-    for (int wd = 128; wd > 0; wd >>= 1) {
-        if (threadIdx.x < wd) red[threadIdx.x] += red[threadIdx.x + wd];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *d.nrm = red[0];
-}
-
-// ARN: V_{j+1} = w / |w|;  INIT/RES: V_0 = w / |w|
-__global__ void __launch_bounds__(256) k_bscale(const WItem *__restrict__ wl, const GDesc *__restrict__ D,
-                                                const GState *__restrict__ S)
-{
+    __shared__ double hs[1024];
+    __shared__ double red[4][8], redc[8][33];
     const WItem it = wl[blockIdx.x];
     const GState s = S[it.inst];
-    if (s.st != G_ARN && s.st != G_RES && s.st != G_INIT) return;
+    const bool arn = s.st == G_ARN;
+    if (!arn && s.st != G_RES && s.st != G_INIT) return;
     const GDesc &d = D[it.inst];
-    const double nr = sqrt(*d.nrm);
-    const double inv = nr > 0.0 ? 1.0 / nr : 0.0;
-    const int64_t off = (s.st == G_ARN ? int64_t(s.j + 1) * d.n : 0);
-    const int64_t k = it.b + threadIdx.x;
-    if (k < d.n) {
-        if (d.vf32) static_cast<float *>(d.V)[off + k] = float(d.w[k] * inv);
-        else static_cast<double *>(d.V)[off + k] = d.w[k] * inv;
+    const int jj = arn ? s.j + 1 : 0;
+    if (arn) {
+        chunk_sums(d, d.part2, jj, hs, redc);
+        if (it.a == 0)
+            for (int i = threadIdx.x; i < jj; i += 256) d.h2[i] = hs[i];
     }
+    const int64_t kend = std::min(it.b + d.chb, d.n);
+    double nrm[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    auto body = [&](auto *V0) {
+        for (int64_t k = it.b + threadIdx.x; k < kend; k += 256) {
+            double v;
+            if (s.st == G_INIT) v = d.b[k];
+            else if (s.st == G_RES) v = d.b[k] - d.w[k];
+            else {
+                v = d.w[k];
+#pragma unroll 8
+                for (int i = 0; i < jj; ++i) v = fma(-hs[i], double(V0[int64_t(i) * d.n + k]), v);
+            }
+            d.w[k] = v;
+            nrm[0] = fma(v, v, nrm[0]);
+        }
+    };
+    if (d.vf32) body(vcol<float>(d, 0));
+    else body(vcol<double>(d, 0));
+    const double t = block_sum8(nrm, red);
+    if (threadIdx.x == 0) d.npart[it.a] = t;
 }
 
 // ---------------------------------------------------------------------------
-// control: one wavefront per instance.  ARN: Hessenberg column, Givens chain
-// (in LDS, one lane), residual estimate, cycle end; at the end of a cycle the
-// triangular solve H y = g (column sweep across the lanes).  INIT/RES: true
-// residual test and cycle start.  Transitions to DONE/FAIL bump ndone.
+// control: one wavefront per instance.  |w| from the chunk partials.  ARN:
+// Hessenberg column, Givens chain (in LDS, one lane), residual estimate, cycle
+// end; at the end of a cycle the triangular solve H y = g (column sweep across
+// the lanes).  INIT/RES: true residual test and cycle start.
+//
+// What the host needs to know goes to pinned host memory at the end of every
+// step of the batch (the last instance writes it): the step, the instances
+// that need no step after the next one (DONE, FAIL or FIN) and those that
+// need none at all (DONE or FAIL).
 // ---------------------------------------------------------------------------
+struct GCount {
+    int tick, ending, ended;
+};
+// the host word: step << 40 | ending << 20 | ended (20 bits hold a batch's instances)
+constexpr int GCOUNT_BITS = 20;
+constexpr int64_t GCOUNT_MAX = (int64_t(1) << GCOUNT_BITS) - 1;
+
 __global__ void __launch_bounds__(64) k_bcontrol(const GDesc *__restrict__ D, GState *__restrict__ S,
-                                                 int *__restrict__ ndone)
+                                                 GCount *__restrict__ C, unsigned long long *__restrict__ host)
 {
     __shared__ double hc[1024], cs[1024], sn[1024], gl[1024];
     __shared__ GState ss;
@@ -444,16 +516,14 @@ __global__ void __launch_bounds__(64) k_bcontrol(const GDesc *__restrict__ D, GS
     if (lane == 0) ss = S[q];
     __syncthreads();
     const int st0 = ss.st;
-    if (st0 == G_FIN) {
-        if (lane == 0) {
-            S[q].st = G_DONE;
-            atomicAdd(ndone, 1);
-        }
-        return;
-    }
-    if (st0 != G_ARN && st0 != G_RES && st0 != G_INIT) return;
     const int m = d.m;
-    const double nr = sqrt(*d.nrm);
+    double nr = 0.0;
+    if (st0 == G_ARN || st0 == G_RES || st0 == G_INIT) {
+        for (int64_t c = lane; c < d.nchb; c += 64) nr += d.npart[c];
+        for (int off = 32; off > 0; off >>= 1) nr += __shfl_xor(nr, off);
+        nr = sqrt(nr);
+        if (lane == 0) *d.nrm = nr;
+    }
     if (st0 == G_ARN) {
         const int j = ss.j;
         for (int i = lane; i <= j; i += 64) {
@@ -464,6 +534,7 @@ __global__ void __launch_bounds__(64) k_bcontrol(const GDesc *__restrict__ D, GS
             }
         }
         __syncthreads();
+        bool cycle_end = false;
         if (lane == 0) {
             double t = hc[0];
             for (int i = 0; i < j; ++i) {
@@ -487,19 +558,18 @@ __global__ void __launch_bounds__(64) k_bcontrol(const GDesc *__restrict__ D, GS
             if (!(res == res)) {
                 ss.st = G_FAIL;
                 ss.code = PBFB_ENAN;
-                atomicAdd(ndone, 1);
             } else if (res <= ss.target || nr == 0.0 || ss.j == m || ss.total >= d.maxit) {
-                ss.st = G_UPD;
                 // converged on the estimate: no true-residual check, except with an
                 // FP32 basis, whose restarts are refinement steps that need it
-                ss.fin = (res <= ss.target || nr == 0.0) && !d.vf32;
+                ss.st = (res <= ss.target || nr == 0.0) && !d.vf32 ? G_FIN : G_RES;
             }
         }
         __syncthreads();
+        cycle_end = ss.st == G_FIN || ss.st == G_RES;
         double *Hj = d.H + int64_t(j) * (m + 1);
         for (int i = lane; i <= j; i += 64) Hj[i] = hc[i];
         if (lane == 0) Hj[j + 1] = 0.0;
-        if (ss.st == G_UPD) {
+        if (cycle_end) {
             // back substitution by columns: y_i = g_i / H_ii, then g_k -= H_ki y_i for k < i
             const int jc = ss.j;
             __threadfence_block();
@@ -513,21 +583,20 @@ __global__ void __launch_bounds__(64) k_bcontrol(const GDesc *__restrict__ D, GS
                 __syncthreads();
             }
         }
-    } else if (lane == 0) {
+    } else if (lane == 0 && st0 == G_FIN) {
+        ss.st = G_DONE;
+    } else if (lane == 0 && (st0 == G_RES || st0 == G_INIT)) {
         if (st0 == G_INIT) ss.target = d.tol * nr;
         else ss.napply += 1; // RES: the true residual took one application
         ss.beta = nr;
         if (!(nr == nr)) {
             ss.st = G_FAIL;
             ss.code = PBFB_ENAN;
-            atomicAdd(ndone, 1);
         } else if (nr <= ss.target) {
             ss.st = G_DONE;
-            atomicAdd(ndone, 1);
         } else if (ss.total >= d.maxit) {
             ss.st = G_FAIL;
             ss.code = PBFB_ENOTCONV;
-            atomicAdd(ndone, 1);
         } else {
             for (int i = 0; i <= m; ++i) d.g[i] = 0.0;
             d.g[0] = nr;
@@ -536,42 +605,51 @@ __global__ void __launch_bounds__(64) k_bcontrol(const GDesc *__restrict__ D, GS
         }
     }
     __syncthreads();
-    if (lane == 0) S[q] = ss;
+    if (lane != 0) return;
+    S[q] = ss;
+    const bool over = ss.st == G_DONE || ss.st == G_FAIL, was = st0 == G_DONE || st0 == G_FAIL;
+    if (over && !was) atomicAdd(&C->ended, 1);
+    if ((over || ss.st == G_FIN) && !was && st0 != G_FIN) atomicAdd(&C->ending, 1);
+    __threadfence(); // the counts before the tick
+    const int nb = int(gridDim.x), t = atomicAdd(&C->tick, 1) + 1;
+    if (t % nb) return;
+    const unsigned long long ending = atomicAdd(&C->ending, 0), ended = atomicAdd(&C->ended, 0);
+    __hip_atomic_store(host, (static_cast<unsigned long long>(t / nb) << (2 * GCOUNT_BITS)) | (ending << GCOUNT_BITS) | ended,
+                       __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// UPD: t = V y; the last workgroup of the instance moves it to RES
-__global__ void __launch_bounds__(256) k_bupdx(const WItem *__restrict__ wl, const GDesc *__restrict__ D,
-                                               GState *__restrict__ S)
+// what the new state asks for: ARN: V_j = w / |w| (j = 0 at a cycle start);
+// RES, FIN (a cycle just ended): t = V y
+__global__ void __launch_bounds__(256) k_bnext(const WItem *__restrict__ wl, const GDesc *__restrict__ D,
+                                               const GState *__restrict__ S)
 {
     __shared__ double ys[1024];
-    __shared__ int last;
     const WItem it = wl[blockIdx.x];
     const GState s = S[it.inst];
-    if (s.st != G_UPD) return;
+    if (!prec_active(s.st)) return;
     const GDesc &d = D[it.inst];
+    const int64_t k = it.b + threadIdx.x;
+    if (s.st == G_ARN) {
+        const double nr = *d.nrm;
+        const double inv = nr > 0.0 ? 1.0 / nr : 0.0;
+        const int64_t off = int64_t(s.j) * d.n;
+        if (k < d.n) {
+            if (d.vf32) static_cast<float *>(d.V)[off + k] = float(d.w[k] * inv);
+            else static_cast<double *>(d.V)[off + k] = d.w[k] * inv;
+        }
+        return;
+    }
     for (int i = threadIdx.x; i < s.j; i += 256) ys[i] = d.y[i];
     __syncthreads();
-    const int64_t k = it.b + threadIdx.x;
-    if (k < d.n) {
-        double v = 0.0;
-        if (d.vf32) {
-            const float *V0 = vcol<float>(d, 0);
-            for (int i = 0; i < s.j; ++i) v = fma(ys[i], double(V0[int64_t(i) * d.n + k]), v);
-        } else {
-            const double *V0 = vcol<double>(d, 0);
-            for (int i = 0; i < s.j; ++i) v = fma(ys[i], V0[int64_t(i) * d.n + k], v);
-        }
-        d.t[k] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int *cnt = d.cnt + 257;
-        last = atomicAdd(cnt, 1) == int(d.nch) - 1;
-        if (last) {
-            *cnt = 0;
-            S[it.inst].st = s.fin ? G_FIN : G_RES;
-        }
-    }
+    if (k >= d.n) return;
+    double v = 0.0;
+    auto body = [&](auto *V0) {
+#pragma unroll 8
+        for (int i = 0; i < s.j; ++i) v = fma(ys[i], double(V0[int64_t(i) * d.n + k]), v);
+    };
+    if (d.vf32) body(vcol<float>(d, 0));
+    else body(vcol<double>(d, 0));
+    d.t[k] = v;
 }
 
 // ===========================================================================
@@ -580,39 +658,54 @@ __global__ void __launch_bounds__(256) k_bupdx(const WItem *__restrict__ wl, con
 // a captured Krylov step is valid for the same device buffer and launch shapes
 struct GraphKey {
     void *dev = nullptr;
-    unsigned nvec = 0, ngemv = 0, nspmv = 0, npack = 0, ndot = 0, ngroups = 0, nb = 0, nfin = 0;
+    unsigned nvec = 0, ngemv = 0, nspmv = 0, nfirst = 0, ndot = 0, nb = 0, nfin = 0;
     int kmax = 0, types = 0; // types: bit 0 FP64 operators present, bit 1 FP32
     bool operator==(const GraphKey &o) const
     {
-        return dev == o.dev && nvec == o.nvec && ngemv == o.ngemv && nspmv == o.nspmv && npack == o.npack &&
-               ndot == o.ndot && ngroups == o.ngroups && nb == o.nb && nfin == o.nfin && kmax == o.kmax &&
-               types == o.types;
+        return dev == o.dev && nvec == o.nvec && ngemv == o.ngemv && nspmv == o.nspmv && nfirst == o.nfirst &&
+               ndot == o.ndot && nb == o.nb && nfin == o.nfin && kmax == o.kmax && types == o.types;
     }
 };
 
+// per host thread: the device copy of a batch's descriptors and work lists,
+// its pinned source, and the word the control kernel reports to
 struct BatchBuffers {
-    void *dev = nullptr;
-    size_t dev_bytes = 0;
-    int *pinned = nullptr;
-    hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
+    void *dev = nullptr, *stage = nullptr;
+    size_t dev_bytes = 0, stage_bytes = 0;
+    unsigned long long *word = nullptr;
     hipGraphExec_t step = nullptr; // the captured Krylov step (left to process exit)
     GraphKey key;
     ~BatchBuffers()
     {
         if (dev) (void)hipFree(dev);
-        if (pinned) (void)hipHostFree(pinned);
-        for (auto e : ev)
-            if (e) (void)hipEventDestroy(e);
+        if (stage) (void)hipHostFree(stage);
+        if (word) (void)hipHostFree(word);
+    }
+    void reserve(size_t bytes)
+    {
+        if (!word) PB_HIP(hipHostMalloc(reinterpret_cast<void **>(&word), 64, hipHostMallocDefault));
+        if (stage_bytes < bytes) {
+            if (stage) PB_HIP(hipHostFree(stage));
+            stage = nullptr;
+            stage_bytes = 0;
+            PB_HIP(hipHostMalloc(&stage, bytes, hipHostMallocDefault));
+            stage_bytes = bytes;
+        }
+        if (dev_bytes < bytes) {
+            if (step) PB_HIP(hipGraphExecDestroy(step));
+            step = nullptr;
+            if (dev) PB_HIP(hipFree(dev));
+            dev = nullptr;
+            dev_bytes = 0;
+            PB_HIP(hipMalloc(&dev, bytes));
+            dev_bytes = bytes;
+        }
     }
 };
 
 static BatchBuffers &batch_buffers()
 {
     static thread_local BatchBuffers B;
-    if (!B.pinned) {
-        PB_HIP(hipHostMalloc(reinterpret_cast<void **>(&B.pinned), 64 * sizeof(int), hipHostMallocDefault));
-        for (auto &e : B.ev) PB_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    }
     return B;
 }
 
@@ -622,11 +715,12 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
     if (nb == 0) return;
     std::vector<GDesc> desc(nb);
     std::vector<GState> st(nb);
-    std::vector<WItem> wl_vec, wl_gemv, wl_spmv, wl_pack, wl_dot, wl_fin;
+    std::vector<WItem> wl_vec, wl_gemv, wl_spmv, wl_surf, wl_dot, wl_fin;
     // GEMV items in the order of gemv_item, over the batch: the heavy V items
     // of every instance, then the K and full-row items, then the other V items
     std::vector<WItem> wl_gemv_k, wl_gemv_v;
     int maxiter_host = 0, kmax = 1;
+    int64_t nmax = 0;
     for (int q = 0; q < nb; ++q) {
         GmresJob &J = *jobs[q];
         Problem &p = *J.p;
@@ -642,8 +736,6 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
         d.f32 = p.precision == PBFB_MIXED;
         d.mf = p.bem_mf ? 1 : 0;
         d.two_field = p.two_field() ? 1 : 0;
-        d.gm = p.bem_mf ? p.surf[0].g : p.surf[0].gmv;
-        d.gs = p.bem_mf ? p.surf[1].g : p.surf[1].gmv;
         d.mvm = p.bem_mf ? nullptr : p.surf[0].mvert;
         d.mvs = p.bem_mf ? nullptr : p.surf[1].mvert;
         d.sptr = p.d_sptr;
@@ -657,6 +749,8 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
         d.cheb_ratio = J.cheb_ratio;
         d.lmax = J.lmax;
         for (int w = 0; w < 2; ++w) {
+            d.nvert[w] = p.surf[w].nvert;
+            d.minv[w] = p.bem_mf ? nullptr : p.surf[w].minv;
             d.sp_ptr[w] = p.surf[w].ring_ptr;
             d.sp_col[w] = p.surf[w].ring;
             d.sp_val[w] = p.surf[w].spai;
@@ -683,7 +777,6 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
         d.xs = scratch<double>(p, SCR_XS, d.lds);
         d.x = J.x;
         d.b = J.b;
-        d.nch = (n + CH - 1) / CH;
         double *kry = scratch<double>(p, SCR_HVEC, size_t(m) * (m + 1) + 3 * m + 3 * (m + 1) + 8);
         d.H = kry;
         d.cs = d.H + size_t(m) * (m + 1);
@@ -692,19 +785,19 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
         d.g = d.y + m;
         d.h1 = d.g + (m + 1);
         d.h2 = d.h1 + (m + 1);
-        d.nchb = (n + CHB - 1) / CHB;
-        d.part = scratch<double>(p, SCR_HPART, size_t(d.nchb) * (m + 1));
-        d.npart = scratch<double>(p, SCR_NRM, d.nch + 1);
-        d.nrm = d.npart + d.nch;
-        d.cnt = scratch<int>(p, SCR_CNT, 258);
-        PB_HIP(hipMemsetAsync(d.cnt, 0, sizeof(int) * 258, s));
+        d.chb = chunk_rows(n);
+        d.nchb = (n + d.chb - 1) / d.chb;
+        d.part = scratch<double>(p, SCR_HPART, 2 * size_t(d.nchb) * (m + 1));
+        d.part2 = d.part + size_t(d.nchb) * (m + 1);
+        d.npart = scratch<double>(p, SCR_NRM, d.nchb + 1);
+        d.nrm = d.npart + d.nchb;
         d.tol = J.tol;
         d.m = m;
         d.maxit = J.maxit;
-        st[q] = GState{G_INIT, 0, 0, 0, 0, 0, 0.0, 0.0, 0.0};
-        PB_HIP(hipMemsetAsync(J.x, 0, sizeof(double) * n, s));
-        for (int64_t c = 0; c < d.nch; ++c) wl_vec.push_back(WItem{q, int(c), c * CH});
-        for (int64_t c = 0; c < d.nchb; ++c) wl_dot.push_back(WItem{q, int(c), c * CHB});
+        st[q] = GState{G_INIT, 0, 0, 0, 0, 0.0, 0.0, 0.0};
+        nmax = std::max(nmax, n);
+        for (int64_t k = 0; k < n; k += CH) wl_vec.push_back(WItem{q, 0, k});
+        for (int64_t c = 0; c < d.nchb; ++c) wl_dot.push_back(WItem{q, int(c), c * d.chb});
         static_assert(GROWS == GSYM, "GEMV work items are the symmetric routine's row blocks");
         {
             // per surface: K (or full-row) items in row order, V items last
@@ -734,47 +827,52 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
             alternate(vit[0], h0, vit[0].size(), vit[1], h1, vit[1].size(), wl_gemv_v);
         }
         for (int64_t r = 0; r < p.nn; r += SLICE) wl_spmv.push_back(WItem{q, 0, r});
-        for (int64_t k = 0; k < std::max(d.ldm, d.lds); k += CH) wl_pack.push_back(WItem{q, 0, k});
+        for (int64_t k = 0; k < n - p.nn; k += CH) wl_surf.push_back(WItem{q, 1, k});
         maxiter_host = std::max(maxiter_host, J.maxit + J.maxit / std::max(m, 1) + 4);
     }
     wl_gemv.insert(wl_gemv.end(), wl_gemv_k.begin(), wl_gemv_k.end());
     wl_gemv.insert(wl_gemv.end(), wl_gemv_v.begin(), wl_gemv_v.end());
-    int maxm = 0;
-    for (auto *J : jobs) maxm = std::max(maxm, J->restart);
-    // device copies of descriptors, states and work lists
+    // k_btail: the second stage of the symmetric use, then the SpMV slices;
+    // k_bfirst: the SpMV slices, then the surface rows
+    const unsigned nvec = unsigned(wl_vec.size()), ngemv = unsigned(wl_gemv.size()),
+                   nspmv = unsigned(wl_spmv.size()), nfirst = unsigned(wl_spmv.size() + wl_surf.size()),
+                   ndot = unsigned(wl_dot.size()), nfin = unsigned(wl_fin.size());
+    PB_CHECK(nb <= GCOUNT_MAX, PBFB_EINVAL, "too many instances in one batch");
+    // descriptors, states, counters and work lists: one pinned block, one copy
     BatchBuffers &BB = batch_buffers();
-    const size_t bytes = sizeof(GDesc) * nb + sizeof(GState) * nb +
-                         sizeof(WItem) * (wl_vec.size() + wl_gemv.size() + wl_spmv.size() + wl_pack.size() +
-                                          wl_dot.size() + wl_fin.size()) + 512;
-    if (BB.dev_bytes < bytes) {
-        if (BB.step) PB_HIP(hipGraphExecDestroy(BB.step));
-        BB.step = nullptr;
-        if (BB.dev) PB_HIP(hipFree(BB.dev));
-        BB.dev = nullptr;
-        PB_HIP(hipMalloc(&BB.dev, bytes));
-        BB.dev_bytes = bytes;
-    }
-    char *cur = static_cast<char *>(BB.dev);
+    const size_t items = wl_vec.size() + wl_gemv.size() + wl_fin.size() + wl_spmv.size() + wl_surf.size() +
+                         wl_dot.size();
+    const size_t bytes = (sizeof(GDesc) + sizeof(GState)) * nb + sizeof(GCount) + sizeof(WItem) * items + 512;
+    BB.reserve(bytes);
+    // the block and the reported word belong to this call until its stream has drained
+    struct Drain {
+        hipStream_t s;
+        ~Drain() { (void)hipStreamSynchronize(s); }
+    } drain{s};
+    size_t cur = 0;
     auto put = [&](const void *src, size_t b) {
-        char *d = cur;
-        PB_HIP(hipMemcpyAsync(d, src, b, hipMemcpyHostToDevice, s));
+        std::memcpy(static_cast<char *>(BB.stage) + cur, src, b);
+        char *d = static_cast<char *>(BB.dev) + cur;
         cur += (b + 15) / 16 * 16;
         return static_cast<void *>(d);
     };
+    auto put_items = [&](std::initializer_list<const std::vector<WItem> *> lists) {
+        const std::vector<WItem> *const *l = lists.begin();
+        std::vector<WItem> v(**l);
+        for (++l; l != lists.end(); ++l) v.insert(v.end(), (*l)->begin(), (*l)->end());
+        return static_cast<WItem *>(put(v.data(), sizeof(WItem) * v.size()));
+    };
     GDesc *dD = static_cast<GDesc *>(put(desc.data(), sizeof(GDesc) * nb));
     GState *dS = static_cast<GState *>(put(st.data(), sizeof(GState) * nb));
-    WItem *dvec = static_cast<WItem *>(put(wl_vec.data(), sizeof(WItem) * wl_vec.size()));
-    WItem *dgemv = static_cast<WItem *>(put(wl_gemv.data(), sizeof(WItem) * wl_gemv.size()));
-    WItem *dspmv = static_cast<WItem *>(put(wl_spmv.data(), sizeof(WItem) * wl_spmv.size()));
-    WItem *dpack = static_cast<WItem *>(put(wl_pack.data(), sizeof(WItem) * wl_pack.size()));
-    WItem *ddot = static_cast<WItem *>(put(wl_dot.data(), sizeof(WItem) * wl_dot.size()));
-    WItem *dfin = static_cast<WItem *>(put(wl_fin.data(), sizeof(WItem) * wl_fin.size()));
-    int *dcount = reinterpret_cast<int *>(cur);
-    PB_HIP(hipMemsetAsync(dcount, 0, sizeof(int), s));
-    const unsigned nvec = unsigned(wl_vec.size()), ngemv = unsigned(wl_gemv.size()),
-                   nspmv = unsigned(wl_spmv.size()), npack = unsigned(wl_pack.size()),
-                   ndot = unsigned(wl_dot.size()), nfin = unsigned(wl_fin.size());
-    const unsigned ngroups = unsigned((maxm + 1 + 7) / 8);
+    const GCount zero{};
+    GCount *dC = static_cast<GCount *>(put(&zero, sizeof(zero)));
+    WItem *dvec = put_items({&wl_vec});
+    WItem *dgemv = put_items({&wl_gemv});
+    WItem *dtail = put_items({&wl_fin, &wl_spmv, &wl_surf});
+    WItem *dspmv = dtail + nfin; // the slices, followed by the surface rows
+    WItem *ddot = put_items({&wl_dot});
+    PB_HIP(hipMemcpyAsync(BB.dev, BB.stage, cur, hipMemcpyHostToDevice, s));
+    __atomic_store_n(BB.word, 0ull, __ATOMIC_RELEASE);
 
     EventTimer *tm = nullptr;
     for (auto *J : jobs)
@@ -782,33 +880,31 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
             tm = &J->p->timer;
             break;
         }
-    // Enqueue iterations; poll a completion counter copied to pinned memory
-    // every POLL iterations, blocking only on the copy of the previous poll:
-    // the device keeps 2 to 4 iterations queued, and at most that many launch
-    // rounds return at once after the last instance has finished.
-    const int POLL = 2;
-    int polls = 0;
-    bool finished = false;
-    hipLaunchKernelGGL(k_cheb_coef, dim3(unsigned((nb + 63) / 64)), dim3(64), 0, s, dD, nb);
+    hipLaunchKernelGGL(k_binit, dim3(unsigned(std::min<int64_t>((nmax + 255) / 256, 512)), unsigned(nb)), dim3(256), 0,
+                       s, dD);
     int types = 0;
     bool any_mf = false;
     for (auto *J : jobs) {
         if (J->p->bem_mf) any_mf = true;
         else types |= J->p->precision == PBFB_MIXED ? 2 : 1;
     }
+    // the end of a step: |w| and control, the next basis vector or t = V y
+    auto enqueue_end = [&]() {
+        hipLaunchKernelGGL(k_bend, dim3(ndot), dim3(256), 0, s, ddot, dD, dS);
+        hipLaunchKernelGGL(k_bcontrol, dim3(unsigned(nb)), dim3(64), 0, s, dD, dS, dC, BB.word);
+        hipLaunchKernelGGL(k_bnext, dim3(nvec), dim3(256), 0, s, dvec, dD, dS);
+    };
     // one Krylov step of the whole batch
     auto enqueue_step = [&]() {
         if (tm) tm->begin(T_PREC, s);
-        hipLaunchKernelGGL(k_bprec0, dim3(nvec), dim3(256), 0, s, dvec, dD, dS);
-        for (int step = 1; step < kmax; ++step)
+        hipLaunchKernelGGL(k_bfirst, dim3(nfirst), dim3(256), 0, s, dspmv, dD, dS);
+        for (int step = 2; step < kmax; ++step)
             hipLaunchKernelGGL(k_bcheb, dim3(nspmv), dim3(256), 0, s, dspmv, dD, dS, step);
         if (tm) tm->end(s);
         if (tm) tm->begin(T_APPLY, s);
-        hipLaunchKernelGGL(k_bpack, dim3(npack), dim3(256), 0, s, dpack, dD, dS);
         if (tm) tm->begin(T_GEMV, s);
         if (types & 1) hipLaunchKernelGGL(k_bgemv<double>, dim3(ngemv), dim3(GEMV_THREADS), 0, s, dgemv, dD, dS);
         if (types & 2) hipLaunchKernelGGL(k_bgemv<float>, dim3(ngemv), dim3(GEMV_THREADS), 0, s, dgemv, dD, dS);
-        if (nfin) hipLaunchKernelGGL(k_bgemv_fin, dim3(nfin), dim3(256), 0, s, dfin, dD, dS);
         // matrix-free instances: their own launches, gated by their state word
         for (size_t q = 0; q < jobs.size() && any_mf; ++q) {
             Problem &pq = *jobs[q]->p;
@@ -817,25 +913,19 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
             mf_apply(pq, 0, desc[q].xm, desc[q].w + pq.nn, stq, s);
             mf_apply(pq, 1, desc[q].xs, desc[q].w + pq.nn + pq.surf[0].nv, stq, s);
         }
-        if (tm) {
+        if (!tm) {
+            hipLaunchKernelGGL(k_btail, dim3(nfin + nspmv), dim3(256), 0, s, dtail, 0u, nfin, dD, dS);
+        } else { // the timed classes apart
+            if (nfin) hipLaunchKernelGGL(k_btail, dim3(nfin), dim3(256), 0, s, dtail, 0u, nfin, dD, dS);
             tm->end(s);
             tm->begin(T_SPMV, s);
-        }
-        hipLaunchKernelGGL(k_bspmv, dim3(nspmv), dim3(256), 0, s, dspmv, dD, dS);
-        if (tm) {
+            hipLaunchKernelGGL(k_btail, dim3(nspmv), dim3(256), 0, s, dtail, nfin, nfin, dD, dS);
             tm->end(s);
             tm->end(s);
         }
-        hipLaunchKernelGGL(k_bmdot, dim3(ndot, ngroups), dim3(256), 0, s, ddot, dD, dS);
-        hipLaunchKernelGGL(k_breduce, dim3(unsigned(nb), ngroups), dim3(256), 0, s, dD, dS, 0);
-        hipLaunchKernelGGL(k_bmsub, dim3(nvec), dim3(256), 0, s, dvec, dD, dS, 0);
-        hipLaunchKernelGGL(k_bmdot, dim3(ndot, ngroups), dim3(256), 0, s, ddot, dD, dS);
-        hipLaunchKernelGGL(k_breduce, dim3(unsigned(nb), ngroups), dim3(256), 0, s, dD, dS, 1);
-        hipLaunchKernelGGL(k_bmsub, dim3(nvec), dim3(256), 0, s, dvec, dD, dS, 1);
-        hipLaunchKernelGGL(k_bnorm, dim3(unsigned(nb)), dim3(256), 0, s, dD, dS);
-        hipLaunchKernelGGL(k_bscale, dim3(nvec), dim3(256), 0, s, dvec, dD, dS);
-        hipLaunchKernelGGL(k_bcontrol, dim3(unsigned(nb)), dim3(64), 0, s, dD, dS, dcount);
-        hipLaunchKernelGGL(k_bupdx, dim3(nvec), dim3(256), 0, s, dvec, dD, dS);
+        hipLaunchKernelGGL(k_bmdot, dim3(ndot, DOT_GROUPS), dim3(256), 0, s, ddot, dD, dS);
+        hipLaunchKernelGGL(k_bmid, dim3(ndot), dim3(256), 0, s, ddot, dD, dS);
+        enqueue_end();
     };
     // Without timers the step is captured once as a HIP graph (kernel nodes
     // only) and replayed; the capture is reused while the buffer and launch
@@ -843,7 +933,7 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
     bool graph = !tm && !any_mf; // matrix-free launches carry per-instance pointers: not captured
     for (auto *J : jobs) graph = graph && J->graph;
     if (graph) {
-        const GraphKey key{BB.dev, nvec, ngemv, nspmv, npack, ndot, ngroups, unsigned(nb), nfin, kmax, types};
+        const GraphKey key{BB.dev, nvec, ngemv, nspmv, nfirst, ndot, unsigned(nb), nfin, kmax, types};
         if (!(BB.step && BB.key == key)) {
             if (BB.step) PB_HIP(hipGraphExecDestroy(BB.step));
             BB.step = nullptr;
@@ -860,39 +950,48 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
             }
         }
     }
-    for (int it = 0; it < maxiter_host && !finished; ++it) {
-        if (graph) PB_HIP(hipGraphLaunch(BB.step, s));
-        else enqueue_step();
-        PB_HIP(hipGetLastError());
-        if ((it + 1) % POLL == 0) {
-            const int slot = polls % 3;
-            PB_HIP(hipMemcpyAsync(BB.pinned + slot, dcount, sizeof(int), hipMemcpyDeviceToHost, s));
-            PB_HIP(hipEventRecord(BB.ev[slot], s));
-            ++polls;
-            if (polls >= 2) {
-                const int old = (polls - 2) % 3; // the copy of the previous poll
-                PB_HIP(hipEventSynchronize(BB.ev[old]));
-                if (BB.pinned[old] >= nb) finished = true;
-            }
-            // a newer copy may already be complete.  A query of a pending
-            // event returns hipErrorNotReady and HIP also records that as the
-            // thread's last error, which the launch checks of the next
-            // iteration would report; it is cleared here (launch errors of
-            // this iteration were checked above).
-            for (int k = 1; k <= 1 && !finished && polls - k >= 0; ++k) {
-                const int sl = (polls - k) % 3;
-                const hipError_t q = hipEventQuery(BB.ev[sl]);
-                if (q == hipErrorNotReady) {
-                    (void)hipGetLastError();
-                    break;
-                }
-                PB_HIP(q);
-                if (BB.pinned[sl] >= nb) finished = true;
-            }
+    // Enqueue steps until the control kernel's word reports every instance
+    // ended, at most DEPTH of them ahead of the step reported.  An instance
+    // that converges on its estimate (FIN) ends with the next step, which is
+    // enqueued by then, so no further one is.
+    const int DEPTH = 2;
+    auto running = [&](int enqueued, int &reported, int &ending) {
+        const unsigned long long v = __atomic_load_n(BB.word, __ATOMIC_ACQUIRE);
+        reported = int(v >> (2 * GCOUNT_BITS));
+        ending = int((v >> GCOUNT_BITS) & GCOUNT_MAX);
+        return int(v & GCOUNT_MAX) < nb && !(enqueued > maxiter_host && reported >= enqueued);
+    };
+    enqueue_end(); // INIT: w = b, V_0
+    PB_HIP(hipGetLastError());
+    int enqueued = 1, reported = 0, ending = 0;
+    for (int spins = 0; running(enqueued, reported, ending);) {
+        if (enqueued <= maxiter_host && enqueued - reported < DEPTH && (ending < nb || enqueued == reported)) {
+            if (graph) PB_HIP(hipGraphLaunch(BB.step, s));
+            else enqueue_step();
+            PB_HIP(hipGetLastError());
+            ++enqueued;
+            spins = 0;
+            continue;
         }
+        if (++spins % 4096) {
+            std::this_thread::yield();
+            continue;
+        }
+        // a drained stream has reported its last step; a device error shows here.
+        // A query of a busy stream leaves hipErrorNotReady as the thread's last
+        // error, which the launch checks would report: it is cleared.
+        const hipError_t q = hipStreamQuery(s);
+        if (q == hipErrorNotReady) {
+            (void)hipGetLastError();
+            continue;
+        }
+        PB_HIP(q);
+        running(enqueued, reported, ending);
+        PB_CHECK(reported >= enqueued, PBFB_EDEVICE, "a Krylov step did not report its end");
     }
-    PB_HIP(hipMemcpyAsync(st.data(), dS, sizeof(GState) * nb, hipMemcpyDeviceToHost, s));
+    PB_HIP(hipMemcpyAsync(BB.stage, dS, sizeof(GState) * nb, hipMemcpyDeviceToHost, s));
     PB_HIP(hipStreamSynchronize(s));
+    std::memcpy(st.data(), BB.stage, sizeof(GState) * nb);
     for (int q = 0; q < nb; ++q) {
         GmresJob &J = *jobs[q];
         J.iters = st[q].total;

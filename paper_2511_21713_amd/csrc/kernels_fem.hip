@@ -644,7 +644,7 @@ void ensure_topology(Problem &p, hipStream_t s)
     A.release();
     p.d_x = A.upload(p.x, s);
     p.d_tet = A.upload(p.tet, s);
-    std::vector<int32_t> sptr, col, n2t_ptr, n2t, slot4, diag, cslot[2];
+    std::vector<int32_t> sptr, col, n2t_ptr, n2t, slot4, diag, cslot[2], nvert[2]; // until the uploads are done
     build_fem_topology(p, sptr, col, n2t_ptr, n2t, slot4, diag, cslot);
     p.nnz = int64_t(col.size());
     p.d_sptr = A.upload(sptr, s);
@@ -682,6 +682,12 @@ void ensure_topology(Problem &p, hipStream_t s)
         S.nrm = A.alloc<double>(3 * T.nt);
         S.area = A.alloc<double>(T.nt);
         S.cslot = w < 2 ? A.upload(cslot[w], s) : nullptr;
+        S.nvert = nullptr;
+        if (w < 2) {
+            nvert[w].assign(p.nn, -1);
+            for (int64_t v = 0; v < T.nv; ++v) nvert[w][T.g[v]] = int32_t(v);
+            S.nvert = A.upload(nvert[w], s);
+        }
         if (w == 2) S.iw = A.alloc<double>(6 * T.nv);
     }
     PB_HIP(hipStreamSynchronize(s));

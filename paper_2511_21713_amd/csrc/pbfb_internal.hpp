@@ -152,6 +152,7 @@ struct SurfaceDev {
     int32_t *itet = nullptr;
     double *iw = nullptr;
     int32_t *mvert = nullptr, *minv = nullptr, *gmv = nullptr; // Morton vertex order (SurfaceTopo)
+    int32_t *nvert = nullptr; // FEM node -> surface vertex, -1 off the surface (Gamma_m, Gamma_s)
     double *qp = nullptr, *nrm = nullptr, *area = nullptr; // original order: 18, 3, 1 per triangle
     // Morton-ordered triangle data for the regular assembly
     int32_t *m_tri = nullptr;
@@ -246,7 +247,7 @@ struct EventTimer {
 enum ScratchSlot {
     SCR_CHK, SCR_TRIF, SCR_Q, SCR_EPART, SCR_UR, SCR_B, SCR_DOT, SCR_XM, SCR_XS, SCR_TPTAU,
     SCR_G0, SCR_G1, SCR_G2, SCR_G3, SCR_G4, SCR_G5, SCR_G6, SCR_G7, SCR_G8, SCR_G9, SCR_G10, SCR_G11, SCR_G12,
-    SCR_BASIS, SCR_BASIS32, SCR_HPART, SCR_HVEC, SCR_NRM, SCR_CNT, SCR_PZ, SCR_PT, SCR_PZB, SCR_PDK, SCR_LMAX, SCR_PCOEF, SCR_TETR, SCR_MF0, SCR_MF1, SCR_MF2, SCR_SYMP0, SCR_SYMP1,
+    SCR_BASIS, SCR_BASIS32, SCR_HPART, SCR_HVEC, SCR_NRM, SCR_PZ, SCR_PT, SCR_PZB, SCR_PDK, SCR_LMAX, SCR_PCOEF, SCR_TETR, SCR_MF0, SCR_MF1, SCR_MF2, SCR_SYMP0, SCR_SYMP1,
     SCR_FM, SCR_PL, SCR_PN, SCR_CGX, SCR_CGV, SCR_PLOC, SCR_TSLOT, SCR_VOL, SCR_SYMP2, SCR_RLOC, SCR_OMEGA,
     SCR_N
 };
@@ -331,7 +332,7 @@ constexpr int SLICE = 64; // FEM rows per sliced-ELL slice: one wavefront
 // Krylov state of a batched GMRES instance (the state word every batched kernel reads)
 // FIN: the cycle ended on the residual estimate; the step only adds the
 // preconditioned update to x (no true-residual apply) and the solve is done
-enum GSt { G_INIT = 0, G_ARN = 1, G_UPD = 2, G_RES = 3, G_DONE = 4, G_FAIL = 5, G_FIN = 6 };
+enum GSt { G_INIT = 0, G_ARN = 1, G_RES = 2, G_DONE = 3, G_FAIL = 4, G_FIN = 5 };
 void build_fem_topology(Problem &p, std::vector<int32_t> &sptr, std::vector<int32_t> &col,
                         std::vector<int32_t> &n2t_ptr, std::vector<int32_t> &n2t, std::vector<int32_t> &slot4,
                         std::vector<int32_t> &diag, std::vector<int32_t> cslot[2]);

@@ -29,11 +29,11 @@ constexpr int SELL_W = 4; // wavefronts per slice (one workgroup of 256 threads)
 constexpr int SELL_U = 4; // entries per lane in flight
 
 // Partial sum of row 64 q + lane over the entries k = wv, wv + 4, ... of
-// slice q.  FEM_ONLY skips the coupling columns (index >= nn).
-template <typename VT, bool FEM_ONLY>
-__device__ inline double sell_part(const int32_t *__restrict__ sptr, const int32_t *__restrict__ col,
-                                   const VT *__restrict__ val, const double *__restrict__ x, int64_t q, int lane,
-                                   int wv, int64_t nn)
+// slice q with input entry x(column).  FEM_ONLY skips the coupling columns
+// (index >= nn).
+template <typename VT, bool FEM_ONLY, typename XF>
+__device__ inline double sell_part_of(const int32_t *__restrict__ sptr, const int32_t *__restrict__ col,
+                                      const VT *__restrict__ val, XF &&x, int64_t q, int lane, int wv, int64_t nn)
 {
     const int32_t b0 = sptr[q], w = (sptr[q + 1] - b0) / 64;
     double acc = 0.0;
@@ -50,12 +50,21 @@ __device__ inline double sell_part(const int32_t *__restrict__ sptr, const int32
         }
         double xv[SELL_U];
 #pragma unroll
-        for (int j = 0; j < SELL_U; ++j) xv[j] = (FEM_ONLY && c[j] >= nn) ? 0.0 : x[c[j]];
+        for (int j = 0; j < SELL_U; ++j) xv[j] = (FEM_ONLY && c[j] >= nn) ? 0.0 : x(c[j]);
 #pragma unroll
         for (int j = 0; j < SELL_U; ++j)
             if (k0 + SELL_W * j < w) acc = fma(double(v[j]), xv[j], acc);
     }
     return acc;
+}
+
+template <typename VT, bool FEM_ONLY>
+__device__ inline double sell_part(const int32_t *__restrict__ sptr, const int32_t *__restrict__ col,
+                                   const VT *__restrict__ val, const double *__restrict__ x, int64_t q, int lane,
+                                   int wv, int64_t nn)
+{
+    return sell_part_of<VT, FEM_ONLY>(
+        sptr, col, val, [x](int32_t c) { return x[c]; }, q, lane, wv, nn);
 }
 
 // Sum of the four wavefront partials of each row of the slice, in order;
