@@ -97,6 +97,62 @@ __device__ inline void gemv_rows(const MT *__restrict__ B, const double *__restr
     }
 }
 
+// Small surfaces (gemv_small): the stored operator lies in the Infinity Cache
+// and a launch is bound by latency, so the 64-row work items of the symmetric
+// use, which leave most CUs without work, and its second launch cost more
+// than the quarter of the bytes they save.  Full rows then, two per wavefront,
+// in the launch that holds the FEM SpMV.  Dense part of one product over both
+// surfaces, FP64 / FP32 storage, symmetric use -> full rows: 642 vertices 21.1
+// -> 7.9 / 21.0 -> 7.0 us, 1 442: 31.2 -> 14.9 / 26.3 -> 10.2, 2 892: 56.5 ->
+// 42.7 / 38.3 -> 23.1, 4 002: 78 -> 99 / 56 -> 47, 5 762: 164 -> 194 / 93 ->
+// 106.  The line lies between the last size that gains (134 MB a surface FP64,
+// 128 MB FP32) and the first that loses (256 MB, 266 MB).
+constexpr int64_t GEMV_SMALL_BYTES = int64_t(160) << 20;
+inline bool gemv_small(int64_t nv, bool f32) { return 2 * nv * nv * (f32 ? 4 : 8) <= GEMV_SMALL_BYTES; }
+constexpr int GSMALL_RW = 2, GSMALL_ROWS = 4 * GSMALL_RW; // rows per wavefront, per workgroup of 256
+
+template <typename MT>
+__device__ inline void gemv_rows_small(const MT *__restrict__ B, const double *__restrict__ x, double *__restrict__ y,
+                                       const int32_t *__restrict__ oidx, int64_t n, int64_t ld, int64_t r0, int tid)
+{
+    constexpr int EL = sizeof(MT) == 8 ? 2 : 4, U = 4;
+    using V = typename GemvLoad<MT>::T;
+    const int lane = tid & 63;
+    const int64_t rw = r0 + GSMALL_RW * (tid >> 6);
+    if (rw >= n) return;
+    const gptr<V> b0 = (gptr<V>)(B + rw * ld), b1 = (gptr<V>)(B + (rw + 1 < n ? rw + 1 : rw) * ld);
+    const gptr<dvec2> xg = (gptr<dvec2>)(x);
+    double a0 = 0.0, a1 = 0.0;
+    const int nc = int(ld / (64 * EL)); // chunks: ld is a multiple of 256
+    for (int c0 = 0; c0 < nc; c0 += U) {
+        V v0[U], v1[U];
+        dvec2 xv[U][EL / 2];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int o = min(c0 + u, nc - 1) * 64 + lane; // a chunk past the end is not used
+            v0[u] = b0[o];
+            v1[u] = b1[o];
+#pragma unroll
+            for (int h = 0; h < EL / 2; ++h) xv[u][h] = xg[o * (EL / 2) + h];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (c0 + u >= nc) break;
+#pragma unroll
+            for (int e = 0; e < EL; ++e) {
+                a0 = fma(double(v0[u][e]), xv[u][e / 2][e % 2], a0);
+                a1 = fma(double(v1[u][e]), xv[u][e / 2][e % 2], a1);
+            }
+        }
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        a0 += __shfl_xor(a0, off);
+        a1 += __shfl_xor(a1, off);
+    }
+    if (lane == 0) y[oidx[rw]] = a0;
+    if (lane == 1 && rw + 1 < n) y[oidx[rw + 1]] = a1;
+}
+
 __device__ inline void gemv_lds_barrier()
 {
     // orders LDS only: loads of the operator stay in flight across it

@@ -263,7 +263,7 @@ __global__ void __launch_bounds__(GEMV_THREADS, gemv_occupancy<MT>()) k_bgemv(co
     const WItem it = wl[blockIdx.x];
     if (!applies(S[it.inst].st)) return;
     const GDesc &d = D[it.inst];
-    if (d.mf || d.f32 != (sizeof(MT) == 4)) return;
+    if (d.f32 != (sizeof(MT) == 4)) return;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int a = it.a & 1; // surface; it.a & 2: K item of the symmetric use
     const int64_t n = a == 0 ? d.nm : d.ns;
@@ -283,8 +283,9 @@ __global__ void __launch_bounds__(GEMV_THREADS, gemv_occupancy<MT>()) k_bgemv(co
 
 // The rest of the apply after k_bgemv, item first + blockIdx: the first nfin
 // items are the second stage of the symmetric use (inst, a = surface, b =
-// first of GFIN_ROWS rows), the others FEM SpMV slices (b = first row), which
-// do not depend on the dense product.
+// first of GFIN_ROWS rows) and the dense rows of small surfaces (a = surface
+// | 2, b = first of GSMALL_ROWS rows), the others FEM SpMV slices (b = first
+// row); only the second stages depend on k_bgemv.
 __global__ void __launch_bounds__(256) k_btail(const WItem *__restrict__ wl, unsigned first, unsigned nfin,
                                                const GDesc *__restrict__ D, const GState *__restrict__ S)
 {
@@ -294,12 +295,19 @@ __global__ void __launch_bounds__(256) k_btail(const WItem *__restrict__ wl, uns
     if (!applies(st)) return;
     const GDesc &d = D[it.inst];
     if (bi < nfin) {
-        if (d.mf || !d.symm[it.a]) return;
-        const int64_t n = it.a == 0 ? d.nm : d.ns;
-        const double *x = it.a == 0 ? d.xm : d.xs;
-        double *y = d.w + d.nn + (it.a == 0 ? 0 : d.nm);
-        gemv_sym_finish(n, static_cast<const double *>(d.symP[it.a]), d.dl_ptr[it.a], d.dl_col[it.a], d.dl_val[it.a],
-                        x, y, it.a == 0 ? d.mvm : d.mvs, it.b, threadIdx.x);
+        const int a = it.a & 1;
+        const int64_t n = a == 0 ? d.nm : d.ns, ld = a == 0 ? d.ldm : d.lds;
+        const double *x = a == 0 ? d.xm : d.xs;
+        double *y = d.w + d.nn + (a == 0 ? 0 : d.nm);
+        const int32_t *oidx = a == 0 ? d.mvm : d.mvs;
+        const void *B = a == 0 ? d.Bm : d.Bs;
+        if (!(it.a & 2))
+            gemv_sym_finish(n, static_cast<const double *>(d.symP[a]), d.dl_ptr[a], d.dl_col[a], d.dl_val[a], x, y,
+                            oidx, it.b, threadIdx.x);
+        else if (d.f32)
+            gemv_rows_small<float>(static_cast<const float *>(B), x, y, oidx, n, ld, it.b, threadIdx.x);
+        else
+            gemv_rows_small<double>(static_cast<const double *>(B), x, y, oidx, n, ld, it.b, threadIdx.x);
         return;
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -755,7 +763,7 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
             d.sp_col[w] = p.surf[w].ring;
             d.sp_val[w] = p.surf[w].spai;
             const SurfaceDev &SD = p.surf[w];
-            d.symm[w] = (!p.bem_mf && SD.sym) ? 1 : 0;
+            d.symm[w] = (!p.bem_mf && SD.sym && !gemv_small(SD.nv, d.f32 != 0)) ? 1 : 0;
             d.symP[w] = d.symm[w] ? scratch<double>(p, w == 0 ? SCR_SYMP0 : SCR_SYMP1,
                                                     size_t(sym_partials_doubles(SD.nv)))
                                   : nullptr;
@@ -807,6 +815,11 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
             std::vector<WItem> kit[2], vit[2];
             for (int a = d.two_field ? 1 : 0; a < 2; ++a) {
                 const int64_t nv = a == 0 ? d.nm : d.ns;
+                if (p.bem_mf) continue; // no stored operator
+                if (gemv_small(nv, d.f32 != 0)) {
+                    for (int64_t r = 0; r < nv; r += GSMALL_ROWS) wl_fin.push_back(WItem{q, a | 2, r});
+                    continue;
+                }
                 for (int64_t r = 0; r < nv; r += GROWS) kit[a].push_back(WItem{q, a | (d.symm[a] ? 2 : 0), r});
                 if (d.symm[a]) {
                     for (int64_t r = (nv - 1) / GROWS * GROWS; r >= 0; r -= GROWS) vit[a].push_back(WItem{q, a, r});
@@ -903,8 +916,8 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
         if (tm) tm->end(s);
         if (tm) tm->begin(T_APPLY, s);
         if (tm) tm->begin(T_GEMV, s);
-        if (types & 1) hipLaunchKernelGGL(k_bgemv<double>, dim3(ngemv), dim3(GEMV_THREADS), 0, s, dgemv, dD, dS);
-        if (types & 2) hipLaunchKernelGGL(k_bgemv<float>, dim3(ngemv), dim3(GEMV_THREADS), 0, s, dgemv, dD, dS);
+        if (ngemv && (types & 1)) hipLaunchKernelGGL(k_bgemv<double>, dim3(ngemv), dim3(GEMV_THREADS), 0, s, dgemv, dD, dS);
+        if (ngemv && (types & 2)) hipLaunchKernelGGL(k_bgemv<float>, dim3(ngemv), dim3(GEMV_THREADS), 0, s, dgemv, dD, dS);
         // matrix-free instances: their own launches, gated by their state word
         for (size_t q = 0; q < jobs.size() && any_mf; ++q) {
             Problem &pq = *jobs[q]->p;

@@ -48,7 +48,7 @@ struct GemvSurf {
     const int32_t *oidx; // output position of each operator row (its vertex)
     void *P; // FP64 column partials of the symmetric use
     int64_t n, ld;
-    int sym, f32;
+    int sym, f32, small; // small: rows in k_rest (gemv_small)
     const int32_t *dptr, *dcol;
     const double *dval;
 };
@@ -74,12 +74,12 @@ __global__ void __launch_bounds__(GEMV_THREADS, gemv_occupancy<MT>()) k_gemv(Gem
         if (rw < S.n) gemv_rows<MT>(B, S.x, S.y, S.oidx, S.n, S.ld, rw, threadIdx.x & 63);
     }
 }
-// the grid of surfaces 0 / 1 (n0 = 0: surface 0 left out)
+// the grid of surfaces 0 / 1 (n0 = 0: surface 0 left out; small surfaces have no items here)
 static GemvGrid gemv_grid(const GemvSurf &S0, int64_t n0, const GemvSurf &S1, int64_t n1)
 {
     GemvGrid W;
-    W.nk0 = (n0 + GSYM - 1) / GSYM;
-    W.nk1 = (n1 + GSYM - 1) / GSYM;
+    W.nk0 = S0.small ? 0 : (n0 + GSYM - 1) / GSYM;
+    W.nk1 = S1.small ? 0 : (n1 + GSYM - 1) / GSYM;
     W.nv0 = S0.sym ? W.nk0 : 0;
     W.nv1 = S1.sym ? W.nk1 : 0;
     W.h0 = gemv_heavy(S0.f32 != 0, W.nv0);
@@ -88,26 +88,37 @@ static GemvGrid gemv_grid(const GemvSurf &S0, int64_t n0, const GemvSurf &S1, in
 }
 static unsigned gemv_items(const GemvGrid &W) { return unsigned(W.nk0 + W.nk1 + W.nv0 + W.nv1); }
 
-// second stage of the symmetric use: transposed column partials and Delta
-__global__ void __launch_bounds__(256) k_gemv_fin(GemvSurf S0, GemvSurf S1, int64_t nb0)
-{
-    const bool s1 = blockIdx.x >= nb0;
-    const GemvSurf &S = s1 ? S1 : S0;
-    if (!S.sym) return;
-    const int64_t i0 = (s1 ? blockIdx.x - nb0 : blockIdx.x) * int64_t(GFIN_ROWS);
-    gemv_sym_finish(S.n, static_cast<const double *>(S.P), S.dptr, S.dcol, S.dval, S.x, S.y, S.oidx, i0, threadIdx.x);
-}
-
-// ---------------------------------------------------------------------------
-// FEM SpMV over the shell rows (sliced ELL): one workgroup per 64-row slice
-// ---------------------------------------------------------------------------
-template <typename VT>
+// The rest of an apply, workgroup first + blockIdx of 256 threads: the second
+// stage of the symmetric use (f items per surface), the rows of small
+// surfaces (s items per surface), then the FEM SpMV (one 64-row slice of the
+// sliced ELL each); only the first depends on k_gemv.
+struct RestGrid {
+    int64_t f0 = 0, f1 = 0, s0 = 0, s1 = 0;
+    int64_t dense() const { return f0 + f1 + s0 + s1; }
+};
+template <typename MT, typename VT>
 __global__ void __launch_bounds__(256)
-    k_spmv(int64_t nrows, const int32_t *__restrict__ sptr, const int32_t *__restrict__ col,
-           const VT *__restrict__ val, const double *__restrict__ x, double *__restrict__ y)
+    k_rest(GemvSurf S0, GemvSurf S1, RestGrid G, int64_t first, int64_t nrows, const int32_t *__restrict__ sptr,
+           const int32_t *__restrict__ col, const VT *__restrict__ val, const double *__restrict__ x,
+           double *__restrict__ y)
 {
+    int64_t bi = first + blockIdx.x;
+    if (bi < G.f0 + G.f1) {
+        const GemvSurf &S = bi < G.f0 ? S0 : S1;
+        const int64_t i0 = (bi < G.f0 ? bi : bi - G.f0) * GFIN_ROWS;
+        gemv_sym_finish(S.n, static_cast<const double *>(S.P), S.dptr, S.dcol, S.dval, S.x, S.y, S.oidx, i0,
+                        threadIdx.x);
+        return;
+    }
+    bi -= G.f0 + G.f1;
+    if (bi < G.s0 + G.s1) {
+        const GemvSurf &S = bi < G.s0 ? S0 : S1;
+        gemv_rows_small<MT>(static_cast<const MT *>(S.B), S.x, S.y, S.oidx, S.n, S.ld,
+                            (bi < G.s0 ? bi : bi - G.s0) * GSMALL_ROWS, threadIdx.x);
+        return;
+    }
+    const int64_t q = bi - G.s0 - G.s1;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int64_t q = blockIdx.x;
     const double part = sell_part<VT, false>(sptr, col, val, x, q, lane, wv, nrows);
     const double s = sell_reduce(part, lane, wv);
     const int64_t row = q * SLICE + lane;
@@ -197,31 +208,45 @@ static GemvSurf gemv_surf(Problem &p, int w, const double *x, double *y, double 
     G.oidx = D.mvert;
     G.n = D.nv;
     G.ld = bem_ld(D.nv);
-    G.sym = D.sym ? 1 : 0;
+    G.small = gemv_small(D.nv, p.precision == PBFB_MIXED) ? 1 : 0;
+    G.sym = D.sym && !G.small ? 1 : 0;
     G.f32 = p.precision == PBFB_MIXED ? 1 : 0;
-    G.P = D.sym ? P : nullptr;
+    G.P = G.sym ? P : nullptr;
     G.dptr = D.d_ptr;
     G.dcol = D.d_col;
     G.dval = D.d_val;
     return G;
 }
 
-// both surfaces' rows in one launch; skip_m leaves out Gamma_m (two-field form)
-static void gemv_launch(Problem &p, const ApplyBufs &bf, double *y, hipStream_t s, bool skip_m, bool timed)
+// dense rows of surfaces 0 / 1 (n0 = 0 or n1 = 0 leaves one out) up to the
+// work that k_rest takes, whose grid is returned
+static RestGrid gemv_launch(bool f32, const GemvSurf &S0, int64_t n0, const GemvSurf &S1, int64_t n1, hipStream_t s)
 {
-    const SurfaceDev &M = p.surf[0], &S = p.surf[1];
-    const GemvSurf G0 = gemv_surf(p, 0, bf.xm, y + p.nn, bf.P[0]), G1 = gemv_surf(p, 1, bf.xs, y + p.nn + M.nv, bf.P[1]);
-    const GemvGrid W = gemv_grid(G0, skip_m ? 0 : M.nv, G1, S.nv);
-    if (timed) p.timer.begin(T_GEMV, s);
-    if (p.precision == PBFB_MIXED)
-        hipLaunchKernelGGL(k_gemv<float>, dim3(gemv_items(W)), dim3(GEMV_THREADS), 0, s, G0, G1, W);
-    else
-        hipLaunchKernelGGL(k_gemv<double>, dim3(gemv_items(W)), dim3(GEMV_THREADS), 0, s, G0, G1, W);
-    if (G0.sym || G1.sym) {
-        const int64_t f0 = skip_m ? 0 : (M.nv + GFIN_ROWS - 1) / GFIN_ROWS, f1 = (S.nv + GFIN_ROWS - 1) / GFIN_ROWS;
-        hipLaunchKernelGGL(k_gemv_fin, dim3(unsigned(f0 + f1)), dim3(256), 0, s, G0, G1, f0);
+    const GemvGrid W = gemv_grid(S0, n0, S1, n1);
+    if (gemv_items(W)) {
+        if (f32) hipLaunchKernelGGL(k_gemv<float>, dim3(gemv_items(W)), dim3(GEMV_THREADS), 0, s, S0, S1, W);
+        else hipLaunchKernelGGL(k_gemv<double>, dim3(gemv_items(W)), dim3(GEMV_THREADS), 0, s, S0, S1, W);
     }
-    if (timed) p.timer.end(s);
+    RestGrid G;
+    if (S0.sym) G.f0 = (n0 + GFIN_ROWS - 1) / GFIN_ROWS;
+    if (S1.sym) G.f1 = (n1 + GFIN_ROWS - 1) / GFIN_ROWS;
+    if (S0.small) G.s0 = (n0 + GSMALL_ROWS - 1) / GSMALL_ROWS;
+    if (S1.small) G.s1 = (n1 + GSMALL_ROWS - 1) / GSMALL_ROWS;
+    return G;
+}
+
+// workgroups first .. first + count - 1 of the rest; the SpMV reads VT values
+template <typename VT>
+static void rest_launch(const Problem &p, const GemvSurf &S0, const GemvSurf &S1, const RestGrid &G, int64_t first,
+                        int64_t count, const VT *val, const double *x, double *y, hipStream_t s)
+{
+    if (count == 0) return;
+    if (p.precision == PBFB_MIXED)
+        hipLaunchKernelGGL((k_rest<float, VT>), dim3(unsigned(count)), dim3(256), 0, s, S0, S1, G, first, p.nn,
+                           p.d_sptr, p.d_col, val, x, y);
+    else
+        hipLaunchKernelGGL((k_rest<double, VT>), dim3(unsigned(count)), dim3(256), 0, s, S0, S1, G, first, p.nn,
+                           p.d_sptr, p.d_col, val, x, y);
 }
 
 // bufs: caller-provided work buffers (no allocation, no timing), else the
@@ -247,27 +272,34 @@ static void apply_impl(Problem &p, const double *x, double *y, bool with_jac, hi
     hipLaunchKernelGGL(k_pack, dim3(nb_(std::max(ldm, lds), 256)), dim3(256), 0, s, p.nn, M.nv, S.nv, ldm, lds,
                        p.bem_mf ? M.g : M.gmv, p.bem_mf ? nullptr : M.mvert, p.bem_mf ? S.g : S.gmv,
                        p.bem_mf ? nullptr : S.mvert, x, bf.xm, bf.xs);
+    if (timed) p.timer.begin(T_GEMV, s);
+    GemvSurf G0{}, G1{};
+    RestGrid R;
     if (p.bem_mf) {
         PB_CHECK(!bufs, PBFB_EINVAL, "matrix-free boundary operators need the problem's own work buffers");
-        if (timed) p.timer.begin(T_GEMV, s);
         mf_apply(p, 0, bf.xm, y + p.nn, nullptr, s);
         mf_apply(p, 1, bf.xs, y + p.nn + p.surf[0].nv, nullptr, s);
-        if (timed) p.timer.end(s);
     } else {
-        gemv_launch(p, bf, y, s, p.two_field(), timed);
+        G0 = gemv_surf(p, 0, bf.xm, y + p.nn, bf.P[0]);
+        G1 = gemv_surf(p, 1, bf.xs, y + p.nn + M.nv, bf.P[1]);
+        R = gemv_launch(p.precision == PBFB_MIXED, G0, p.two_field() ? 0 : M.nv, G1, S.nv, s);
     }
     // two-field form: lambda_m is not an unknown of the solve; its row is the identity
     if (p.two_field())
         PB_HIP(hipMemcpyAsync(y + p.nn, x + p.nn, sizeof(double) * M.nv, hipMemcpyDeviceToDevice, s));
-    if (timed) p.timer.begin(T_SPMV, s);
-    const unsigned g = nb_(p.nn, SLICE);
-    if (!with_jac)
-        hipLaunchKernelGGL(k_spmv<double>, dim3(g), dim3(256), 0, s, p.nn, p.d_sptr, p.d_col, p.d_val0, x, y);
-    else if (p.precision == PBFB_MIXED)
-        hipLaunchKernelGGL(k_spmv<float>, dim3(g), dim3(256), 0, s, p.nn, p.d_sptr, p.d_col, p.d_val32, x, y);
-    else
-        hipLaunchKernelGGL(k_spmv<double>, dim3(g), dim3(256), 0, s, p.nn, p.d_sptr, p.d_col, p.d_val, x, y);
-    if (timed) {
+    auto rest = [&](int64_t first, int64_t count) {
+        if (!with_jac) rest_launch(p, G0, G1, R, first, count, p.d_val0, x, y, s);
+        else if (p.precision == PBFB_MIXED) rest_launch(p, G0, G1, R, first, count, p.d_val32, x, y, s);
+        else rest_launch(p, G0, G1, R, first, count, p.d_val, x, y, s);
+    };
+    const int64_t slices = nb_(p.nn, SLICE);
+    if (!timed) {
+        rest(0, R.dense() + slices);
+    } else { // the timed classes apart
+        rest(0, R.dense());
+        p.timer.end(s);
+        p.timer.begin(T_SPMV, s);
+        rest(R.dense(), slices);
         p.timer.end(s); // spmv
         p.timer.end(s); // apply
     }
@@ -333,13 +365,8 @@ static void gemv_m(Problem &p, int w, const double *xm, double *y, hipStream_t s
                                  p.surf[w].sym ? scratch<double>(p, w == 0 ? SCR_SYMP0 : SCR_SYMP2,
                                                                  sym_partials_doubles(p.surf[w].nv))
                                                : nullptr);
-    const int64_t f0 = (G.n + GFIN_ROWS - 1) / GFIN_ROWS;
-    const GemvGrid W = gemv_grid(G, G.n, G, 0);
-    if (p.precision == PBFB_MIXED)
-        hipLaunchKernelGGL(k_gemv<float>, dim3(gemv_items(W)), dim3(GEMV_THREADS), 0, s, G, G, W);
-    else
-        hipLaunchKernelGGL(k_gemv<double>, dim3(gemv_items(W)), dim3(GEMV_THREADS), 0, s, G, G, W);
-    if (G.sym) hipLaunchKernelGGL(k_gemv_fin, dim3(unsigned(f0)), dim3(256), 0, s, G, G, f0);
+    const RestGrid R = gemv_launch(p.precision == PBFB_MIXED, G, G.n, G, 0, s);
+    rest_launch(p, G, G, R, 0, R.dense(), p.d_val0, xm, y, s); // no SpMV slices
 }
 
 // CG scalars kept on the device (sc[0] = r.z, sc[1] = alpha, sc[2] = beta,

@@ -103,3 +103,29 @@ def test_gram_schmidt_chunks_around_their_edge(ctx, layers):
     print(f"  unknowns {g.n}: {rel:.2e} after {r['gmres_lin']} steps", flush=True)
     assert rel < 1.1e-8  # 1e-8 on the estimate, which differs from the residual by rounding
     g.close()
+
+
+# full rows beside the SpMV below 160 MiB a surface (FP64: n = 17 the last, 18
+# the first past it; FP32: 21 and 22), the symmetric use above; n = 1: one
+# ragged workgroup
+@pytest.mark.parametrize("n,precision", [(1, 0), (1, 1), (6, 0), (6, 1), (17, 0), (18, 0), (21, 1), (22, 1)])
+def test_dense_rows_of_either_form_match_the_stored_blocks(ctx, n, precision):
+    """The surface rows of a product against numpy's with the exported blocks:
+    FP64 sums of up to 1e4 terms, 1e-13 in the 2-norm, in both precisions (the
+    export is what is stored)."""
+    import paper_2511_21713_amd as pb
+    prob = pbgen.make_problem(n=n, a=6.0, c=9.0, bump=n > 2, t=3.0, L=1, helix=0, partials=0, kappa=0.2, seed=(9, n),
+                              center_charge=1.0)
+    g = pb.Problem.from_inputs(ctx, prob, precision=precision)
+    g.set_tile_shape(16, 16)
+    rng = np.random.default_rng(n)
+    v, phi = rng.standard_normal(g.n), rng.standard_normal(g.n)
+    y = g.apply_jacobian(pb.LIN, phi, v)
+    nn, nm = g.n_nodes, g.n_m
+    for surf, ids, lo in ((0, np.unique(prob.tri_m), nn), (1, np.unique(prob.tri_s), nn + nm)):
+        V, K = g.export_bem(surf)
+        ref = K @ v[ids] + V @ v[lo:lo + ids.size]
+        e = rel2(y[lo:lo + ids.size], ref)
+        print(f"  n {n} precision {precision} surface {surf}: {e:.2e}", flush=True)
+        assert e < 1e-13
+    g.close()
