@@ -175,6 +175,21 @@ __device__ inline void prec_final(const GDesc &d, const GState &s, int64_t k, do
     }
 }
 
+// surface row k of the preconditioner stage
+__device__ inline void prec_surface(const GDesc &d, const GState &s, int64_t k)
+{
+    double zv = 0.0;
+    if (d.pc == PBFB_PC_CHEB_SPAI) {
+        const int w = k < d.nn + d.nm ? 0 : 1;
+        const int64_t off = d.nn + (w == 0 ? 0 : d.nm), i = k - off;
+        for (int32_t e = d.sp_ptr[w][i]; e < d.sp_ptr[w][i + 1]; ++e)
+            zv = fma(d.sp_val[w][e], pc_src(d, s, off + d.sp_col[w][e]), zv);
+    } else {
+        zv = d.dinv[k] * pc_src(d, s, k);
+    }
+    prec_final(d, s, k, zv);
+}
+
 // Work items: a = 0: the 64 FEM rows from b, a = 1: the 256 surface rows from
 // nn + b.  Surface rows: the approximate inverse.  FEM rows: the first two
 // Chebyshev terms in one pass -- the first, z_0 = D^-1 src / theta, is
@@ -190,17 +205,7 @@ __global__ void __launch_bounds__(256) k_bfirst(const WItem *__restrict__ wl, co
     const bool cheb = d.pc == PBFB_PC_CHEB_SPAI;
     if (it.a) {
         const int64_t k = d.nn + it.b + threadIdx.x;
-        if (k >= d.n) return;
-        double zv = 0.0;
-        if (cheb) {
-            const int w = k < d.nn + d.nm ? 0 : 1;
-            const int64_t off = d.nn + (w == 0 ? 0 : d.nm), i = k - off;
-            for (int32_t e = d.sp_ptr[w][i]; e < d.sp_ptr[w][i + 1]; ++e)
-                zv = fma(d.sp_val[w][e], pc_src(d, s, off + d.sp_col[w][e]), zv);
-        } else {
-            zv = d.dinv[k] * pc_src(d, s, k);
-        }
-        prec_final(d, s, k, zv);
+        if (k < d.n) prec_surface(d, s, k);
         return;
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -250,6 +255,80 @@ __global__ void __launch_bounds__(256) k_bcheb(const WItem *__restrict__ wl, con
     const double zv = zp[row] + dv;
     if (step == d.cheb_k - 1) prec_final(d, s, row, zv);
     else zn[row] = zv;
+}
+
+// The whole preconditioner stage of a small FEM block (prec_tiny) in one
+// workgroup: the terms follow each other in LDS, with a barrier where k_bcheb
+// needs a launch.  The matrix is read once, into registers (two rows of up
+// to TINY_W FEM entries per thread), and a term is then LDS gathers on one CU:
+// 23 terms of 1 134 rows take 44 us, as launches about 100 (sphere of 320
+// triangles: 8.8 -> 6.8 ms per solve).  With the values streamed from L2 at
+// every term one workgroup was slower than the launches (11.0 ms).
+constexpr int TINY_T = 1024, TINY_H = 2, TINY_ROWS = TINY_T * TINY_H, TINY_W = 16;
+static bool prec_tiny(const Problem &p, int pc, int cheb_k)
+{
+    return pc == PBFB_PC_CHEB_SPAI && cheb_k >= 2 && p.nn <= TINY_ROWS && p.max_fem <= TINY_W;
+}
+template <typename VT>
+__device__ inline void tiny_terms(const GDesc &d, const GState &s, double (&zs)[2][TINY_ROWS])
+{
+    const int tid = threadIdx.x, nn = int(d.nn);
+    const VT *val = static_cast<const VT *>(d.val);
+    VT v[TINY_H][TINY_W];
+    uint32_t c2[TINY_H][TINY_W / 2]; // two 16-bit columns each
+    double src[TINY_H], di[TINY_H], dk[TINY_H];
+#pragma unroll
+    for (int h = 0; h < TINY_H; ++h) {
+        const int r = tid + h * TINY_T;
+        const bool in = r < nn;
+        src[h] = in ? pc_src(d, s, r) : 0.0;
+        di[h] = in ? d.dinv[r] : 0.0;
+        dk[h] = di[h] * src[h] / d.coef[0];
+        zs[0][r] = dk[h];
+        const int b = in ? d.sptr[r / SLICE] : 0, w = in ? (d.sptr[r / SLICE + 1] - b) / SLICE : 0;
+#pragma unroll
+        for (int k = 0; k < TINY_W; ++k) {
+            // past the row, and coupling columns (after the FEM ones): the row itself with value 0
+            const int e = b + SLICE * (k < w ? k : 0) + r % SLICE;
+            const int32_t c = k < w ? d.col[e] : nn;
+            v[h][k] = c < nn ? val[e] : VT(0);
+            const uint32_t cc = uint32_t(c < nn ? c : r);
+            if (k % 2 == 0) c2[h][k / 2] = cc;
+            else c2[h][k / 2] |= cc << 16;
+        }
+    }
+    __syncthreads();
+    for (int step = 1; step < d.cheb_k; ++step) {
+        const double *zp = zs[(step - 1) & 1];
+        double *zn = zs[step & 1];
+        const double c0 = d.coef[2 * step], c1 = d.coef[2 * step + 1];
+#pragma unroll
+        for (int h = 0; h < TINY_H; ++h) {
+            const int r = tid + h * TINY_T;
+            if (h * TINY_T >= nn) break; // uniform
+            double acc = 0.0;
+#pragma unroll
+            for (int k = 0; k < TINY_W; ++k)
+                acc = fma(double(v[h][k]), zp[k % 2 == 0 ? c2[h][k / 2] & 0xffff : c2[h][k / 2] >> 16], acc);
+            dk[h] = c0 * dk[h] + c1 * di[h] * (src[h] - acc);
+            const double zv = zp[r] + dk[h];
+            zn[r] = zv;
+            if (step == d.cheb_k - 1 && r < nn) prec_final(d, s, r, zv);
+        }
+        __syncthreads();
+    }
+}
+__global__ void __launch_bounds__(TINY_T) k_btiny(const WItem *__restrict__ wl, const GDesc *__restrict__ D,
+                                                  const GState *__restrict__ S)
+{
+    __shared__ double zs[2][TINY_ROWS];
+    const WItem it = wl[blockIdx.x];
+    const GState s = S[it.inst];
+    if (!prec_active(s.st)) return;
+    const GDesc &d = D[it.inst];
+    for (int64_t k = d.nn + threadIdx.x; k < d.n; k += TINY_T) prec_surface(d, s, k);
+    if (d.f32) tiny_terms<float>(d, s, zs);
+    else tiny_terms<double>(d, s, zs);
 }
 
 // work item: inst, a = interface (0/1), b = first row of the workgroup.  One
@@ -666,12 +745,12 @@ __global__ void __launch_bounds__(256) k_bnext(const WItem *__restrict__ wl, con
 // a captured Krylov step is valid for the same device buffer and launch shapes
 struct GraphKey {
     void *dev = nullptr;
-    unsigned nvec = 0, ngemv = 0, nspmv = 0, nfirst = 0, ndot = 0, nb = 0, nfin = 0;
+    unsigned nvec = 0, ngemv = 0, nspmv = 0, ncheb = 0, nfirst = 0, ntiny = 0, ndot = 0, nb = 0, nfin = 0;
     int kmax = 0, types = 0; // types: bit 0 FP64 operators present, bit 1 FP32
     bool operator==(const GraphKey &o) const
     {
-        return dev == o.dev && nvec == o.nvec && ngemv == o.ngemv && nspmv == o.nspmv && nfirst == o.nfirst &&
-               ndot == o.ndot && nb == o.nb && nfin == o.nfin && kmax == o.kmax && types == o.types;
+        return dev == o.dev && nvec == o.nvec && ngemv == o.ngemv && nspmv == o.nspmv && ncheb == o.ncheb &&
+               nfirst == o.nfirst && ntiny == o.ntiny && ndot == o.ndot && nb == o.nb && nfin == o.nfin && kmax == o.kmax && types == o.types;
     }
 };
 
@@ -723,7 +802,7 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
     if (nb == 0) return;
     std::vector<GDesc> desc(nb);
     std::vector<GState> st(nb);
-    std::vector<WItem> wl_vec, wl_gemv, wl_spmv, wl_surf, wl_dot, wl_fin;
+    std::vector<WItem> wl_vec, wl_gemv, wl_spmv, wl_cheb, wl_surf, wl_tiny, wl_dot, wl_fin;
     // GEMV items in the order of gemv_item, over the batch: the heavy V items
     // of every instance, then the K and full-row items, then the other V items
     std::vector<WItem> wl_gemv_k, wl_gemv_v;
@@ -776,7 +855,6 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
         d.zb = scratch<double>(p, SCR_PZB, p.nn);
         d.dk = scratch<double>(p, SCR_PDK, p.nn);
         d.coef = scratch<double>(p, SCR_PCOEF, 2 * 64 + 2);
-        if (J.pc == PBFB_PC_CHEB_SPAI) kmax = std::max(kmax, J.cheb_k);
         d.vf32 = J.basis32 && p.precision == PBFB_MIXED;
         if (d.vf32) d.V = scratch<float>(p, SCR_BASIS32, size_t(m + 1) * n);
         else d.V = scratch<double>(p, SCR_BASIS, size_t(m + 1) * n);
@@ -840,21 +918,28 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
             alternate(vit[0], h0, vit[0].size(), vit[1], h1, vit[1].size(), wl_gemv_v);
         }
         for (int64_t r = 0; r < p.nn; r += SLICE) wl_spmv.push_back(WItem{q, 0, r});
-        for (int64_t k = 0; k < n - p.nn; k += CH) wl_surf.push_back(WItem{q, 1, k});
+        if (prec_tiny(p, J.pc, J.cheb_k)) {
+            wl_tiny.push_back(WItem{q, 0, 0});
+        } else {
+            for (int64_t r = 0; r < p.nn; r += SLICE) wl_cheb.push_back(WItem{q, 0, r});
+            for (int64_t k = 0; k < n - p.nn; k += CH) wl_surf.push_back(WItem{q, 1, k});
+            if (J.pc == PBFB_PC_CHEB_SPAI) kmax = std::max(kmax, J.cheb_k);
+        }
         maxiter_host = std::max(maxiter_host, J.maxit + J.maxit / std::max(m, 1) + 4);
     }
     wl_gemv.insert(wl_gemv.end(), wl_gemv_k.begin(), wl_gemv_k.end());
     wl_gemv.insert(wl_gemv.end(), wl_gemv_v.begin(), wl_gemv_v.end());
-    // k_btail: the second stage of the symmetric use, then the SpMV slices;
-    // k_bfirst: the SpMV slices, then the surface rows
+    // k_btail: the dense items, then the SpMV slices; k_bfirst: the FEM slices
+    // of the instances that are not tiny (k_bcheb's list), then the surface rows
     const unsigned nvec = unsigned(wl_vec.size()), ngemv = unsigned(wl_gemv.size()),
-                   nspmv = unsigned(wl_spmv.size()), nfirst = unsigned(wl_spmv.size() + wl_surf.size()),
+                   nspmv = unsigned(wl_spmv.size()), ncheb = unsigned(wl_cheb.size()),
+                   nfirst = ncheb + unsigned(wl_surf.size()), ntiny = unsigned(wl_tiny.size()),
                    ndot = unsigned(wl_dot.size()), nfin = unsigned(wl_fin.size());
     PB_CHECK(nb <= GCOUNT_MAX, PBFB_EINVAL, "too many instances in one batch");
     // descriptors, states, counters and work lists: one pinned block, one copy
     BatchBuffers &BB = batch_buffers();
-    const size_t items = wl_vec.size() + wl_gemv.size() + wl_fin.size() + wl_spmv.size() + wl_surf.size() +
-                         wl_dot.size();
+    const size_t items = wl_vec.size() + wl_gemv.size() + wl_fin.size() + wl_spmv.size() + nfirst +
+                         ntiny + wl_dot.size();
     const size_t bytes = (sizeof(GDesc) + sizeof(GState)) * nb + sizeof(GCount) + sizeof(WItem) * items + 512;
     BB.reserve(bytes);
     // the block and the reported word belong to this call until its stream has drained
@@ -881,8 +966,9 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
     GCount *dC = static_cast<GCount *>(put(&zero, sizeof(zero)));
     WItem *dvec = put_items({&wl_vec});
     WItem *dgemv = put_items({&wl_gemv});
-    WItem *dtail = put_items({&wl_fin, &wl_spmv, &wl_surf});
-    WItem *dspmv = dtail + nfin; // the slices, followed by the surface rows
+    WItem *dtail = put_items({&wl_fin, &wl_spmv});
+    WItem *dfirst = put_items({&wl_cheb, &wl_surf});
+    WItem *dtiny = put_items({&wl_tiny});
     WItem *ddot = put_items({&wl_dot});
     PB_HIP(hipMemcpyAsync(BB.dev, BB.stage, cur, hipMemcpyHostToDevice, s));
     __atomic_store_n(BB.word, 0ull, __ATOMIC_RELEASE);
@@ -910,9 +996,10 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
     // one Krylov step of the whole batch
     auto enqueue_step = [&]() {
         if (tm) tm->begin(T_PREC, s);
-        hipLaunchKernelGGL(k_bfirst, dim3(nfirst), dim3(256), 0, s, dspmv, dD, dS);
+        if (ntiny) hipLaunchKernelGGL(k_btiny, dim3(ntiny), dim3(TINY_T), 0, s, dtiny, dD, dS);
+        if (nfirst) hipLaunchKernelGGL(k_bfirst, dim3(nfirst), dim3(256), 0, s, dfirst, dD, dS);
         for (int step = 2; step < kmax; ++step)
-            hipLaunchKernelGGL(k_bcheb, dim3(nspmv), dim3(256), 0, s, dspmv, dD, dS, step);
+            hipLaunchKernelGGL(k_bcheb, dim3(ncheb), dim3(256), 0, s, dfirst, dD, dS, step);
         if (tm) tm->end(s);
         if (tm) tm->begin(T_APPLY, s);
         if (tm) tm->begin(T_GEMV, s);
@@ -946,7 +1033,7 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
     bool graph = !tm && !any_mf; // matrix-free launches carry per-instance pointers: not captured
     for (auto *J : jobs) graph = graph && J->graph;
     if (graph) {
-        const GraphKey key{BB.dev, nvec, ngemv, nspmv, nfirst, ndot, unsigned(nb), nfin, kmax, types};
+        const GraphKey key{BB.dev, nvec, ngemv, nspmv, ncheb, nfirst, ntiny, ndot, unsigned(nb), nfin, kmax, types};
         if (!(BB.step && BB.key == key)) {
             if (BB.step) PB_HIP(hipGraphExecDestroy(BB.step));
             BB.step = nullptr;

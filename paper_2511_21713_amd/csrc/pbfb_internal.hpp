@@ -300,6 +300,7 @@ struct Problem {
     float *d_val32 = nullptr;
     int64_t nnz = 0;     // stored entries (with the slice padding)
     int64_t nnz_row = 0; // nonzeros of the rows (without it)
+    int max_fem = 0;     // most FEM columns of a row
     double *d_b = nullptr; // right-hand side, length n
     int *d_bad = nullptr;
     SurfaceDev surf[NSURF];

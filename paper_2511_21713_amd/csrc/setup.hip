@@ -264,6 +264,7 @@ void build_fem_topology(Problem &p, std::vector<int32_t> &sptr, std::vector<int3
     // coupling columns of the triangles at it (surface nodes), ascending
     std::vector<int32_t> rowptr(nn + 1, 0), rc;
     std::vector<int32_t> cols;
+    p.max_fem = 0;
     for (int64_t a = 0; a < nn; ++a) {
         cols.clear();
         for (int32_t e = n2t_ptr[a]; e < n2t_ptr[a + 1]; ++e) {
@@ -281,6 +282,7 @@ void build_fem_topology(Problem &p, std::vector<int32_t> &sptr, std::vector<int3
         }
         std::sort(cols.begin(), cols.end());
         cols.erase(std::unique(cols.begin(), cols.end()), cols.end());
+        p.max_fem = std::max(p.max_fem, int(std::lower_bound(cols.begin(), cols.end(), int32_t(nn)) - cols.begin()));
         rc.insert(rc.end(), cols.begin(), cols.end());
         rowptr[a + 1] = int32_t(rc.size());
     }
