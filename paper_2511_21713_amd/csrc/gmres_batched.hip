@@ -796,6 +796,30 @@ static BatchBuffers &batch_buffers()
     return B;
 }
 
+// Workgroups go to the eight XCDs in turn, each with its own L2: the item list
+// whose first item is workgroup `first` of its launch, reordered so that every
+// XCD gets a contiguous eighth.  Neighbouring slices gather the same input
+// entries, and each slice returns to the same XCD in every launch (5 120
+// triangles FP64 24.0 -> 23.4 ms per solve, 20 480: 105.3 -> 104.7).
+static void xcd_order(std::vector<WItem> &v, size_t first)
+{
+    constexpr size_t NX = 8;
+    const size_t n = v.size();
+    std::vector<WItem> out;
+    out.reserve(n);
+    size_t next[NX], end[NX];
+    for (size_t x = 0; x < NX; ++x) {
+        next[x] = n * x / NX;
+        end[x] = n * (x + 1) / NX;
+    }
+    for (size_t i = 0; i < n; ++i) {
+        size_t x = (first + i) % NX;
+        while (next[x] == end[x]) x = (x + 1) % NX; // the last round
+        out.push_back(v[next[x]++]);
+    }
+    v.swap(out);
+}
+
 void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
 {
     const int nb = int(jobs.size());
@@ -929,6 +953,8 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
     }
     wl_gemv.insert(wl_gemv.end(), wl_gemv_k.begin(), wl_gemv_k.end());
     wl_gemv.insert(wl_gemv.end(), wl_gemv_v.begin(), wl_gemv_v.end());
+    xcd_order(wl_cheb, 0);
+    xcd_order(wl_spmv, wl_fin.size());
     // k_btail: the dense items, then the SpMV slices; k_bfirst: the FEM slices
     // of the instances that are not tiny (k_bcheb's list), then the surface rows
     const unsigned nvec = unsigned(wl_vec.size()), ngemv = unsigned(wl_gemv.size()),
