@@ -69,6 +69,7 @@ struct GDesc {
     // FEM node -> surface vertex and surface vertex -> operator index (null: the same), per surface
     const int32_t *nvert[2], *minv[2];
     const int32_t *sptr, *col; // FEM rows, sliced ELL
+    SellLong lng;              // its long rows
     const void *val;
     int64_t nn, n;
     const double *dinv;
@@ -113,6 +114,16 @@ __device__ inline double vget(const GDesc &d, int64_t i, int64_t k)
 template <typename VT> __device__ inline const VT *vcol(const GDesc &d, int64_t i)
 {
     return static_cast<const VT *>(d.V) + i * d.n;
+}
+
+// product of the FEM rows of slice q with the input x(column), valid in wavefront 0
+template <bool FEM_ONLY, typename XF>
+__device__ inline double fem_rows(const GDesc &d, XF &&x, int64_t q, int lane, int wv)
+{
+    return d.f32 ? sell_rows<float, FEM_ONLY>(d.sptr, d.lng, d.col, static_cast<const float *>(d.val), x, q, lane, wv,
+                                              d.nn)
+                 : sell_rows<double, FEM_ONLY>(d.sptr, d.lng, d.col, static_cast<const double *>(d.val), x, q, lane, wv,
+                                               d.nn);
 }
 
 // ---------------------------------------------------------------------------
@@ -217,11 +228,7 @@ __global__ void __launch_bounds__(256) k_bfirst(const WItem *__restrict__ wl, co
     }
     const double theta = d.coef[0];
     auto z0 = [&](int64_t c) { return d.dinv[c] * pc_src(d, s, c) / theta; };
-    const double part = d.f32 ? sell_part_of<float, true>(d.sptr, d.col, static_cast<const float *>(d.val), z0,
-                                                          it.b / SLICE, lane, wv, d.nn)
-                              : sell_part_of<double, true>(d.sptr, d.col, static_cast<const double *>(d.val), z0,
-                                                           it.b / SLICE, lane, wv, d.nn);
-    const double acc = sell_reduce(part, lane, wv);
+    const double acc = fem_rows<true>(d, z0, it.b / SLICE, lane, wv);
     if (wv != 0 || row >= d.nn) return;
     const double zp = z0(row);
     const double dv = d.coef[2] * zp + d.coef[3] * d.dinv[row] * (pc_src(d, s, row) - acc);
@@ -244,11 +251,7 @@ __global__ void __launch_bounds__(256) k_bcheb(const WItem *__restrict__ wl, con
     const int64_t q = it.b / SLICE, row = it.b + lane;
     const double *zp = ((d.cheb_k - step) % 2 == 0) ? d.z : d.zb; // term step - 1
     double *zn = ((d.cheb_k - 1 - step) % 2 == 0) ? d.z : d.zb;
-    const double part = d.f32 ? sell_part<float, true>(d.sptr, d.col, static_cast<const float *>(d.val), zp, q,
-                                                       lane, wv, d.nn)
-                              : sell_part<double, true>(d.sptr, d.col, static_cast<const double *>(d.val), zp, q,
-                                                        lane, wv, d.nn);
-    const double acc = sell_reduce(part, lane, wv);
+    const double acc = fem_rows<true>(d, [zp](int64_t c) { return zp[c]; }, q, lane, wv);
     if (wv != 0 || row >= d.nn) return;
     const double dv = d.coef[2 * step] * d.dk[row] + d.coef[2 * step + 1] * d.dinv[row] * (pc_src(d, s, row) - acc);
     d.dk[row] = dv;
@@ -392,11 +395,7 @@ __global__ void __launch_bounds__(256) k_btail(const WItem *__restrict__ wl, uns
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t q = it.b / SLICE, row = it.b + lane;
     const double *in = st == G_ARN ? d.z : d.x;
-    const double part = d.f32 ? sell_part<float, false>(d.sptr, d.col, static_cast<const float *>(d.val), in, q,
-                                                        lane, wv, d.nn)
-                              : sell_part<double, false>(d.sptr, d.col, static_cast<const double *>(d.val), in, q,
-                                                         lane, wv, d.nn);
-    const double acc = sell_reduce(part, lane, wv);
+    const double acc = fem_rows<false>(d, [in](int64_t c) { return in[c]; }, q, lane, wv);
     if (wv == 0 && row < d.nn) d.w[row] = acc;
 }
 
@@ -851,6 +850,7 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
         d.mvs = p.bem_mf ? nullptr : p.surf[1].mvert;
         d.sptr = p.d_sptr;
         d.col = p.d_col;
+        d.lng = p.fr.sell();
         d.val = d.f32 ? static_cast<const void *>(p.d_val32) : static_cast<const void *>(p.d_val);
         d.nn = p.nn;
         d.n = n;

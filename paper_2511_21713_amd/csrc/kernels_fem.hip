@@ -1,11 +1,10 @@
 // Geometry, shell FEM (stiffness, reaction terms by row gather), surface mass
 // coupling, Coulomb load, charge validation and the solvation energy pieces.
 //
-// Every FEM kernel is "row owned": one thread per FEM node visits the tets
-// around that node and adds the node's own row/entry, so no two threads ever
-// write the same value (deterministic, no atomics).  Each tet is therefore
-// evaluated once per corner; the reaction terms are cheap beside the coupled
-// apply, so the 4x redundancy is a good trade for determinism.
+// The FEM element terms are evaluated once per tet; the sums over the tets at a
+// node are "row owned" gathers in a fixed order, so no two threads ever write
+// the same value (deterministic, no atomics).
+#include <algorithm>
 #include <cmath>
 
 #include "pbfb_internal.hpp"
@@ -144,21 +143,19 @@ __global__ void __launch_bounds__(256) k_enclosed_volume(int64_t nt, const doubl
 // ---------------------------------------------------------------------------
 // stiffness and coupling values (row gather)
 // ---------------------------------------------------------------------------
-__global__ void k_stiffness(int64_t nn, const int32_t *__restrict__ n2t_ptr, const int32_t *__restrict__ n2t,
-                            const int32_t *__restrict__ slot4, const double *__restrict__ tg, double eps_s,
-                            int64_t nt_i, double eps_m, double *__restrict__ val0)
+// element matrix of tet t (16 values, k_fem_rows adds them up)
+__global__ void __launch_bounds__(256) k_tet_stiffness(int64_t ntet, const double *__restrict__ tg, double eps_s,
+                                                       int64_t nt_i, double eps_m, double *__restrict__ out)
 {
-    int64_t a = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-    if (a >= nn) return;
-    for (int32_t e = n2t_ptr[a]; e < n2t_ptr[a + 1]; ++e) {
-        int32_t t = n2t[e] >> 2, la = n2t[e] & 3;
-        const double *G = tg + 16 * int64_t(t);
-        const double vol = G[12], eps = t < nt_i ? eps_s : eps_m; // tets from nt_i on: solute
-        for (int b = 0; b < 4; ++b) {
-            double gg = G[3 * la] * G[3 * b] + G[3 * la + 1] * G[3 * b + 1] + G[3 * la + 2] * G[3 * b + 2];
-            val0[slot4[4 * int64_t(e) + b]] += eps * vol * gg;
-        }
-    }
+    const int64_t t = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
+    if (t >= ntet) return;
+    const double *G = tg + 16 * t;
+    const double ev = (t < nt_i ? eps_s : eps_m) * G[12]; // tets from nt_i on: solute
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+            out[16 * t + 4 * a + b] = ev * (G[3 * a] * G[3 * b] + G[3 * a + 1] * G[3 * b + 1] + G[3 * a + 2] * G[3 * b + 2]);
 }
 
 // Surface mass coupling of the FEM rows: coef * |tau| (1 + delta_ab) / 12,
@@ -235,8 +232,8 @@ __device__ inline void scheme_eval(int s, double t, double &f0, double &f1, doub
 // once and leaves its contributions to its four nodes (row gathers below add
 // them up in a fixed order, so no atomics are needed).
 //   MODE_N: N_a           = c sum_q w_q |T| calN(u_h)  phi_a                 (4 per tet)
-//   MODE_W: N_a, J_a, H_a at u + omega D: calN, calN' D_h, calN'' D_h^2        (12 per tet)
-//   MODE_J: J_ab          = c sum_q w_q |T| calN'(u_h) phi_a phi_b           (16 per tet)
+//   MODE_W: N_a, J_a, H_a at u + omega D: calN, calN' D_h, calN'' D_h^2        (3 per corner, 12 per tet)
+//   MODE_J: J_ab          = c sum_q w_q |T| calN'(u_h) phi_a phi_b           (16 per tet; the symmetric 10 are summed)
 enum { MODE_N = 0, MODE_W = 1, MODE_J = 2 };
 template <int MODE>
 __global__ void __launch_bounds__(128)
@@ -263,7 +260,7 @@ __global__ void __launch_bounds__(128)
         uk[k] = u[T[k]] + (MODE == MODE_W ? omega * dk[k] : 0.0);
     }
     const double cv = c * tg[16 * t + 12];
-    constexpr int NO = MODE == MODE_N ? 4 : MODE == MODE_W ? 12 : 16;
+    constexpr int NO = MODE == MODE_N ? 4 : MODE == MODE_W ? 12 : 10;
     double acc[NO];
 #pragma unroll
     for (int k = 0; k < NO; ++k) acc[k] = 0.0;
@@ -279,68 +276,146 @@ __global__ void __launch_bounds__(128)
 #pragma unroll
             for (int a = 0; a < 4; ++a) {
                 const double w = cv * R.w[q] * R.b[q][a];
-                acc[a] += w * f0;
-                acc[4 + a] += w * f1 * dh;
-                acc[8 + a] += w * f2 * dh * dh;
+                acc[3 * a] += w * f0;
+                acc[3 * a + 1] += w * f1 * dh;
+                acc[3 * a + 2] += w * f2 * dh * dh;
             }
         } else {
 #pragma unroll
             for (int a = 0; a < 4; ++a) {
                 const double wq = cv * R.w[q] * f1 * R.b[q][a];
 #pragma unroll
-                for (int b = 0; b < 4; ++b) acc[4 * a + b] += wq * R.b[q][b];
+                for (int b = 0; b <= a; ++b) acc[a * (a + 1) / 2 + b] += wq * R.b[q][b];
             }
         }
     }
+    if constexpr (MODE == MODE_J) {
 #pragma unroll
-    for (int k = 0; k < NO; ++k) out[NO * t + k] = acc[k];
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) out[16 * t + 4 * a + b] = acc[a >= b ? a * (a + 1) / 2 + b : b * (b + 1) / 2 + a];
+    } else {
+#pragma unroll
+        for (int k = 0; k < NO; ++k) out[NO * t + k] = acc[k];
+    }
 }
 
-// d_val = d_val0 + J_scheme(u) on the u columns of each FEM row, from the
-// element blocks (16 per tet), row by row (Jt null: d_val = d_val0, the
-// operator without reaction term); the copy covers the slice padding (zero
-// in d_val0) and is coalesced across the rows of a slice
-__global__ void k_jacobian(int64_t nn, const int32_t *__restrict__ sptr, const double *__restrict__ val0,
-                           double *__restrict__ val, float *__restrict__ val32, const int32_t *__restrict__ n2t_ptr,
-                           const int32_t *__restrict__ n2t, const int32_t *__restrict__ slot4,
-                           const double *__restrict__ Jt)
+// FEM rows from element matrices (16 values per tet): val = val0 + the sum over
+// the tets (val0 null: 0; E null: val0 only), val32 (nullable) its FP32 copy.
+// One workgroup per slice of 64 rows; wavefront v adds the tets v, v + P, ...
+// of its 64 nodes into a plane of LDS of its own, where a lane owns a column,
+// and the P planes are then added in order.  (One thread per row that added
+// into global memory, four scattered read-modify-writes per tet and node, took
+// 140 us at 112k nodes and 750 us at 450k.)  Four planes for slices up to 32
+// entries wide (64 KB of LDS), one for wider ones.
+template <int P>
+__global__ void __launch_bounds__(256)
+    k_fem_rows(int64_t nn, const int32_t *__restrict__ sptr, int width, const int32_t *__restrict__ tptr,
+               const int32_t *__restrict__ n2t, const uint32_t *__restrict__ k4, const double *__restrict__ E,
+               const double *__restrict__ val0, double *__restrict__ val, float *__restrict__ val32)
 {
-    int64_t a = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-    if (a >= nn) return;
-    const int64_t q = a / SLICE;
-    const int32_t b0 = sptr[q] + int32_t(a - q * SLICE), b1 = sptr[q + 1];
-    for (int32_t s = b0; s < b1; s += SLICE) val[s] = val0[s];
-    if (Jt)
-        for (int32_t e = n2t_ptr[a]; e < n2t_ptr[a + 1]; ++e) {
-            const int64_t t = n2t[e] >> 2;
-            const int la = n2t[e] & 3;
-            for (int b = 0; b < 4; ++b) val[slot4[4 * int64_t(e) + b]] += Jt[16 * t + 4 * la + b];
+    extern __shared__ double acc[]; // P planes x width x 64
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t q = blockIdx.x;
+    const int32_t b0 = sptr[q], w = (sptr[q + 1] - b0) / SLICE;
+    if (E && wv < P) {
+        double *my = acc + wv * width * 64 + lane;
+        for (int k = 0; k < w; ++k) my[64 * k] = 0.0;
+        const int32_t t0 = tptr[q], nt = (tptr[q + 1] - t0) / SLICE;
+#pragma unroll 4
+        for (int e = wv; e < nt; e += P) {
+            const int32_t at = t0 + SLICE * e + lane, tc = n2t[at];
+            const uint32_t kk = k4[at];
+            if (tc < 0) continue;
+            const double2 *row = reinterpret_cast<const double2 *>(E + 4 * int64_t(tc));
+            const double2 r0 = row[0], r1 = row[1];
+            my[64 * (kk & 255)] += r0.x;
+            my[64 * ((kk >> 8) & 255)] += r0.y;
+            my[64 * ((kk >> 16) & 255)] += r1.x;
+            my[64 * (kk >> 24)] += r1.y;
         }
-    if (val32)
-        for (int32_t s = b0; s < b1; s += SLICE) val32[s] = float(val[s]);
+    }
+    __syncthreads();
+    for (int k = wv; k < w; k += 4) {
+        const int64_t at = b0 + int64_t(SLICE) * k + lane;
+        double v = val0 ? val0[at] : 0.0;
+        if (E) {
+            double t = acc[64 * k + lane];
+#pragma unroll
+            for (int p = 1; p < P; ++p) t += acc[(p * width + k) * 64 + lane];
+            v += t;
+        }
+        val[at] = v;
+        if (val32) val32[at] = float(v);
+    }
 }
 
-// out_k[a] = sum over the tets at node a of their contribution k to a (K per tet and node)
+// the entries of the long rows, one wavefront each (first: the first of them)
+__global__ void __launch_bounds__(256)
+    k_fem_long(int64_t n, int64_t first, const int32_t *__restrict__ eptr, const int64_t *__restrict__ src,
+               const double *__restrict__ E, const double *__restrict__ val0, double *__restrict__ val,
+               float *__restrict__ val32)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t i = (blockIdx.x * int64_t(256) + threadIdx.x) >> 6;
+    if (i >= n) return;
+    double t = 0.0;
+    if (E)
+        for (int32_t e = eptr[i] + lane; e < eptr[i + 1]; e += 64) t += E[src[e]];
+    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
+    if (lane != 0) return;
+    const double v = (val0 ? val0[first + i] : 0.0) + t;
+    val[first + i] = v;
+    if (val32) val32[first + i] = float(v);
+}
+
+// out_k[a] = sum over the tets at node a of their contribution k to a (K
+// values per tet and corner, contiguous).  One workgroup per slice of 64
+// nodes, wavefront v the tets v, v + 4, ..., then (workgroups past the slices)
+// one per long row.
 template <int K>
-__global__ void k_node_gather(int64_t nn, const int32_t *__restrict__ n2t_ptr, const int32_t *__restrict__ n2t,
-                              const double *__restrict__ per_tet, double *__restrict__ o0, double *__restrict__ o1,
-                              double *__restrict__ o2, const int *__restrict__ skip)
+__global__ void __launch_bounds__(256)
+    k_node_gather(int64_t nn, int64_t nsl, const int32_t *__restrict__ tptr, const int32_t *__restrict__ n2t,
+                  FemRowsDev R, const double *__restrict__ per_tet, double *__restrict__ o0, double *__restrict__ o1,
+                  double *__restrict__ o2, const int *__restrict__ skip)
 {
     if (skip && *skip) return;
-    int64_t a = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-    if (a >= nn) return;
+    __shared__ double red[4][K][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t q = blockIdx.x;
     double s[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) s[k] = 0.0;
-    for (int32_t e = n2t_ptr[a]; e < n2t_ptr[a + 1]; ++e) {
-        const int64_t t = n2t[e] >> 2;
-        const int la = n2t[e] & 3;
+    int64_t a;
+    if (q < nsl) {
+        a = q * SLICE + lane;
+        const int32_t t0 = tptr[q], nt = (tptr[q + 1] - t0) / SLICE;
+#pragma unroll 4
+        for (int e = wv; e < nt; e += 4) {
+            const int32_t tc = n2t[t0 + SLICE * e + lane];
+            if (tc < 0) continue;
 #pragma unroll
-        for (int k = 0; k < K; ++k) s[k] += per_tet[4 * K * t + 4 * k + la];
+            for (int k = 0; k < K; ++k) s[k] += per_tet[K * int64_t(tc) + k];
+        }
+        if (R.nlong && a < nn)
+            for (int32_t l = R.long_ptr[q]; l < R.long_ptr[q + 1]; ++l)
+                if (R.long_row[l] == a) a = nn; // written by its own workgroup
+    } else {
+        const int64_t l = q - nsl;
+        a = lane == 0 ? R.long_row[l] : nn;
+        for (int32_t e = R.tptr[l] + int32_t(threadIdx.x); e < R.tptr[l + 1]; e += 256)
+#pragma unroll
+            for (int k = 0; k < K; ++k) s[k] += per_tet[K * int64_t(R.t2[e]) + k];
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            for (int o = 32; o > 0; o >>= 1) s[k] += __shfl_xor(s[k], o);
     }
-    o0[a] = s[0];
-    if (K > 1) o1[a] = s[1];
-    if (K > 2) o2[a] = s[2];
+#pragma unroll
+    for (int k = 0; k < K; ++k) red[wv][k][lane] = s[k];
+    __syncthreads();
+    if (wv >= K || a >= nn) return;
+    const double v = (red[0][wv][lane] + red[1][wv][lane]) + (red[2][wv][lane] + red[3][wv][lane]);
+    (wv == 0 ? o0 : wv == 1 ? o1 : o2)[a] = v;
 }
 
 // per-tet integral of u sinh u - 2 cosh u + 2 for u = u_lin + u_nl (block partial sums)
@@ -644,14 +719,28 @@ void ensure_topology(Problem &p, hipStream_t s)
     A.release();
     p.d_x = A.upload(p.x, s);
     p.d_tet = A.upload(p.tet, s);
-    std::vector<int32_t> sptr, col, n2t_ptr, n2t, slot4, diag, cslot[2], nvert[2]; // until the uploads are done
-    build_fem_topology(p, sptr, col, n2t_ptr, n2t, slot4, diag, cslot);
+    std::vector<int32_t> sptr, col, diag, cslot[2], nvert[2]; // until the uploads are done
+    FemRows R;
+    build_fem_topology(p, sptr, col, R, diag, cslot);
     p.nnz = int64_t(col.size());
     p.d_sptr = A.upload(sptr, s);
     p.d_col = A.upload(col, s);
-    p.d_n2t_ptr = A.upload(n2t_ptr, s);
-    p.d_n2t = A.upload(n2t, s);
-    p.d_slot4 = A.upload(slot4, s);
+    p.fr = FemRowsDev();
+    p.fr.ptr = A.upload(R.ptr, s);
+    p.fr.n2t = A.upload(R.n2t, s);
+    p.fr.k4 = A.upload(R.k4, s);
+    for (size_t q = 0; q + 1 < sptr.size(); ++q) p.fr.width = std::max(p.fr.width, (sptr[q + 1] - sptr[q]) / SLICE);
+    p.fr.nlong = int64_t(R.long_row.size());
+    if (p.fr.nlong) {
+        p.fr.nlong_entries = int64_t(R.eptr.size()) - 1;
+        p.fr.long_ptr = A.upload(R.long_ptr, s);
+        p.fr.long_row = A.upload(R.long_row, s);
+        p.fr.long_off = A.upload(R.long_off, s);
+        p.fr.tptr = A.upload(R.tptr, s);
+        p.fr.t2 = A.upload(R.t2, s);
+        p.fr.eptr = A.upload(R.eptr, s);
+        p.fr.src = A.upload(R.src, s);
+    }
     p.d_diag = A.upload(diag, s);
     p.d_tgeo = A.alloc<double>(16 * p.ntet);
     p.d_val0 = A.alloc<double>(p.nnz);
@@ -748,15 +837,45 @@ void ensure_geometry(Problem &p, hipStream_t s)
     p.geom_ready = true;
 }
 
+// val = val0 + the element matrices E of the tets (k_fem_rows), long rows included
+static void fem_rows(Problem &p, const double *E, const double *val0, double *val, float *val32, hipStream_t s)
+{
+    const FemRowsDev &R = p.fr;
+    const unsigned nsl = nblocks(p.nn, SLICE);
+    const size_t plane = sizeof(double) * 64 * size_t(R.width);
+    if (R.width <= 32)
+        hipLaunchKernelGGL(k_fem_rows<4>, dim3(nsl), dim3(256), E ? 4 * plane : 0, s, p.nn, p.d_sptr, R.width, R.ptr,
+                           R.n2t, R.k4, E, val0, val, val32);
+    else
+        hipLaunchKernelGGL(k_fem_rows<1>, dim3(nsl), dim3(256), E ? plane : 0, s, p.nn, p.d_sptr, R.width, R.ptr, R.n2t,
+                           R.k4, E, val0, val, val32);
+    if (R.nlong)
+        hipLaunchKernelGGL(k_fem_long, dim3(nblocks(R.nlong_entries * 64, 256)), dim3(256), 0, s, R.nlong_entries,
+                           p.nnz - R.nlong_entries, R.eptr, R.src, E, val0, val, val32);
+    PB_HIP(hipGetLastError());
+}
+
+// sums over the tets at the nodes (k_node_gather)
+template <int K>
+static void node_gather(Problem &p, const double *per_tet, double *o0, double *o1, double *o2, const int *skip,
+                        hipStream_t s)
+{
+    const unsigned nsl = nblocks(p.nn, SLICE);
+    hipLaunchKernelGGL(k_node_gather<K>, dim3(nsl + unsigned(p.fr.nlong)), dim3(256), 0, s, p.nn, int64_t(nsl), p.fr.ptr,
+                       p.fr.n2t, p.fr, per_tet, o0, o1, o2, skip);
+    PB_HIP(hipGetLastError());
+}
+
 // Stiffness and surface-coupling values of the FEM rows (they carry the
 // permittivities; the boundary operators do not).
 void ensure_values(Problem &p, hipStream_t s)
 {
     if (p.val_ready) return;
     ensure_geometry(p, s);
-    PB_HIP(hipMemsetAsync(p.d_val0, 0, sizeof(double) * p.nnz, s));
-    hipLaunchKernelGGL(k_stiffness, dim3(nblocks(p.nn, 256)), dim3(256), 0, s, p.nn, p.d_n2t_ptr, p.d_n2t,
-                       p.d_slot4, p.d_tgeo, p.eps_s, p.ntet_i(), p.eps_m, p.d_val0);
+    double *E = scratch<double>(p, SCR_TETR, 16 * size_t(p.ntet));
+    hipLaunchKernelGGL(k_tet_stiffness, dim3(nblocks(p.ntet, 256)), dim3(256), 0, s, p.ntet, p.d_tgeo, p.eps_s,
+                       p.ntet_i(), p.eps_m, E);
+    fem_rows(p, E, nullptr, p.d_val0, nullptr, s);
     // the two-field form has Gamma_m inside the FEM domain: no lambda_m columns
     for (int w = p.two_field() ? 1 : 0; w < 2; ++w) {
         SurfaceDev &S = p.surf[w];
@@ -826,17 +945,13 @@ void fem_assemble_jacobian(Problem &p, int scheme, const double *u, hipStream_t 
     hipLaunchKernelGGL(k_tet_reaction<MODE_J>, dim3(nblocks(p.ntet, 128)), dim3(128), 0, s, p.ntet, p.d_tgeo, p.d_tet,
                        u, (const double *)nullptr, 0.0, scheme, c, tet_rule_arg(), p.ntet_i(), Jt,
                        (const double *)nullptr, (const int *)nullptr);
-    hipLaunchKernelGGL(k_jacobian, dim3(nblocks(p.nn, 128)), dim3(128), 0, s, p.nn, p.d_sptr, p.d_val0, p.d_val,
-                       p.d_val32, p.d_n2t_ptr, p.d_n2t, p.d_slot4, Jt);
-    PB_HIP(hipGetLastError());
+    fem_rows(p, Jt, p.d_val0, p.d_val, p.d_val32, s);
 }
 
 // FEM values of the coupled operator without reaction term (the Picard step)
 void fem_assemble_linear(Problem &p, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_jacobian, dim3(nblocks(p.nn, 128)), dim3(128), 0, s, p.nn, p.d_sptr, p.d_val0, p.d_val,
-                       p.d_val32, p.d_n2t_ptr, p.d_n2t, p.d_slot4, (const double *)nullptr);
-    PB_HIP(hipGetLastError());
+    fem_rows(p, nullptr, p.d_val0, p.d_val, p.d_val32, s);
 }
 
 void fem_nonlinear(Problem &p, int scheme, const double *u, double *out, hipStream_t s)
@@ -850,9 +965,7 @@ void fem_nonlinear_buf(Problem &p, int scheme, const double *u, double *out, dou
     hipLaunchKernelGGL(k_tet_reaction<MODE_N>, dim3(nblocks(p.ntet, 128)), dim3(128), 0, s, p.ntet, p.d_tgeo, p.d_tet,
                        u, (const double *)nullptr, 0.0, scheme, c, tet_rule_arg(), p.ntet_i(), Nt,
                        (const double *)nullptr, (const int *)nullptr);
-    hipLaunchKernelGGL(k_node_gather<1>, dim3(nblocks(p.nn, 128)), dim3(128), 0, s, p.nn, p.d_n2t_ptr, p.d_n2t, Nt,
-                       out, (double *)nullptr, (double *)nullptr, (const int *)nullptr);
-    PB_HIP(hipGetLastError());
+    node_gather<1>(p, Nt, out, nullptr, nullptr, nullptr, s);
 }
 
 void fem_omega_terms_dev(Problem &p, int scheme, const double *u, const double *D, const double *wdev,
@@ -862,9 +975,7 @@ void fem_omega_terms_dev(Problem &p, int scheme, const double *u, const double *
     double *Wt = scratch<double>(p, SCR_TETR, 16 * size_t(p.ntet));
     hipLaunchKernelGGL(k_tet_reaction<MODE_W>, dim3(nblocks(p.ntet, 128)), dim3(128), 0, s, p.ntet, p.d_tgeo, p.d_tet,
                        u, D, 0.0, scheme, c, tet_rule_arg(), p.ntet_i(), Wt, wdev, skip);
-    hipLaunchKernelGGL(k_node_gather<3>, dim3(nblocks(p.nn, 128)), dim3(128), 0, s, p.nn, p.d_n2t_ptr, p.d_n2t, Wt,
-                       rN, rJ, rH, skip);
-    PB_HIP(hipGetLastError());
+    node_gather<3>(p, Wt, rN, rJ, rH, skip, s);
 }
 
 double fem_energy_integral(Problem &p, const double *ul, const double *unl, hipStream_t s)

@@ -99,7 +99,7 @@ struct RestGrid {
 template <typename MT, typename VT>
 __global__ void __launch_bounds__(256)
     k_rest(GemvSurf S0, GemvSurf S1, RestGrid G, int64_t first, int64_t nrows, const int32_t *__restrict__ sptr,
-           const int32_t *__restrict__ col, const VT *__restrict__ val, const double *__restrict__ x,
+           SellLong lng, const int32_t *__restrict__ col, const VT *__restrict__ val, const double *__restrict__ x,
            double *__restrict__ y)
 {
     int64_t bi = first + blockIdx.x;
@@ -119,8 +119,8 @@ __global__ void __launch_bounds__(256)
     }
     const int64_t q = bi - G.s0 - G.s1;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const double part = sell_part<VT, false>(sptr, col, val, x, q, lane, wv, nrows);
-    const double s = sell_reduce(part, lane, wv);
+    const double s =
+        sell_rows<VT, false>(sptr, lng, col, val, [x](int64_t c) { return x[c]; }, q, lane, wv, nrows);
     const int64_t row = q * SLICE + lane;
     if (wv == 0 && row < nrows) y[row] = s;
 }
@@ -243,10 +243,10 @@ static void rest_launch(const Problem &p, const GemvSurf &S0, const GemvSurf &S1
     if (count == 0) return;
     if (p.precision == PBFB_MIXED)
         hipLaunchKernelGGL((k_rest<float, VT>), dim3(unsigned(count)), dim3(256), 0, s, S0, S1, G, first, p.nn,
-                           p.d_sptr, p.d_col, val, x, y);
+                           p.d_sptr, p.fr.sell(), p.d_col, val, x, y);
     else
         hipLaunchKernelGGL((k_rest<double, VT>), dim3(unsigned(count)), dim3(256), 0, s, S0, S1, G, first, p.nn,
-                           p.d_sptr, p.d_col, val, x, y);
+                           p.d_sptr, p.fr.sell(), p.d_col, val, x, y);
 }
 
 // bufs: caller-provided work buffers (no allocation, no timing), else the

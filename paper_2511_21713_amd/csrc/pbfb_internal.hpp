@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "../../include/pbfb.h"
+#include "sell_slice.hpp"
 
 namespace pbfb {
 
@@ -199,6 +200,31 @@ struct Workspace {
     double *doubles(size_t n);
 };
 
+// Tets around the nodes, for the row gathers: a slice of SLICE nodes holds its
+// e-th tet of node SLICE q + l at ptr[q] + SLICE e + l (tet * 4 + corner, -1
+// past the node's last), and beside it the positions k, in the node's matrix
+// row, of the tet's four nodes (8 bits each).  Long rows (sell_slice.hpp) hold
+// no tets there; theirs are listed per row (tptr, t2) and, for every stored
+// entry of the long rows, the element-matrix entries that add up to it (eptr,
+// src: 16 * tet + 4 * corner + other corner).
+struct FemRows {
+    std::vector<int32_t> ptr, n2t;
+    std::vector<uint32_t> k4;
+    std::vector<int32_t> long_ptr, long_row, long_off, tptr, t2, eptr;
+    std::vector<int64_t> src;
+};
+struct FemRowsDev {
+    int32_t *ptr = nullptr, *n2t = nullptr;
+    uint32_t *k4 = nullptr;
+    int64_t nlong = 0, nlong_entries = 0; // long rows, their stored entries
+    int32_t *long_ptr = nullptr, *long_row = nullptr, *long_off = nullptr, *tptr = nullptr, *t2 = nullptr,
+            *eptr = nullptr;
+    int64_t *src = nullptr;
+    int width = 0; // widest slice of the matrix
+    SellLong sell() const { return SellLong{long_ptr, long_row, long_off}; }
+};
+constexpr int LONG_ROW = 64; // a row of more entries is long (k4 holds positions below 256)
+
 struct Problem;
 // assemblies of one context that may run at once (the device setup of a
 // batch runs on this many host threads and streams)
@@ -290,7 +316,8 @@ struct Problem {
     Arena mesh_arena, bem_arena[NSURF];
     ScratchBuf scr[SCR_N];
     double *d_x = nullptr, *d_tgeo = nullptr, *d_q = nullptr;
-    int32_t *d_tet = nullptr, *d_n2t_ptr = nullptr, *d_n2t = nullptr, *d_slot4 = nullptr;
+    int32_t *d_tet = nullptr;
+    FemRowsDev fr;
     // FEM rows in sliced ELL: slice q holds rows [64q, 64q + 64); its entry k
     // of row 64q + l sits at d_sptr[q] + 64 k + l for k below the slice width
     // (d_sptr[q + 1] - d_sptr[q]) / 64, in ascending column order; entries past
@@ -334,8 +361,7 @@ constexpr int SLICE = 64; // FEM rows per sliced-ELL slice: one wavefront
 // FIN: the cycle ended on the residual estimate; the step only adds the
 // preconditioned update to x (no true-residual apply) and the solve is done
 enum GSt { G_INIT = 0, G_ARN = 1, G_RES = 2, G_DONE = 3, G_FAIL = 4, G_FIN = 5 };
-void build_fem_topology(Problem &p, std::vector<int32_t> &sptr, std::vector<int32_t> &col,
-                        std::vector<int32_t> &n2t_ptr, std::vector<int32_t> &n2t, std::vector<int32_t> &slot4,
+void build_fem_topology(Problem &p, std::vector<int32_t> &sptr, std::vector<int32_t> &col, FemRows &R,
                         std::vector<int32_t> &diag, std::vector<int32_t> cslot[2]);
 
 // device setup and operators (kernels_*.hip, solver.hip)

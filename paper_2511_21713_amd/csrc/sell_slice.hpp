@@ -14,6 +14,12 @@
 // a row are added in wavefront order through LDS (bitwise reproducible).
 // FP32 values are widened; products and sums are FP64.
 //
+// A row of more than LONG_ROW entries (a node where a coarse fan of tets
+// meets, such as the centre of a meshed solute) would set the width of its
+// whole slice and be walked by one lane.  Such rows hold padding only in their
+// slice; their entries follow the slices, contiguous, and the workgroup of the
+// slice adds each of them with all its lanes (sell_long).
+//
 // This is the bandwidth-bound sparse kernel of every coupled apply and of
 // every Chebyshev term of the FEM-block preconditioner.  Its loads are plain
 // (cached): the Chebyshev terms read the same slices many times in a row.
@@ -27,6 +33,12 @@ namespace pbfb {
 
 constexpr int SELL_W = 4; // wavefronts per slice (one workgroup of 256 threads)
 constexpr int SELL_U = 4; // entries per lane in flight
+
+// long rows of a matrix: those of slice q are ptr[q] .. ptr[q + 1] - 1 (null:
+// the matrix has none), long row l is row[l] with entries off[l] .. off[l + 1] - 1
+struct SellLong {
+    const int32_t *ptr = nullptr, *row = nullptr, *off = nullptr;
+};
 
 // Partial sum of row 64 q + lane over the entries k = wv, wv + 4, ... of
 // slice q with input entry x(column).  FEM_ONLY skips the coupling columns
@@ -58,15 +70,6 @@ __device__ inline double sell_part_of(const int32_t *__restrict__ sptr, const in
     return acc;
 }
 
-template <typename VT, bool FEM_ONLY>
-__device__ inline double sell_part(const int32_t *__restrict__ sptr, const int32_t *__restrict__ col,
-                                   const VT *__restrict__ val, const double *__restrict__ x, int64_t q, int lane,
-                                   int wv, int64_t nn)
-{
-    return sell_part_of<VT, FEM_ONLY>(
-        sptr, col, val, [x](int32_t c) { return x[c]; }, q, lane, wv, nn);
-}
-
 // Sum of the four wavefront partials of each row of the slice, in order;
 // valid in wavefront 0 (every thread of the workgroup must call it).
 __device__ inline double sell_reduce(double part, int lane, int wv)
@@ -81,6 +84,39 @@ __device__ inline double sell_reduce(double part, int lane, int wv)
         for (int v = 1; v < SELL_W; ++v) s += red[v][lane];
     }
     return s;
+}
+
+// The long rows of slice q into acc of their lanes of wavefront 0 (every thread
+// of the workgroup must call it; x and FEM_ONLY as in sell_part_of)
+template <typename VT, bool FEM_ONLY, typename XF>
+__device__ inline void sell_long(const SellLong &L, const int32_t *__restrict__ col, const VT *__restrict__ val, XF &&x,
+                                 int64_t q, int lane, int wv, int64_t nn, double &acc)
+{
+    if (!L.ptr) return;
+    __shared__ double red[SELL_W];
+    for (int32_t l = L.ptr[q]; l < L.ptr[q + 1]; ++l) {
+        double t = 0.0;
+        for (int32_t e = L.off[l] + 64 * wv + lane; e < L.off[l + 1]; e += 64 * SELL_W) {
+            const int32_t c = col[e];
+            if (!FEM_ONLY || c < nn) t = fma(double(val[e]), x(c), t);
+        }
+        for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
+        if (lane == 0) red[wv] = t;
+        __syncthreads();
+        if (wv == 0 && lane == int(L.row[l] - q * 64)) acc = (red[0] + red[1]) + (red[2] + red[3]);
+        __syncthreads();
+    }
+}
+
+// One row product per lane of wavefront 0 for the 64 rows of slice q, long
+// rows included
+template <typename VT, bool FEM_ONLY, typename XF>
+__device__ inline double sell_rows(const int32_t *__restrict__ sptr, const SellLong &L, const int32_t *__restrict__ col,
+                                   const VT *__restrict__ val, XF &&x, int64_t q, int lane, int wv, int64_t nn)
+{
+    double acc = sell_reduce(sell_part_of<VT, FEM_ONLY>(sptr, col, val, x, q, lane, wv, nn), lane, wv);
+    sell_long<VT, FEM_ONLY>(L, col, val, x, q, lane, wv, nn, acc);
+    return acc;
 }
 
 } // namespace pbfb

@@ -239,11 +239,11 @@ void build_surface_topo_on(SurfaceTopo &S, int64_t nverts, const double *x, int6
     }
 }
 
-void build_fem_topology(Problem &p, std::vector<int32_t> &sptr, std::vector<int32_t> &col,
-                        std::vector<int32_t> &n2t_ptr, std::vector<int32_t> &n2t, std::vector<int32_t> &slot4,
+void build_fem_topology(Problem &p, std::vector<int32_t> &sptr, std::vector<int32_t> &col, FemRows &R,
                         std::vector<int32_t> &diag, std::vector<int32_t> cslot[2])
 {
     const int64_t nn = p.nn, nt = p.ntet;
+    std::vector<int32_t> n2t_ptr, n2t; // node -> tet * 4 + corner
     n2t_ptr.assign(nn + 1, 0);
     for (int64_t k = 0; k < 4 * nt; ++k) n2t_ptr[p.tet[k] + 1]++;
     for (int64_t i = 0; i < nn; ++i) n2t_ptr[i + 1] += n2t_ptr[i];
@@ -287,27 +287,42 @@ void build_fem_topology(Problem &p, std::vector<int32_t> &sptr, std::vector<int3
         rowptr[a + 1] = int32_t(rc.size());
     }
     p.nnz_row = int64_t(rc.size());
-    // sliced ELL: slice width = longest row of the slice; entry k of row
-    // 64 q + l at sptr[q] + 64 k + l; padding: column = row, value 0
+    // sliced ELL: slice width = longest row of the slice that is not long;
+    // entry k of row 64 q + l at sptr[q] + 64 k + l; padding: column = row,
+    // value 0.  The entries of the long rows follow the slices.
     const int64_t nsl = (nn + SLICE - 1) / SLICE;
+    auto len = [&](int64_t a) { return rowptr[a + 1] - rowptr[a]; };
+    auto slice_end = [&](int64_t q) { return std::min(nn, (q + 1) * SLICE); };
     sptr.assign(nsl + 1, 0);
+    R = FemRows();
+    R.long_ptr.assign(nsl + 1, 0);
     for (int64_t q = 0; q < nsl; ++q) {
         int32_t w = 0;
-        for (int64_t a = q * SLICE; a < std::min(nn, (q + 1) * SLICE); ++a) w = std::max(w, rowptr[a + 1] - rowptr[a]);
+        for (int64_t a = q * SLICE; a < slice_end(q); ++a) {
+            if (len(a) > LONG_ROW) R.long_row.push_back(int32_t(a));
+            else w = std::max(w, len(a));
+        }
         PB_CHECK(int64_t(sptr[q]) + int64_t(SLICE) * w < (int64_t(1) << 31), PBFB_EINVAL,
                  "FEM block too large for 32-bit slice offsets");
         sptr[q + 1] = sptr[q] + SLICE * w;
+        R.long_ptr[q + 1] = int32_t(R.long_row.size());
     }
-    col.assign(sptr[nsl], 0);
+    R.long_off.assign(1, sptr[nsl]);
+    for (int32_t a : R.long_row) {
+        PB_CHECK(int64_t(R.long_off.back()) + len(a) < (int64_t(1) << 31), PBFB_EINVAL,
+                 "FEM block too large for 32-bit slice offsets");
+        R.long_off.push_back(R.long_off.back() + len(a));
+    }
+    col.assign(R.long_off.back(), 0);
     std::vector<int32_t> pos(rc.size()); // row-pattern index -> stored slot
     for (int64_t q = 0; q < nsl; ++q) {
         const int32_t w = (sptr[q + 1] - sptr[q]) / SLICE;
         for (int l = 0; l < SLICE; ++l) {
             const int64_t a = q * SLICE + l;
-            const int32_t len = a < nn ? rowptr[a + 1] - rowptr[a] : 0;
+            const int32_t n = a < nn && len(a) <= LONG_ROW ? len(a) : 0;
             for (int32_t k = 0; k < w; ++k) {
                 const int64_t at = sptr[q] + int64_t(SLICE) * k + l;
-                if (k < len) {
+                if (k < n) {
                     col[at] = rc[rowptr[a] + k];
                     pos[rowptr[a] + k] = int32_t(at);
                 } else {
@@ -316,17 +331,58 @@ void build_fem_topology(Problem &p, std::vector<int32_t> &sptr, std::vector<int3
             }
         }
     }
+    for (size_t r = 0; r < R.long_row.size(); ++r)
+        for (int32_t k = 0; k < len(R.long_row[r]); ++k) {
+            const int32_t at = R.long_off[r] + k, i = rowptr[R.long_row[r]] + k;
+            col[at] = rc[i];
+            pos[i] = at;
+        }
     auto find = [&](int64_t row, int64_t c) {
         auto b = rc.begin() + rowptr[row], e = rc.begin() + rowptr[row + 1];
         auto it = std::lower_bound(b, e, int32_t(c));
         return pos[it - rc.begin()];
     };
-    slot4.resize(4 * n2t.size());
-    for (int64_t a = 0; a < nn; ++a)
-        for (int32_t e = n2t_ptr[a]; e < n2t_ptr[a + 1]; ++e) {
-            int32_t t = n2t[e] / 4;
-            for (int b = 0; b < 4; ++b) slot4[4 * int64_t(e) + b] = find(a, p.tet[4 * t + b]);
+    // the tets around the nodes (FemRows)
+    R.ptr.assign(nsl + 1, 0);
+    for (int64_t q = 0; q < nsl; ++q) {
+        int32_t w = 0;
+        for (int64_t a = q * SLICE; a < slice_end(q); ++a)
+            if (len(a) <= LONG_ROW) w = std::max(w, n2t_ptr[a + 1] - n2t_ptr[a]);
+        PB_CHECK(int64_t(R.ptr[q]) + int64_t(SLICE) * w < (int64_t(1) << 31), PBFB_EINVAL,
+                 "FEM block too large for 32-bit slice offsets");
+        R.ptr[q + 1] = R.ptr[q] + SLICE * w;
+    }
+    R.n2t.assign(R.ptr[nsl], -1);
+    R.k4.assign(R.ptr[nsl], 0);
+    R.tptr.assign(1, 0);
+    std::vector<std::vector<int64_t>> lists; // per entry of one long row
+    R.eptr.assign(1, 0);
+    for (int64_t a = 0; a < nn; ++a) {
+        const int64_t q = a / SLICE, l = a % SLICE;
+        if (len(a) <= LONG_ROW) {
+            for (int32_t e = n2t_ptr[a]; e < n2t_ptr[a + 1]; ++e) {
+                const int64_t at = R.ptr[q] + int64_t(SLICE) * (e - n2t_ptr[a]) + l;
+                R.n2t[at] = n2t[e];
+                uint32_t k4 = 0;
+                for (int b = 0; b < 4; ++b)
+                    k4 |= uint32_t((find(a, p.tet[4 * (n2t[e] / 4) + b]) - sptr[q]) / SLICE) << (8 * b);
+                R.k4[at] = k4;
+            }
+            continue;
         }
+        lists.assign(len(a), {});
+        const int32_t first = pos[rowptr[a]];
+        for (int32_t e = n2t_ptr[a]; e < n2t_ptr[a + 1]; ++e) {
+            R.t2.push_back(n2t[e]);
+            for (int b = 0; b < 4; ++b)
+                lists[find(a, p.tet[4 * (n2t[e] / 4) + b]) - first].push_back(4 * int64_t(n2t[e]) + b);
+        }
+        R.tptr.push_back(int32_t(R.t2.size()));
+        for (const auto &v : lists) {
+            R.src.insert(R.src.end(), v.begin(), v.end());
+            R.eptr.push_back(int32_t(R.src.size()));
+        }
+    }
     diag.resize(nn);
     for (int64_t a = 0; a < nn; ++a) diag[a] = find(a, a);
     for (int w = 0; w < 2; ++w) {

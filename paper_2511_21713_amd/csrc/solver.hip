@@ -51,30 +51,37 @@ void build_precond(Problem &p, double *dinv, hipStream_t s)
 }
 
 // Gershgorin bound of diag(F)^-1 F for the FEM block F = A + J_N (the upper
-// end of the Chebyshev interval): per-block maxima, then one block.  A
-// maximum does not depend on the order, so the bound is exact and
-// reproducible.
-__global__ void __launch_bounds__(256) k_gershgorin(int64_t nn, const int32_t *__restrict__ sptr,
+// end of the Chebyshev interval): a maximum per slice, then one block.
+__global__ void __launch_bounds__(256) k_gershgorin(int64_t nn, const int32_t *__restrict__ sptr, SellLong lng,
                                                     const int32_t *__restrict__ col, const double *__restrict__ val,
                                                     const int32_t *__restrict__ diag, double *__restrict__ part)
 {
-    __shared__ double red[256];
-    const int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-    double v = 0.0;
-    if (i < nn) {
-        const int64_t q = i / SLICE;
-        double sum = 0.0; // slice padding adds zeros
-        for (int32_t e = sptr[q] + int32_t(i - q * SLICE); e < sptr[q + 1]; e += SLICE)
-            if (col[e] < nn) sum += fabs(val[e]);
-        v = sum / val[diag[i]];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t q = blockIdx.x, i = q * SLICE + lane;
+    const int32_t b0 = sptr[q], w = (sptr[q + 1] - b0) / SLICE;
+    double sum = 0.0; // slice padding adds zeros
+    for (int32_t k = wv; k < w; k += SELL_W) {
+        const int64_t e = b0 + int64_t(SLICE) * k + lane;
+        if (col[e] < nn) sum += fabs(val[e]);
     }
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
-        __syncthreads();
+    sum = sell_reduce(sum, lane, wv);
+    if (lng.ptr) {
+        __shared__ double red[SELL_W];
+        for (int32_t l = lng.ptr[q]; l < lng.ptr[q + 1]; ++l) {
+            double t = 0.0;
+            for (int32_t e = lng.off[l] + int32_t(threadIdx.x); e < lng.off[l + 1]; e += 256)
+                if (col[e] < nn) t += fabs(val[e]);
+            for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
+            if (lane == 0) red[wv] = t;
+            __syncthreads();
+            if (wv == 0 && i == lng.row[l]) sum = (red[0] + red[1]) + (red[2] + red[3]);
+            __syncthreads();
+        }
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+    if (wv != 0) return;
+    double v = i < nn ? sum / val[diag[i]] : 0.0;
+    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
+    if (lane == 0) part[q] = v;
 }
 
 __global__ void __launch_bounds__(256) k_max_final(int64_t nb, const double *__restrict__ part,
@@ -92,12 +99,12 @@ __global__ void __launch_bounds__(256) k_max_final(int64_t nb, const double *__r
     if (threadIdx.x == 0) *out = red[0];
 }
 
-// lmax_dev[0] = bound; lmax_dev[1 ..] partial maxima (1 + ceil(nn / 256) doubles)
+// lmax_dev[0] = bound; lmax_dev[1 ..] partial maxima (1 + one per slice)
 void fem_gershgorin(Problem &p, double *lmax_dev, hipStream_t s)
 {
-    const unsigned nb = nbk(p.nn, 256);
-    hipLaunchKernelGGL(k_gershgorin, dim3(nb), dim3(256), 0, s, p.nn, p.d_sptr, p.d_col, p.d_val, p.d_diag,
-                       lmax_dev + 1);
+    const unsigned nb = nbk(p.nn, SLICE);
+    hipLaunchKernelGGL(k_gershgorin, dim3(nb), dim3(256), 0, s, p.nn, p.d_sptr, p.fr.sell(), p.d_col, p.d_val,
+                       p.d_diag, lmax_dev + 1);
     hipLaunchKernelGGL(k_max_final, dim3(1), dim3(256), 0, s, int64_t(nb), lmax_dev + 1, lmax_dev);
     PB_HIP(hipGetLastError());
 }
@@ -594,7 +601,7 @@ static bool advance_impl(NewtonRun &r, hipStream_t s)
         r.tol = r.o.tol_gr0;
         PB_HIP(hipMemsetAsync(r.phinl, 0, sizeof(double) * n, s));
         // linear component: (A + eps_s kappa^2 M) Phi_L = b
-        r.lmax = scratch<double>(p, SCR_LMAX, 1 + nbk(nn, 256));
+        r.lmax = scratch<double>(p, SCR_LMAX, 1 + nbk(nn, SLICE));
         fem_assemble_jacobian(p, PBFB_LIN, r.phinl, s);
         r.job = make_job(r, p.d_b, r.phil, s);
         r.phase = PH_LINEAR;

@@ -133,3 +133,33 @@ def test_dense_rows_of_either_form_match_the_stored_blocks(ctx, n, precision):
         print(f"  n {n} precision {precision} surface {surf}: {e:.2e}", flush=True)
         assert e < 1e-13
     g.close()
+
+
+# the centre of a meshed solute joins 12 (n = 1), 42 (2: a 43-entry row, so the
+# element sums take one plane of LDS), 92 (3) and 252 (5) nodes: the last two
+# are rows past 64 entries, kept outside their slice
+@pytest.mark.parametrize("n", [1, 2, 3, 5])
+def test_rows_of_many_neighbours_match_oracle(ctx, n):
+    """Residual, Jacobian product (FP64, 1e-12 of the largest entry, the bar of
+    the other products) and a tight solve with the relaxation search on meshes
+    with one long row."""
+    import paper_2511_21713_amd as pb
+    prob = pbgen.make_problem(n=n, a=5.0, c=6.0, bump=False, t=3.0, L=2, helix=0, partials=0, kappa=0.2,
+                              center_charge=2.0, solute_layers=1, seed=(4, n))
+    o = oracle.Oracle.from_problem(prob)
+    g = pb.Problem.from_inputs(ctx, prob)
+    rng = np.random.default_rng(n)
+    phi, v = rng.standard_normal(g.n), rng.standard_normal(g.n)
+    for scheme in (pb.T3, pb.HS):
+        for got, ref in ((g.residual(scheme, phi), o.residual(scheme, phi)),
+                         (g.apply_jacobian(scheme, phi, v), o.apply_jacobian(scheme, phi, v))):
+            e = np.abs(got - ref).max() / np.abs(ref).max()
+            print(f"  n {n} scheme {scheme}: {e:.2e}", flush=True)
+            assert e < 1e-12
+    ref = o.solve(**TIGHT)[0]["total"]
+    r = g.solve(**TIGHT)
+    assert abs(r["total"] - ref) < 1e-10 * abs(ref)
+    m = pb.Problem.from_inputs(ctx, prob, precision=pb.MIXED)
+    assert abs(m.solve()["total"] - ref) < 1e-5 * abs(ref)
+    m.close()
+    g.close()
