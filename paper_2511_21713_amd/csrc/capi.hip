@@ -375,6 +375,7 @@ void pbfb_ctx_destroy(pbfb_ctx *ctx)
         }
     for (Workspace &w : ctx->c.asm_ws)
         if (w.ptr) (void)hipFree(w.ptr);
+    if (ctx->c.ss_points) (void)hipFree(ctx->c.ss_points);
     delete ctx;
 }
 

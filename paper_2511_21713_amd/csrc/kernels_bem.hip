@@ -24,7 +24,7 @@
 //  2. square shapes: a transpose pass completes V' = U + U^T and K' += T^T
 //     (the regular part of V' bitwise symmetric);
 //  3. touching pairs (identical, common edge, common vertex) are integrated
-//     with the Sauter-Schwab rules (one wavefront per pair) and added, with
+//     with the Sauter-Schwab rules (one lane per pair) and added, with
 //     the 1/2 M term, by a row-owned scatter.
 //
 // In mixed precision the regular tiles evaluate the kernels in FP32: each
@@ -45,21 +45,6 @@
 #include "pbfb_internal.hpp"
 
 namespace pbfb {
-
-struct GL4 {
-    double x[4];
-    double w[4];
-};
-
-static GL4 gl4arg()
-{
-    GL4 r;
-    for (int i = 0; i < 4; ++i) {
-        r.x[i] = rules().gl_x[i];
-        r.w[i] = rules().gl_w[i];
-    }
-    return r;
-}
 
 static inline unsigned nblk(int64_t n, int bs) { return unsigned((n + bs - 1) / bs); }
 
@@ -721,38 +706,33 @@ struct RefPair {
     double x1, x2, y1, y2;
 };
 
-__device__ inline int ss_region(int kind, int r, double xi, double e1, double e2, double e3, RefPair &m)
+// the r-th region map for `kind` shared vertices; the Jacobian is ss_jac
+static RefPair ss_region(int kind, int r, double xi, double e1, double e2, double e3)
 {
-    // returns via m the r-th region map; the Jacobian is applied by the caller
     if (kind == 3) {
         switch (r) {
-        case 0: m = {xi, xi * (1 - e1 + e1 * e2), xi * (1 - e1 * e2 * e3), xi * (1 - e1)}; break;
-        case 1: m = {xi * (1 - e1 * e2 * e3), xi * (1 - e1), xi, xi * (1 - e1 + e1 * e2)}; break;
-        case 2: m = {xi, xi * e1 * (1 - e2 + e2 * e3), xi * (1 - e1 * e2), xi * e1 * (1 - e2)}; break;
-        case 3: m = {xi * (1 - e1 * e2), xi * e1 * (1 - e2), xi, xi * e1 * (1 - e2 + e2 * e3)}; break;
-        case 4: m = {xi * (1 - e1 * e2 * e3), xi * e1 * (1 - e2 * e3), xi, xi * e1 * (1 - e2)}; break;
-        default: m = {xi, xi * e1 * (1 - e2), xi * (1 - e1 * e2 * e3), xi * e1 * (1 - e2 * e3)}; break;
+        case 0: return {xi, xi * (1 - e1 + e1 * e2), xi * (1 - e1 * e2 * e3), xi * (1 - e1)};
+        case 1: return {xi * (1 - e1 * e2 * e3), xi * (1 - e1), xi, xi * (1 - e1 + e1 * e2)};
+        case 2: return {xi, xi * e1 * (1 - e2 + e2 * e3), xi * (1 - e1 * e2), xi * e1 * (1 - e2)};
+        case 3: return {xi * (1 - e1 * e2), xi * e1 * (1 - e2), xi, xi * e1 * (1 - e2 + e2 * e3)};
+        case 4: return {xi * (1 - e1 * e2 * e3), xi * e1 * (1 - e2 * e3), xi, xi * e1 * (1 - e2)};
+        default: return {xi, xi * e1 * (1 - e2), xi * (1 - e1 * e2 * e3), xi * e1 * (1 - e2 * e3)};
         }
-        return 0;
     }
     if (kind == 2) {
         switch (r) {
-        case 0: m = {xi, xi * e1 * e3, xi * (1 - e1 * e2), xi * e1 * (1 - e2)}; break;
-        case 1: m = {xi, xi * e1, xi * (1 - e1 * e2 * e3), xi * e1 * e2 * (1 - e3)}; break;
-        case 2: m = {xi * (1 - e1 * e2), xi * e1 * (1 - e2), xi, xi * e1 * e2 * e3}; break;
-        case 3: m = {xi * (1 - e1 * e2 * e3), xi * e1 * e2 * (1 - e3), xi, xi * e1}; break;
-        default: m = {xi * (1 - e1 * e2 * e3), xi * e1 * (1 - e2 * e3), xi, xi * e1 * e2}; break;
+        case 0: return {xi, xi * e1 * e3, xi * (1 - e1 * e2), xi * e1 * (1 - e2)};
+        case 1: return {xi, xi * e1, xi * (1 - e1 * e2 * e3), xi * e1 * e2 * (1 - e3)};
+        case 2: return {xi * (1 - e1 * e2), xi * e1 * (1 - e2), xi, xi * e1 * e2 * e3};
+        case 3: return {xi * (1 - e1 * e2 * e3), xi * e1 * e2 * (1 - e3), xi, xi * e1};
+        default: return {xi * (1 - e1 * e2 * e3), xi * e1 * (1 - e2 * e3), xi, xi * e1 * e2};
         }
-        return 0;
     }
-    if (r == 0)
-        m = {xi, xi * e1, xi * e2, xi * e2 * e3};
-    else
-        m = {xi * e2, xi * e2 * e3, xi, xi * e1};
-    return 0;
+    if (r == 0) return {xi, xi * e1, xi * e2, xi * e2 * e3};
+    return {xi * e2, xi * e2 * e3, xi, xi * e1};
 }
 
-__device__ inline double ss_jac(int kind, int r, double xi, double e1, double e2)
+static double ss_jac(int kind, int r, double xi, double e1, double e2)
 {
     const double x3 = xi * xi * xi;
     if (kind == 3) return x3 * e1 * e1 * e2;
@@ -760,139 +740,249 @@ __device__ inline double ss_jac(int kind, int r, double xi, double e1, double e2
     return x3 * e2;
 }
 
-// One wavefront per touching ordered pair (tau, sigma); lanes split the
-// regions x n^4 Gauss points; the 3x3 V and K blocks (in the triangles' own
-// vertex order) go to out[18 * pair].
-template <bool YUK>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
-    k_bem_singular(int64_t ntp, const int32_t *__restrict__ tp_tau, const int32_t *__restrict__ tp_sig,
-                   const int32_t *__restrict__ tri, const double *__restrict__ vx, const double *__restrict__ nrm,
-                   const double *__restrict__ area, double kappa, GL4 G, double *__restrict__ out)
+// The points of the three rules, kind 3, 2, 1 after each other, SS_STRIDE
+// doubles each: x1, x2, y1, y2, then the nine weights w phi_a(x) phi_b(y)
+constexpr int SS_STRIDE = 16; // 13 used; one aligned 128-byte line
+constexpr int SS_NPT[3] = {6 * 256, 5 * 256, 2 * 256}, SS_OFF[3] = {0, 6 * 256, 11 * 256}, SS_ALL = 13 * 256;
+
+// device copy of the table, once per context
+static const double *ss_points(Ctx &C)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t pair = (blockIdx.x * int64_t(blockDim.x) + threadIdx.x) >> 6;
-    if (pair >= ntp) return;
+    std::lock_guard<std::mutex> lk(C.setup_mu);
+    if (C.ss_points) return C.ss_points;
+    const Rules &R = rules();
+    std::vector<double> t(size_t(SS_ALL) * SS_STRIDE, 0.0);
+    for (int g = 0; g < 3; ++g)
+        for (int i = 0; i < SS_NPT[g]; ++i) {
+            const int kind = 3 - g, r = i >> 8, i0 = (i >> 6) & 3, i1 = (i >> 4) & 3, i2 = (i >> 2) & 3, i3 = i & 3;
+            const double xi = R.gl_x[i0], e1 = R.gl_x[i1], e2 = R.gl_x[i2], e3 = R.gl_x[i3];
+            const RefPair m = ss_region(kind, r, xi, e1, e2, e3);
+            const double w = R.gl_w[i0] * R.gl_w[i1] * R.gl_w[i2] * R.gl_w[i3] * ss_jac(kind, r, xi, e1, e2);
+            const double fx[3] = {1.0 - m.x1, m.x1 - m.x2, m.x2}, fy[3] = {1.0 - m.y1, m.y1 - m.y2, m.y2};
+            double *o = t.data() + size_t(SS_OFF[g] + i) * SS_STRIDE;
+            o[0] = m.x1;
+            o[1] = m.x2;
+            o[2] = m.y1;
+            o[3] = m.y2;
+            for (int k = 0; k < 9; ++k) o[4 + k] = w * fx[k / 3] * fy[k % 3];
+        }
+    double *dev = nullptr;
+    PB_HIP(hipMalloc(&dev, sizeof(double) * t.size()));
+    const hipError_t e = hipMemcpy(dev, t.data(), sizeof(double) * t.size(), hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        (void)hipFree(dev);
+        PB_HIP(e);
+    }
+    C.ss_points = dev;
+    return dev;
+}
+
+// One lane per touching ordered pair (tau, sigma), 64 pairs of one kind per
+// workgroup (ord: the pairs by kind, cnt of each); its SING_W wavefronts split
+// the rule's points, which are uniform and come through scalar loads, and
+// their sums are added in wavefront order.  The 3x3 V and K blocks (in the
+// triangles' own vertex order) go to out[18 * pair].  Both panels start at a
+// shared vertex, so x - y is formed from edge vectors alone, and its normal
+// distance from x's edges (y and the shared vertex lie in sigma's plane).
+//
+// Bound by FP64 vector issue: about 47 instruction slots per point (Yukawa
+// 71), 9 984 points per triangle.  One wavefront per pair, which formed the
+// region maps, shape products and 18 cross-lane sums for every pair, took
+// 1.44 / 1.58 ms (Laplace / Yukawa) at 20 480 triangles and 0.40 ms at 5 120.
+constexpr int SING_W = 8;
+template <bool YUK>
+__global__ void __launch_bounds__(64 * SING_W)
+    k_bem_singular(int64_t n3, int64_t n2, int64_t n1, const int32_t *__restrict__ ord,
+                   const int32_t *__restrict__ tp_tau, const int32_t *__restrict__ tp_sig,
+                   const int32_t *__restrict__ tri, const double *__restrict__ vx, const double *__restrict__ nrm,
+                   const double *__restrict__ area, double kappa, const double *__restrict__ points,
+                   double *__restrict__ out)
+{
+    constexpr int RND = 6; // sums exchanged at a time
+    __shared__ double red[SING_W][RND][64];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t g3 = (n3 + 63) / 64, g2 = (n2 + 63) / 64;
+    int64_t bi = blockIdx.x, seg = 0, n = n3;
+    int g = 0; // kind 3 - g
+    if (bi >= g3) {
+        bi -= g3;
+        seg = n3;
+        n = n2;
+        g = 1;
+        if (bi >= g2) {
+            bi -= g2;
+            seg = n3 + n2;
+            n = n1;
+            g = 2;
+        }
+    }
+    const int64_t i = bi * 64 + lane;
+    const bool in = i < n;
+    const int64_t pair = ord[seg + (in ? i : n - 1)];
     const int32_t ta = tp_tau[pair], sb = tp_sig[pair];
     int A[3], B[3];
     for (int k = 0; k < 3; ++k) {
         A[k] = tri[3 * ta + k];
         B[k] = tri[3 * sb + k];
     }
-    int shared = 0, ia[3] = {0, 0, 0}, ib[3] = {0, 0, 0};
+    int shared = 0, ia0 = 0, ia1 = 0, ib0 = 0, ib1 = 0; // the first two shared corners
     for (int a = 0; a < 3; ++a)
         for (int b = 0; b < 3; ++b)
             if (A[a] == B[b]) {
-                ia[shared] = a;
-                ib[shared] = b;
+                if (shared == 0) {
+                    ia0 = a;
+                    ib0 = b;
+                } else if (shared == 1) {
+                    ia1 = a;
+                    ib1 = b;
+                }
                 ++shared;
             }
     int pa[3], pb[3];
-    if (shared == 3) {
+    if (g == 0) { // identical
         pa[0] = pb[0] = 0;
         pa[1] = pb[1] = 1;
         pa[2] = pb[2] = 2;
-    } else if (shared == 2) {
-        pa[0] = ia[0];
-        pa[1] = ia[1];
-        pa[2] = 3 - ia[0] - ia[1];
-        pb[0] = ib[0];
-        pb[1] = ib[1];
-        pb[2] = 3 - ib[0] - ib[1];
-    } else {
-        pa[0] = ia[0];
-        pa[1] = (ia[0] + 1) % 3;
-        pa[2] = (ia[0] + 2) % 3;
-        pb[0] = ib[0];
-        pb[1] = (ib[0] + 1) % 3;
-        pb[2] = (ib[0] + 2) % 3;
+    } else if (g == 1) { // common edge: first
+        pa[0] = ia0;
+        pa[1] = ia1;
+        pa[2] = 3 - ia0 - ia1;
+        pb[0] = ib0;
+        pb[1] = ib1;
+        pb[2] = 3 - ib0 - ib1;
+    } else { // common vertex first
+        pa[0] = ia0;
+        pa[1] = (ia0 + 1) % 3;
+        pa[2] = (ia0 + 2) % 3;
+        pb[0] = ib0;
+        pb[1] = (ib0 + 1) % 3;
+        pb[2] = (ib0 + 2) % 3;
     }
-    double P[3][3], Q[3][3];
-    for (int k = 0; k < 3; ++k)
-        for (int d = 0; d < 3; ++d) {
-            P[k][d] = vx[3 * A[pa[k]] + d];
-            Q[k][d] = vx[3 * B[pb[k]] + d];
-        }
-    const double ny0 = nrm[3 * sb], ny1 = nrm[3 * sb + 1], ny2 = nrm[3 * sb + 2];
-    const int nreg = shared == 3 ? 6 : shared == 2 ? 5 : 2;
+    auto corner = [](const int(&T)[3], int k) { return k == 0 ? T[0] : k == 1 ? T[1] : T[2]; };
+    double E1[3], E2[3], F1[3], F2[3], a1 = 0.0, a2 = 0.0;
+    for (int d = 0; d < 3; ++d) {
+        const double p0 = vx[3 * corner(A, pa[0]) + d], p1 = vx[3 * corner(A, pa[1]) + d],
+                     p2 = vx[3 * corner(A, pa[2]) + d];
+        const double q0 = vx[3 * corner(B, pb[0]) + d], q1 = vx[3 * corner(B, pb[1]) + d],
+                     q2 = vx[3 * corner(B, pb[2]) + d], ny = nrm[3 * sb + d];
+        E1[d] = p1 - p0;
+        E2[d] = p2 - p1;
+        F1[d] = q1 - q0;
+        F2[d] = q2 - q1;
+        a1 = fma(E1[d], ny, a1);
+        a2 = fma(E2[d], ny, a2);
+    }
     double V[9], K[9];
     for (int k = 0; k < 9; ++k) V[k] = K[k] = 0.0;
-    const int npt = nreg * 256;
-    for (int idx = lane; idx < npt; idx += 64) {
-        const int r = idx >> 8, pt = idx & 255;
-        const int i0 = pt >> 6, i1 = (pt >> 4) & 3, i2 = (pt >> 2) & 3, i3 = pt & 3;
-        const double xi = G.x[i0], e1 = G.x[i1], e2 = G.x[i2], e3 = G.x[i3];
-        RefPair m;
-        ss_region(shared, r, xi, e1, e2, e3, m);
-        const double w = G.w[i0] * G.w[i1] * G.w[i2] * G.w[i3] * ss_jac(shared, r, xi, e1, e2);
-        double x[3], y[3];
+    const int npt = (g == 0 ? SS_NPT[0] : g == 1 ? SS_NPT[1] : SS_NPT[2]) / SING_W;
+    const double *T = points + int64_t((g == 0 ? SS_OFF[0] : g == 1 ? SS_OFF[1] : SS_OFF[2]) + w * npt) * SS_STRIDE;
+    for (int k = 0; k < npt; ++k, T += SS_STRIDE) {
+        const double x1 = T[0], x2 = T[1], y1 = T[2], y2 = T[3];
+        double r2 = 0.0;
+#pragma unroll
         for (int d = 0; d < 3; ++d) {
-            x[d] = P[0][d] + m.x1 * (P[1][d] - P[0][d]) + m.x2 * (P[2][d] - P[1][d]);
-            y[d] = Q[0][d] + m.y1 * (Q[1][d] - Q[0][d]) + m.y2 * (Q[2][d] - Q[1][d]);
+            const double dd = fma(x1, E1[d], x2 * E2[d]) - fma(y1, F1[d], y2 * F2[d]);
+            r2 = fma(dd, dd, r2);
         }
-        const double d0 = x[0] - y[0], d1 = x[1] - y[1], d2 = x[2] - y[2];
-        const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
-        const double ri = rsqrt(r2);
-        double gv, gk;
-        if (YUK) {
-            const double rr = r2 * ri;
-            const double e = exp(-kappa * rr);
-            gv = e * ri;
-            gk = (d0 * ny0 + d1 * ny1 + d2 * ny2) * (1.0 + kappa * rr) * e * ri * ri * ri;
-        } else {
-            gv = ri;
-            gk = (d0 * ny0 + d1 * ny1 + d2 * ny2) * ri * ri * ri;
+        const double ri = rsqrt_pos(r2);
+        double gv = ri, gk = ri * ri * ri;
+        if constexpr (YUK) {
+            gv = exp_neg(kappa * (r2 * ri)) * ri;
+            gk = gv * ri * (ri + kappa); // e (1 + kappa r) / r^3
         }
-        if (shared == 3) gk = 0.0; // (x - y).n_y vanishes on a flat panel
-        const double fx[3] = {1.0 - m.x1, m.x1 - m.x2, m.x2};
-        const double fy[3] = {1.0 - m.y1, m.y1 - m.y2, m.y2};
-        for (int a = 0; a < 3; ++a)
-            for (int b = 0; b < 3; ++b) {
-                const double ww = w * fx[a] * fy[b];
-                V[3 * a + b] += ww * gv;
-                K[3 * a + b] += ww * gk;
-            }
+#pragma unroll
+        for (int c = 0; c < 9; ++c) V[c] = fma(T[4 + c], gv, V[c]);
+        if (g == 0) continue; // (x - y).n_y vanishes on a flat panel
+        gk *= fma(x1, a1, x2 * a2);
+#pragma unroll
+        for (int c = 0; c < 9; ++c) K[c] = fma(T[4 + c], gk, K[c]);
     }
-    for (int k = 0; k < 9; ++k)
-        for (int off = 32; off > 0; off >>= 1) {
-            V[k] += __shfl_xor(V[k], off);
-            K[k] += __shfl_xor(K[k], off);
+    const double sc = 4.0 * area[ta] * area[sb] * INV4PI;
+#pragma unroll
+    for (int r0 = 0; r0 < 18; r0 += RND) {
+#pragma unroll
+        for (int k = 0; k < RND; ++k) red[w][k][lane] = r0 + k < 9 ? V[(r0 + k) % 9] : K[(r0 + k) % 9];
+        __syncthreads();
+        if (w < RND) {
+            double s = 0.0;
+#pragma unroll
+            for (int v = 0; v < SING_W; ++v) s += red[v][w][lane];
+            const int c = (r0 + w) % 9, a = c / 3, b = c % 3;
+            if (in) out[18 * pair + (r0 + w < 9 ? 0 : 9) + 3 * corner(pa, a) + corner(pb, b)] = sc * s;
         }
-    if (lane == 0) {
-        const double sc = 4.0 * area[ta] * area[sb] * INV4PI;
-        for (int a = 0; a < 3; ++a)
-            for (int b = 0; b < 3; ++b) {
-                out[18 * pair + 3 * pa[a] + pb[b]] = sc * V[3 * a + b];
-                out[18 * pair + 9 + 3 * pa[a] + pb[b]] = sc * K[3 * a + b];
-            }
+        __syncthreads();
     }
 }
 
 // Row-owned scatter of the touching-pair blocks and of the 1/2 M term into
-// the stored operator (Morton vertex order: vertex i is row minv[i]).
+// the stored operator (Morton vertex order: vertex i is row minv[i]).  One
+// wavefront per row: what the pairs at the vertex contribute (about 240
+// values of V' and K') is staged in LDS with its column, and the lane that
+// holds a column's first contribution adds up the column's, in order, and
+// adds the sum to the stored entry once.  (One thread per row that added every
+// contribution into global memory took 140-330 us whatever the surface's size.)
+constexpr int SCAT_CAP = 640; // staged at once: more than the pairs of any one triangle give
 template <typename MT>
-__global__ void k_bem_scatter(int64_t nv, int64_t ld, const int32_t *__restrict__ minv,
-                              const int32_t *__restrict__ v2t_ptr, const int32_t *__restrict__ v2t,
-                              const int32_t *__restrict__ tri, const int32_t *__restrict__ tp_ptr,
-                              const int32_t *__restrict__ tp_sig, const double *__restrict__ tpv,
-                              const double *__restrict__ area, double sV, double sK, MT *__restrict__ Bo)
+__global__ void __launch_bounds__(64)
+    k_bem_scatter(int64_t nv, int64_t ld, const int32_t *__restrict__ minv, const int32_t *__restrict__ v2t_ptr,
+                  const int32_t *__restrict__ v2t, const int32_t *__restrict__ tri,
+                  const int32_t *__restrict__ tp_ptr, const int32_t *__restrict__ tp_sig,
+                  const double *__restrict__ tpv, const double *__restrict__ area, double sV, double sK,
+                  MT *__restrict__ Bo)
 {
-    const int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-    if (i >= nv) return;
+    __shared__ int cj[SCAT_CAP];
+    __shared__ double cv[SCAT_CAP], ck[SCAT_CAP];
+    const int lane = threadIdx.x;
+    const int64_t i = blockIdx.x;
     MT *row = Bo + int64_t(minv[i]) * ld;
-    for (int32_t e = v2t_ptr[i]; e < v2t_ptr[i + 1]; ++e) {
-        const int32_t ta = v2t[e] / 3, a = v2t[e] % 3;
-        for (int32_t pp = tp_ptr[ta]; pp < tp_ptr[ta + 1]; ++pp) {
-            const int32_t sb = tp_sig[pp];
-            const double *blk = tpv + 18 * int64_t(pp);
-            for (int b = 0; b < 3; ++b) {
-                const int64_t j = minv[tri[3 * sb + b]];
-                add_entry(row, nv + j, sV * blk[3 * a + b]);
-                add_entry(row, j, sK * blk[9 + 3 * a + b]);
+    int m = 0; // staged
+    auto flush = [&]() {
+        __syncthreads();
+        for (int c = lane; c < m; c += 64) {
+            const int j = cj[c];
+            bool first = true;
+            double v = 0.0, k = 0.0;
+            for (int e = 0; e < m; ++e)
+                if (cj[e] == j) {
+                    first = first && e >= c;
+                    v += cv[e];
+                    k += ck[e];
+                }
+            if (first) {
+                add_entry(row, nv + j, v);
+                add_entry(row, int64_t(j), k);
             }
         }
-        for (int b = 0; b < 3; ++b)
-            add_entry(row, minv[tri[3 * ta + b]], 0.5 * area[ta] * (a == b ? 2.0 : 1.0) / 12.0);
+        __syncthreads();
+        m = 0;
+    };
+    for (int32_t e = v2t_ptr[i]; e < v2t_ptr[i + 1]; ++e) {
+        const int32_t ta = v2t[e] / 3, a = v2t[e] % 3, p0 = tp_ptr[ta];
+        const int np = tp_ptr[ta + 1] - p0;
+        for (int c0 = 0; c0 < 3 * np + 3; c0 += SCAT_CAP) { // one round, except at extreme valences
+            const int cn = min(3 * np + 3 - c0, SCAT_CAP);
+            if (m + cn > SCAT_CAP) flush();
+            for (int c = lane; c < cn; c += 64) {
+                const int q = c0 + c, b = q % 3;
+                int j;
+                double v = 0.0, k;
+                if (q < 3 * np) {
+                    const int64_t pp = p0 + q / 3;
+                    j = tri[3 * tp_sig[pp] + b];
+                    v = sV * tpv[18 * pp + 3 * a + b];
+                    k = sK * tpv[18 * pp + 9 + 3 * a + b];
+                } else {
+                    j = tri[3 * ta + b];
+                    k = 0.5 * area[ta] * (a == b ? 2.0 : 1.0) / 12.0;
+                }
+                cj[m + c] = minv[j];
+                cv[m + c] = v;
+                ck[m + c] = k;
+            }
+            m += cn;
+        }
     }
+    flush();
 }
 
 __global__ void k_gather_coords(int64_t nv, const int32_t *__restrict__ g, const double *__restrict__ x,
@@ -1356,6 +1446,23 @@ static int tile_tune(Problem &p, int w, RegArgs a, bool yuk, bool f32, hipStream
     return best;
 }
 
+// the touching-pair blocks of a surface (vertex coordinates vx) into tpv
+static void singular_pairs(Problem &p, const SurfaceDev &S, bool yuk, double kappa, const double *vx, double *tpv,
+                           hipStream_t s)
+{
+    const double *pts = ss_points(*p.ctx);
+    const unsigned g = nblk(S.tp_cnt[0], 64) + nblk(S.tp_cnt[1], 64) + nblk(S.tp_cnt[2], 64);
+    if (p.timing) p.timer.begin(T_SING, s);
+    if (yuk)
+        hipLaunchKernelGGL(k_bem_singular<true>, dim3(g), dim3(64 * SING_W), 0, s, S.tp_cnt[0], S.tp_cnt[1],
+                           S.tp_cnt[2], S.tp_ord, S.tp_tau, S.tp_sig, S.tri, vx, S.nrm, S.area, kappa, pts, tpv);
+    else
+        hipLaunchKernelGGL(k_bem_singular<false>, dim3(g), dim3(64 * SING_W), 0, s, S.tp_cnt[0], S.tp_cnt[1],
+                           S.tp_cnt[2], S.tp_ord, S.tp_tau, S.tp_sig, S.tri, vx, S.nrm, S.area, kappa, pts, tpv);
+    if (p.timing) p.timer.end(s);
+    PB_HIP(hipGetLastError());
+}
+
 void ensure_bem(Problem &p, int w, hipStream_t s)
 {
     if (p.bem_ready[w]) return;
@@ -1393,6 +1500,22 @@ void ensure_bem(Problem &p, int w, hipStream_t s)
         for (int64_t t = 0; t < T.nt; ++t)
             for (int32_t k = T.tp_ptr[t]; k < T.tp_ptr[t + 1]; ++k) tp_tau[k] = int32_t(t);
         S.tp_tau = A.upload(tp_tau, s);
+        std::vector<int32_t> tp_ord; // by shared vertices: 3, 2, 1
+        tp_ord.reserve(S.ntp);
+        std::vector<int8_t> kind(S.ntp);
+        for (int64_t k = 0; k < S.ntp; ++k) {
+            int n = 0;
+            for (int a = 0; a < 3; ++a)
+                for (int b = 0; b < 3; ++b) n += T.tri[3 * int64_t(tp_tau[k]) + a] == T.tri[3 * int64_t(T.tp_sig[k]) + b];
+            kind[k] = int8_t(n);
+        }
+        for (int g = 0; g < 3; ++g) {
+            const size_t before = tp_ord.size();
+            for (int64_t k = 0; k < S.ntp; ++k)
+                if (kind[k] == 3 - g) tp_ord.push_back(int32_t(k));
+            S.tp_cnt[g] = int64_t(tp_ord.size() - before);
+        }
+        S.tp_ord = A.upload(tp_ord, s);
         S.vdiag = A.alloc<double>(T.nv);
         S.tpv = nullptr;
         S.mpos = nullptr;
@@ -1433,7 +1556,6 @@ void ensure_bem(Problem &p, int w, hipStream_t s)
         PB_HIP(hipStreamSynchronize(s));
         p.bem_topo_ready[w] = true;
     }
-    int32_t *d_tptau = S.tp_tau;
     hipLaunchKernelGGL(k_tri_morton, dim3(nblk(T.nt, 256)), dim3(256), 0, s, T.nt, S.morton, S.tri, S.qp, S.nrm,
                        S.area, S.g, S.x, S.m_tri, S.m_qp, S.m_nrm, S.m_area, S.m_cen, S.m_qf, S.m_nf);
 
@@ -1459,16 +1581,7 @@ void ensure_bem(Problem &p, int w, hipStream_t s)
         // matrix-free: only the touching-pair blocks (kept) and the diagonal of V'
         double *vxm = wsp->doubles(3 * T.nv);
         hipLaunchKernelGGL(k_gather_coords, dim3(nblk(T.nv, 256)), dim3(256), 0, s, T.nv, S.g, S.x, vxm);
-        GL4 G = gl4arg();
-        if (p.timing) p.timer.begin(T_SING, s);
-        if (yuk)
-            hipLaunchKernelGGL(k_bem_singular<true>, dim3(nblk(S.ntp * 64, 256)), dim3(256), 0, s, S.ntp, d_tptau,
-                               S.tp_sig, S.tri, vxm, S.nrm, S.area, kappa, G, S.tpv);
-        else
-            hipLaunchKernelGGL(k_bem_singular<false>, dim3(nblk(S.ntp * 64, 256)), dim3(256), 0, s, S.ntp, d_tptau,
-                               S.tp_sig, S.tri, vxm, S.nrm, S.area, kappa, G, S.tpv);
-        if (p.timing) p.timer.end(s);
-        PB_HIP(hipGetLastError());
+        singular_pairs(p, S, yuk, kappa, vxm, S.tpv, s);
         mf_vdiag(p, w, s);
         mf_spai(p, w, s);
         PB_HIP(hipStreamSynchronize(s));
@@ -1550,21 +1663,12 @@ void ensure_bem(Problem &p, int w, hipStream_t s)
     }
     // touching pairs
     hipLaunchKernelGGL(k_gather_coords, dim3(nblk(nv, 256)), dim3(256), 0, s, nv, S.g, S.x, vx);
-    GL4 G = gl4arg();
-    if (p.timing) p.timer.begin(T_SING, s);
-    if (yuk)
-        hipLaunchKernelGGL(k_bem_singular<true>, dim3(nblk(S.ntp * 64, 256)), dim3(256), 0, s, S.ntp, d_tptau,
-                           S.tp_sig, S.tri, vx, S.nrm, S.area, kappa, G, tpv);
-    else
-        hipLaunchKernelGGL(k_bem_singular<false>, dim3(nblk(S.ntp * 64, 256)), dim3(256), 0, s, S.ntp, d_tptau,
-                           S.tp_sig, S.tri, vx, S.nrm, S.area, kappa, G, tpv);
-    if (p.timing) p.timer.end(s);
-    PB_HIP(hipGetLastError());
+    singular_pairs(p, S, yuk, kappa, vx, tpv, s);
     if (f32)
-        hipLaunchKernelGGL(k_bem_scatter<float>, dim3(nblk(nv, 64)), dim3(64), 0, s, nv, ld, S.minv, S.v2t_ptr, S.v2t,
+        hipLaunchKernelGGL(k_bem_scatter<float>, dim3(unsigned(nv)), dim3(64), 0, s, nv, ld, S.minv, S.v2t_ptr, S.v2t,
                            S.tri, S.tp_ptr, S.tp_sig, tpv, S.area, sV, sK, static_cast<float *>(S.B));
     else
-        hipLaunchKernelGGL(k_bem_scatter<double>, dim3(nblk(nv, 64)), dim3(64), 0, s, nv, ld, S.minv, S.v2t_ptr,
+        hipLaunchKernelGGL(k_bem_scatter<double>, dim3(unsigned(nv)), dim3(64), 0, s, nv, ld, S.minv, S.v2t_ptr,
                            S.v2t, S.tri, S.tp_ptr, S.tp_sig, tpv, S.area, sV, sK, static_cast<double *>(S.B));
     PB_HIP(hipGetLastError());
     // diagonal of V', symmetric storage use (Delta from the stored values),

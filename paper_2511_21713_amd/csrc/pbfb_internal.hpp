@@ -168,6 +168,10 @@ struct SurfaceDev {
     int32_t *mpos = nullptr;
     int32_t *tp_ptr = nullptr, *tp_sig = nullptr, *tp_tau = nullptr, *morton = nullptr;
     int64_t ntp = 0;
+    // the touching pairs ordered by shared vertices: identical panels, common
+    // edge, common vertex (tp_cnt of each)
+    int32_t *tp_ord = nullptr;
+    int64_t tp_cnt[3] = {0, 0, 0};
     int32_t *cslot = nullptr; // FEM-row slot of the coupling entry per (v2t entry, b)
     // matrix-free mode: near-field V' on the 3-ring pattern (rows ascending)
     int32_t *nf_ptr = nullptr, *nf_col = nullptr, *nf_row = nullptr;
@@ -235,7 +239,8 @@ struct Ctx {
     hipStream_t stream = nullptr;
     Workspace asm_ws[N_ASM_WS];
     hipStream_t setup_stream[N_ASM_WS] = {}; // streams of a batch's parallel device setup, created on first use
-    std::mutex setup_mu;                     // guards their creation
+    std::mutex setup_mu;                     // guards their creation and that of ss_points
+    double *ss_points = nullptr;             // Sauter-Schwab points and weights (kernels_bem.hip), created on first use
     // tuned tile shape per (precision, kernel, size class); tune_mu guards it
     // and serialises the tuning, so every problem of the context sees one choice
     std::mutex tune_mu;
