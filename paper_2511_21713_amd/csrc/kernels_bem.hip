@@ -788,7 +788,8 @@ static const double *ss_points(Ctx &C)
 // Bound by FP64 vector issue: about 47 instruction slots per point (Yukawa
 // 71), 9 984 points per triangle.  One wavefront per pair, which formed the
 // region maps, shape products and 18 cross-lane sums for every pair, took
-// 1.44 / 1.58 ms (Laplace / Yukawa) at 20 480 triangles and 0.40 ms at 5 120.
+// 1.53 ms at 20 480 triangles and 0.40 at 5 120 (mean of Laplace and Yukawa);
+// this 0.47 and 0.13.
 constexpr int SING_W = 8;
 template <bool YUK>
 __global__ void __launch_bounds__(64 * SING_W)
@@ -876,6 +877,7 @@ __global__ void __launch_bounds__(64 * SING_W)
     for (int k = 0; k < 9; ++k) V[k] = K[k] = 0.0;
     const int npt = (g == 0 ? SS_NPT[0] : g == 1 ? SS_NPT[1] : SS_NPT[2]) / SING_W;
     const double *T = points + int64_t((g == 0 ? SS_OFF[0] : g == 1 ? SS_OFF[1] : SS_OFF[2]) + w * npt) * SS_STRIDE;
+#pragma unroll 4 // several points' scalar loads in flight
     for (int k = 0; k < npt; ++k, T += SS_STRIDE) {
         const double x1 = T[0], x2 = T[1], y1 = T[2], y2 = T[3];
         double r2 = 0.0;
