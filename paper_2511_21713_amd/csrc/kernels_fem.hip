@@ -733,8 +733,9 @@ void ensure_topology(Problem &p, hipStream_t s)
     A.release();
     p.d_x = A.upload(p.x, s);
     p.d_tet = A.upload(p.tet, s);
-    std::vector<int32_t> sptr, col, diag, cslot[2], nvert[2]; // until the uploads are done
+    std::vector<int32_t> col, diag, cslot[2], nvert[2]; // until the uploads are done
     FemRows R;
+    std::vector<int32_t> &sptr = p.sptr;
     build_fem_topology(p, sptr, col, R, diag, cslot);
     p.nnz = int64_t(col.size());
     p.d_sptr = A.upload(sptr, s);

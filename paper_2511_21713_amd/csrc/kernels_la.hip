@@ -120,7 +120,7 @@ __global__ void __launch_bounds__(256)
     const int64_t q = bi - G.s0 - G.s1;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const double s =
-        sell_rows<VT, false>(sptr, lng, col, val, [x](int64_t c) { return x[c]; }, q, lane, wv, nrows);
+        sell_rows<VT, false>(sptr[q], (sptr[q + 1] - sptr[q]) / SLICE, lng, col, val, [x](int64_t c) { return x[c]; }, q, lane, wv, nrows);
     const int64_t row = q * SLICE + lane;
     if (wv == 0 && row < nrows) y[row] = s;
 }

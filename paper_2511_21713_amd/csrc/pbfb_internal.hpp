@@ -327,6 +327,7 @@ struct Problem {
     // of row 64q + l sits at d_sptr[q] + 64 k + l for k below the slice width
     // (d_sptr[q + 1] - d_sptr[q]) / 64, in ascending column order; entries past
     // a row's length hold column = the row itself and value 0.
+    std::vector<int32_t> sptr; // host copy of d_sptr
     int32_t *d_sptr = nullptr, *d_col = nullptr, *d_diag = nullptr;
     double *d_val0 = nullptr, *d_val = nullptr;
     float *d_val32 = nullptr;

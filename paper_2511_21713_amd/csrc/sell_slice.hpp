@@ -41,13 +41,12 @@ struct SellLong {
 };
 
 // Partial sum of row 64 q + lane over the entries k = wv, wv + 4, ... of
-// slice q with input entry x(column).  FEM_ONLY skips the coupling columns
+// slice q (entries from b0, width w) with input entry x(column).  FEM_ONLY skips the coupling columns
 // (index >= nn).
 template <typename VT, bool FEM_ONLY, typename XF>
-__device__ inline double sell_part_of(const int32_t *__restrict__ sptr, const int32_t *__restrict__ col,
-                                      const VT *__restrict__ val, XF &&x, int64_t q, int lane, int wv, int64_t nn)
+__device__ inline double sell_part_of(int32_t b0, int32_t w, const int32_t *__restrict__ col,
+                                      const VT *__restrict__ val, XF &&x, int lane, int wv, int64_t nn)
 {
-    const int32_t b0 = sptr[q], w = (sptr[q + 1] - b0) / 64;
     double acc = 0.0;
     for (int k0 = wv; k0 < w; k0 += SELL_W * SELL_U) {
         int32_t c[SELL_U];
@@ -111,10 +110,10 @@ __device__ inline void sell_long(const SellLong &L, const int32_t *__restrict__ 
 // One row product per lane of wavefront 0 for the 64 rows of slice q, long
 // rows included
 template <typename VT, bool FEM_ONLY, typename XF>
-__device__ inline double sell_rows(const int32_t *__restrict__ sptr, const SellLong &L, const int32_t *__restrict__ col,
+__device__ inline double sell_rows(int32_t b0, int32_t w, const SellLong &L, const int32_t *__restrict__ col,
                                    const VT *__restrict__ val, XF &&x, int64_t q, int lane, int wv, int64_t nn)
 {
-    double acc = sell_reduce(sell_part_of<VT, FEM_ONLY>(sptr, col, val, x, q, lane, wv, nn), lane, wv);
+    double acc = sell_reduce(sell_part_of<VT, FEM_ONLY>(b0, w, col, val, x, lane, wv, nn), lane, wv);
     sell_long<VT, FEM_ONLY>(L, col, val, x, q, lane, wv, nn, acc);
     return acc;
 }
