@@ -919,10 +919,11 @@ __global__ void __launch_bounds__(64 * SING_W)
 // Row-owned scatter of the touching-pair blocks and of the 1/2 M term into
 // the stored operator (Morton vertex order: vertex i is row minv[i]).  One
 // wavefront per row: what the pairs at the vertex contribute (about 240
-// values of V' and K') is staged in LDS with its column, and the lane that
-// holds a column's first contribution adds up the column's, in order, and
-// adds the sum to the stored entry once.  (One thread per row that added every
-// contribution into global memory took 140-330 us whatever the surface's size.)
+// values of V' and K') is staged in LDS with its column; the wavefront then
+// walks the contributions in order, a lane per distinct column adding its own,
+// and adds each column's sum to the stored entry once.  (One thread per row
+// that added every contribution into global memory took 140-330 us whatever
+// the surface's size.)
 constexpr int SCAT_CAP = 640; // staged at once: more than the pairs of any one triangle give
 template <typename MT>
 __global__ void __launch_bounds__(64)
@@ -940,22 +941,37 @@ __global__ void __launch_bounds__(64)
     int m = 0; // staged
     auto flush = [&]() {
         __syncthreads();
-        for (int c = lane; c < m; c += 64) {
-            const int j = cj[c];
-            bool first = true;
-            double v = 0.0, k = 0.0;
-            for (int e = 0; e < m; ++e)
-                if (cj[e] == j) {
-                    first = first && e >= c;
-                    v += cv[e];
-                    k += ck[e];
+        int col = -1, nu = 0; // this lane's column, columns in use
+        double v = 0.0, k = 0.0;
+        auto store = [&]() {
+            if (lane < nu) {
+                add_entry(row, nv + col, v);
+                add_entry(row, int64_t(col), k);
+            }
+            col = -1;
+            nu = 0;
+            v = k = 0.0;
+            __threadfence_block(); // a column may come back to another lane
+            __syncthreads();
+        };
+        for (int c0 = 0; c0 < m; c0 += 64) {
+            const int cn = min(m - c0, 64);
+            const int jj = lane < cn ? cj[c0 + lane] : -1;
+            for (int e = 0; e < cn; ++e) {
+                const int j = __builtin_amdgcn_readlane(jj, e);
+                if (__ballot(col == j) == 0) { // a new column
+                    if (nu == 64) store();
+                    if (lane == nu) col = j;
+                    ++nu;
                 }
-            if (first) {
-                add_entry(row, nv + j, v);
-                add_entry(row, int64_t(j), k);
+                const double ev = cv[c0 + e], ek = ck[c0 + e]; // one address: broadcast
+                if (col == j) {
+                    v += ev;
+                    k += ek;
+                }
             }
         }
-        __syncthreads();
+        store();
         m = 0;
     };
     for (int32_t e = v2t_ptr[i]; e < v2t_ptr[i + 1]; ++e) {
