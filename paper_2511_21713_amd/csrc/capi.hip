@@ -533,11 +533,8 @@ pbfb_status pbfb_residual(pbfb_problem *pp, int scheme, const double *phi, doubl
     const int64_t n = p.n();
     const double *dphi = dev_in(p, SCR_G3, phi, n, mem, s);
     double *dF = mem == PBFB_MEM_DEVICE ? F : scratch<double>(p, SCR_G4, n);
-    double *tmp = scratch<double>(p, SCR_G5, n);
     coupled_apply_linear(p, dphi, dF, s);
-    fem_nonlinear(p, scheme, dphi, tmp, s);
-    vec_axpby(p.nn, 1.0, tmp, 1.0, dF, s);
-    vec_axpby(n, -1.0, p.d_b, 1.0, dF, s);
+    fem_nonlinear(p, scheme, dphi, dF, 1.0, p.d_b, dF, s); // F = A phi + N - b
     if (mem != PBFB_MEM_DEVICE) PB_HIP(hipMemcpyAsync(F, dF, sizeof(double) * n, hipMemcpyDeviceToHost, s));
     PB_HIP(hipStreamSynchronize(s));
     API_END

@@ -97,7 +97,7 @@ struct GState {
 
 struct WItem {
     int inst, a;
-    int64_t b;
+    int64_t b; // no padding: lists are compared byte by byte
     // FEM slices: first stored entry and width.  A small launch is a chain of
     // dependent loads, about 0.2 us each: item -> state and descriptor -> values
     // and columns -> inputs, with nothing to wait for in between (offsets read
@@ -134,7 +134,7 @@ __device__ inline double fem_rows(const GDesc &d, XF &&x, const WItem &it, int l
 
 // ---------------------------------------------------------------------------
 // start of a batched solve: x = 0, the padding of the packed inputs, the
-// Chebyshev coefficients from the bound lmax (grid: blocks x instances)
+// Chebyshev coefficients from the bound's maxima (grid: blocks x instances)
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_binit(const GDesc *__restrict__ D)
 {
@@ -143,8 +143,16 @@ __global__ void __launch_bounds__(256) k_binit(const GDesc *__restrict__ D)
     for (int64_t k = i0; k < d.n; k += step) d.x[k] = 0.0;
     for (int64_t k = 2 * d.nm + i0; k < d.ldm; k += step) d.xm[k] = 0.0;
     for (int64_t k = 2 * d.ns + i0; k < d.lds; k += step) d.xs[k] = 0.0;
-    if (i0 != 0 || d.pc != PBFB_PC_CHEB_SPAI) return;
-    const double hi = *d.lmax, lo = hi / d.cheb_ratio;
+    if (blockIdx.x != 0 || d.pc != PBFB_PC_CHEB_SPAI) return;
+    __shared__ double red[4];
+    double hi = 0.0; // the bound: the largest of the slices' maxima
+    for (int64_t q = threadIdx.x; q < (d.nn + SLICE - 1) / SLICE; q += 256) hi = fmax(hi, d.lmax[q]);
+    for (int o = 32; o > 0; o >>= 1) hi = fmax(hi, __shfl_xor(hi, o));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = hi;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    hi = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+    const double lo = hi / d.cheb_ratio;
     const double theta = 0.5 * (hi + lo), delta = 0.5 * (hi - lo), sigma = theta / delta;
     double rho = 1.0 / sigma;
     d.coef[0] = theta;
@@ -207,6 +215,13 @@ __device__ inline void prec_surface(const GDesc &d, const GState &s, int64_t k)
     prec_final(d, s, k, zv);
 }
 
+// One Chebyshev term of a row: its direction (written out so that the slices
+// and the single workgroup below round alike)
+__device__ inline double cheb_dir(double c0, double dk, double c1, double di, double src, double acc)
+{
+    return fma(c0, dk, (c1 * di) * (src - acc));
+}
+
 // Work items: a = 0: the 64 FEM rows from b, a = 1: the 256 surface rows from
 // nn + b.  Surface rows: the approximate inverse.  FEM rows: the first two
 // Chebyshev terms in one pass -- the first, z_0 = D^-1 src / theta, is
@@ -237,7 +252,7 @@ __global__ void __launch_bounds__(256) k_bfirst(const WItem *__restrict__ wl, co
     const double acc = fem_rows<true>(d, z0, it, lane, wv);
     if (wv != 0 || row >= d.nn) return;
     const double zp = z0(row);
-    const double dv = d.coef[2] * zp + d.coef[3] * d.dinv[row] * (pc_src(d, s, row) - acc);
+    const double dv = cheb_dir(d.coef[2], zp, d.coef[3], d.dinv[row], pc_src(d, s, row), acc);
     d.dk[row] = dv;
     if (d.cheb_k == 2) prec_final(d, s, row, zp + dv);
     else ((d.cheb_k - 2) % 2 == 0 ? d.z : d.zb)[row] = zp + dv;
@@ -269,7 +284,7 @@ __global__ void __launch_bounds__(256) k_bcheb(const WItem *__restrict__ wl, con
     }
     const double acc = fem_rows<true>(d, [zp](int64_t c) { return zp[c]; }, it, lane, wv);
     if (wv != 0 || row >= d.nn) return;
-    const double dv = c0 * dk + c1 * di * (src - acc);
+    const double dv = cheb_dir(c0, dk, c1, di, src, acc);
     d.dk[row] = dv;
     const double zv = z0 + dv;
     if (step == d.cheb_k - 1) prec_final(d, s, row, zv);
@@ -282,7 +297,10 @@ __global__ void __launch_bounds__(256) k_bcheb(const WItem *__restrict__ wl, con
 // to TINY_W FEM entries per thread), and a term is then LDS gathers on one CU:
 // 23 terms of 1 134 rows take 44 us, as launches about 100 (sphere of 320
 // triangles: 8.8 -> 6.8 ms per solve).  With the values streamed from L2 at
-// every term one workgroup was slower than the launches (11.0 ms).
+// every term one workgroup was slower than the launches (11.0 ms).  The
+// arithmetic is that of the slices, so a batch may take either path: it takes
+// this one only when every instance can, since beside larger instances the
+// slices ride in launches that run anyway.
 constexpr int TINY_T = 1024, TINY_H = 2, TINY_ROWS = TINY_T * TINY_H, TINY_W = 16;
 static bool prec_tiny(const Problem &p, int pc, int cheb_k)
 {
@@ -325,11 +343,13 @@ __device__ inline void tiny_terms(const GDesc &d, const GState &s, double (&zs)[
         for (int h = 0; h < TINY_H; ++h) {
             const int r = tid + h * TINY_T;
             if (h * TINY_T >= nn) break; // uniform
-            double acc = 0.0;
+            double a4[SELL_W] = {}; // the order of sell_part_of and sell_reduce
 #pragma unroll
             for (int k = 0; k < TINY_W; ++k)
-                acc = fma(double(v[h][k]), zp[k % 2 == 0 ? c2[h][k / 2] & 0xffff : c2[h][k / 2] >> 16], acc);
-            dk[h] = c0 * dk[h] + c1 * di[h] * (src[h] - acc);
+                a4[k % SELL_W] = fma(double(v[h][k]), zp[k % 2 == 0 ? c2[h][k / 2] & 0xffff : c2[h][k / 2] >> 16],
+                                     a4[k % SELL_W]);
+            const double acc = ((a4[0] + a4[1]) + a4[2]) + a4[3];
+            dk[h] = cheb_dir(c0, dk[h], c1, di[h], src[h], acc);
             const double zv = zp[r] + dk[h];
             zn[r] = zv;
             if (step == d.cheb_k - 1 && r < nn) prec_final(d, s, r, zv);
@@ -609,7 +629,8 @@ constexpr int GCOUNT_BITS = 20;
 constexpr int64_t GCOUNT_MAX = (int64_t(1) << GCOUNT_BITS) - 1;
 
 __global__ void __launch_bounds__(64) k_bcontrol(const GDesc *__restrict__ D, GState *__restrict__ S,
-                                                 GCount *__restrict__ C, unsigned long long *__restrict__ host)
+                                                 GCount *__restrict__ C, unsigned long long *__restrict__ host,
+                                                 GState *__restrict__ hstate)
 {
     __shared__ double hc[1024], cs[1024], sn[1024], gl[1024];
     __shared__ GState ss;
@@ -691,7 +712,7 @@ __global__ void __launch_bounds__(64) k_bcontrol(const GDesc *__restrict__ D, GS
         if (st0 == G_INIT) ss.target = d.tol * nr;
         else ss.napply += 1; // RES: the true residual took one application
         ss.beta = nr;
-        if (!(nr == nr)) {
+        if (!(nr <= 1.7976931348623157e308)) { // NaN or infinite
             ss.st = G_FAIL;
             ss.code = PBFB_ENAN;
         } else if (nr <= ss.target) {
@@ -710,6 +731,7 @@ __global__ void __launch_bounds__(64) k_bcontrol(const GDesc *__restrict__ D, GS
     if (lane != 0) return;
     S[q] = ss;
     const bool over = ss.st == G_DONE || ss.st == G_FAIL, was = st0 == G_DONE || st0 == G_FAIL;
+    if (!was) hstate[q] = ss; // read by the host after its last synchronisation
     if (over && !was) atomicAdd(&C->ended, 1);
     if ((over || ss.st == G_FIN) && !was && st0 != G_FIN) atomicAdd(&C->ending, 1);
     __threadfence(); // the counts before the tick
@@ -775,6 +797,9 @@ struct BatchBuffers {
     void *dev = nullptr, *stage = nullptr;
     size_t dev_bytes = 0, stage_bytes = 0;
     unsigned long long *word = nullptr;
+    GState *state = nullptr; // pinned: every instance's state as control left it
+    size_t nstate = 0;
+    size_t listed = 0, head = 0; // bytes of the stage that the device copy holds (0: none), of them before the lists
     hipGraphExec_t step = nullptr; // the captured Krylov step (left to process exit)
     GraphKey key;
     ~BatchBuffers()
@@ -782,14 +807,25 @@ struct BatchBuffers {
         if (dev) (void)hipFree(dev);
         if (stage) (void)hipHostFree(stage);
         if (word) (void)hipHostFree(word);
+        if (state) (void)hipHostFree(state);
     }
-    void reserve(size_t bytes)
+    void reserve(size_t bytes, size_t nb)
     {
+        if (nstate < nb) {
+            if (step) PB_HIP(hipGraphExecDestroy(step)); // it holds the pointer
+            step = nullptr;
+            if (state) PB_HIP(hipHostFree(state));
+            state = nullptr;
+            nstate = 0;
+            PB_HIP(hipHostMalloc(reinterpret_cast<void **>(&state), sizeof(GState) * nb, hipHostMallocDefault));
+            nstate = nb;
+        }
         if (!word) PB_HIP(hipHostMalloc(reinterpret_cast<void **>(&word), 64, hipHostMallocDefault));
         if (stage_bytes < bytes) {
             if (stage) PB_HIP(hipHostFree(stage));
             stage = nullptr;
             stage_bytes = 0;
+            listed = 0;
             PB_HIP(hipHostMalloc(&stage, bytes, hipHostMallocDefault));
             stage_bytes = bytes;
         }
@@ -799,6 +835,7 @@ struct BatchBuffers {
             if (dev) PB_HIP(hipFree(dev));
             dev = nullptr;
             dev_bytes = 0;
+            listed = 0;
             PB_HIP(hipMalloc(&dev, bytes));
             dev_bytes = bytes;
         }
@@ -847,6 +884,8 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
     std::vector<WItem> wl_gemv_k, wl_gemv_v;
     int maxiter_host = 0, kmax = 1;
     int64_t nmax = 0;
+    const bool tiny = std::all_of(jobs.begin(), jobs.end(),
+                                  [](const GmresJob *J) { return prec_tiny(*J->p, J->pc, J->cheb_k); });
     for (int q = 0; q < nb; ++q) {
         GmresJob &J = *jobs[q];
         Problem &p = *J.p;
@@ -962,7 +1001,7 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
             return WItem{q, 0, r, e0, (p.sptr[r / SLICE + 1] - e0) / SLICE};
         };
         for (int64_t r = 0; r < p.nn; r += SLICE) wl_spmv.push_back(slice(r));
-        if (prec_tiny(p, J.pc, J.cheb_k)) {
+        if (tiny) {
             wl_tiny.push_back(WItem{q, 0, 0});
         } else {
             for (int64_t r = 0; r < p.nn; r += SLICE) wl_cheb.push_back(slice(r));
@@ -987,15 +1026,22 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
     const size_t items = wl_vec.size() + wl_gemv.size() + wl_fin.size() + wl_spmv.size() + nfirst +
                          ntiny + wl_dot.size();
     const size_t bytes = (sizeof(GDesc) + sizeof(GState)) * nb + sizeof(GCount) + sizeof(WItem) * items + 512;
-    BB.reserve(bytes);
+    BB.reserve(bytes, size_t(nb));
     // the block and the reported word belong to this call until its stream has drained
     struct Drain {
         hipStream_t s;
         ~Drain() { (void)hipStreamSynchronize(s); }
     } drain{s};
     size_t cur = 0;
-    auto put = [&](const void *src, size_t b) {
-        std::memcpy(static_cast<char *>(BB.stage) + cur, src, b);
+    bool same = true; // the lists are those of the previous call
+    auto put = [&](const void *src, size_t b, bool list) {
+        char *to = static_cast<char *>(BB.stage) + cur;
+        if (!list) {
+            std::memcpy(to, src, b);
+        } else if (!same || cur + b > BB.listed || std::memcmp(to, src, b)) {
+            same = false;
+            std::memcpy(to, src, b);
+        }
         char *d = static_cast<char *>(BB.dev) + cur;
         cur += (b + 15) / 16 * 16;
         return static_cast<void *>(d);
@@ -1004,19 +1050,24 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
         const std::vector<WItem> *const *l = lists.begin();
         std::vector<WItem> v(**l);
         for (++l; l != lists.end(); ++l) v.insert(v.end(), (*l)->begin(), (*l)->end());
-        return static_cast<WItem *>(put(v.data(), sizeof(WItem) * v.size()));
+        return static_cast<WItem *>(put(v.data(), sizeof(WItem) * v.size(), true));
     };
-    GDesc *dD = static_cast<GDesc *>(put(desc.data(), sizeof(GDesc) * nb));
-    GState *dS = static_cast<GState *>(put(st.data(), sizeof(GState) * nb));
+    GDesc *dD = static_cast<GDesc *>(put(desc.data(), sizeof(GDesc) * nb, false));
+    GState *dS = static_cast<GState *>(put(st.data(), sizeof(GState) * nb, false));
     const GCount zero{};
-    GCount *dC = static_cast<GCount *>(put(&zero, sizeof(zero)));
+    GCount *dC = static_cast<GCount *>(put(&zero, sizeof(zero), false));
+    const size_t head = cur;
     WItem *dvec = put_items({&wl_vec});
     WItem *dgemv = put_items({&wl_gemv});
     WItem *dtail = put_items({&wl_fin, &wl_spmv});
     WItem *dfirst = put_items({&wl_cheb, &wl_surf});
     WItem *dtiny = put_items({&wl_tiny});
     WItem *ddot = put_items({&wl_dot});
-    PB_HIP(hipMemcpyAsync(BB.dev, BB.stage, cur, hipMemcpyHostToDevice, s));
+    if (BB.listed != cur || BB.head != head) same = false;
+    BB.listed = 0; // until the copy is enqueued
+    PB_HIP(hipMemcpyAsync(BB.dev, BB.stage, same ? head : cur, hipMemcpyHostToDevice, s));
+    BB.listed = cur;
+    BB.head = head;
     __atomic_store_n(BB.word, 0ull, __ATOMIC_RELEASE);
 
     EventTimer *tm = nullptr;
@@ -1036,7 +1087,7 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
     // the end of a step: |w| and control, the next basis vector or t = V y
     auto enqueue_end = [&]() {
         hipLaunchKernelGGL(k_bend, dim3(ndot), dim3(256), 0, s, ddot, dD, dS);
-        hipLaunchKernelGGL(k_bcontrol, dim3(unsigned(nb)), dim3(64), 0, s, dD, dS, dC, BB.word);
+        hipLaunchKernelGGL(k_bcontrol, dim3(unsigned(nb)), dim3(64), 0, s, dD, dS, dC, BB.word, BB.state);
         hipLaunchKernelGGL(k_bnext, dim3(nvec), dim3(256), 0, s, dvec, dD, dS);
     };
     // one Krylov step of the whole batch
@@ -1135,9 +1186,8 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
         running(enqueued, reported, ending);
         PB_CHECK(reported >= enqueued, PBFB_EDEVICE, "a Krylov step did not report its end");
     }
-    PB_HIP(hipMemcpyAsync(BB.stage, dS, sizeof(GState) * nb, hipMemcpyDeviceToHost, s));
     PB_HIP(hipStreamSynchronize(s));
-    std::memcpy(st.data(), BB.stage, sizeof(GState) * nb);
+    std::copy(BB.state, BB.state + nb, st.begin());
     for (int q = 0; q < nb; ++q) {
         GmresJob &J = *jobs[q];
         J.iters = st[q].total;

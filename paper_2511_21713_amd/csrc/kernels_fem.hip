@@ -418,6 +418,47 @@ __global__ void __launch_bounds__(256)
     (wv == 0 ? o0 : wv == 1 ? o1 : o2)[a] = v;
 }
 
+// out = x + sgn [N; 0; 0] - y over all n unknowns (y null: 0), N the node sums of
+// per_tet as in k_node_gather<1>: workgroups of the slices, of the long rows,
+// then 256 surface rows each
+__global__ void __launch_bounds__(256)
+    k_node_combine(int64_t nn, int64_t n, int64_t nsl, const int32_t *__restrict__ tptr,
+                   const int32_t *__restrict__ n2t, FemRowsDev R, const double *__restrict__ per_tet,
+                   const double *x, double sgn, const double *__restrict__ y, double *out)
+{
+    __shared__ double red[4][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t q = blockIdx.x;
+    double s = 0.0;
+    int64_t a;
+    if (q < nsl) {
+        a = q * SLICE + lane;
+        const int32_t t0 = tptr[q], nt = (tptr[q + 1] - t0) / SLICE;
+#pragma unroll 4
+        for (int e = wv; e < nt; e += 4) {
+            const int32_t tc = n2t[t0 + SLICE * e + lane];
+            if (tc >= 0) s += per_tet[tc];
+        }
+        if (R.nlong && a < nn)
+            for (int32_t l = R.long_ptr[q]; l < R.long_ptr[q + 1]; ++l)
+                if (R.long_row[l] == a) a = nn; // written by its own workgroup
+    } else if (q < nsl + R.nlong) {
+        const int64_t l = q - nsl;
+        a = lane == 0 ? R.long_row[l] : nn;
+        for (int32_t e = R.tptr[l] + int32_t(threadIdx.x); e < R.tptr[l + 1]; e += 256) s += per_tet[R.t2[e]];
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    } else {
+        a = nn + (q - nsl - R.nlong) * 256 + threadIdx.x;
+        if (a < n) out[a] = y ? x[a] - y[a] : x[a];
+        return;
+    }
+    red[wv][lane] = s;
+    __syncthreads();
+    if (wv != 0 || a >= nn) return;
+    const double v = x[a] + sgn * ((red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]));
+    out[a] = y ? v - y[a] : v;
+}
+
 // per-tet integral of u sinh u - 2 cosh u + 2 for u = u_lin + u_nl (block partial sums)
 __global__ void k_energy_integral(int64_t nt, const double *__restrict__ tg, const int32_t *__restrict__ tet,
                                   const double *__restrict__ ul, const double *__restrict__ unl, TetRuleArg R,
@@ -969,18 +1010,23 @@ void fem_assemble_linear(Problem &p, hipStream_t s)
     fem_rows(p, nullptr, p.d_val0, p.d_val, p.d_val32, s);
 }
 
-void fem_nonlinear(Problem &p, int scheme, const double *u, double *out, hipStream_t s)
+void fem_nonlinear(Problem &p, int scheme, const double *u, const double *x, double sgn, const double *y, double *out,
+                   hipStream_t s)
 {
-    fem_nonlinear_buf(p, scheme, u, out, scratch<double>(p, SCR_TETR, 16 * size_t(p.ntet)), s);
+    fem_nonlinear_buf(p, scheme, u, x, sgn, y, out, scratch<double>(p, SCR_TETR, 16 * size_t(p.ntet)), s);
 }
 
-void fem_nonlinear_buf(Problem &p, int scheme, const double *u, double *out, double *Nt, hipStream_t s)
+void fem_nonlinear_buf(Problem &p, int scheme, const double *u, const double *x, double sgn, const double *y,
+                       double *out, double *Nt, hipStream_t s)
 {
     const double c = p.eps_s * p.kappa * p.kappa;
     hipLaunchKernelGGL(k_tet_reaction<MODE_N>, dim3(nblocks(p.ntet, 128)), dim3(128), 0, s, p.ntet, p.d_tgeo, p.d_tet,
                        u, (const double *)nullptr, 0.0, scheme, c, tet_rule_arg(), p.ntet_i(), Nt,
                        (const double *)nullptr, (const int *)nullptr);
-    node_gather<1>(p, Nt, out, nullptr, nullptr, nullptr, s);
+    const int64_t nsl = nblocks(p.nn, SLICE);
+    hipLaunchKernelGGL(k_node_combine, dim3(unsigned(nsl + p.fr.nlong) + nblocks(p.n() - p.nn, 256)), dim3(256), 0, s,
+                       p.nn, p.n(), nsl, p.fr.ptr, p.fr.n2t, p.fr, Nt, x, sgn, y, out);
+    PB_HIP(hipGetLastError());
 }
 
 void fem_omega_terms_dev(Problem &p, int scheme, const double *u, const double *D, const double *wdev,
@@ -991,20 +1037,6 @@ void fem_omega_terms_dev(Problem &p, int scheme, const double *u, const double *
     hipLaunchKernelGGL(k_tet_reaction<MODE_W>, dim3(nblocks(p.ntet, 128)), dim3(128), 0, s, p.ntet, p.d_tgeo, p.d_tet,
                        u, D, 0.0, scheme, c, tet_rule_arg(), p.ntet_i(), Wt, wdev, skip);
     node_gather<3>(p, Wt, rN, rJ, rH, skip, s);
-}
-
-double fem_energy_integral(Problem &p, const double *ul, const double *unl, hipStream_t s)
-{
-    const int nb = 512;
-    double *part = scratch<double>(p, SCR_EPART, nb);
-    hipLaunchKernelGGL(k_energy_integral, dim3(nb), dim3(256), 0, s, p.ntet_i(), p.d_tgeo, p.d_tet, ul, unl,
-                       tet_rule_arg(), part); // Omega_i: the shell tets come first
-    std::vector<double> h(nb);
-    PB_HIP(hipMemcpyAsync(h.data(), part, sizeof(double) * nb, hipMemcpyDeviceToHost, s));
-    PB_HIP(hipStreamSynchronize(s));
-    double sum = 0.0;
-    for (double v : h) sum += v;
-    return sum;
 }
 
 void energy(Problem &p, const double *phi_lin, const double *phi_nl, double out[4], hipStream_t s)
@@ -1026,22 +1058,29 @@ void energy(Problem &p, const double *phi_lin, const double *phi_nl, double out[
             lam_n = ln;
         }
     }
-    double lc = 0.0, nc = 0.0;
-    if (p.nq > 0) {
-        double *d_ur = scratch<double>(p, SCR_UR, 2 * p.nq);
+    // the reaction potentials at the charges and the block sums of the energy
+    // integral, read back together
+    constexpr int NB = 512;
+    double *d_en = scratch<double>(p, SCR_UR, 2 * p.nq + NB);
+    if (p.nq > 0)
         hipLaunchKernelGGL(k_reaction_potential, dim3(unsigned(p.nq)), dim3(256), 0, s, S.nt, S.qp, S.nrm, S.area,
-                           S.tri, S.g, S.iw, p.d_tet, p.d_q, phi_lin, lam_l, phi_nl, lam_n, tri_rule_arg(), d_ur);
-        std::vector<double> ur(2 * p.nq);
-        PB_HIP(hipMemcpyAsync(ur.data(), d_ur, sizeof(double) * 2 * p.nq, hipMemcpyDeviceToHost, s));
-        PB_HIP(hipStreamSynchronize(s));
-        for (int64_t k = 0; k < p.nq; ++k) {
-            lc += 0.5 * p.kT * p.q[4 * k + 3] * ur[2 * k];
-            nc += 0.5 * p.kT * p.q[4 * k + 3] * ur[2 * k + 1];
-        }
+                           S.tri, S.g, S.iw, p.d_tet, p.d_q, phi_lin, lam_l, phi_nl, lam_n, tri_rule_arg(), d_en);
+    if (phi_nl) // Omega_i: the shell tets come first
+        hipLaunchKernelGGL(k_energy_integral, dim3(NB), dim3(256), 0, s, p.ntet_i(), p.d_tgeo, p.d_tet, phi_lin,
+                           phi_nl, tet_rule_arg(), d_en + 2 * p.nq);
+    PB_HIP(hipGetLastError());
+    const size_t nen = 2 * size_t(p.nq) + (phi_nl ? NB : 0);
+    double *en = pinned_doubles(nen);
+    if (nen) PB_HIP(hipMemcpyAsync(en, d_en, sizeof(double) * nen, hipMemcpyDeviceToHost, s));
+    PB_HIP(hipStreamSynchronize(s));
+    double lc = 0.0, nc = 0.0, dg = 0.0;
+    for (int64_t k = 0; k < p.nq; ++k) {
+        lc += 0.5 * p.kT * p.q[4 * k + 3] * en[2 * k];
+        nc += 0.5 * p.kT * p.q[4 * k + 3] * en[2 * k + 1];
     }
-    double dg = 0.0;
     if (phi_nl) {
-        double integral = fem_energy_integral(p, phi_lin, phi_nl, s);
+        double integral = 0.0;
+        for (int b = 0; b < NB; ++b) integral += en[2 * p.nq + b];
         dg = p.kT / (4.0 * M_PI * p.lB) * 0.5 * p.eps_s * p.kappa * p.kappa * integral;
     }
     out[0] = lc + nc + dg;

@@ -2,6 +2,7 @@
 // omega search, the C-ABI apply): surface packing, the dense Galerkin GEMV,
 // the FEM sliced-ELL SpMV and small vector kernels.  Reductions use a fixed grid
 // and a fixed tree, so every result is bitwise reproducible run to run.
+#include <algorithm>
 #include <cmath>
 
 #include "gemv_rows.hpp"
@@ -139,7 +140,7 @@ __global__ void k_mul(int64_t n, const double *__restrict__ a, const double *__r
     if (i < n) y[i] = a[i] * x[i];
 }
 
-constexpr int RED_BLOCKS = 256;
+constexpr int RED_BLOCKS = DOT_BLOCKS;
 
 struct PtrTab {
     const double *a[8];
@@ -184,12 +185,6 @@ __global__ void k_reduce_partial(int nb, int k, const double *__restrict__ parti
         __syncthreads();
     }
     if (threadIdx.x == 0) out[j] = red[0];
-}
-
-__global__ void k_add_vec(int64_t n, const double *__restrict__ a, const double *__restrict__ b, double *__restrict__ y)
-{
-    const int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-    if (i < n) y[i] = a[i] + b[i];
 }
 
 // ===========================================================================
@@ -427,7 +422,7 @@ void lambda_m_recover(Problem &p, const double *phi, bool with_load, double *lam
     double *wv = scratch<double>(p, SCR_CGV, 6 * nm + 8);
     double *b = wv, *r = wv + nm, *z = wv + 2 * nm, *d = wv + 3 * nm, *q = wv + 4 * nm, *dinv = wv + 5 * nm,
            *sc = wv + 6 * nm;
-    double *part = scratch<double>(p, SCR_DOT, RED_BLOCKS * 8 + 8), *red = part + RED_BLOCKS * 8;
+    double *part = dot_partials(p), *red = part + RED_BLOCKS * 8;
     const unsigned g = nb_(ldm, 256), gn = nb_(nm, 256);
     auto dev_dots = [&](int k, const double *a0, const double *b0, const double *a1, const double *b1) {
         PtrTab T{};
@@ -522,33 +517,28 @@ void lambda_m_recover(Problem &p, const double *phi, bool with_load, double *lam
 }
 void coupled_apply_linear(Problem &p, const double *x, double *y, hipStream_t s) { apply_impl(p, x, y, false, s); }
 
-void dots_dev(Problem &p, int k, const double *const *a, const double *const *b, int64_t n, double *out,
-              const int *skip, hipStream_t s)
+double *dot_partials(Problem &p) { return scratch<double>(p, SCR_DOT, DOT_BLOCKS * 8 + 8); }
+
+double *pinned_doubles(size_t n)
 {
-    // k <= 8 pairs; fixed-order partial sums over RED_BLOCKS blocks, then one block each
-    double *part = scratch<double>(p, SCR_DOT, RED_BLOCKS * 8 + 8);
-    PtrTab T{};
-    for (int j = 0; j < k; ++j) {
-        T.a[j] = a[j];
-        T.b[j] = b[j];
+    struct Words {
+        double *p = nullptr;
+        size_t n = 0;
+        ~Words()
+        {
+            if (p) (void)hipHostFree(p);
+        }
+    };
+    static thread_local Words W;
+    if (W.n < n || !W.p) {
+        if (W.p) PB_HIP(hipHostFree(W.p));
+        W.p = nullptr;
+        W.n = 0;
+        const size_t want = std::max<size_t>(n, 1024);
+        PB_HIP(hipHostMalloc(reinterpret_cast<void **>(&W.p), sizeof(double) * want, hipHostMallocDefault));
+        W.n = want;
     }
-    hipLaunchKernelGGL(k_dots_partial, dim3(RED_BLOCKS), dim3(256), 0, s, n, k, T, part, skip);
-    hipLaunchKernelGGL(k_reduce_partial, dim3(k), dim3(256), 0, s, RED_BLOCKS, k, part, out, skip);
-}
-
-void dots(Problem &p, int k, const double *const *a, const double *const *b, int64_t n, double *out, hipStream_t s)
-{
-    double *res = scratch<double>(p, SCR_DOT, RED_BLOCKS * 8 + 8) + RED_BLOCKS * 8;
-    dots_dev(p, k, a, b, n, res, nullptr, s);
-    PB_HIP(hipMemcpyAsync(out, res, sizeof(double) * k, hipMemcpyDeviceToHost, s));
-    PB_HIP(hipStreamSynchronize(s));
-}
-
-double dot(Problem &p, const double *a, const double *b, int64_t n, hipStream_t s)
-{
-    double r;
-    dots(p, 1, &a, &b, n, &r, s);
-    return r;
+    return W.p;
 }
 
 // ---- kernels used by the solver (exported through small wrappers) ----------
@@ -559,10 +549,6 @@ void vec_axpby(int64_t n, double a, const double *x, double b, double *y, hipStr
 void vec_mul(int64_t n, const double *a, const double *x, double *y, hipStream_t s)
 {
     hipLaunchKernelGGL(k_mul, dim3(nb_(n, 256)), dim3(256), 0, s, n, a, x, y);
-}
-void vec_add(int64_t n, const double *a, const double *b, double *y, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_add_vec, dim3(nb_(n, 256)), dim3(256), 0, s, n, a, b, y);
 }
 
 } // namespace pbfb

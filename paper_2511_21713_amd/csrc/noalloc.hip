@@ -42,8 +42,7 @@ static void *noalloc_base(int device)
 
 static size_t round256(size_t b) { return (b + 255) / 256 * 256; }
 
-// Work bytes of one residual: N(u) on the FEM rows, 4 element terms per tet,
-// the packed surface inputs, and (when a surface is stored symmetric, which
+// Work bytes of one residual: 4 element terms per tet, the packed surface inputs, and (when a surface is stored symmetric, which
 // is assumed here so that the bound holds before setup) its column partials.
 size_t noalloc_residual_bytes(const Problem &p)
 {
@@ -91,7 +90,6 @@ extern "C" pbfb_status pbfb_residual_noalloc(pbfb_problem *pp, int scheme, const
             off += round256(sizeof(double) * n);
             return d;
         };
-        double *tmp = take(size_t(p.nn));
         double *Nt = take(4 * size_t(p.ntet));
         ApplyBufs bf;
         bf.xm = take(size_t(bem_ld(p.topo[0].nv)));
@@ -100,11 +98,8 @@ extern "C" pbfb_status pbfb_residual_noalloc(pbfb_problem *pp, int scheme, const
             double *P = take(size_t(sym_partials_doubles(p.topo[w].nv)));
             bf.P[w] = p.surf[w].sym ? P : nullptr;
         }
-        const int64_t n = p.n();
         coupled_apply_linear_bufs(p, phi, F, s, bf);
-        fem_nonlinear_buf(p, scheme, phi, tmp, Nt, s);
-        vec_axpby(p.nn, 1.0, tmp, 1.0, F, s);
-        vec_axpby(n, -1.0, p.d_b, 1.0, F, s);
+        fem_nonlinear_buf(p, scheme, phi, F, 1.0, p.d_b, F, Nt, s);
         PB_HIP(hipGetLastError());
         return PBFB_OK;
     } catch (const Error &e) {

@@ -390,12 +390,13 @@ void mf_vdiag(Problem &p, int w, hipStream_t s); // diagonal of V' from the resi
 void mf_spai(Problem &p, int w, hipStream_t s);
 void near_pattern(SurfaceTopo &S); // host: the 3-ring pattern (nf_ptr, nf_col), once
 void delta_pattern(SurfaceTopo &S); // host: the upper two-ring pattern (d2_ptr, d2_col), once
-void fem_nonlinear(Problem &p, int scheme, const double *u, double *out, hipStream_t s);
+// out = x + sgn [N_scheme(u); 0; 0] - y over all unknowns (y may be null; out may be x)
+void fem_nonlinear(Problem &p, int scheme, const double *u, const double *x, double sgn, const double *y, double *out,
+                   hipStream_t s);
 // f_d terms of the relaxation search at the omega held in device memory
 // (wdev); every kernel returns at once while *skip is nonzero
 void fem_omega_terms_dev(Problem &p, int scheme, const double *u, const double *D, const double *wdev,
                          const int *skip, double *rN, double *rJ, double *rH, hipStream_t s);
-double fem_energy_integral(Problem &p, const double *u_lin, const double *u_nl, hipStream_t s);
 
 // coupled operator y = J x with the current CSR values (pack + GEMV + SpMV)
 void coupled_apply(Problem &p, const double *x, double *y, hipStream_t s);
@@ -411,20 +412,23 @@ int64_t sym_partials_doubles(int64_t nv);
 void noalloc_init(int device); // noalloc.hip: once per device, with the device current
 // A only (no J_N), with caller-provided buffers (no allocation, no timing)
 void coupled_apply_linear_bufs(Problem &p, const double *x, double *y, hipStream_t s, const ApplyBufs &bufs);
-// N_scheme(u) into out (FEM rows) with a caller-provided element buffer of 4 ntet doubles
-void fem_nonlinear_buf(Problem &p, int scheme, const double *u, double *out, double *Nt, hipStream_t s);
+// the same with a caller-provided element buffer of 4 ntet doubles
+void fem_nonlinear_buf(Problem &p, int scheme, const double *u, const double *x, double sgn, const double *y,
+                       double *out, double *Nt, hipStream_t s);
 void coupled_apply_linear(Problem &p, const double *x, double *y, hipStream_t s); // A only (no J_N)
 
 // vector helpers
 int64_t bem_ld(int64_t nv); // padded row length of the dense surface operator
 void vec_axpby(int64_t n, double a, const double *x, double b, double *y, hipStream_t s);
 void vec_mul(int64_t n, const double *a, const double *x, double *y, hipStream_t s);
-void vec_add(int64_t n, const double *a, const double *b, double *y, hipStream_t s);
-double dot(Problem &p, const double *a, const double *b, int64_t n, hipStream_t s);
-void dots(Problem &p, int k, const double *const *a, const double *const *b, int64_t n, double *out, hipStream_t s);
-// the same into device memory (out[0..k)), no host round trip; skip as above
-void dots_dev(Problem &p, int k, const double *const *a, const double *const *b, int64_t n, double *out,
-              const int *skip, hipStream_t s);
+// the host thread's pinned words, at least n of them (contents are not kept):
+// kernels write what the host reads after its next synchronisation
+double *pinned_doubles(size_t n);
+// Sums over the unknowns in two stages: DOT_BLOCKS workgroups of 256 threads
+// leave partial sums (dot_partials: block-major, k <= 8 values each), one
+// workgroup adds them (block_sums); fixed grid and order, so reproducible
+constexpr int DOT_BLOCKS = 256;
+double *dot_partials(Problem &p);
 
 // energy
 void energy(Problem &p, const double *phi_lin, const double *phi_nl, double out[4], hipStream_t s);
@@ -445,14 +449,12 @@ struct GmresJob {
     int basis32; // Krylov basis in FP32 (mixed precision only)
     int pc, cheb_k;       // preconditioner (PBFB_PC_*), Chebyshev terms
     double cheb_ratio;
-    const double *lmax;   // device scalar: Gershgorin bound of diag(F)^-1 F
+    const double *lmax;   // device: partial maxima (one per FEM slice) of the Gershgorin bound of diag(F)^-1 F
     int applies;          // out: operator applications that did work
     int graph;            // replay the Krylov step from a captured HIP graph
 };
 void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s);
-void build_precond(Problem &p, double *dinv, hipStream_t s);
 void check_opts(const pbfb_solve_opts &o); // throws PBFB_EINVAL
-void fem_gershgorin(Problem &p, double *lmax_dev, hipStream_t s); // bound of diag(F)^-1 F, F = A + J_N
 
 // Newton driver (solver.hip): one state machine per instance
 struct NewtonRun {
@@ -466,8 +468,8 @@ struct NewtonRun {
     bool frozen = false;
     bool c_ready = false; // c already holds b - A Phi for the next step
     double *phil = nullptr, *phinl = nullptr, *phi = nullptr, *c = nullptr, *d = nullptr, *D = nullptr;
-    double *pv = nullptr, *rv = nullptr, *rN = nullptr, *rJ = nullptr, *rH = nullptr, *dinv = nullptr;
-    double *lmax = nullptr; // Chebyshev bound (device) and its partial maxima
+    double *pv = nullptr, *rN = nullptr, *rJ = nullptr, *rH = nullptr, *dinv = nullptr;
+    double *lmax = nullptr; // partial maxima of the Chebyshev bound (device)
     GmresJob job{};
     std::string message;
     std::chrono::steady_clock::time_point t0, t1;
@@ -476,7 +478,8 @@ struct NewtonRun {
     bool searching = false, searched = false;
     double omega = 1.0;
     void *om_dev = nullptr;  // the device state
-    double om_host[4] = {0, 0, 0, 0}; // read back: done, omega, evaluations, fallback
+    int evals = 0;           // evaluations of f_d
+    double dd = 0.0;         // Delta.Delta of the step
     NewtonRun(Problem *p_, const pbfb_solve_opts &o_, pbfb_result *res_, double *out);
 };
 bool advance(NewtonRun &r, hipStream_t s);               // true: needs its linear solve

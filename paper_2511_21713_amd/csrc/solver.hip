@@ -25,39 +25,40 @@ namespace pbfb {
 
 static inline unsigned nbk(int64_t n, int bs) { return unsigned((n + bs - 1) / bs); }
 
-__global__ void k_precond(int64_t nn, int64_t nm, int64_t ns, const double *__restrict__ val,
-                          const int32_t *__restrict__ diag, const double *__restrict__ vdm,
-                          const double *__restrict__ vds, double *__restrict__ dinv)
+// sums over the 256 threads of a workgroup, valid in thread 0
+template <int K> __device__ inline void block_sums(double (&v)[K])
 {
-    const int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-    if (i < nn) dinv[i] = 1.0 / val[diag[i]];
-    else if (i < nn + nm) dinv[i] = 1.0 / vdm[i - nn];
-    else if (i < nn + nm + ns) dinv[i] = 1.0 / vds[i - nn - nm];
+    __shared__ double red[4][K];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o);
+        if (lane == 0) red[wv][k] = v[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]);
 }
 
-__global__ void k_sub_fem(int64_t nn, const double *__restrict__ c, const double *__restrict__ f,
-                          double *__restrict__ out)
-{
-    const int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-    if (i < nn) out[i] = c[i] - f[i];
-}
-
-// block diagonal of the Newton matrix: diag(A + J) on the FEM rows, the
-// diagonals of the signed single layers on the surface rows
-void build_precond(Problem &p, double *dinv, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_precond, dim3(nbk(p.n(), 256)), dim3(256), 0, s, p.nn, p.surf[0].nv, p.surf[1].nv, p.d_val,
-                       p.d_diag, p.surf[0].vdiag, p.surf[1].vdiag, dinv);
-}
-
+// Inverse diagonal of the Newton matrix (diag(A + J) on the FEM rows, the
+// diagonals of the signed single layers on the surface rows), and the
 // Gershgorin bound of diag(F)^-1 F for the FEM block F = A + J_N (the upper
-// end of the Chebyshev interval): a maximum per slice, then one block.
-__global__ void __launch_bounds__(256) k_gershgorin(int64_t nn, const int32_t *__restrict__ sptr, SellLong lng,
-                                                    const int32_t *__restrict__ col, const double *__restrict__ val,
-                                                    const int32_t *__restrict__ diag, double *__restrict__ part)
+// end of the Chebyshev interval) as one maximum per slice, which the batched
+// solve reduces.  Workgroups of the slices, then 256 surface rows each.
+__global__ void __launch_bounds__(256)
+    k_diag_bound(int64_t nn, int64_t nm, int64_t n, int64_t nsl, const int32_t *__restrict__ sptr, SellLong lng,
+                 const int32_t *__restrict__ col, const double *__restrict__ val, const int32_t *__restrict__ diag,
+                 const double *__restrict__ vdm, const double *__restrict__ vds, double *__restrict__ dinv,
+                 double *__restrict__ part)
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int64_t q = blockIdx.x, i = q * SLICE + lane;
+    const int64_t q = blockIdx.x;
+    if (q >= nsl) {
+        const int64_t i = nn + (q - nsl) * 256 + threadIdx.x;
+        if (i < n) dinv[i] = 1.0 / (i < nn + nm ? vdm[i - nn] : vds[i - nn - nm]);
+        return;
+    }
+    const int64_t i = q * SLICE + lane;
     const int32_t b0 = sptr[q], w = (sptr[q + 1] - b0) / SLICE;
     double sum = 0.0; // slice padding adds zeros
     for (int32_t k = wv; k < w; k += SELL_W) {
@@ -79,34 +80,14 @@ __global__ void __launch_bounds__(256) k_gershgorin(int64_t nn, const int32_t *_
         }
     }
     if (wv != 0) return;
-    double v = i < nn ? sum / val[diag[i]] : 0.0;
+    double v = 0.0;
+    if (i < nn) {
+        const double dg = val[diag[i]];
+        dinv[i] = 1.0 / dg;
+        v = sum / dg;
+    }
     for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
     if (lane == 0) part[q] = v;
-}
-
-__global__ void __launch_bounds__(256) k_max_final(int64_t nb, const double *__restrict__ part,
-                                                   double *__restrict__ out)
-{
-    __shared__ double red[256];
-    double v = 0.0;
-    for (int64_t b = threadIdx.x; b < nb; b += 256) v = fmax(v, part[b]);
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = red[0];
-}
-
-// lmax_dev[0] = bound; lmax_dev[1 ..] partial maxima (1 + one per slice)
-void fem_gershgorin(Problem &p, double *lmax_dev, hipStream_t s)
-{
-    const unsigned nb = nbk(p.nn, SLICE);
-    hipLaunchKernelGGL(k_gershgorin, dim3(nb), dim3(256), 0, s, p.nn, p.d_sptr, p.fr.sell(), p.d_col, p.d_val,
-                       p.d_diag, lmax_dev + 1);
-    hipLaunchKernelGGL(k_max_final, dim3(1), dim3(256), 0, s, int64_t(nb), lmax_dev + 1, lmax_dev);
-    PB_HIP(hipGetLastError());
 }
 
 enum RunPhase { PH_START = 0, PH_LINEAR = 1, PH_NEWTON = 2, PH_DONE = 3, PH_POST = 4 };
@@ -117,8 +98,11 @@ enum RunPhase { PH_START = 0, PH_LINEAR = 1, PH_NEWTON = 2, PH_DONE = 3, PH_POST
 static GmresJob make_job(NewtonRun &r, const double *b, double *x, hipStream_t s)
 {
     Problem &p = *r.p;
-    build_precond(p, r.dinv, s);
-    if (r.o.precond == PBFB_PC_CHEB_SPAI) fem_gershgorin(p, r.lmax, s);
+    const int64_t n = p.n(), nsl = nbk(p.nn, SLICE);
+    hipLaunchKernelGGL(k_diag_bound, dim3(unsigned(nsl) + nbk(n - p.nn, 256)), dim3(256), 0, s, p.nn, p.surf[0].nv, n,
+                       nsl, p.d_sptr, p.fr.sell(), p.d_col, p.d_val, p.d_diag, p.surf[0].vdiag, p.surf[1].vdiag, r.dinv,
+                       r.lmax);
+    PB_HIP(hipGetLastError());
     GmresJob J{&p, b, x, r.dinv, r.tol, r.o.gmres_restart, r.o.max_gmres, 0, 0, r.o.krylov_fp32};
     J.pc = r.o.precond;
     J.cheb_k = r.o.cheb_degree;
@@ -162,32 +146,24 @@ static void finish(NewtonRun &r, hipStream_t s)
 }
 
 // Newton pre-step: residual, Jacobian values, preconditioner, linear solve request
-static bool newton_pre(NewtonRun &r, hipStream_t s)
+static void newton_pre(NewtonRun &r, hipStream_t s)
 {
     Problem &p = *r.p;
-    const int64_t n = p.n(), nn = p.nn;
+    const int64_t n = p.n();
     if (r.o.n_schedule > 0) r.sch = r.k <= r.o.n_schedule ? r.o.schedule[r.k - 1] : PBFB_HS;
     else r.sch = (r.k == 1 && r.o.scheme_first == PBFB_T3) ? PBFB_T3 : PBFB_HS;
-    vec_add(n, r.phil, r.phinl, r.phi, s);
     if (!r.c_ready) { // else c was carried over from the last step's omega search
         coupled_apply_linear(p, r.phi, r.c, s);
         vec_axpby(n, 1.0, p.d_b, -1.0, r.c, s);
         r.res->applies += 1; // c = b - A Phi
     }
     r.c_ready = false;
-    fem_nonlinear(p, r.sch, r.phi, r.rN, s);
-    PB_HIP(hipMemcpyAsync(r.d, r.c, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
-    hipLaunchKernelGGL(k_sub_fem, dim3(nbk(nn, 256)), dim3(256), 0, s, nn, r.c, r.rN, r.d);
-    const double dd = dot(p, r.d, r.d, n, s);
-    if (!std::isfinite(dd)) {
-        r.status = PBFB_ENAN;
-        return false;
-    }
+    // d = c - N; a residual that is not finite ends the linear solve with ENAN
+    fem_nonlinear(p, r.sch, r.phi, r.c, -1.0, nullptr, r.d, s);
     // Newton: (A + J_N) Delta = d; Picard: A Delta = d
     if (r.o.nonlinear_method == PBFB_PICARD) fem_assemble_linear(p, s);
     else fem_assemble_jacobian(p, r.sch, r.phi, s);
     r.job = make_job(r, r.d, r.D, s);
-    return true;
 }
 
 // ---------------------------------------------------------------------------
@@ -198,13 +174,14 @@ static bool newton_pre(NewtonRun &r, hipStream_t s)
 // f_d (beta = 0) or a vanishing derivative / secant slope gives omega = 1.
 //
 // The search of one instance is a small state machine in device memory
-// (OmegaSearch).  One evaluation round is: the f_d terms at S.w (the element
-// kernel reads omega from S.w), their six dot products into S.v, then
-// k_omega_step, one thread that forms f_d and f_d' and moves the state to
-// the next point to evaluate or to its result.  Once S.done is set the
-// round's kernels return at once.  The host enqueues rounds for every
-// searching instance of the batch and reads the done flags back only every
-// few rounds, one copy and one synchronisation for all of them.
+// (OmegaSearch).  One evaluation round is four launches: the f_d terms at S.w
+// per tet (the element kernel reads omega from S.w) and per node, the partial
+// sums of their six dot products (which form the residual on the way), then
+// k_omega_step, which adds them, forms f_d and f_d' and moves the state to the
+// next point to evaluate or to its result, leaving what the host asks for in
+// pinned memory.  Once S.done is set the round's kernels return at once.  The
+// host enqueues rounds for every searching instance of the batch and looks
+// only every few rounds, one synchronisation for all of them.
 // ---------------------------------------------------------------------------
 enum OmPhase {
     OM_NEWTON = 0, // evaluating w of the Newton iteration
@@ -230,7 +207,6 @@ struct OmegaSearch {
     double w0, f0, w1, f1;
     double blo, bhi, bw[3], bf[3];
     double result;
-    double v[6]; // (p . r) over all unknowns, then (rJ.r, rJ.p, rJ.rJ, r.rH, p.rH) over the FEM rows
 };
 
 __device__ inline double om_clamp(const OmegaSearch &S, double w) { return fmin(S.wmax, fmax(S.wmin, w)); }
@@ -277,11 +253,29 @@ __device__ inline void om_bs_loop(OmegaSearch &S)
     S.w = w2;
 }
 
-__global__ void k_omega_init(OmegaSearch *__restrict__ S_, int method, int k, int max_it, double tol, double wmin,
-                             double wmax, double omega0)
+// p = -A Delta from A Delta, and the partial sums of p.p
+__global__ void __launch_bounds__(256) k_search_begin(int64_t n, double *__restrict__ pv, double *__restrict__ part)
 {
+    double t[1] = {0.0};
+    for (int64_t i = blockIdx.x * int64_t(256) + threadIdx.x; i < n; i += int64_t(DOT_BLOCKS) * 256) {
+        const double v = -pv[i];
+        pv[i] = v;
+        t[0] = fma(v, v, t[0]);
+    }
+    block_sums(t);
+    if (threadIdx.x == 0) part[blockIdx.x] = t[0];
+}
+
+static_assert(DOT_BLOCKS == 256, "one partial per thread of the summing workgroup");
+__global__ void __launch_bounds__(256) k_omega_init(OmegaSearch *__restrict__ S_, int method, int k, int max_it,
+                                                    double tol, double wmin, double wmax, double omega0,
+                                                    const double *__restrict__ part)
+{
+    double pp[1] = {part[threadIdx.x]};
+    block_sums(pp);
     if (threadIdx.x != 0) return;
     OmegaSearch S{};
+    S.pp = pp[0];
     S.method = method;
     S.k = k;
     S.max_it = max_it;
@@ -322,26 +316,67 @@ __global__ void k_omega_init(OmegaSearch *__restrict__ S_, int method, int k, in
 
 // f_d and f_d' at S.w from the dot products (eq. fd=0 and its derivative,
 // r' = -[rJ; 0; 0], r'' = -[rH; 0; 0]), then the next state
-__global__ void k_omega_step(OmegaSearch *__restrict__ S_)
+//
+// six partial sums per block: p.r over all unknowns, then rJ.r, rJ.p, rJ.rJ,
+// r.rH, p.rH over the FEM rows, with r = c - N
+__global__ void __launch_bounds__(256)
+    k_omega_dots(int64_t n, int64_t nn, const double *__restrict__ c, const double *__restrict__ pv,
+                 const double *__restrict__ rN, const double *__restrict__ rJ, const double *__restrict__ rH,
+                 double *__restrict__ part, const int *__restrict__ skip)
 {
+    if (*skip) return;
+    double t[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int64_t i = blockIdx.x * int64_t(256) + threadIdx.x; i < n; i += int64_t(DOT_BLOCKS) * 256) {
+        const double p = pv[i];
+        if (i >= nn) {
+            t[0] = fma(p, c[i], t[0]);
+            continue;
+        }
+        const double r = c[i] - rN[i], J = rJ[i], H = rH[i];
+        t[0] = fma(p, r, t[0]);
+        t[1] = fma(J, r, t[1]);
+        t[2] = fma(J, p, t[2]);
+        t[3] = fma(J, J, t[3]);
+        t[4] = fma(r, H, t[4]);
+        t[5] = fma(p, H, t[5]);
+    }
+    block_sums(t);
+    if (threadIdx.x == 0)
+        for (int k = 0; k < 6; ++k) part[6 * blockIdx.x + k] = t[k];
+}
+
+// host: done, omega, evaluations (pinned)
+__device__ inline void om_next(OmegaSearch &S, const double (&v)[6]);
+__global__ void __launch_bounds__(256) k_omega_step(OmegaSearch *__restrict__ S_, const double *__restrict__ part,
+                                                    double *__restrict__ host)
+{
+    if (S_->done) return;
+    double v[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) v[k] = part[6 * threadIdx.x + k];
+    block_sums(v);
     if (threadIdx.x != 0) return;
     OmegaSearch S = *S_;
-    if (S.done) return;
+    om_next(S, v);
+    *S_ = S;
+    host[0] = S.done;
+    host[1] = S.result;
+    host[2] = S.ev;
+}
+
+__device__ inline void om_next(OmegaSearch &S, const double (&v)[6])
+{
     const double w = S.w;
-    const double a = S.v[0] - S.v[1];     // (p + r').r
-    const double beta = S.pp - S.v[2];    // (p + r').p
+    const double a = v[0] - v[1];     // (p + r').r
+    const double beta = S.pp - v[2];  // (p + r').p
     const bool ok = beta != 0.0;
     double fd = 0.0, dfd = 0.0;
     if (ok) {
         fd = -a / beta - w;
-        dfd = -(-S.v[2] + S.v[3] - S.v[4]) / beta + a * (-S.v[5]) / (beta * beta) - 1.0;
+        dfd = -(-v[2] + v[3] - v[4]) / beta + a * (-v[5]) / (beta * beta) - 1.0;
     }
     ++S.ev;
-    if (!ok) {
-        om_finish(S, 1.0, true);
-        *S_ = S;
-        return;
-    }
+    if (!ok) return om_finish(S, 1.0, true);
     switch (S.phase) {
     case OM_NEWTON:
         if (fabs(fd) < S.tol) om_finish(S, w, false);
@@ -436,64 +471,42 @@ __global__ void k_omega_step(OmegaSearch *__restrict__ S_)
         break;
     default: om_finish(S, 1.0, true); break;
     }
-    *S_ = S;
-}
-
-__global__ void k_omega_read(const OmegaSearch *__restrict__ S, double *__restrict__ out)
-{
-    if (threadIdx.x != 0) return;
-    out[0] = S->done;
-    out[1] = S->result;
-    out[2] = S->ev;
-    out[3] = S->fb;
-}
-
-__global__ void k_sub_fem_skip(int64_t nn, const double *__restrict__ c, const double *__restrict__ f,
-                               double *__restrict__ out, const int *__restrict__ skip)
-{
-    if (*skip) return;
-    const int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-    if (i < nn) out[i] = c[i] - f[i];
 }
 
 static OmegaSearch *om_state(NewtonRun &r) { return static_cast<OmegaSearch *>(r.om_dev); }
 
-// one evaluation round of a search: f_d terms at S.w, the dot products, the step
-static void omega_round(NewtonRun &r, hipStream_t s)
+// one evaluation round of a search; host: its three pinned words
+static void omega_round(NewtonRun &r, double *host, hipStream_t s)
 {
     Problem &p = *r.p;
     const int64_t n = p.n(), nn = p.nn;
     OmegaSearch *S = om_state(r);
     const int *skip = &S->done;
+    double *part = dot_partials(p);
     fem_omega_terms_dev(p, r.sch, r.phi, r.D, &S->w, skip, r.rN, r.rJ, r.rH, s);
-    hipLaunchKernelGGL(k_sub_fem_skip, dim3(nbk(nn, 256)), dim3(256), 0, s, nn, r.c, r.rN, r.rv, skip);
-    const double *pa = r.pv, *pb = r.rv;
-    dots_dev(p, 1, &pa, &pb, n, S->v, skip, s);
-    const double *A5[5] = {r.rJ, r.rJ, r.rJ, r.rv, r.pv};
-    const double *B5[5] = {r.rv, r.pv, r.rJ, r.rH, r.rH};
-    dots_dev(p, 5, A5, B5, nn, S->v + 1, skip, s);
-    hipLaunchKernelGGL(k_omega_step, dim3(1), dim3(64), 0, s, S);
+    hipLaunchKernelGGL(k_omega_dots, dim3(DOT_BLOCKS), dim3(256), 0, s, n, nn, r.c, r.pv, r.rN, r.rJ, r.rH, part, skip);
+    hipLaunchKernelGGL(k_omega_step, dim3(1), dim3(256), 0, s, S, part, host);
+    PB_HIP(hipGetLastError());
 }
 
 // the searches of all runs in `srch` together: rounds for every run whose
-// search is not known to be done, the done flags read back every few rounds
+// search is not known to be done, looked at every few rounds
 static void omega_search_all(std::vector<NewtonRun *> &srch, hipStream_t s)
 {
     constexpr int ROUNDS = 2; // evaluation rounds between two host checks
     std::vector<NewtonRun *> act = srch;
     while (!act.empty()) {
+        double *host = pinned_doubles(3 * act.size());
+        for (size_t i = 0; i < act.size(); ++i) host[3 * i] = 0.0;
         for (int q = 0; q < ROUNDS; ++q)
-            for (NewtonRun *r : act) omega_round(*r, s);
-        for (NewtonRun *r : act) {
-            double *h = scratch<double>(*r->p, SCR_OMEGA, sizeof(OmegaSearch) / 8 + 8) + sizeof(OmegaSearch) / 8 + 2;
-            hipLaunchKernelGGL(k_omega_read, dim3(1), dim3(64), 0, s, om_state(*r), h);
-            PB_HIP(hipMemcpyAsync(r->om_host, h, sizeof(r->om_host), hipMemcpyDeviceToHost, s));
-        }
+            for (size_t i = 0; i < act.size(); ++i) omega_round(*act[i], host + 3 * i, s);
         PB_HIP(hipStreamSynchronize(s));
         std::vector<NewtonRun *> next;
-        for (NewtonRun *r : act) {
-            if (r->om_host[0] != 0.0) {
-                r->omega = r->om_host[1];
+        for (size_t i = 0; i < act.size(); ++i) {
+            NewtonRun *r = act[i];
+            if (host[3 * i] != 0.0) {
+                r->omega = host[3 * i + 1];
+                r->evals = int(host[3 * i + 2]);
                 r->searching = false;
             } else {
                 next.push_back(r);
@@ -524,38 +537,65 @@ static void newton_post_begin(NewtonRun &r, hipStream_t s)
         coupled_apply_linear(p, r.D, r.pv, s);
         r.res->applies += 1;
         r.searched = r.searching = true;
-        vec_axpby(n, -1.0, r.pv, 0.0, r.pv, s);
-        PB_HIP(hipMemcpyAsync(r.rv, r.c, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
         r.om_dev = scratch<double>(p, SCR_OMEGA, sizeof(OmegaSearch) / 8 + 8);
-        OmegaSearch *S = om_state(r);
-        hipLaunchKernelGGL(k_omega_init, dim3(1), dim3(64), 0, s, S, o.omega_method, r.k, o.max_omega_it, o.tol_omega,
-                           o.omega_min, o.omega_max, omega0);
-        const double *pa = r.pv;
-        dots_dev(p, 1, &pa, &pa, n, &S->pp, nullptr, s);
+        double *part = dot_partials(p);
+        hipLaunchKernelGGL(k_search_begin, dim3(DOT_BLOCKS), dim3(256), 0, s, n, r.pv, part);
+        hipLaunchKernelGGL(k_omega_init, dim3(1), dim3(256), 0, s, om_state(r), o.omega_method, r.k, o.max_omega_it,
+                           o.tol_omega, o.omega_min, o.omega_max, omega0, part);
+        PB_HIP(hipGetLastError());
     }
 }
 
-// update and stop test after the search (or without one); true when converged
-static bool newton_post_end(NewtonRun &r, hipStream_t s)
+// Phi_NL += omega Delta, Phi = Phi_L + Phi_NL, after a search also the next
+// c = b - A Phi without an apply (A (Phi + omega Delta) = A Phi - omega p),
+// and the partial sums of Delta.Delta
+__global__ void __launch_bounds__(256)
+    k_newton_update(int64_t n, double omega, const double *__restrict__ D, const double *__restrict__ pv,
+                    const double *__restrict__ phil, double *__restrict__ phinl, double *__restrict__ phi,
+                    double *__restrict__ c, double *__restrict__ part)
+{
+    double t[1] = {0.0};
+    for (int64_t i = blockIdx.x * int64_t(256) + threadIdx.x; i < n; i += int64_t(DOT_BLOCKS) * 256) {
+        const double dv = D[i], u = fma(omega, dv, phinl[i]);
+        phinl[i] = u;
+        phi[i] = phil[i] + u;
+        if (pv) c[i] = fma(omega, pv[i], c[i]);
+        t[0] = fma(dv, dv, t[0]);
+    }
+    block_sums(t);
+    if (threadIdx.x == 0) part[blockIdx.x] = t[0];
+}
+__global__ void __launch_bounds__(256) k_partials_sum(const double *__restrict__ part, double *__restrict__ out)
+{
+    double t[1] = {part[threadIdx.x]};
+    block_sums(t);
+    if (threadIdx.x == 0) *out = t[0];
+}
+
+// the update of a step whose omega is known; Delta.Delta goes to the pinned word
+static void newton_post_update(NewtonRun &r, double *host, hipStream_t s)
 {
     Problem &p = *r.p;
-    const int64_t n = p.n();
+    double *part = dot_partials(p);
+    hipLaunchKernelGGL(k_newton_update, dim3(DOT_BLOCKS), dim3(256), 0, s, p.n(), r.omega, r.D,
+                       r.searched ? r.pv : (const double *)nullptr, r.phil, r.phinl, r.phi, r.c, part);
+    hipLaunchKernelGGL(k_partials_sum, dim3(1), dim3(256), 0, s, part, host);
+    PB_HIP(hipGetLastError());
+}
+
+// stop test after the update; true when converged
+static bool newton_post_end(NewtonRun &r)
+{
     const pbfb_solve_opts &o = r.o;
     const int idx = std::min(r.k - 1, 63);
     const double omega = r.omega;
     int oit = 0;
     if (r.searched) {
-        const int evals = int(r.om_host[2]);
-        oit = evals > 0 ? evals - 1 : 0;
+        oit = r.evals > 0 ? r.evals - 1 : 0;
         r.omega_last = omega;
-    }
-    vec_axpby(n, omega, r.D, 1.0, r.phinl, s);
-    if (r.searched) {
-        // A (Phi + omega Delta) = A Phi - omega p: the next c = b - A Phi without an apply
-        vec_axpby(n, omega, r.pv, 1.0, r.c, s);
         r.c_ready = true;
     }
-    const double ek = omega * std::sqrt(dot(p, r.D, r.D, n, s));
+    const double ek = omega * std::sqrt(r.dd);
     r.res->omega[idx] = omega;
     r.res->e_k[idx] = ek;
     r.res->omega_iters[idx] = oit;
@@ -592,8 +632,7 @@ static bool advance_impl(NewtonRun &r, hipStream_t s)
         r.d = scratch<double>(p, SCR_G7, n);
         r.D = scratch<double>(p, SCR_G8, n);
         r.pv = scratch<double>(p, SCR_G9, n);
-        r.rv = scratch<double>(p, SCR_G10, n);
-        double *t3 = scratch<double>(p, SCR_G11, 3 * nn);
+            double *t3 = scratch<double>(p, SCR_G11, 3 * nn);
         r.rN = t3;
         r.rJ = t3 + nn;
         r.rH = t3 + 2 * nn;
@@ -601,7 +640,7 @@ static bool advance_impl(NewtonRun &r, hipStream_t s)
         r.tol = r.o.tol_gr0;
         PB_HIP(hipMemsetAsync(r.phinl, 0, sizeof(double) * n, s));
         // linear component: (A + eps_s kappa^2 M) Phi_L = b
-        r.lmax = scratch<double>(p, SCR_LMAX, 1 + nbk(nn, SLICE));
+        r.lmax = scratch<double>(p, SCR_LMAX, nbk(nn, SLICE));
         fem_assemble_jacobian(p, PBFB_LIN, r.phinl, s);
         r.job = make_job(r, p.d_b, r.phil, s);
         r.phase = PH_LINEAR;
@@ -617,11 +656,10 @@ static bool advance_impl(NewtonRun &r, hipStream_t s)
             return false;
         }
         r.k = 1;
+        // Phi = Phi_L (Phi_NL = 0); newton_post_update keeps it from here on
+        PB_HIP(hipMemcpyAsync(r.phi, r.phil, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
         r.phase = PH_NEWTON;
-        if (!newton_pre(r, s)) {
-            finish(r, s);
-            return false;
-        }
+        newton_pre(r, s);
         return true;
     }
     if (r.phase == PH_NEWTON) {
@@ -639,16 +677,13 @@ static bool advance_impl(NewtonRun &r, hipStream_t s)
         return false;
     }
     if (r.phase == PH_POST) {
-        if (newton_post_end(r, s)) {
+        if (newton_post_end(r)) {
             finish(r, s);
             return false;
         }
         ++r.k;
         r.phase = PH_NEWTON;
-        if (!newton_pre(r, s)) {
-            finish(r, s);
-            return false;
-        }
+        newton_pre(r, s);
         return true;
     }
     return false;
@@ -738,8 +773,28 @@ void advance_all(std::vector<NewtonRun *> &runs, std::vector<GmresJob *> &jobs, 
             }
         }
     }
+    // the updates of every instance, then one look at their norms
+    std::vector<NewtonRun *> post;
     for (NewtonRun *r : runs)
-        if (r->phase == PH_POST) step(r);
+        if (r->phase == PH_POST) post.push_back(r);
+    if (!post.empty()) {
+        try {
+            double *host = pinned_doubles(post.size());
+            for (size_t i = 0; i < post.size(); ++i) newton_post_update(*post[i], host + i, s);
+            PB_HIP(hipStreamSynchronize(s));
+            for (size_t i = 0; i < post.size(); ++i) post[i]->dd = host[i];
+        } catch (const Error &e) {
+            for (NewtonRun *r : post) {
+                r->status = e.code;
+                r->message = e.msg;
+                r->res->status = e.code;
+                r->phase = PH_DONE;
+                if (finished) finished->push_back(r);
+            }
+            post.clear();
+        }
+    }
+    for (NewtonRun *r : post) step(r);
 }
 
 void run_newton(std::vector<NewtonRun *> &runs, hipStream_t s)
