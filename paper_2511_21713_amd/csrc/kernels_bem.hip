@@ -96,6 +96,14 @@ template <typename MT> __device__ inline void add_entry(MT *__restrict__ U, int6
     U[at] = MT(double(U[at]) + v);
 }
 
+// A folded entry: added to the stored operator, or (SLOT) stored to the tile's
+// own place in a matrix over the blocks' local vertices (see k_bem_gather)
+template <bool SLOT, typename MT> __device__ inline void put_entry(MT *__restrict__ U, int64_t at, double v)
+{
+    if constexpr (SLOT) U[at] = MT(v);
+    else add_entry(U, at, v);
+}
+
 // Rows of the fold's last stage whose operator entries a thread reads ahead
 // (the rest are read when they are added to): FP32 tiles one, before the
 // quadrature (342 -> 325 ms per 80k-triangle assembly; two cost registers and
@@ -141,7 +149,7 @@ __device__ inline FoldMap<MS> fold_map(int tid, int nB, const int (*sSb)[MS], in
 // column), so the reads pipeline.  MS >= the largest number of corners of
 // any vertex of either block: the lists past it hold only absent corners,
 // whose +0 terms are skipped.
-template <int TA, int TB, int MS, int SLOT, typename MT, typename ST, typename XT>
+template <int TA, int TB, int MS, bool SLOT, int PL, typename MT, typename ST, typename XT>
 __device__ inline void fold_tile_one(int tid, int tl, int sl, int nA, const FoldMap<MS> &fm, const int (*sSa)[MS],
                                      ST (*acc)[TB * 3 + 1], const XT *Xl, const int *vA,
                                      const int *vB, MT *__restrict__ U, int64_t ld, int64_t off, double sc,
@@ -202,9 +210,10 @@ __device__ inline void fold_tile_one(int tid, int tl, int sl, int nA, const Fold
 #pragma unroll
         for (int k = 0; k < fold_pf<MT>(); ++k) {
             const int ia = r0 + k * rstep;
-            if (ia < nA) U[int64_t(vA[ia]) * ld + col] = MT(double(pre[k][SLOT]) + sc * rowsum(ia));
+            if (ia < nA) U[int64_t(vA[ia]) * ld + col] = MT(double(pre[k][PL]) + sc * rowsum(ia));
         }
-        for (int ia = r0 + fold_pf<MT>() * rstep; ia < nA; ia += rstep) add_entry(U, int64_t(vA[ia]) * ld + col, sc * rowsum(ia));
+        for (int ia = r0 + fold_pf<MT>() * rstep; ia < nA; ia += rstep)
+            put_entry<SLOT>(U, int64_t(vA[ia]) * ld + col, sc * rowsum(ia));
     }
     __syncthreads();
 }
@@ -215,7 +224,7 @@ __device__ inline void fold_tile_one(int tid, int tl, int sl, int nA, const Fold
 // with factor s0, K to column vB[jb] with factor s1 of row vA[ia] of U), or
 // the mirrored K of a square tile in one plane (TOT = true: to column vB[jb]
 // of row vA[ia] of U = T with factor s0); otherwise as fold_tile_one.
-template <int TA, int TB, int MS, bool TOT, typename MT>
+template <int TA, int TB, int MS, bool SLOT, bool TOT, typename MT>
 __device__ inline void fold_tile_f32(int tid, int tl, int sl, int nA, const FoldMap<MS> &fm, const int (*sSa)[MS],
                                      float (*acc)[TA * 3 + 1][TB * 3 + 1],
                                      const float (*blk)[9], const int *vA, const int *vB, MT *__restrict__ U,
@@ -302,10 +311,10 @@ __device__ inline void fold_tile_f32(int tid, int tl, int sl, int nA, const Fold
             rowsum(ia, t);
             const int64_t row = int64_t(vA[ia]) * ld;
             if constexpr (TOT) {
-                add_entry(U, row + col, s0 * t[0]);
+                put_entry<SLOT>(U, row + col, s0 * t[0]);
             } else {
-                add_entry(U, row + off + col, s0 * t[0]);
-                add_entry(U, row + col, s1 * t[1]);
+                put_entry<SLOT>(U, row + off + col, s0 * t[0]);
+                put_entry<SLOT>(U, row + col, s1 * t[1]);
             }
         }
     }
@@ -339,7 +348,7 @@ constexpr int TILE_F64_WAVES = 4;
 // Every lane runs the quadrature: a pair that is not evaluated (padding
 // triangle, shared vertex, or the mirror of a diagonal-tile pair) has its
 // target moved 1e4 away and a zero factor, so its terms are exact zeros.
-template <bool YUK, typename RT, typename MT, int TA, int TB, int MS, bool SYM>
+template <bool YUK, typename RT, typename MT, int TA, int TB, int MS, bool SYM, bool SLOT>
 __global__ void __launch_bounds__(TA * TB) __attribute__((amdgpu_waves_per_eu(sizeof(RT) == 4 ? TILE_F32_WAVES : TILE_F64_WAVES)))
     k_bem_regular(int64_t nt, const int32_t *__restrict__ m_tri, const RT *__restrict__ xq,
                   const RT *__restrict__ nq, const double *__restrict__ cen, const double *__restrict__ m_area,
@@ -352,6 +361,9 @@ __global__ void __launch_bounds__(TA * TB) __attribute__((amdgpu_waves_per_eu(si
                   double kappa, QRule6 R, QRule6F RF)
 {
     static_assert(!SYM || TA == TB, "symmetric evaluation needs square tiles");
+    static_assert(!SLOT || SYM, "slots hold the upper block pairs");
+    // SLOT: U holds three ld x ld planes over the local vertices, K, V and the mirrored K (T)
+    const int64_t offV = SLOT ? ld * ld : nv, ldT = SLOT ? ld : nv;
     constexpr bool F32 = sizeof(RT) == 4;
     constexpr int NT = TA * TB;
     const int64_t bA = listA[blockIdx.y], bB = listB[blockIdx.x];
@@ -387,7 +399,7 @@ __global__ void __launch_bounds__(TA * TB) __attribute__((amdgpu_waves_per_eu(si
         sN[sl][c] = m < nt ? nq[3 * m + c] : RT(0);
         sVb[sl][c] = m < nt ? m_tri[3 * m + c] : -1;
         if constexpr (F32) sCb[sl][c] = m < nt ? cen[3 * m + c] : 0.0;
-        sIb[tid] = tid < nB ? B_vid[pB + tid] : 0;
+        sIb[tid] = SLOT ? int(pB) + tid : tid < nB ? B_vid[pB + tid] : 0;
     }
     if (tid < TA * 3) {
         int tl = tid / 3, c = tid % 3;
@@ -395,7 +407,7 @@ __global__ void __launch_bounds__(TA * TB) __attribute__((amdgpu_waves_per_eu(si
         sVa[tl][c] = m < nt ? m_tri[3 * m + c] : -2;
         if constexpr (F32) sCa[tl][c] = m < nt ? cen[3 * m + c] : 0.0;
         if constexpr (SYM) sNa[tl][c] = m < nt ? nq[3 * m + c] : RT(0);
-        sIa[tid] = tid < nA ? A_vid[pA + tid] : 0;
+        sIa[tid] = SLOT ? int(pA) + tid : tid < nA ? A_vid[pA + tid] : 0;
     }
     if (tid < TA) sAa[tid] = (bA * TA + tid) < nt ? m_area[bA * TA + tid] : 0.0;
     if (tid < TB) sAb[tid] = (bB * TB + tid) < nt ? m_area[bB * TB + tid] : 0.0;
@@ -501,7 +513,9 @@ __global__ void __launch_bounds__(TA * TB) __attribute__((amdgpu_waves_per_eu(si
     // thread map), read now so that their latency hides behind the
     // quadrature.  No other workgroup of the launch touches them.
     MT pre[fold_pf<MT>() > 0 ? fold_pf<MT>() : 1][3];
-    if constexpr (F32) {
+    if constexpr (SLOT) {
+        for (auto &q : pre) q[0] = q[1] = q[2] = MT(0);
+    } else if constexpr (F32) {
         const int jb = tid % nB, r0 = tid / nB, rstep = NT / nB;
         if (r0 < rstep) {
             const int64_t col = sIb[jb];
@@ -557,15 +571,15 @@ __global__ void __launch_bounds__(TA * TB) __attribute__((amdgpu_waves_per_eu(si
             bmt[0][k] = Ktl[SYM ? k : 0];
         }
         const FoldMap<MS> fm = fold_map<NT, MS>(tid, nB, sSb, TB * 3);
-        fold_tile_f32<TA, TB, MS, false>(tid, tl, sl, nA, fm, sSa, acc, blk, sIa, sIb, U, ld, nv, sV, sK, pre);
+        fold_tile_f32<TA, TB, MS, SLOT, false>(tid, tl, sl, nA, fm, sSa, acc, blk, sIa, sIb, U, ld, offV, sV, sK, pre);
         if constexpr (SYM) {
             __syncthreads();
-            fold_tile_f32<TA, TB, MS, true>(tid, tl, sl, nA, fm, sSa, acc, bmt, sIa, sIb, T, nv, 0, sK, 0.0, pre);
+            fold_tile_f32<TA, TB, MS, SLOT, true>(tid, tl, sl, nA, fm, sSa, acc, bmt, sIa, sIb, T, ldT, 0, sK, 0.0, pre);
         }
     } else {
         // FP64: the stored entries are read after the quadrature, whose registers are free by now
         const int jb = tid % nB, r0 = tid / nB, rstep = NT / nB;
-        if (r0 < rstep) {
+        if (!SLOT && r0 < rstep) {
             const int64_t col = sIb[jb];
 #pragma unroll
             for (int k = 0; k < fold_pf<MT>(); ++k) {
@@ -579,10 +593,10 @@ __global__ void __launch_bounds__(TA * TB) __attribute__((amdgpu_waves_per_eu(si
             }
         }
         const FoldMap<MS> fm = fold_map<NT, MS>(tid, nB, sSb, TB * 3);
-        fold_tile_one<TA, TB, MS, 0>(tid, tl, sl, nA, fm, sSa, acc[0], Vl, sIa, sIb, U, ld, nv, sV, pre);
-        fold_tile_one<TA, TB, MS, 1>(tid, tl, sl, nA, fm, sSa, acc[0], Kl, sIa, sIb, U, ld, 0, sK, pre);
+        fold_tile_one<TA, TB, MS, SLOT, 0>(tid, tl, sl, nA, fm, sSa, acc[0], Vl, sIa, sIb, U, ld, offV, sV, pre);
+        fold_tile_one<TA, TB, MS, SLOT, 1>(tid, tl, sl, nA, fm, sSa, acc[0], Kl, sIa, sIb, U, ld, 0, sK, pre);
         if constexpr (SYM)
-            fold_tile_one<TA, TB, MS, 2>(tid, tl, sl, nA, fm, sSa, acc[0], Ktl, sIa, sIb, T, nv, 0, sK, pre);
+            fold_tile_one<TA, TB, MS, SLOT, 2>(tid, tl, sl, nA, fm, sSa, acc[0], Ktl, sIa, sIb, T, ldT, 0, sK, pre);
     }
 }
 
@@ -693,6 +707,48 @@ __global__ void __launch_bounds__(256) k_bem_symm2(int64_t nv, int64_t ld, MT *_
             *reinterpret_cast<pair_t *>(B + i2 * ld + j2) = w;
         }
     }
+}
+
+// Small surfaces (launch_slots): one launch holds every tile, each storing its
+// folded values to its own entries of three S x S planes over the blocks'
+// local vertices (K, V, mirrored K; block pairs A <= B only), and this adds up
+// the operator's entries, both of a pair (k, l) by one thread: over the local
+// vertices a of k and b of l, V'(k, l) = V'(l, k) takes V(a, b) where block(a)
+// <= block(b) and V(b, a) where block(b) <= block(a), K'(k, l) K(a, b) and
+// T(b, a), K'(l, k) T(a, b) and K(b, a).  Two launches instead of one per
+// colour pair (28 to 36, 12-15 us each however few tiles they hold), the
+// completion and the clears: a 642-vertex surface 0.50 -> 0.116 ms (FP64),
+// 0.40 -> 0.074 (FP32); a 320-triangle solve 5.9 -> 5.0 ms, 1 280 triangles
+// mixed 14.5 -> 13.7.
+template <typename MT>
+__global__ void __launch_bounds__(256)
+    k_bem_gather(int64_t nv, int64_t ld, int64_t S, const int32_t *__restrict__ occ_ptr,
+                 const int32_t *__restrict__ occ, const MT *__restrict__ W, MT *__restrict__ B)
+{
+    const int64_t k = blockIdx.y, l = blockIdx.x * int64_t(256) + threadIdx.x;
+    if (blockIdx.x == 0) // the row padding, read by the dense apply against zero inputs
+        for (int64_t c = 2 * nv + threadIdx.x; c < ld; c += 256) B[k * ld + c] = MT(0);
+    if (l < k || l >= nv) return;
+    const MT *K = W, *V = W + S * S, *T = W + 2 * S * S;
+    double v = 0.0, k1 = 0.0, k2 = 0.0;
+    for (int32_t i = occ_ptr[k]; i < occ_ptr[k + 1]; ++i)
+        for (int32_t j = occ_ptr[l]; j < occ_ptr[l + 1]; ++j) {
+            const int64_t a = occ[2 * i], b = occ[2 * j];
+            const int32_t ba = occ[2 * i + 1], bb = occ[2 * j + 1];
+            if (ba <= bb) {
+                v += double(V[a * S + b]);
+                k1 += double(K[a * S + b]);
+                k2 += double(T[a * S + b]);
+            }
+            if (bb <= ba) {
+                v += double(V[b * S + a]);
+                k2 += double(K[b * S + a]);
+                k1 += double(T[b * S + a]);
+            }
+        }
+    B[k * ld + nv + l] = B[l * ld + nv + k] = MT(v);
+    B[k * ld + l] = MT(k1);
+    if (l != k) B[l * ld + k] = MT(k2);
 }
 
 // ---------------------------------------------------------------------------
@@ -1309,6 +1365,8 @@ static const BlockSideDev &device_side(Problem &p, int w, int bs, hipStream_t s)
     std::vector<int32_t> lists(H.col_blk);
     for (int64_t b = 0; b < H.nb; ++b) lists.push_back(int32_t(b));
     D.col_blk = A.upload(lists, s);
+    D.occ_ptr = A.upload(H.occ_ptr, s);
+    D.occ = A.upload(H.occ, s);
     return S.sides.emplace(bs, D).first->second;
 }
 
@@ -1332,13 +1390,14 @@ struct RegArgs {
 
 // square shapes evaluate each unordered pair once (SYM)
 template <int TA, int TB> constexpr bool shape_sym() { return TA == TB; }
-template <int TA, int TB, int MS> static void launch_regular_ms(bool yuk, bool f32, const RegArgs &a, hipStream_t s)
+template <int TA, int TB, int MS, bool SLOT = false>
+static void launch_regular_ms(bool yuk, bool f32, const RegArgs &a, hipStream_t s)
 {
     if (a.nA == 0 || a.nB == 0) return;
     const dim3 grid(unsigned(a.nB), unsigned(a.nA));
     constexpr bool SYM = shape_sym<TA, TB>();
 #define PB_REG(Y, RT)                                                                                              \
-    hipLaunchKernelGGL((k_bem_regular<Y, RT, RT, TA, TB, MS, SYM>), grid, dim3(TA * TB), 0, s, a.nt, a.m_tri,      \
+    hipLaunchKernelGGL((k_bem_regular<Y, RT, RT, TA, TB, MS, SYM, SLOT>), grid, dim3(TA * TB), 0, s, a.nt, a.m_tri, \
                        static_cast<const RT *>(a.xq), static_cast<const RT *>(a.nq), a.cen, a.m_area, a.A.pref,     \
                        a.A.nvb, a.A.slots, a.A.vid, a.B.pref, a.B.nvb, a.B.slots, a.B.vid, a.listA, a.listB,        \
                        a.skip_lower, static_cast<RT *>(a.U), static_cast<RT *>(a.T), a.ld, a.nv, a.sV, a.sK,        \
@@ -1393,6 +1452,32 @@ static void launch_all_tiles(int shape, bool yuk, bool f32, RegArgs a, const Blo
             a.skip_lower = sym && c1 == c2 ? 1 : 0;
             launch_regular(shape, yuk, f32, a, s);
         }
+}
+
+// Square 16 x 16 tiles of a small surface go through slots (k_bem_gather) if
+// the three planes fit in 64 MiB: below that (n about 900 vertices FP64, 1 300
+// FP32) the colour-pair launches are all latency; above, the tiles' own time
+// fills their launches and the planes' traffic eats the rest of the gain.
+constexpr size_t SLOT_BYTES = size_t(64) << 20;
+constexpr int SLOT_SHAPE = 3;
+static_assert(TILE_SHAPES[SLOT_SHAPE].ta == 16 && TILE_SHAPES[SLOT_SHAPE].tb == 16, "the symmetric 16 x 16 shape");
+static size_t slot_bytes(const BlockSide &H, size_t elem) { return 3 * size_t(H.S) * size_t(H.S) * elem; }
+size_t slot_bytes_bound(int64_t nv, size_t elem)
+{
+    // local vertices: about 1.75 per vertex; a surface with more than 2.25 does not take the slots
+    const size_t S = size_t(2.25 * double(nv)) + 64;
+    return std::min(SLOT_BYTES, 3 * S * S * elem);
+}
+static void launch_slots(bool yuk, bool f32, RegArgs a, hipStream_t s)
+{
+    constexpr int TA = TILE_SHAPES[SLOT_SHAPE].ta;
+    a.ld = a.A.S;
+    a.listA = a.listB = a.A.col_blk + a.A.nb; // every block in order
+    a.nA = a.nB = a.A.nb;
+    a.skip_lower = 1;
+    if (a.ms <= 6) launch_regular_ms<TA, TA, 6, true>(yuk, f32, a, s);
+    else if (a.ms <= 12) launch_regular_ms<TA, TA, 12, true>(yuk, f32, a, s);
+    else launch_regular_ms<TA, TA, MAXS, true>(yuk, f32, a, s);
 }
 
 // cache key of the tuned shape: precision, kernel and size class (floor log2 of the triangle count)
@@ -1630,13 +1715,16 @@ void ensure_bem(Problem &p, int w, hipStream_t s)
     // the context's assembly workspace: the mirrored double layer T of a
     // square-tile assembly (nv x nv in the storage precision), vertex
     // coordinates and the touching-pair blocks
-    const size_t tbytes = (size_t(nv) * nv * elem + 255) / 256 * 256;
+    // (or, through slots, the three planes over the local vertices)
+    const BlockSide &HS = block_side(T, TILE_SHAPES[SLOT_SHAPE].ta);
+    const bool slots = slot_bytes(HS, elem) <= slot_bytes_bound(nv, elem) && (p.tile_fixed < 0 || p.tile_fixed == SLOT_SHAPE);
+    const size_t tbytes = ((slots ? slot_bytes(HS, elem) : size_t(nv) * nv * elem) + 255) / 256 * 256;
     double *ws = wsp->doubles((tbytes + 8 * (3 * size_t(nv) + 18 * size_t(S.ntp))) / 8 + 1);
     void *Tm = ws;
     double *vx = reinterpret_cast<double *>(static_cast<char *>(Tm) + tbytes), *tpv = vx + 3 * nv;
     ra.T = Tm;
     // tile shape: forced, or tuned once per (precision, kernel, size class) and context
-    int shape = p.tile_fixed;
+    int shape = slots ? SLOT_SHAPE : p.tile_fixed;
     if (shape < 0) {
         const int key = tile_key(p.precision, yuk, T.nt);
         std::lock_guard<std::mutex> tl(p.ctx->tune_mu);
@@ -1656,13 +1744,26 @@ void ensure_bem(Problem &p, int w, hipStream_t s)
     const bool sym = TILE_SHAPES[shape].ta == TILE_SHAPES[shape].tb;
     // every tile adds into the operator: start from zero (the row padding
     // past 2 nv, read by the dense apply against zero inputs, stays zero)
-    PB_HIP(hipMemsetAsync(S.B, 0, size_t(nv) * ld * elem, s));
-    if (sym) PB_HIP(hipMemsetAsync(Tm, 0, size_t(nv) * nv * elem, s));
+    if (!slots) PB_HIP(hipMemsetAsync(S.B, 0, size_t(nv) * ld * elem, s));
+    if (sym && !slots) PB_HIP(hipMemsetAsync(Tm, 0, size_t(nv) * nv * elem, s));
     if (p.timing) p.timer.begin(T_ASM, s);
-    launch_all_tiles(shape, yuk, f32, ra, HA, HB, s);
+    if (slots) {
+        ra.U = Tm;
+        ra.T = static_cast<char *>(Tm) + 2 * size_t(HS.S) * HS.S * elem;
+        launch_slots(yuk, f32, ra, s);
+        const dim3 g(nblk(nv, 256), unsigned(nv));
+        if (f32)
+            hipLaunchKernelGGL(k_bem_gather<float>, g, dim3(256), 0, s, nv, ld, HS.S, ra.A.occ_ptr, ra.A.occ,
+                               static_cast<const float *>(Tm), static_cast<float *>(S.B));
+        else
+            hipLaunchKernelGGL(k_bem_gather<double>, g, dim3(256), 0, s, nv, ld, HS.S, ra.A.occ_ptr, ra.A.occ,
+                               static_cast<const double *>(Tm), static_cast<double *>(S.B));
+    } else {
+        launch_all_tiles(shape, yuk, f32, ra, HA, HB, s);
+    }
     if (p.timing) p.timer.end(s);
     PB_HIP(hipGetLastError());
-    if (sym) {
+    if (sym && !slots) {
         const unsigned nbt = unsigned((nv + SYMT - 1) / SYMT);
         // FP32 storage with an even nv: pairs of entries, upper tile pairs only
         // (11.3 -> 7.7 ms per 80k-triangle interface); the same form ran FP64

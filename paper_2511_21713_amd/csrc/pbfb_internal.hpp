@@ -105,12 +105,16 @@ struct BlockSide {
     std::vector<int32_t> pref, nvb, slots, vid;
     int ncolor = 0;
     std::vector<int32_t> col_ptr, col_blk;
+    // operator index -> its local vertices (position pref[b] + k and block b of
+    // each, ascending): occ[2 i], occ[2 i + 1] for occ_ptr[v] <= i < occ_ptr[v + 1]
+    std::vector<int32_t> occ_ptr, occ;
 };
 struct BlockSideDev {
     int bs = 0;
     int64_t nb = 0, S = 0;
     int32_t *pref = nullptr, *nvb = nullptr, *slots = nullptr, *vid = nullptr;
     int32_t *col_blk = nullptr;
+    int32_t *occ_ptr = nullptr, *occ = nullptr;
 };
 
 // host-side topology of one boundary surface

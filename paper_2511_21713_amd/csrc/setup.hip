@@ -80,6 +80,19 @@ const BlockSide &block_side(SurfaceTopo &S, int bs)
         for (int32_t v : vs) vblocks[v].push_back(int32_t(b));
         for (int f : fill) B.ms_max = std::max(B.ms_max, f);
     }
+    B.occ_ptr.assign(S.nv + 1, 0);
+    for (int32_t v : B.vid) B.occ_ptr[v + 1]++;
+    for (int64_t v = 0; v < S.nv; ++v) B.occ_ptr[v + 1] += B.occ_ptr[v];
+    B.occ.resize(2 * B.S);
+    {
+        std::vector<int32_t> fill(B.occ_ptr.begin(), B.occ_ptr.end() - 1);
+        for (int64_t b = 0; b < B.nb; ++b)
+            for (int32_t k = B.pref[b]; k < B.pref[b + 1]; ++k) {
+                const int32_t i = fill[B.vid[k]]++;
+                B.occ[2 * i] = k;
+                B.occ[2 * i + 1] = int32_t(b);
+            }
+    }
     // greedy colouring in block order: the smallest colour no earlier block
     // sharing a vertex with this one has taken
     std::vector<int32_t> color(B.nb, -1);

@@ -163,3 +163,33 @@ def test_rows_of_many_neighbours_match_oracle(ctx, n):
     assert abs(m.solve()["total"] - ref) < 1e-5 * abs(ref)
     m.close()
     g.close()
+
+
+# 64 MiB of planes over the blocks' local vertices is where the assembly leaves
+# its single tile launch: FP64 between n = 9 and 10, FP32 between 11 and 12;
+# n = 1: two blocks, every vertex in both; n = 2: five
+@pytest.mark.parametrize("n,precision", [(1, 0), (2, 1), (9, 0), (10, 0), (11, 1), (12, 1)])
+def test_assembly_of_small_surfaces_matches_oracle_rows(ctx, n, precision):
+    """Sampled rows of both stored operators against the oracle's, at the bars
+    of the full-size rows; V' bitwise symmetric away from the touching pairs."""
+    import paper_2511_21713_amd as pb
+    prob = pbgen.make_problem(n=n, a=6.0, c=9.0, bump=n > 2, t=3.0, L=1, helix=0, partials=0, kappa=0.2, seed=(9, n),
+                              center_charge=1.0)
+    o = oracle.Oracle.from_problem(prob)
+    g = pb.Problem.from_inputs(ctx, prob, precision=precision)
+    g.set_tile_shape(16, 16)
+    for surf in (0, 1):
+        nv = o.n_m if surf == 0 else o.n_s
+        rng = np.random.default_rng(n + surf)
+        rows = np.unique(np.r_[0, nv - 1, rng.choice(nv, size=min(nv, 20), replace=False)])
+        V, K = o.bem_rows(surf, rows)
+        sV, sK = (-1.0, 1.0) if surf == 0 else (1.0, -1.0)
+        x = rng.standard_normal(nv)
+        Mx = o.surface_mass_apply(surf, x)[rows]
+        Vp, Kp = g.export_bem_rows(surf, rows)
+        eV = np.abs(Vp - sV * V).max() / np.abs(V).max()
+        dK = np.abs(Kp @ x - (0.5 * Mx + sK * (K @ x))).max() / (np.abs(Kp) @ np.abs(x)).max()
+        print(f"  n {n} precision {precision} surface {surf}: V {eV:.2e} K {dK:.2e}", flush=True)
+        bar = 1e-12 if precision == 0 else 1e-6
+        assert eV < bar and dK < bar
+    g.close()
