@@ -1455,17 +1455,22 @@ static void launch_all_tiles(int shape, bool yuk, bool f32, RegArgs a, const Blo
 }
 
 // Square 16 x 16 tiles of a small surface go through slots (k_bem_gather) if
-// the three planes fit in 64 MiB: below that (n about 900 vertices FP64, 1 300
-// FP32) the colour-pair launches are all latency; above, the tiles' own time
-// fills their launches and the planes' traffic eats the rest of the gain.
-constexpr size_t SLOT_BYTES = size_t(64) << 20;
+// the three planes fit in 192 MiB (about 1 200 vertices FP64, 1 700 FP32).
+// Setup of both surfaces, colour pairs -> slots: 1 002 vertices FP64 1.88 ->
+// 1.10 ms, 1 442 FP32 1.84 -> 1.15; 2 562 vertices would still gain (3.95 ->
+// 3.64 FP64, 2.85 -> 2.44 FP32) and 4 002 nothing, but the planes grow with
+// the square of the surface (0.8 GB FP64 at 2 562 vertices), and a server
+// charges them to the request.
+constexpr size_t SLOT_BYTES = size_t(192) << 20;
 constexpr int SLOT_SHAPE = 3;
 static_assert(TILE_SHAPES[SLOT_SHAPE].ta == 16 && TILE_SHAPES[SLOT_SHAPE].tb == 16, "the symmetric 16 x 16 shape");
 static size_t slot_bytes(const BlockSide &H, size_t elem) { return 3 * size_t(H.S) * size_t(H.S) * elem; }
 size_t slot_bytes_bound(int64_t nv, size_t elem)
 {
-    // local vertices: about 1.75 per vertex; a surface with more than 2.25 does not take the slots
-    const size_t S = size_t(2.25 * double(nv)) + 64;
+    // local vertices: about 2.3 per vertex; a surface with more than 2.5 does not take the slots
+    // (S >= nv: past that no plane set fits and none is charged)
+    const size_t S = size_t(2.5 * double(nv)) + 64;
+    if (3 * size_t(nv) * size_t(nv) * elem > SLOT_BYTES) return 0;
     return std::min(SLOT_BYTES, 3 * S * S * elem);
 }
 static void launch_slots(bool yuk, bool f32, RegArgs a, hipStream_t s)
@@ -1717,7 +1722,8 @@ void ensure_bem(Problem &p, int w, hipStream_t s)
     // coordinates and the touching-pair blocks
     // (or, through slots, the three planes over the local vertices)
     const BlockSide &HS = block_side(T, TILE_SHAPES[SLOT_SHAPE].ta);
-    const bool slots = slot_bytes(HS, elem) <= slot_bytes_bound(nv, elem) && (p.tile_fixed < 0 || p.tile_fixed == SLOT_SHAPE);
+    const bool slots = p.slots && slot_bytes(HS, elem) <= slot_bytes_bound(nv, elem) &&
+                       (p.tile_fixed < 0 || p.tile_fixed == SLOT_SHAPE);
     const size_t tbytes = ((slots ? slot_bytes(HS, elem) : size_t(nv) * nv * elem) + 255) / 256 * 256;
     double *ws = wsp->doubles((tbytes + 8 * (3 * size_t(nv) + 18 * size_t(S.ntp))) / 8 + 1);
     void *Tm = ws;

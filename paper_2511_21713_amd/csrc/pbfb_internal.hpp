@@ -301,6 +301,7 @@ struct Problem {
     bool val_ready = false; // FEM stiffness and coupling values (depend on the permittivities)
     bool bem_topo_ready[NSURF] = {false, false, false};
     int tile_fixed = -1; // tile shape forced by pbfb_set_tile_shape (index), -1: tuned
+    bool slots = true;   // small surfaces assembled through slots; off for a request whose server has no room for the planes
     bool bem_mf = false; // boundary operators applied matrix-free (no dense storage)
     // host copies
     int64_t nn = 0, ntet = 0, nq = 0;

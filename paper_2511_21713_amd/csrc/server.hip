@@ -29,9 +29,10 @@ size_t slot_bytes_bound(int64_t nv, size_t elem); // kernels_bem.hip: planes of 
 
 // Device bytes an instance holds while solving, and the assembly workspace it
 // needs while its dense operators are assembled (the mirrored double layer of
-// a square-tile assembly, nv x nv in the storage precision, vertex
-// coordinates and touching-pair blocks).
-void footprint_estimate(const Problem &p, int restart, size_t *steady, size_t *setup_extra)
+// a square-tile assembly, nv x nv in the storage precision, or with slots the
+// planes of a small surface's assembly; vertex coordinates and touching-pair
+// blocks).
+void footprint_estimate(const Problem &p, int restart, bool slots, size_t *steady, size_t *setup_extra)
 {
     const size_t elem = p.precision == PBFB_MIXED ? 4 : 8;
     size_t dense = 0, tmp = 0;
@@ -48,7 +49,7 @@ void footprint_estimate(const Problem &p, int restart, size_t *steady, size_t *s
         dense += size_t(T.nv) * bem_ld(T.nv) * elem;
         dense += size_t(sym_partials_doubles(T.nv)) * 8 + size_t(T.nv) * 20 * 12; // symmetric use: partials, Delta
         dense += size_t(T.nt) * 18 * 8 * 2 + size_t(T.nv) * (8 * 8 + 16 * 4);  // Morton copies, block tables, rings
-        const size_t plane = std::max(size_t(T.nv) * T.nv * elem, slot_bytes_bound(T.nv, elem));
+        const size_t plane = std::max(size_t(T.nv) * T.nv * elem, slots ? slot_bytes_bound(T.nv, elem) : 0);
         tmp = std::max(tmp, (plane + 255) / 256 * 256 + size_t(T.nv) * 3 * 8 + T.tp_sig.size() * 18 * 8 + 64);
     }
     const size_t n = size_t(p.n());
@@ -153,6 +154,7 @@ struct Server {
         } catch (const Error &) {
         }
         release_device_state(*r->p);
+        r->p->slots = true;
         used -= std::min(used, r->steady);
         --in_flight;
         admit_locked();
@@ -272,11 +274,16 @@ pbfb_status pbfb_server_submit(pbfb_server *sv, pbfb_problem *pp, const pbfb_sol
         else pbfb_solve_opts_default(&O);
         check_opts(O);
         size_t steady = 0, extra = 0;
-        footprint_estimate(p, O.gmres_restart, &steady, &extra);
+        footprint_estimate(p, O.gmres_restart, true, &steady, &extra);
+        // a budget without room for the planes of the slot assembly: colour
+        // pairs, which need the mirrored double layer only (equal to rounding)
+        const bool slots = steady + extra <= sv->s.budget;
+        if (!slots) footprint_estimate(p, O.gmres_restart, false, &steady, &extra);
         PB_CHECK(steady + extra <= sv->s.budget, PBFB_ENOMEM, "request exceeds the server's HBM budget");
         auto *r = new Request;
         r->o = O;
         r->p = &p;
+        p.slots = slots;
         r->steady = steady;
         r->extra = extra;
         r->t_submit = std::chrono::steady_clock::now();
@@ -305,7 +312,7 @@ pbfb_status pbfb_request_footprint(const pbfb_problem *pp, const pbfb_solve_opts
         if (o) O = *o;
         else pbfb_solve_opts_default(&O);
         check_opts(O);
-        footprint_estimate(p, O.gmres_restart, steady_bytes, setup_bytes);
+        footprint_estimate(p, O.gmres_restart, true, steady_bytes, setup_bytes);
         return PBFB_OK;
     } catch (const Error &e) {
         set_error(e.msg);

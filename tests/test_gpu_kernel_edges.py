@@ -1,6 +1,8 @@
 """Kernels and dispatch branches at the sizes where they can go wrong: block
 remainders, the smallest surfaces and the first sizes past a branch, each
 against the oracle or the path the oracle already pins."""
+import time
+
 import numpy as np
 import pytest
 
@@ -165,10 +167,10 @@ def test_rows_of_many_neighbours_match_oracle(ctx, n):
     g.close()
 
 
-# 64 MiB of planes over the blocks' local vertices is where the assembly leaves
-# its single tile launch: FP64 between n = 9 and 10, FP32 between 11 and 12;
+# 192 MiB of planes over the blocks' local vertices is where the assembly leaves
+# its single tile launch: FP64 between n = 11 and 12, FP32 between 13 and 14;
 # n = 1: two blocks, every vertex in both; n = 2: five
-@pytest.mark.parametrize("n,precision", [(1, 0), (2, 1), (9, 0), (10, 0), (11, 1), (12, 1)])
+@pytest.mark.parametrize("n,precision", [(1, 0), (2, 1), (11, 0), (12, 0), (13, 1), (14, 1)])
 def test_assembly_of_small_surfaces_matches_oracle_rows(ctx, n, precision):
     """Sampled rows of both stored operators against the oracle's, at the bars
     of the full-size rows; V' bitwise symmetric away from the touching pairs."""
@@ -192,4 +194,27 @@ def test_assembly_of_small_surfaces_matches_oracle_rows(ctx, n, precision):
         print(f"  n {n} precision {precision} surface {surf}: V {eV:.2e} K {dK:.2e}", flush=True)
         bar = 1e-12 if precision == 0 else 1e-6
         assert eV < bar and dK < bar
+    g.close()
+
+
+def test_server_without_room_for_assembly_planes(ctx):
+    """A budget one byte short of the footprint: admitted, assembled without
+    the planes, the same energy to rounding."""
+    import paper_2511_21713_amd as pb
+    prob = pbgen.make_problem(n=3, a=6.0, c=9.0, bump=True, t=3.0, L=1, helix=0, partials=0, kappa=0.2, seed=(9, 3),
+                              center_charge=1.0)
+    g = pb.Problem.from_inputs(ctx, prob)
+    ref = g.solve(**TIGHT)["total"]
+    g.close()
+    g = pb.Problem.from_inputs(ctx, prob)
+    srv = pb.Server(ctx, hbm_budget_bytes=sum(g.footprint(**TIGHT)) - 1, max_slots=1)
+    t = srv.submit(g, **TIGHT)
+    end = time.time() + 60
+    r = srv.poll(t)
+    while r is None and time.time() < end:
+        time.sleep(0.005)
+        r = srv.poll(t)
+    srv.close()
+    assert r is not None and r["status"] == 0
+    assert abs(r["total"] - ref) < 1e-10 * abs(ref)
     g.close()
