@@ -32,7 +32,7 @@
 // the centroid difference of a pair is formed in FP64 and rounded once, so
 // x - y never cancels large coordinates in FP32.  A pair's 3x3 V and K
 // blocks are summed over its 36 quadrature pairs in FP32, and so are the
-// fold's corner sums onto a tile's vertices (at most MS terms each); each
+// fold's corner sums onto a tile's vertices (at most MAXS terms each); each
 // tile's sum is added to the FP32 stored entry in FP64 and rounded once (an
 // entry receives one tile's sum for each pair of blocks holding its two
 // vertices).  The touching pairs stay FP64 throughout.
@@ -96,240 +96,177 @@ template <typename MT> __device__ inline void add_entry(MT *__restrict__ U, int6
     U[at] = MT(double(U[at]) + v);
 }
 
-// A folded entry: added to the stored operator, or (SLOT) stored to the tile's
-// own place in a matrix over the blocks' local vertices (see k_bem_gather)
-template <bool SLOT, typename MT> __device__ inline void put_entry(MT *__restrict__ U, int64_t at, double v)
-{
-    if constexpr (SLOT) U[at] = MT(v);
-    else add_entry(U, at, v);
-}
-
-// Rows of the fold's last stage whose operator entries a thread reads ahead
-// (the rest are read when they are added to): FP32 tiles one, before the
-// quadrature (342 -> 325 ms per 80k-triangle assembly; two cost registers and
-// gained nothing more); FP64 tiles one, after the quadrature, whose registers
-// are free by then, so that the reads overlap the fold's LDS passes (before
-// it they spill; 572 -> 565 ms).  The two reads are written out in place:
-// the FP32 kernels' register allocation (six wavefronts per SIMD) did not
-// survive moving them into a shared function.
-constexpr int FOLD_PF32 = 1, FOLD_PF64 = 1;
-template <typename MT> constexpr int fold_pf() { return sizeof(MT) == 4 ? FOLD_PF32 : FOLD_PF64; }
-
-// A thread's part of the fold of a tile, the same for every operator
-// folded: source vertex jb, first row r0 and row step of its strided rows, and
-// the tile columns of jb's corners (absent corners: the zero column CMAX)
-template <int MS> struct FoldMap {
-    int jb, r0, rstep;
-    int cb[MS];
+// The fold of a tile's 3x3 pair blocks onto the blocks' vertices, in LDS
+// planes of one block per pair.  Rows and columns are permuted so that the
+// corners of one local vertex lie side by side (BlockSide::cpos; seg: first
+// position and number of each vertex), which gives both passes exact,
+// wavefront-uniform trip counts and addresses:
+//  1. a wavefront takes a source vertex at a time, a lane per tile row: its
+//     columns are added up into the first of them, in place (a vertex with one
+//     corner in the block needs nothing);
+//  2. a wavefront takes a target vertex at a time, a lane per (plane, source
+//     vertex): its rows are added up and the sum goes into the operator.
+// Corners are added in ascending order.  A fold over corner lists padded to
+// the longest (6 of 2.6 on average, the absent ones reading a zero row or
+// column) took a third of the tiles' vector instructions (1 324 per wavefront
+// in FP32, now 1 050), and operator entries and inputs read under conditions
+// or in loops, each with a wait of its own, most of the waiting.  Per surface
+// (mean of Laplace and Yukawa): 10 242 vertices FP64 18.3 -> 17.3 ms, FP32
+// 10.5 -> 8.8, 40 962 vertices FP32 152.9 -> 133.3.  FP32 tiles are now bound
+// by vector issue (86 % busy), FP64 ones by that (55 to 70 %) and LDS bank
+// conflicts of the first store into the planes.
+//
+// Operator entries: plane V to U + offV, plane K to U, the mirrored K to T.
+template <typename MT> struct FoldOut {
+    MT *U, *T;
+    int64_t offV, ld, ldT;
+    double sV, sK;
 };
-template <int NT, int MS>
-__device__ inline FoldMap<MS> fold_map(int tid, int nB, const int (*sSb)[MS], int cmax)
+template <int TB> constexpr int fold_rs() { return TB * 3 + 1; } // row stride, odd
+template <int TA, int TB> constexpr int fold_ps() { return TA * 3 * fold_rs<TB>(); }
+
+// lane t of the second pass over NP planes from plane FIRST (0: V, 1: K, 2: mirrored K)
+template <typename MT> struct FoldLane {
+    MT *at;
+    int64_t stride;
+    double sc;
+    int col;
+    bool on;
+};
+template <int TA, int TB, int FIRST, int NP, typename MT>
+__device__ inline FoldLane<MT> fold_lane(int t, int nB, const int *sIb, const int *sSb, const FoldOut<MT> &o)
 {
-    FoldMap<MS> fm;
-    fm.jb = tid % nB;
-    fm.r0 = tid / nB;
-    fm.rstep = NT / nB;
+    int q = 0, jb = t;
 #pragma unroll
-    for (int l = 0; l < MS; ++l) {
-        const int c = sSb[fm.jb][l];
-        fm.cb[l] = c < 0 ? cmax : c;
-    }
-    return fm;
+    for (int k = 1; k < NP; ++k)
+        if (jb >= nB) {
+            jb -= nB;
+            ++q;
+        }
+    FoldLane<MT> L;
+    L.on = jb < nB;
+    if (!L.on) jb = 0;
+    L.col = q * fold_ps<TA, TB>() + (sSb[jb] & 255);
+    q += FIRST;
+    L.at = (q == 2 ? o.T : o.U) + (q == 0 ? o.offV : 0) + sIb[jb];
+    L.stride = q == 2 ? o.ldT : o.ld;
+    L.sc = q == 0 ? o.sV : o.sK;
+    return L;
 }
 
-// Fold of a tile's pair blocks onto the blocks' vertices through the shared
-// tile, one operator at a time (FP64 evaluation: V, K and the mirrored K in
-// turn through one FP64 plane, which keeps the LDS of a workgroup small
-// enough for four per CU): first
-// the source corners of each source vertex (in place, row by row), then the
-// target corners of each target vertex, added into U at row vA[ia], column
-// off + vB[jb] with factor sc.  A thread owns one source vertex jb and a
-// strided set of rows; the corner lists are read once into registers and
-// every tile read is independent (an absent corner reads the zero row /
-// column), so the reads pipeline.  MS >= the largest number of corners of
-// any vertex of either block: the lists past it hold only absent corners,
-// whose +0 terms are skipped.
-template <int TA, int TB, int MS, bool SLOT, int PL, typename MT, typename ST, typename XT>
-__device__ inline void fold_tile_one(int tid, int tl, int sl, int nA, const FoldMap<MS> &fm, const int (*sSa)[MS],
-                                     ST (*acc)[TB * 3 + 1], const XT *Xl, const int *vA,
-                                     const int *vB, MT *__restrict__ U, int64_t ld, int64_t off, double sc,
-                                     const MT (*pre)[3])
+// Vertices of a wavefront's round (of 4.6 in all on average): their list
+// entries come through independent scalar loads and, of a round of target
+// vertices, a lane's operator entries together: the first round's before the
+// quadrature (FP32) or, where they would spill, right after it (FP64), so that
+// their latency hides.  No other workgroup of the launch touches them.  Six
+// rows cover most blocks in one round; FP64 has registers for four.
+template <typename MT> constexpr int fold_rnd() { return sizeof(MT) == 4 ? 6 : 4; }
+template <bool SLOT, int NW, typename MT>
+__device__ inline void fold_read(int i0, int nA, const int32_t *__restrict__ vA, const FoldLane<MT> &L,
+                                 MT (&pre)[fold_rnd<MT>()])
 {
-    constexpr int NT = TA * TB;
-    const int jb = fm.jb, r0 = fm.r0, rstep = fm.rstep;
-    const bool colthread = r0 < rstep; // NT - rstep * nB threads stay idle
-    const int (&cb)[MS] = fm.cb;
-    for (int k = tid; k < TB * 3 + 1; k += NT) acc[TA * 3][k] = 0.0;
-    if (tid < TA * 3) acc[tid][TB * 3] = 0.0;
+    // past the end: the last row again, not used (a read under a condition
+    // would be waited for where the condition ends)
+#pragma unroll
+    for (int k = 0; k < fold_rnd<MT>(); ++k)
+        pre[k] = SLOT ? MT(0) : L.at[int64_t(vA[min(i0 + k * NW, nA - 1)]) * L.stride];
+}
+
+// sum of n values (uniform n) at q, q + step, ...
+template <int STEP, typename ST> __device__ inline ST fold_sum(const ST *q, int n)
+{
+    auto sum = [&](auto N) {
+        ST v[decltype(N)::value];
+#pragma unroll
+        for (int k = 0; k < decltype(N)::value; ++k) v[k] = q[k * STEP];
+        ST t = v[0];
+#pragma unroll
+        for (int k = 1; k < decltype(N)::value; ++k) t += v[k];
+        return t;
+    };
+    switch (n) {
+    case 1: return sum(std::integral_constant<int, 1>{});
+    case 2: return sum(std::integral_constant<int, 2>{});
+    case 3: return sum(std::integral_constant<int, 3>{});
+    case 4: return sum(std::integral_constant<int, 4>{});
+    case 5: return sum(std::integral_constant<int, 5>{});
+    case 6: return sum(std::integral_constant<int, 6>{});
+    }
+    ST t = sum(std::integral_constant<int, 6>{});
+    for (int k = 6; k < n; ++k) t += q[k * STEP];
+    return t;
+}
+
+// acc: NP planes, free; blk: the pair's blocks; pa, pb: the packed positions of
+// the pair's triangles; segA, vA, segB: lists of the two blocks; pre: the
+// entries of this wavefront's first rows (fold_read)
+template <bool SLOT, int TA, int TB, int FIRST, int NP, typename ST, typename MT>
+__device__ inline void fold_tile(int tid, int nA, int nB, const int32_t *__restrict__ segA,
+                                 const int32_t *__restrict__ vA, const int32_t *__restrict__ segB, const int *sIb,
+                                 const int *sSb, int pa, int pb, ST *acc, const ST (&blk)[NP][9],
+                                 const FoldOut<MT> &o, MT (&pre)[fold_rnd<MT>()])
+{
+    constexpr int RND = fold_rnd<MT>();
+    constexpr int NW = TA * TB / 64, RS = fold_rs<TB>(), PS = fold_ps<TA, TB>();
+    const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int b = 0; b < 3; ++b) acc[3 * tl + a][3 * sl + b] = ST(Xl[3 * a + b]);
+        for (int b = 0; b < 3; ++b) {
+            ST *q = acc + ((pa >> (8 * a)) & 255) * RS + ((pb >> (8 * b)) & 255);
+#pragma unroll
+            for (int pl = 0; pl < NP; ++pl) q[pl * PS] = blk[pl][3 * a + b];
+        }
     __syncthreads();
-    constexpr int RMAX = TA * 3;
-    constexpr int RPT = (RMAX + NT / (TB * 3) - 1) / (NT / (TB * 3)); // rows per thread, nB <= TB * 3
-    double colsum[RPT];
-    int nrow = 0;
-    if (colthread) {
+    for (int j0 = w; j0 < nB; j0 += NW * RND) {
+        int seg[RND];
 #pragma unroll
-        for (int r = 0; r < RPT; ++r) {
-            const int sa = r0 + r * rstep;
-            double t = 0.0;
-            if (sa < RMAX) {
-                double v[MS];
+        for (int k = 0; k < RND; ++k) seg[k] = segB[min(j0 + k * NW, nB - 1)];
 #pragma unroll
-                for (int l = 0; l < MS; ++l) v[l] = double(acc[sa][cb[l]]);
+        for (int k = 0; k < RND; ++k) {
+            const int n = seg[k] >> 8;
+            if (j0 + k * NW < nB && n > 1 && lane < TA * 3) {
+                ST *q = acc + lane * RS + (seg[k] & 255);
+                ST t[NP];
 #pragma unroll
-                for (int l = 0; l < MS; ++l) t += v[l];
-                nrow = r + 1;
+                for (int pl = 0; pl < NP; ++pl) t[pl] = fold_sum<1>(q + pl * PS, n);
+#pragma unroll
+                for (int pl = 0; pl < NP; ++pl) q[pl * PS] = t[pl];
             }
-            colsum[r] = t;
         }
     }
     __syncthreads();
-    if (colthread)
+    for (int t0 = 0; t0 < NP * nB; t0 += 64) {
+        const FoldLane<MT> L = fold_lane<TA, TB, FIRST, NP>(t0 + lane, nB, sIb, sSb, o);
+        for (int i0 = w; i0 < nA; i0 += NW * RND) {
+            if (t0 > 0 || i0 > w) fold_read<SLOT, NW>(i0, nA, vA, L, pre);
+            int seg[RND], v[RND];
+            ST t[RND];
 #pragma unroll
-        for (int r = 0; r < RPT; ++r)
-            if (r < nrow) acc[r0 + r * rstep][jb] = ST(colsum[r]);
-    __syncthreads();
-    if (colthread) {
-        const int64_t col = off + vB[jb];
-        auto rowsum = [&](int ia) {
-            double v[MS];
-#pragma unroll
-            for (int k = 0; k < MS; ++k) {
-                const int ra = sSa[ia][k];
-                v[k] = double(acc[ra < 0 ? TA * 3 : ra][jb]);
+            for (int k = 0; k < RND; ++k) {
+                seg[k] = segA[min(i0 + k * NW, nA - 1)];
+                v[k] = SLOT ? i0 + k * NW : vA[min(i0 + k * NW, nA - 1)];
             }
-            double t = 0.0;
 #pragma unroll
-            for (int k = 0; k < MS; ++k) t += v[k];
-            return t;
-        };
-        // the first fold_pf rows add to the entries read before the quadrature
-#pragma unroll
-        for (int k = 0; k < fold_pf<MT>(); ++k) {
-            const int ia = r0 + k * rstep;
-            if (ia < nA) U[int64_t(vA[ia]) * ld + col] = MT(double(pre[k][PL]) + sc * rowsum(ia));
-        }
-        for (int ia = r0 + fold_pf<MT>() * rstep; ia < nA; ia += rstep)
-            put_entry<SLOT>(U, int64_t(vA[ia]) * ld + col, sc * rowsum(ia));
-    }
-    __syncthreads();
-}
-
-// Fold of an FP32 tile's pair blocks (corner sums in FP32, the evaluation
-// precision), V and K in two FP32 planes of the shared tile read at the same
-// index (TOT = false: V to column off + vB[jb]
-// with factor s0, K to column vB[jb] with factor s1 of row vA[ia] of U), or
-// the mirrored K of a square tile in one plane (TOT = true: to column vB[jb]
-// of row vA[ia] of U = T with factor s0); otherwise as fold_tile_one.
-template <int TA, int TB, int MS, bool SLOT, bool TOT, typename MT>
-__device__ inline void fold_tile_f32(int tid, int tl, int sl, int nA, const FoldMap<MS> &fm, const int (*sSa)[MS],
-                                     float (*acc)[TA * 3 + 1][TB * 3 + 1],
-                                     const float (*blk)[9], const int *vA, const int *vB, MT *__restrict__ U,
-                                     int64_t ld, int64_t off, double s0, double s1, const MT (*pre)[3])
-{
-    constexpr int NT = TA * TB, RMAX = TA * 3, CMAX = TB * 3, RC = 4, NPL = TOT ? 1 : 2;
-    const int jb = fm.jb, r0 = fm.r0, rstep = fm.rstep;
-    const bool colthread = r0 < rstep; // NT - rstep * nB threads stay idle
-    const int (&cb)[MS] = fm.cb;
-    for (int k = tid; k < CMAX + 1; k += NT)
-#pragma unroll
-        for (int pl = 0; pl < NPL; ++pl) acc[pl][RMAX][k] = 0.0f;
-    if (tid < RMAX)
-#pragma unroll
-        for (int pl = 0; pl < NPL; ++pl) acc[pl][tid][CMAX] = 0.0f;
-#pragma unroll
-    for (int pl = 0; pl < NPL; ++pl)
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) acc[pl][3 * tl + a][3 * sl + b] = blk[pl][3 * a + b];
-    __syncthreads();
-    const int rows_pt = (RMAX + rstep - 1) / rstep; // uniform
-    for (int rb = 0; rb < rows_pt; rb += RC) {
-        float colsum[RC][NPL];
-        int nrow = 0;
-        if (colthread) {
-#pragma unroll
-            for (int r = 0; r < RC; ++r) {
-                const int sa = r0 + (rb + r) * rstep;
-#pragma unroll
-                for (int pl = 0; pl < NPL; ++pl) colsum[r][pl] = 0.0f;
-                if (sa < RMAX) {
-#pragma unroll
-                    for (int l = 0; l < MS; ++l)
-#pragma unroll
-                        for (int pl = 0; pl < NPL; ++pl) colsum[r][pl] += acc[pl][sa][cb[l]];
-                    nrow = r + 1;
+            for (int k = 0; k < RND; ++k)
+                if (i0 + k * NW < nA) {
+                    t[k] = fold_sum<RS>(acc + L.col + (seg[k] & 255) * RS, seg[k] >> 8);
+                    if (L.on) L.at[int64_t(v[k]) * L.stride] = MT(double(pre[k]) + L.sc * double(t[k]));
                 }
-            }
-        }
-        __syncthreads();
-        if (colthread)
-#pragma unroll
-            for (int r = 0; r < RC; ++r)
-                if (r < nrow)
-#pragma unroll
-                    for (int pl = 0; pl < NPL; ++pl) acc[pl][r0 + (rb + r) * rstep][jb] = colsum[r][pl];
-        __syncthreads();
-    }
-    if (colthread) {
-        const int64_t col = vB[jb];
-        auto rowsum = [&](int ia, double (&t)[NPL]) {
-            float f[NPL];
-#pragma unroll
-            for (int pl = 0; pl < NPL; ++pl) f[pl] = 0.0f;
-#pragma unroll
-            for (int k = 0; k < MS; ++k) {
-                const int ra = sSa[ia][k] < 0 ? RMAX : sSa[ia][k];
-#pragma unroll
-                for (int pl = 0; pl < NPL; ++pl) f[pl] += acc[pl][ra][jb];
-            }
-#pragma unroll
-            for (int pl = 0; pl < NPL; ++pl) t[pl] = double(f[pl]);
-        };
-        // the first fold_pf rows add to the entries read before the quadrature
-#pragma unroll
-        for (int k = 0; k < fold_pf<MT>(); ++k) {
-            const int ia = r0 + k * rstep;
-            if (ia < nA) {
-                double t[NPL];
-                rowsum(ia, t);
-                const int64_t row = int64_t(vA[ia]) * ld;
-                if constexpr (TOT) {
-                    U[row + col] = MT(double(pre[k][2]) + s0 * t[0]);
-                } else {
-                    U[row + off + col] = MT(double(pre[k][0]) + s0 * t[0]);
-                    U[row + col] = MT(double(pre[k][1]) + s1 * t[1]);
-                }
-            }
-        }
-        for (int ia = r0 + fold_pf<MT>() * rstep; ia < nA; ia += rstep) {
-            double t[NPL];
-            rowsum(ia, t);
-            const int64_t row = int64_t(vA[ia]) * ld;
-            if constexpr (TOT) {
-                put_entry<SLOT>(U, row + col, s0 * t[0]);
-            } else {
-                put_entry<SLOT>(U, row + off + col, s0 * t[0]);
-                put_entry<SLOT>(U, row + col, s1 * t[1]);
-            }
         }
     }
 }
 
-// occupancy asked of the compiler: FP32 tiles fit in 80 VGPRs (six
-// wavefronts per SIMD by registers and LDS), FP64 tiles in 128 (four)
+// occupancy asked of the compiler: FP32 tiles fit in 96 VGPRs (five
+// wavefronts per SIMD, as many as the LDS of five workgroups leaves), FP64
+// tiles in 128 (four)
 constexpr int TILE_F32_WAVES = 5;
 constexpr int TILE_F64_WAVES = 4;
 
 // RT = double: positions and normals in FP64 (xq, nq: m_qp, m_nrm; cen unused)
 // RT = float : FP32 offsets from FP64 centroids (xq, nq: m_qf, m_nf; cen: m_cen)
 // MT: storage of the operator (double, or float in mixed precision)
-// TA x TB: target x source triangles of the tile, one pair per thread; MS:
-// bound on the corners of one vertex in one block (6, 12 or MAXS).  The
+// TA x TB: target x source triangles of the tile, one pair per thread.  The
 // tile of workgroup (x, y) is target block listA[y] x source block listB[x]
 // (skip_lower: tiles whose source block precedes the target block return).
 // The tile's V and K blocks are folded onto its vertices and added into the
@@ -348,14 +285,16 @@ constexpr int TILE_F64_WAVES = 4;
 // Every lane runs the quadrature: a pair that is not evaluated (padding
 // triangle, shared vertex, or the mirror of a diagonal-tile pair) has its
 // target moved 1e4 away and a zero factor, so its terms are exact zeros.
-template <bool YUK, typename RT, typename MT, int TA, int TB, int MS, bool SYM, bool SLOT>
+template <bool YUK, typename RT, typename MT, int TA, int TB, bool SYM, bool SLOT>
 __global__ void __launch_bounds__(TA * TB) __attribute__((amdgpu_waves_per_eu(sizeof(RT) == 4 ? TILE_F32_WAVES : TILE_F64_WAVES)))
     k_bem_regular(int64_t nt, const int32_t *__restrict__ m_tri, const RT *__restrict__ xq,
                   const RT *__restrict__ nq, const double *__restrict__ cen, const double *__restrict__ m_area,
                   const int32_t *__restrict__ A_pref, const int32_t *__restrict__ A_nv,
-                  const int32_t *__restrict__ A_slots, const int32_t *__restrict__ A_vid,
+                  const int32_t *__restrict__ A_seg, const int32_t *__restrict__ A_vid,
+                  const int32_t *__restrict__ A_cpos,
                   const int32_t *__restrict__ B_pref, const int32_t *__restrict__ B_nv,
-                  const int32_t *__restrict__ B_slots, const int32_t *__restrict__ B_vid,
+                  const int32_t *__restrict__ B_seg, const int32_t *__restrict__ B_vid,
+                  const int32_t *__restrict__ B_cpos,
                   const int32_t *__restrict__ listA, const int32_t *__restrict__ listB, int skip_lower,
                   MT *__restrict__ U, MT *__restrict__ T, int64_t ld, int64_t nv, double sV, double sK,
                   double kappa, QRule6 R, QRule6F RF)
@@ -368,66 +307,95 @@ __global__ void __launch_bounds__(TA * TB) __attribute__((amdgpu_waves_per_eu(si
     constexpr int NT = TA * TB;
     const int64_t bA = listA[blockIdx.y], bB = listB[blockIdx.x];
     if (SYM && skip_lower && bB < bA) return; // evaluated as (bB, bA)
-    __shared__ RT sX[TA * 18]; // quadrature points, 18 values per triangle
-    __shared__ RT sY[TB * 18];
-    __shared__ RT sN[TB][3];
-    __shared__ RT sNa[SYM ? TA : 1][3];
-    __shared__ double sCa[F32 ? TA : 1][3], sCb[F32 ? TB : 1][3];
-    __shared__ double sAa[TA], sAb[TB];
-    __shared__ int sVa[TA][3], sVb[TB][3];
-    __shared__ int sSa[TA * 3][MS], sSb[TB * 3][MS];
-    __shared__ int sIa[TA * 3], sIb[TB * 3]; // operator index of each block vertex
-    // the tile of pair blocks in the evaluation precision, + a zero row and a
-    // zero column: FP32 one plane each for V and K, then the mirrored K of a
-    // square tile in the first; FP64 one plane, one operator at a time
-    constexpr int NPL = F32 ? 2 : 1;
-    __shared__ std::conditional_t<F32, float, double> acc[NPL][TA * 3 + 1][TB * 3 + 1];
+    // quadrature inputs, then in the same memory the planes of the fold: FP32
+    // all of them, FP64 V and K, then the mirrored K (four workgroups per CU)
+    struct In {
+        RT X[TA * 18], Y[TB * 18]; // quadrature points, 18 values per triangle
+        RT N[TB][3], Na[SYM ? TA : 1][3];
+        double Ca[F32 ? TA : 1][3], Cb[F32 ? TB : 1][3], Aa[TA], Ab[TB];
+        int Va[TA][3], Vb[TB][3];
+    };
+    constexpr int NPL = F32 && SYM ? 3 : 2, NW = NT / 64;
+    __shared__ union {
+        In in;
+        RT acc[NPL * fold_ps<TA, TB>()];
+    } sh;
+    RT *const sX = sh.in.X, *const sY = sh.in.Y;
+    auto &sN = sh.in.N;
+    auto &sNa = sh.in.Na;
+    auto &sCa = sh.in.Ca;
+    auto &sCb = sh.in.Cb;
+    auto &sAa = sh.in.Aa;
+    auto &sAb = sh.in.Ab;
+    auto &sVa = sh.in.Va;
+    auto &sVb = sh.in.Vb;
+    __shared__ int sIb[TB * 3], sSb[TB * 3]; // operator index and segment of each source vertex
 
     const int tid = threadIdx.x;
     const int nA = A_nv[bA], nB = B_nv[bB];
     const int64_t pA = A_pref[bA], pB = B_pref[bB];
 
+    // Every input is read at once, at an index within its array, and waited for
+    // together; in loops and under conditions, each with a wait of its own,
+    // the inputs took longer than the quadrature.
     {
-        // a block's quadrature points are contiguous
-        const int64_t xa = 18 * bA * TA, xb = 18 * bB * TB, xe = 18 * nt;
-        for (int k = tid; k < TA * 18; k += NT) sX[k] = xa + k < xe ? xq[xa + k] : RT(0);
-        for (int k = tid; k < TB * 18; k += NT) sY[k] = xb + k < xe ? xq[xb + k] : RT(0);
-    }
-    if (tid < TB * 3) {
-        int sl = tid / 3, c = tid % 3;
-        int64_t m = bB * TB + sl;
-        sN[sl][c] = m < nt ? nq[3 * m + c] : RT(0);
-        sVb[sl][c] = m < nt ? m_tri[3 * m + c] : -1;
-        if constexpr (F32) sCb[sl][c] = m < nt ? cen[3 * m + c] : 0.0;
-        sIb[tid] = SLOT ? int(pB) + tid : tid < nB ? B_vid[pB + tid] : 0;
-    }
-    if (tid < TA * 3) {
-        int tl = tid / 3, c = tid % 3;
-        int64_t m = bA * TA + tl;
-        sVa[tl][c] = m < nt ? m_tri[3 * m + c] : -2;
-        if constexpr (F32) sCa[tl][c] = m < nt ? cen[3 * m + c] : 0.0;
-        if constexpr (SYM) sNa[tl][c] = m < nt ? nq[3 * m + c] : RT(0);
-        sIa[tid] = SLOT ? int(pA) + tid : tid < nA ? A_vid[pA + tid] : 0;
-    }
-    if (tid < TA) sAa[tid] = (bA * TA + tid) < nt ? m_area[bA * TA + tid] : 0.0;
-    if (tid < TB) sAb[tid] = (bB * TB + tid) < nt ? m_area[bB * TB + tid] : 0.0;
-    for (int k = tid; k < TA * 3 * MS; k += NT) {
-        int r = k / MS, c = k % MS;
-        sSa[r][c] = r < nA ? A_slots[(pA + r) * MAXS + c] : -1;
-    }
-    for (int k = tid; k < TB * 3 * MS; k += NT) {
-        int r = k / MS, c = k % MS;
-        sSb[r][c] = r < nB ? B_slots[(pB + r) * MAXS + c] : -1;
+        constexpr int NX = (TA * 18 + NT - 1) / NT, NY = (TB * 18 + NT - 1) / NT;
+        const int64_t xa = 18 * bA * TA, xb = 18 * bB * TB, xe = 18 * nt; // a block's points are contiguous
+        RT x[NX], y[NY];
+#pragma unroll
+        for (int k = 0; k < NX; ++k) x[k] = xq[min(xa + tid + k * NT, xe - 1)];
+#pragma unroll
+        for (int k = 0; k < NY; ++k) y[k] = xq[min(xb + tid + k * NT, xe - 1)];
+        const int64_t ka = 3 * bA * TA + tid, kb = 3 * bB * TB + tid; // triangle * 3 + corner / component
+        const int64_t la = min(ka, 3 * nt - 1), lb = min(kb, 3 * nt - 1);
+        int va = m_tri[la], vb = m_tri[lb];
+        RT nb = nq[lb], na = RT(0);
+        if constexpr (SYM) na = nq[la];
+        double ca = 0.0, cb = 0.0;
+        if constexpr (F32) ca = cen[la], cb = cen[lb];
+        double aa = m_area[min(bA * TA + tid, nt - 1)], ab = m_area[min(bB * TB + tid, nt - 1)];
+        int ib = SLOT ? int(pB) + tid : B_vid[pB + min(tid, nB - 1)], sb = B_seg[pB + min(tid, nB - 1)];
+        // (keeps the reads out of the conditions below)
+        asm volatile("" : "+v"(va), "+v"(vb), "+v"(nb), "+v"(na), "+v"(aa), "+v"(ab), "+v"(ib), "+v"(sb), "+v"(ca), "+v"(cb));
+#pragma unroll
+        for (int k = 0; k < NX; ++k) {
+            asm volatile("" : "+v"(x[k]));
+            if (tid + k * NT < TA * 18) sX[tid + k * NT] = xa + tid + k * NT < xe ? x[k] : RT(0);
+        }
+#pragma unroll
+        for (int k = 0; k < NY; ++k) {
+            asm volatile("" : "+v"(y[k]));
+            if (tid + k * NT < TB * 18) sY[tid + k * NT] = xb + tid + k * NT < xe ? y[k] : RT(0);
+        }
+        const bool ina = ka < 3 * nt, inb = kb < 3 * nt;
+        if (tid < TB * 3) {
+            (&sN[0][0])[tid] = inb ? nb : RT(0);
+            (&sVb[0][0])[tid] = inb ? vb : -1;
+            if constexpr (F32) (&sCb[0][0])[tid] = inb ? cb : 0.0;
+            sIb[tid] = ib;
+            sSb[tid] = sb;
+        }
+        if (tid < TA * 3) {
+            (&sVa[0][0])[tid] = ina ? va : -2;
+            if constexpr (F32) (&sCa[0][0])[tid] = ina ? ca : 0.0;
+            if constexpr (SYM) (&sNa[0][0])[tid] = ina ? na : RT(0);
+        }
+        if (tid < TA) sAa[tid] = bA * TA + tid < nt ? aa : 0.0;
+        if (tid < TB) sAb[tid] = bB * TB + tid < nt ? ab : 0.0;
     }
     __syncthreads();
 
     // this thread's pair (target tl, source sl)
     const int tl = tid / TB, sl = tid % TB;
+    // (FP32: every read at once; FP64: one after the other, for its registers)
     bool live = sVa[tl][0] >= 0 && sVb[sl][0] >= 0;
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int b = 0; b < 3; ++b) live = live && sVa[tl][a] != sVb[sl][b];
+        for (int b = 0; b < 3; ++b) {
+            if constexpr (F32) live &= sVa[tl][a] != sVb[sl][b];
+            else live = live && sVa[tl][a] != sVb[sl][b];
+        }
     if (SYM && bA == bB && sl <= tl) live = false; // the mirror pair carries it
     RT c0 = RT(0), c1 = RT(0), c2 = RT(0); // FP32: target frame relative to the source centroid
     if constexpr (F32) {
@@ -508,29 +476,16 @@ __global__ void __launch_bounds__(TA * TB) __attribute__((amdgpu_waves_per_eu(si
         }
     };
 
-    // FP32: the stored entries this thread adds to in the fold's last stage
-    // (row vA[ia], column vB[jb] of V', K' and, square tiles, T; the fold's
-    // thread map), read now so that their latency hides behind the
-    // quadrature.  No other workgroup of the launch touches them.
-    MT pre[fold_pf<MT>() > 0 ? fold_pf<MT>() : 1][3];
+    const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // SLOT: rows are the block's own local vertices
+    FoldOut<MT> out{U, T, offV, ld, ldT, sV, sK};
     if constexpr (SLOT) {
-        for (auto &q : pre) q[0] = q[1] = q[2] = MT(0);
-    } else if constexpr (F32) {
-        const int jb = tid % nB, r0 = tid / nB, rstep = NT / nB;
-        if (r0 < rstep) {
-            const int64_t col = sIb[jb];
-#pragma unroll
-            for (int k = 0; k < fold_pf<MT>(); ++k) {
-                const int ia = r0 + k * rstep;
-                if (ia < nA) {
-                    const int64_t row = sIa[ia];
-                    pre[k][0] = U[row * ld + nv + col];
-                    pre[k][1] = U[row * ld + col];
-                    if constexpr (SYM) pre[k][2] = T[row * nv + col];
-                }
-            }
-        }
+        out.U += pA * ld;
+        out.T += pA * ldT;
     }
+    MT pre[fold_rnd<MT>()];
+    if constexpr (F32)
+        fold_read<SLOT, NW>(w, nA, A_vid + pA, fold_lane<TA, TB, 0, NPL>(lane, nB, sIb, sSb, out), pre);
 
     // the pair's 3x3 blocks, summed over its 36 quadrature pairs; the first
     // target point assigns them
@@ -562,41 +517,25 @@ __global__ void __launch_bounds__(TA * TB) __attribute__((amdgpu_waves_per_eu(si
 #pragma unroll 1
     for (int p = 1; p < 6; ++p) accumulate(std::false_type{}, p);
 
-    if constexpr (F32) {
-        float blk[2][9], bmt[1][9];
+    RT vk[NPL][9];
 #pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            blk[0][k] = Vl[k];
-            blk[1][k] = Kl[k];
-            bmt[0][k] = Ktl[SYM ? k : 0];
-        }
-        const FoldMap<MS> fm = fold_map<NT, MS>(tid, nB, sSb, TB * 3);
-        fold_tile_f32<TA, TB, MS, SLOT, false>(tid, tl, sl, nA, fm, sSa, acc, blk, sIa, sIb, U, ld, offV, sV, sK, pre);
-        if constexpr (SYM) {
-            __syncthreads();
-            fold_tile_f32<TA, TB, MS, SLOT, true>(tid, tl, sl, nA, fm, sSa, acc, bmt, sIa, sIb, T, ldT, 0, sK, 0.0, pre);
-        }
-    } else {
-        // FP64: the stored entries are read after the quadrature, whose registers are free by now
-        const int jb = tid % nB, r0 = tid / nB, rstep = NT / nB;
-        if (!SLOT && r0 < rstep) {
-            const int64_t col = sIb[jb];
+    for (int k = 0; k < 9; ++k) {
+        vk[0][k] = Vl[k];
+        vk[1][k] = Kl[k];
+        if constexpr (NPL == 3) vk[NPL - 1][k] = Ktl[k];
+    }
+    const int pa = A_cpos[bA * TA + tl], pb = B_cpos[bB * TB + sl];
+    const int32_t *segA = A_seg + pA, *vA = A_vid + pA, *segB = B_seg + pB;
+    __syncthreads();
+    if constexpr (!F32) fold_read<SLOT, NW>(w, nA, vA, fold_lane<TA, TB, 0, NPL>(lane, nB, sIb, sSb, out), pre);
+    fold_tile<SLOT, TA, TB, 0, NPL>(tid, nA, nB, segA, vA, segB, sIb, sSb, pa, pb, sh.acc, vk, out, pre);
+    if constexpr (SYM && !F32) {
+        RT kt[1][9];
 #pragma unroll
-            for (int k = 0; k < fold_pf<MT>(); ++k) {
-                const int ia = r0 + k * rstep;
-                if (ia < nA) {
-                    const int64_t row = sIa[ia];
-                    pre[k][0] = U[row * ld + nv + col];
-                    pre[k][1] = U[row * ld + col];
-                    if constexpr (SYM) pre[k][2] = T[row * nv + col];
-                }
-            }
-        }
-        const FoldMap<MS> fm = fold_map<NT, MS>(tid, nB, sSb, TB * 3);
-        fold_tile_one<TA, TB, MS, SLOT, 0>(tid, tl, sl, nA, fm, sSa, acc[0], Vl, sIa, sIb, U, ld, offV, sV, pre);
-        fold_tile_one<TA, TB, MS, SLOT, 1>(tid, tl, sl, nA, fm, sSa, acc[0], Kl, sIa, sIb, U, ld, 0, sK, pre);
-        if constexpr (SYM)
-            fold_tile_one<TA, TB, MS, SLOT, 2>(tid, tl, sl, nA, fm, sSa, acc[0], Ktl, sIa, sIb, T, ldT, 0, sK, pre);
+        for (int k = 0; k < 9; ++k) kt[0][k] = Ktl[k];
+        fold_read<SLOT, NW>(w, nA, vA, fold_lane<TA, TB, 2, 1>(lane, nB, sIb, sSb, out), pre);
+        __syncthreads();
+        fold_tile<SLOT, TA, TB, 2, 1>(tid, nA, nB, segA, vA, segB, sIb, sSb, pa, pb, sh.acc, kt, out, pre);
     }
 }
 
@@ -1359,7 +1298,8 @@ static const BlockSideDev &device_side(Problem &p, int w, int bs, hipStream_t s)
     D.S = H.S;
     D.pref = A.upload(H.pref, s);
     D.nvb = A.upload(H.nvb, s);
-    D.slots = A.upload(H.slots, s);
+    D.seg = A.upload(H.seg, s);
+    D.cpos = A.upload(H.cpos, s);
     D.vid = A.upload(H.vid, s);
     // the blocks of each colour, then every block in order (the tuner's lists)
     std::vector<int32_t> lists(H.col_blk);
@@ -1383,24 +1323,23 @@ struct RegArgs {
     int64_t ld = 0, nv = 0;
     double sV = 0.0, sK = 0.0;
     double kappa = 0.0;
-    int ms = MAXS; // largest corner count of a vertex in a block, both sides
     QRule6 R;
     QRule6F RF;
 };
 
 // square shapes evaluate each unordered pair once (SYM)
 template <int TA, int TB> constexpr bool shape_sym() { return TA == TB; }
-template <int TA, int TB, int MS, bool SLOT = false>
-static void launch_regular_ms(bool yuk, bool f32, const RegArgs &a, hipStream_t s)
+template <int TA, int TB, bool SLOT = false>
+static void launch_regular_t(bool yuk, bool f32, const RegArgs &a, hipStream_t s)
 {
     if (a.nA == 0 || a.nB == 0) return;
     const dim3 grid(unsigned(a.nB), unsigned(a.nA));
     constexpr bool SYM = shape_sym<TA, TB>();
 #define PB_REG(Y, RT)                                                                                              \
-    hipLaunchKernelGGL((k_bem_regular<Y, RT, RT, TA, TB, MS, SYM, SLOT>), grid, dim3(TA * TB), 0, s, a.nt, a.m_tri, \
+    hipLaunchKernelGGL((k_bem_regular<Y, RT, RT, TA, TB, SYM, SLOT>), grid, dim3(TA * TB), 0, s, a.nt, a.m_tri,     \
                        static_cast<const RT *>(a.xq), static_cast<const RT *>(a.nq), a.cen, a.m_area, a.A.pref,     \
-                       a.A.nvb, a.A.slots, a.A.vid, a.B.pref, a.B.nvb, a.B.slots, a.B.vid, a.listA, a.listB,        \
-                       a.skip_lower, static_cast<RT *>(a.U), static_cast<RT *>(a.T), a.ld, a.nv, a.sV, a.sK,        \
+                       a.A.nvb, a.A.seg, a.A.vid, a.A.cpos, a.B.pref, a.B.nvb, a.B.seg, a.B.vid, a.B.cpos, a.listA, \
+                       a.listB, a.skip_lower, static_cast<RT *>(a.U), static_cast<RT *>(a.T), a.ld, a.nv, a.sV, a.sK,        \
                        a.kappa, a.R, a.RF)
     if (f32) {
         if (yuk) PB_REG(true, float);
@@ -1411,13 +1350,6 @@ static void launch_regular_ms(bool yuk, bool f32, const RegArgs &a, hipStream_t 
     }
 #undef PB_REG
 }
-template <int TA, int TB> static void launch_regular_t(bool yuk, bool f32, const RegArgs &a, hipStream_t s)
-{
-    if (a.ms <= 6) launch_regular_ms<TA, TB, 6>(yuk, f32, a, s);
-    else if (a.ms <= 12) launch_regular_ms<TA, TB, 12>(yuk, f32, a, s);
-    else launch_regular_ms<TA, TB, MAXS>(yuk, f32, a, s);
-}
-
 static_assert(N_TILE_SHAPES == 5, "one launch case per candidate tile shape");
 static void launch_regular(int shape, bool yuk, bool f32, const RegArgs &a, hipStream_t s)
 {
@@ -1480,9 +1412,7 @@ static void launch_slots(bool yuk, bool f32, RegArgs a, hipStream_t s)
     a.listA = a.listB = a.A.col_blk + a.A.nb; // every block in order
     a.nA = a.nB = a.A.nb;
     a.skip_lower = 1;
-    if (a.ms <= 6) launch_regular_ms<TA, TA, 6, true>(yuk, f32, a, s);
-    else if (a.ms <= 12) launch_regular_ms<TA, TA, 12, true>(yuk, f32, a, s);
-    else launch_regular_ms<TA, TA, MAXS, true>(yuk, f32, a, s);
+    launch_regular_t<TA, TA, true>(yuk, f32, a, s);
 }
 
 // cache key of the tuned shape: precision, kernel and size class (floor log2 of the triangle count)
@@ -1522,7 +1452,6 @@ static int tile_tune(Problem &p, int w, RegArgs a, bool yuk, bool f32, hipStream
         const BlockSide &HA = block_side(T, TILE_SHAPES[k].ta), &HB = block_side(T, TILE_SHAPES[k].tb);
         a.A = device_side(p, w, HA.bs, s);
         a.B = device_side(p, w, HB.bs, s);
-        a.ms = std::max(HA.ms_max, HB.ms_max);
         int64_t b0, b1;
         tune_range(HA, nsample, b0, b1);
         a.listA = a.A.col_blk + HA.nb + b0; // blocks b0 .. b1 - 1 of the in-order list
@@ -1746,7 +1675,6 @@ void ensure_bem(Problem &p, int w, hipStream_t s)
     const BlockSide &HA = block_side(T, TILE_SHAPES[shape].ta), &HB = block_side(T, TILE_SHAPES[shape].tb);
     ra.A = device_side(p, w, TILE_SHAPES[shape].ta, s);
     ra.B = device_side(p, w, TILE_SHAPES[shape].tb, s);
-    ra.ms = std::max(HA.ms_max, HB.ms_max);
     const bool sym = TILE_SHAPES[shape].ta == TILE_SHAPES[shape].tb;
     // every tile adds into the operator: start from zero (the row padding
     // past 2 nv, read by the dense apply against zero inputs, stays zero)

@@ -83,7 +83,7 @@ struct TileShape {
 };
 constexpr TileShape TILE_SHAPES[] = {{16, 32}, {8, 32}, {8, 64}, {16, 16}, {8, 16}};
 constexpr int N_TILE_SHAPES = int(sizeof(TILE_SHAPES) / sizeof(TILE_SHAPES[0]));
-constexpr int MAXS = 24; // slots per local vertex in a block (max triangles of a block at one vertex)
+constexpr int MAXS = 24; // corners of a local vertex in a block (max triangles of a block at one vertex)
 int tile_shape_index(int ta, int tb); // -1 if not a candidate
 constexpr int MAXRING = 64; // largest 1-ring (vertex and its neighbours) of the approximate inverse
 
@@ -92,17 +92,19 @@ constexpr int MAXRING = 64; // largest 1-ring (vertex and its neighbours) of the
 // local-vertex index and vertex count; per local vertex (block, k) its
 // operator index (vid: the surface vertex's position in the Morton vertex
 // order, the row / column of the stored operator; ascending within a block)
-// and the MAXS (triangle-in-block * 3 + corner) slots touching it (-1
-// padded); ms_max = the largest slot count of any vertex in any block.
+// and the corners of the block's triangles at it, side by side in an order of
+// the block's 3 bs corners: seg = first position | count << 8; per triangle of
+// every block (the last one's missing triangles included) cpos = the positions
+// of its corners, 8 bits each.
 // A greedy colouring of the blocks such that two blocks of one colour share
 // no vertex: col_blk[col_ptr[c] .. col_ptr[c + 1]) lists the blocks of
 // colour c, ascending.  Tiles whose target blocks share one colour and whose
 // source blocks share one colour touch disjoint operator entries, so such a
 // set of tiles can add into the operator in one launch without atomics.
 struct BlockSide {
-    int bs = 0, ms_max = 0;
+    int bs = 0;
     int64_t nb = 0, S = 0;
-    std::vector<int32_t> pref, nvb, slots, vid;
+    std::vector<int32_t> pref, nvb, seg, cpos, vid;
     int ncolor = 0;
     std::vector<int32_t> col_ptr, col_blk;
     // operator index -> its local vertices (position pref[b] + k and block b of
@@ -112,7 +114,7 @@ struct BlockSide {
 struct BlockSideDev {
     int bs = 0;
     int64_t nb = 0, S = 0;
-    int32_t *pref = nullptr, *nvb = nullptr, *slots = nullptr, *vid = nullptr;
+    int32_t *pref = nullptr, *nvb = nullptr, *seg = nullptr, *cpos = nullptr, *vid = nullptr;
     int32_t *col_blk = nullptr;
     int32_t *occ_ptr = nullptr, *occ = nullptr;
 };

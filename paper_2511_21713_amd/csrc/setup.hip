@@ -30,9 +30,8 @@ int tile_shape_index(int ta, int tb)
 }
 
 // Blocks of `bs` consecutive Morton-ordered triangles: their vertex lists
-// (ascending operator index), for every local vertex the (triangle-in-block
-// * 3 + corner) slots that touch it, and a colouring of the blocks in which
-// blocks of one colour share no vertex.
+// (ascending operator index), the corners at every local vertex, and a
+// colouring of the blocks in which blocks of one colour share no vertex.
 const BlockSide &block_side(SurfaceTopo &S, int bs)
 {
     auto found = S.sides.find(bs);
@@ -59,26 +58,35 @@ const BlockSide &block_side(SurfaceTopo &S, int bs)
     }
     B.S = B.pref[B.nb];
     B.vid.resize(B.S);
-    B.slots.assign(B.S * MAXS, -1);
+    B.seg.assign(B.S, 0);
+    B.cpos.assign(B.nb * bs, 0);
     std::vector<std::vector<int32_t>> vblocks(S.nv); // blocks of each operator index
     for (int64_t b = 0; b < B.nb; ++b) {
         const auto &vs = blk_verts[b];
         std::copy(vs.begin(), vs.end(), B.vid.begin() + B.pref[b]);
-        std::vector<int> fill(vs.size(), 0);
+        // corners counted per vertex, then placed in ascending order
+        std::vector<int32_t> cnt(vs.size(), 0), li(3 * bs, -1);
         for (int k = 0; k < bs; ++k) {
             int64_t m = b * bs + k;
             if (m >= S.nt) break;
             int32_t t = S.morton[m];
             for (int a = 0; a < 3; ++a) {
                 int32_t v = S.minv[S.tri[3 * t + a]];
-                int32_t li = int32_t(std::lower_bound(vs.begin(), vs.end(), v) - vs.begin());
-                PB_CHECK(fill[li] < MAXS, PBFB_EMESH,
+                li[3 * k + a] = int32_t(std::lower_bound(vs.begin(), vs.end(), v) - vs.begin());
+                PB_CHECK(cnt[li[3 * k + a]] < MAXS, PBFB_EMESH,
                          "a surface vertex has more than " + std::to_string(MAXS) + " triangles");
-                B.slots[(int64_t(B.pref[b]) + li) * MAXS + fill[li]++] = k * 3 + a;
+                ++cnt[li[3 * k + a]];
             }
         }
+        std::vector<int32_t> at(vs.size());
+        int32_t next = 0;
+        for (size_t i = 0; i < vs.size(); ++i) {
+            B.seg[B.pref[b] + i] = next | cnt[i] << 8;
+            at[i] = next;
+            next += cnt[i];
+        }
+        for (int c = 0; c < 3 * bs; ++c) B.cpos[b * bs + c / 3] |= (li[c] < 0 ? next++ : at[li[c]]++) << 8 * (c % 3);
         for (int32_t v : vs) vblocks[v].push_back(int32_t(b));
-        for (int f : fill) B.ms_max = std::max(B.ms_max, f);
     }
     B.occ_ptr.assign(S.nv + 1, 0);
     for (int32_t v : B.vid) B.occ_ptr[v + 1]++;
