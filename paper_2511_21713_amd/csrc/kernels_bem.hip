@@ -111,10 +111,10 @@ template <typename MT> __device__ inline void add_entry(MT *__restrict__ U, int6
 // column) took a third of the tiles' vector instructions (1 324 per wavefront
 // in FP32, now 1 050), and operator entries and inputs read under conditions
 // or in loops, each with a wait of its own, most of the waiting.  Per surface
-// (mean of Laplace and Yukawa): 10 242 vertices FP64 18.3 -> 17.3 ms, FP32
+// (mean of Laplace and Yukawa): 10 242 vertices FP64 18.3 -> 16.2 ms, FP32
 // 10.5 -> 8.8, 40 962 vertices FP32 152.9 -> 133.3.  FP32 tiles are now bound
-// by vector issue (86 % busy), FP64 ones by that (55 to 70 %) and LDS bank
-// conflicts of the first store into the planes.
+// by vector issue (86 % busy), FP64 ones by that (56 % Laplace, 74 % Yukawa)
+// and by what four wavefronts per SIMD leave waiting.
 //
 // Operator entries: plane V to U + offV, plane K to U, the mirrored K to T.
 template <typename MT> struct FoldOut {
@@ -124,6 +124,11 @@ template <typename MT> struct FoldOut {
 };
 template <int TB> constexpr int fold_rs() { return TB * 3 + 1; } // row stride, odd
 template <int TA, int TB> constexpr int fold_ps() { return TA * 3 * fold_rs<TB>(); }
+// FP64 V and K alternate, so that a pair of values moves at once: the first
+// store's columns, in no order, collide less (LDS conflicts 598 -> 172 cycles
+// per wavefront, 10 242 vertices 17.2 -> 16.2 ms).  FP32, three planes and
+// bound by vector issue, has them one after the other.
+template <int NP, typename ST> constexpr bool fold_pairs() { return NP == 2 && sizeof(ST) == 8; }
 
 // lane t of the second pass over NP planes from plane FIRST (0: V, 1: K, 2: mirrored K)
 template <typename MT> struct FoldLane {
@@ -133,7 +138,7 @@ template <typename MT> struct FoldLane {
     int col;
     bool on;
 };
-template <int TA, int TB, int FIRST, int NP, typename MT>
+template <int TA, int TB, int FIRST, int NP, typename ST, typename MT>
 __device__ inline FoldLane<MT> fold_lane(int t, int nB, const int *sIb, const int *sSb, const FoldOut<MT> &o)
 {
     int q = 0, jb = t;
@@ -146,7 +151,7 @@ __device__ inline FoldLane<MT> fold_lane(int t, int nB, const int *sIb, const in
     FoldLane<MT> L;
     L.on = jb < nB;
     if (!L.on) jb = 0;
-    L.col = q * fold_ps<TA, TB>() + (sSb[jb] & 255);
+    L.col = fold_pairs<NP, ST>() ? 2 * (sSb[jb] & 255) + q : q * fold_ps<TA, TB>() + (sSb[jb] & 255);
     q += FIRST;
     L.at = (q == 2 ? o.T : o.U) + (q == 0 ? o.offV : 0) + sIb[jb];
     L.stride = q == 2 ? o.ldT : o.ld;
@@ -208,14 +213,23 @@ __device__ inline void fold_tile(int tid, int nA, int nB, const int32_t *__restr
 {
     constexpr int RND = fold_rnd<MT>();
     constexpr int NW = TA * TB / 64, RS = fold_rs<TB>(), PS = fold_ps<TA, TB>();
+    constexpr bool PAIRS = fold_pairs<NP, ST>();
+    constexpr int NV = PAIRS ? 1 : NP, UN = PAIRS ? 2 : 1; // vectors of UN values
+    typedef ST vec __attribute__((ext_vector_type(2)));
+    using V = std::conditional_t<PAIRS, vec, ST>;
+    V *const accv = reinterpret_cast<V *>(acc);
     const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
-            ST *q = acc + ((pa >> (8 * a)) & 255) * RS + ((pb >> (8 * b)) & 255);
+            V *q = accv + ((pa >> (8 * a)) & 255) * RS + ((pb >> (8 * b)) & 255);
+            if constexpr (PAIRS) {
+                *q = V{blk[0][3 * a + b], blk[1][3 * a + b]};
+            } else {
 #pragma unroll
-            for (int pl = 0; pl < NP; ++pl) q[pl * PS] = blk[pl][3 * a + b];
+                for (int pl = 0; pl < NP; ++pl) q[pl * PS] = blk[pl][3 * a + b];
+            }
         }
     __syncthreads();
     for (int j0 = w; j0 < nB; j0 += NW * RND) {
@@ -226,18 +240,18 @@ __device__ inline void fold_tile(int tid, int nA, int nB, const int32_t *__restr
         for (int k = 0; k < RND; ++k) {
             const int n = seg[k] >> 8;
             if (j0 + k * NW < nB && n > 1 && lane < TA * 3) {
-                ST *q = acc + lane * RS + (seg[k] & 255);
-                ST t[NP];
+                V *q = accv + lane * RS + (seg[k] & 255);
+                V t[NV];
 #pragma unroll
-                for (int pl = 0; pl < NP; ++pl) t[pl] = fold_sum<1>(q + pl * PS, n);
+                for (int pl = 0; pl < NV; ++pl) t[pl] = fold_sum<1>(q + pl * PS, n);
 #pragma unroll
-                for (int pl = 0; pl < NP; ++pl) q[pl * PS] = t[pl];
+                for (int pl = 0; pl < NV; ++pl) q[pl * PS] = t[pl];
             }
         }
     }
     __syncthreads();
     for (int t0 = 0; t0 < NP * nB; t0 += 64) {
-        const FoldLane<MT> L = fold_lane<TA, TB, FIRST, NP>(t0 + lane, nB, sIb, sSb, o);
+        const FoldLane<MT> L = fold_lane<TA, TB, FIRST, NP, ST>(t0 + lane, nB, sIb, sSb, o);
         for (int i0 = w; i0 < nA; i0 += NW * RND) {
             if (t0 > 0 || i0 > w) fold_read<SLOT, NW>(i0, nA, vA, L, pre);
             int seg[RND], v[RND];
@@ -250,7 +264,7 @@ __device__ inline void fold_tile(int tid, int nA, int nB, const int32_t *__restr
 #pragma unroll
             for (int k = 0; k < RND; ++k)
                 if (i0 + k * NW < nA) {
-                    t[k] = fold_sum<RS>(acc + L.col + (seg[k] & 255) * RS, seg[k] >> 8);
+                    t[k] = fold_sum<UN * RS>(acc + L.col + (seg[k] & 255) * (UN * RS), seg[k] >> 8);
                     if (L.on) L.at[int64_t(v[k]) * L.stride] = MT(double(pre[k]) + L.sc * double(t[k]));
                 }
         }
@@ -316,7 +330,7 @@ __global__ void __launch_bounds__(TA * TB) __attribute__((amdgpu_waves_per_eu(si
         int Va[TA][3], Vb[TB][3];
     };
     constexpr int NPL = F32 && SYM ? 3 : 2, NW = NT / 64;
-    __shared__ union {
+    __shared__ union alignas(16) {
         In in;
         RT acc[NPL * fold_ps<TA, TB>()];
     } sh;
@@ -485,7 +499,7 @@ __global__ void __launch_bounds__(TA * TB) __attribute__((amdgpu_waves_per_eu(si
     }
     MT pre[fold_rnd<MT>()];
     if constexpr (F32)
-        fold_read<SLOT, NW>(w, nA, A_vid + pA, fold_lane<TA, TB, 0, NPL>(lane, nB, sIb, sSb, out), pre);
+        fold_read<SLOT, NW>(w, nA, A_vid + pA, fold_lane<TA, TB, 0, NPL, RT>(lane, nB, sIb, sSb, out), pre);
 
     // the pair's 3x3 blocks, summed over its 36 quadrature pairs; the first
     // target point assigns them
@@ -527,13 +541,13 @@ __global__ void __launch_bounds__(TA * TB) __attribute__((amdgpu_waves_per_eu(si
     const int pa = A_cpos[bA * TA + tl], pb = B_cpos[bB * TB + sl];
     const int32_t *segA = A_seg + pA, *vA = A_vid + pA, *segB = B_seg + pB;
     __syncthreads();
-    if constexpr (!F32) fold_read<SLOT, NW>(w, nA, vA, fold_lane<TA, TB, 0, NPL>(lane, nB, sIb, sSb, out), pre);
+    if constexpr (!F32) fold_read<SLOT, NW>(w, nA, vA, fold_lane<TA, TB, 0, NPL, RT>(lane, nB, sIb, sSb, out), pre);
     fold_tile<SLOT, TA, TB, 0, NPL>(tid, nA, nB, segA, vA, segB, sIb, sSb, pa, pb, sh.acc, vk, out, pre);
     if constexpr (SYM && !F32) {
         RT kt[1][9];
 #pragma unroll
         for (int k = 0; k < 9; ++k) kt[0][k] = Ktl[k];
-        fold_read<SLOT, NW>(w, nA, vA, fold_lane<TA, TB, 2, 1>(lane, nB, sIb, sSb, out), pre);
+        fold_read<SLOT, NW>(w, nA, vA, fold_lane<TA, TB, 2, 1, RT>(lane, nB, sIb, sSb, out), pre);
         __syncthreads();
         fold_tile<SLOT, TA, TB, 2, 1>(tid, nA, nB, segA, vA, segB, sIb, sSb, pa, pb, sh.acc, kt, out, pre);
     }
