@@ -32,16 +32,17 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 
-# HBM bytes per dense apply (k_bgemv + k_bgemv_fin, both interfaces) at the
+# HBM bytes per dense apply (k_bgemv, and the second stage measured while it
+# was a launch of its own; both interfaces) at the
 # 80k-triangle size from two rocprofv3 --pmc runs (FETCH_SIZE x 2: the
 # counter reads 0.5 x the bytes of a plain device copy; WRITE_SIZE x 1), valid
 # for the row routines whose source hash is recorded with them; see
 # profiles/gemv_rna80k_hbm_counters.md.
 GEMV_TRAFFIC = {
-    "rna80k_f32": {"src_sha256_16": "9066d2ee5bfca69e",
-                   "bytes": 9868269.03 * 2048 + 207677.50 * 1024 + 157896.09 * 2048 + 1235.06 * 1024},
-    "rna80k_f64": {"src_sha256_16": "9066d2ee5bfca69e",
-                   "bytes": 19708630.60 * 2048 + 210751.00 * 1024 + 157896.09 * 2048 + 1235.06 * 1024},
+    "rna80k_f32": {"src_sha256_16": "63b4d5ac2bbe4a09",
+                   "bytes": 9868495.89 * 2048 + 207680.13 * 1024 + 157896.09 * 2048 + 1235.06 * 1024},
+    "rna80k_f64": {"src_sha256_16": "63b4d5ac2bbe4a09",
+                   "bytes": 19708652.32 * 2048 + 210785.92 * 1024 + 157896.09 * 2048 + 1235.06 * 1024},
 }
 
 
@@ -517,7 +518,7 @@ def main():
     nn = prob.nodes.shape[0]
     flops = apply_flops(nm, ns, nnz)
     sym_tiles = all(a == b for a, b in f64["tiles"].values())
-    kname = ("k_bgemv + k_bgemv_fin / k_gemv + k_gemv_fin (gemv_rows_symK / gemv_rows_symV work items: K' and "
+    kname = ("k_bgemv / k_gemv and their second stage (gemv_rows_symK / gemv_rows_symV work items: K' and "
              f"the lower triangle of V', {'FP32' if elem == 4 else 'FP64'} storage, FP64 accumulation, both "
              "interfaces)" if sym else
              f"k_bgemv / k_gemv (gemv_rows: dense [K'|V'] {'FP32' if elem == 4 else 'FP64'} GEMV, both interfaces)")
@@ -593,7 +594,7 @@ def main():
         ms, cnt = leg["timing"]["spmv"]
         b = spmv_bytes(nnz, nn, leg["n"], e)
         gbs = b / (ms * 1e-3) / 1e9 if ms else None
-        return {"kernel": "k_bspmv / k_spmv (sell_part: sliced-ELL FEM rows)", "bound": "hbm",
+        return {"kernel": "k_btail / k_rest (sell_part: sliced-ELL FEM rows)", "bound": "hbm",
                 "bytes_per_launch": b, "working_set_bytes": b, "ms_per_launch": ms, "launches": cnt,
                 "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS if gbs else None,
                 "nnz": nnz, "value_bytes": e,
