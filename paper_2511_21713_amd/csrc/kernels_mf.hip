@@ -70,8 +70,10 @@ __global__ void k_mf_src(int64_t nt, int64_t nv, const int32_t *__restrict__ m_t
 // s = 16 w .. 16 w + 15, in which lane i meets source triangle (i + s) mod 64
 // of block b, read from LDS.  In one step the lanes of a wavefront meet 64
 // different source triangles, so what they add to the sources' potentials
-// (one LDS array per wavefront) never collides; targets accumulate in
-// registers.  Both are added over the wavefronts in a fixed order at the end.
+// (one LDS array per wavefront) never collides within a step; the next step
+// moves every source on to the next lane, so a wavefront fence separates the
+// steps.  Targets accumulate in registers.  Both are added over the wavefronts
+// in a fixed order at the end.
 // fwd: slots [bl][al] of the targets (row length na), rev: slots [al][bl] of
 // the sources (row length nb); a diagonal tile meets every ordered pair as a
 // target and leaves no reverse slot.
@@ -173,66 +175,72 @@ __global__ void __launch_bounds__(64 * MF_W, sizeof(RT) == 8 ? 3 : 4)
         bool skip = !inA || u0 < 0;
         skip |= (v0 == u0) | (v0 == u1) | (v0 == u2) | (v1 == u0) | (v1 == u1) | (v1 == u2) | (v2 == u0) |
                 (v2 == u1) | (v2 == u2);
-        if (skip) continue;
-        RT c0 = 0, c1 = 0, c2 = 0; // FP32: target centroid relative to the source's
-        if constexpr (F32) {
-            c0 = float(g0 - sC[0][j]);
-            c1 = float(g1 - sC[1][j]);
-            c2 = float(g2 - sC[2][j]);
-        }
-        RT av[6], ak[6]; // the target points' sums (av: FP32 only)
+        if (!skip) {
+            RT c0 = 0, c1 = 0, c2 = 0; // FP32: target centroid relative to the source's
+            if constexpr (F32) {
+                c0 = float(g0 - sC[0][j]);
+                c1 = float(g1 - sC[1][j]);
+                c2 = float(g2 - sC[2][j]);
+            }
+            RT av[6], ak[6]; // the target points' sums (av: FP32 only)
 #pragma unroll
-        for (int p = 0; p < 6; ++p) av[p] = ak[p] = RT(0);
+            for (int p = 0; p < 6; ++p) av[p] = ak[p] = RT(0);
 #pragma unroll 1
-        for (int q = 0; q < 6; ++q) {
-            RT y0 = src[3 * q][j], y1 = src[3 * q + 1][j], y2 = src[3 * q + 2][j];
+            for (int q = 0; q < 6; ++q) {
+                RT y0 = src[3 * q][j], y1 = src[3 * q + 1][j], y2 = src[3 * q + 2][j];
+                if constexpr (F32) {
+                    y0 -= c0;
+                    y1 -= c1;
+                    y2 -= c2;
+                }
+                const RT ql = src[18 + q][j], qu = src[24 + q][j];
+                // (y_q - x).n_tau, the same for the six target points
+                const RT dm = (y0 - X[0]) * m0 + (y1 - X[1]) * m1 + (y2 - X[2]) * m2;
+                RT bv = RT(0), bk = RT(0);
+#pragma unroll
+                for (int p = 0; p < 6; ++p) {
+                    const RT d0 = X[3 * p] - y0, d1 = X[3 * p + 1] - y1, d2 = X[3 * p + 2] - y2;
+                    const RT r2 = d0 * d0 + d1 * d1 + d2 * d2;
+                    const RT ri = rsqrt_pos(r2);
+                    RT gv, hk; // single-layer kernel, double-layer kernel / normal distance
+                    if constexpr (YUK) {
+                        const RT r = r2 * ri;
+                        RT e;
+                        if constexpr (F32) e = __builtin_amdgcn_exp2f(kl2 * r);
+                        else e = exp_neg(kap * r);
+                        gv = e * ri;
+                        hk = gv * ri * (ri + kap); // e (1 + kappa r) / r^3
+                    } else {
+                        gv = ri;
+                        hk = ri * ri * ri;
+                    }
+                    if constexpr (F32) av[p] = fma(gv, ql, av[p]);
+                    else P[p] = fma(gv, ql, P[p]);
+                    ak[p] = fma(hk, qu, ak[p]);
+                    bv = fma(gv, tl[p], bv);
+                    bk = fma(hk, tu[p], bk);
+                }
+                acc[w][q][j] += double(fma(bk, dm, bv));
+            }
+            RT y0 = src[0][j], y1 = src[1][j], y2 = src[2][j];
             if constexpr (F32) {
                 y0 -= c0;
                 y1 -= c1;
                 y2 -= c2;
             }
-            const RT ql = src[18 + q][j], qu = src[24 + q][j];
-            // (y_q - x).n_tau, the same for the six target points
-            const RT dm = (y0 - X[0]) * m0 + (y1 - X[1]) * m1 + (y2 - X[2]) * m2;
-            RT bv = RT(0), bk = RT(0);
+            const RT n0 = src[30][j], n1 = src[31][j], n2 = src[32][j];
 #pragma unroll
             for (int p = 0; p < 6; ++p) {
-                const RT d0 = X[3 * p] - y0, d1 = X[3 * p + 1] - y1, d2 = X[3 * p + 2] - y2;
-                const RT r2 = d0 * d0 + d1 * d1 + d2 * d2;
-                const RT ri = rsqrt_pos(r2);
-                RT gv, hk; // single-layer kernel, double-layer kernel / normal distance
-                if constexpr (YUK) {
-                    const RT r = r2 * ri;
-                    RT e;
-                    if constexpr (F32) e = __builtin_amdgcn_exp2f(kl2 * r);
-                    else e = exp_neg(kap * r);
-                    gv = e * ri;
-                    hk = gv * ri * (ri + kap); // e (1 + kappa r) / r^3
-                } else {
-                    gv = ri;
-                    hk = ri * ri * ri;
-                }
-                if constexpr (F32) av[p] = fma(gv, ql, av[p]);
-                else P[p] = fma(gv, ql, P[p]);
-                ak[p] = fma(hk, qu, ak[p]);
-                bv = fma(gv, tl[p], bv);
-                bk = fma(hk, tu[p], bk);
+                const RT dn = (X[3 * p] - y0) * n0 + (X[3 * p + 1] - y1) * n1 + (X[3 * p + 2] - y2) * n2;
+                if constexpr (F32) P[p] += double(fma(ak[p], dn, av[p]));
+                else P[p] = fma(ak[p], dn, P[p]);
             }
-            acc[w][q][j] += double(fma(bk, dm, bv));
         }
-        RT y0 = src[0][j], y1 = src[1][j], y2 = src[2][j];
-        if constexpr (F32) {
-            y0 -= c0;
-            y1 -= c1;
-            y2 -= c2;
-        }
-        const RT n0 = src[30][j], n1 = src[31][j], n2 = src[32][j];
-#pragma unroll
-        for (int p = 0; p < 6; ++p) {
-            const RT dn = (X[3 * p] - y0) * n0 + (X[3 * p + 1] - y1) * n1 + (X[3 * p + 2] - y2) * n2;
-            if constexpr (F32) P[p] += double(fma(ak[p], dn, av[p]));
-            else P[p] = fma(ak[p], dn, P[p]);
-        }
+        // lane i - 1 adds to this source next: no access to acc may cross the
+        // steps (a wavefront's LDS operations complete in order, so the fence
+        // binds the compiler only and costs no instruction)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
     __syncthreads(); // the sources are no longer read: their space takes the targets' sums
     double(*fw)[6][MF_T] = reinterpret_cast<double(*)[6][MF_T]>(raw);
