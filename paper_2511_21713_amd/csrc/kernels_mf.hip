@@ -12,8 +12,9 @@
 //      evaluated once and serves both directions (the double layers differ
 //      only in the normal distance, which is the same for the six points of
 //      one panel against a point of the other).  Sums over a triangle's six
-//      points in the evaluation precision, as in the dense assembly, sums
-//      over triangles in FP64; each block pair leaves the corner values
+//      points in the evaluation precision, as in the dense assembly, single
+//      and double layer apart; the two are added, and the sums over triangles
+//      formed, in FP64; each block pair leaves the corner values
 //      |tau| / (4 pi) sum_p w_p b_p[a] (potential at x_p) it contributes to
 //      either block in a slot of its own;
 //   3. k_mf_sum: the slots of each block added in a fixed order;
@@ -81,7 +82,7 @@ __global__ void k_mf_src(int64_t nt, int64_t nv, const int32_t *__restrict__ m_t
 // Bound by FP64 / FP32 vector issue (about 21 instruction slots per
 // quadrature pair and two directions for FP64 Laplace, 43 for Yukawa).
 // Whole products of both surfaces: 13.6 -> 5.5 ms (FP64, 11 520 triangles)
-// and 17.6 -> 7.9 ms (FP32 evaluation, 20 480 triangles) against one thread
+// and 17.6 -> 8.0 ms (FP32 evaluation, 20 480 triangles) against one thread
 // per target and source triangle that read the source from LDS at every
 // quadrature pair (five LDS reads a pair) and served one direction.
 //
@@ -220,7 +221,8 @@ __global__ void __launch_bounds__(64 * MF_W, sizeof(RT) == 8 ? 3 : 4)
                     bv = fma(gv, tl[p], bv);
                     bk = fma(hk, tu[p], bk);
                 }
-                acc[w][q][j] += double(fma(bk, dm, bv));
+                if constexpr (F32) acc[w][q][j] += double(bv) + double(bk * dm);
+                else acc[w][q][j] += fma(bk, dm, bv);
             }
             RT y0 = src[0][j], y1 = src[1][j], y2 = src[2][j];
             if constexpr (F32) {
@@ -232,7 +234,7 @@ __global__ void __launch_bounds__(64 * MF_W, sizeof(RT) == 8 ? 3 : 4)
 #pragma unroll
             for (int p = 0; p < 6; ++p) {
                 const RT dn = (X[3 * p] - y0) * n0 + (X[3 * p + 1] - y1) * n1 + (X[3 * p + 2] - y2) * n2;
-                if constexpr (F32) P[p] += double(fma(ak[p], dn, av[p]));
+                if constexpr (F32) P[p] += double(av[p]) + double(ak[p] * dn);
                 else P[p] = fma(ak[p], dn, P[p]);
             }
         }

@@ -134,3 +134,27 @@ def test_export_refused_in_matrix_free_mode(case):
     name, prob, o, g = case
     with pytest.raises(pb.PbfbError):
         g.export_bem(0)
+
+
+@pytest.mark.parametrize("n", [3, 8])
+def test_mixed_layers_are_added_in_fp64(ctx, n):
+    """FP32 evaluation sums a triangle pair's single and double layer in FP32,
+    each by itself, and adds the two in FP64: the surface rows of a product
+    are then those of its two layers alone, up to FP64 rounding of sums of a
+    few thousand terms (1e-12; added in FP32 first they differ by 1e-9)."""
+    import paper_2511_21713_amd as pb
+    prob = pbgen.make_problem(n=n, a=6.0, c=9.0, bump=True, t=3.0, L=2, helix=0, partials=0, kappa=0.2, seed=(9, n),
+                              center_charge=1.0)
+    g = pb.Problem.from_inputs(ctx, prob, precision=pb.MIXED)
+    g.set_bem_mode(pb.BEM_MATRIX_FREE)
+    rng = np.random.default_rng(n)
+    phi = np.zeros(g.n)
+    u, lam = rng.standard_normal(g.n), 0.1 * rng.standard_normal(g.n)
+    u[g.n_nodes:] = 0.0
+    lam[:g.n_nodes] = 0.0
+    both, yu, yl = (g.apply_jacobian(pb.LIN, phi, v)[g.n_nodes:] for v in (u + lam, u, lam))
+    for name, s in (("inner", slice(0, g.n_m)), ("outer", slice(g.n_m, None))):
+        e = np.linalg.norm(both[s] - (yu[s] + yl[s])) / (np.linalg.norm(yu[s]) + np.linalg.norm(yl[s]))
+        log(f"  n {n} {name}: {e:.2e}")
+        assert e < 1e-12
+    g.close()
