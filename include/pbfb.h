@@ -259,8 +259,8 @@ pbfb_status pbfb_server_submit(pbfb_server *s, pbfb_problem *p, const pbfb_solve
  * admission to completion) and setup (the context's assembly workspace the
  * request's setup needs; charged once per context, see above).  A budget of
  * at least steady + setup admits the request; one short of it by no more than
- * a small surface's assembly planes does too, and assembles without them
- * (results equal to rounding). */
+ * a small surface's assembly planes does too, and assembles without them (the
+ * same results bit for bit). */
 pbfb_status pbfb_request_footprint(const pbfb_problem *p, const pbfb_solve_opts *o, size_t *steady_bytes,
                                    size_t *setup_bytes);
 /* done = 1 once the request finished; res (nullable) then receives its result */

@@ -320,7 +320,9 @@ __global__ void __launch_bounds__(TA * TB) __attribute__((amdgpu_waves_per_eu(si
     constexpr bool F32 = sizeof(RT) == 4;
     constexpr int NT = TA * TB;
     const int64_t bA = listA[blockIdx.y], bB = listB[blockIdx.x];
-    if (SYM && skip_lower && bB < bA) return; // evaluated as (bB, bA)
+    // evaluated as (bB, bA); SLOT: the lists are in the order of the colours,
+    // and the block of the lower one is the target, as in the colour pairs' launches
+    if (SYM && skip_lower && (SLOT ? blockIdx.x < blockIdx.y : bB < bA)) return;
     // quadrature inputs, then in the same memory the planes of the fold: FP32
     // all of them, FP64 V and K, then the mirrored K (four workgroups per CU)
     struct In {
@@ -664,12 +666,16 @@ __global__ void __launch_bounds__(256) k_bem_symm2(int64_t nv, int64_t ld, MT *_
 
 // Small surfaces (launch_slots): one launch holds every tile, each storing its
 // folded values to its own entries of three S x S planes over the blocks'
-// local vertices (K, V, mirrored K; block pairs A <= B only), and this adds up
-// the operator's entries, both of a pair (k, l) by one thread: over the local
-// vertices a of k and b of l, V'(k, l) = V'(l, k) takes V(a, b) where block(a)
-// <= block(b) and V(b, a) where block(b) <= block(a), K'(k, l) K(a, b) and
-// T(b, a), K'(l, k) T(a, b) and K(b, a).  Two launches instead of one per
-// colour pair (28 to 36, 12-15 us each however few tiles they hold), the
+// local vertices (K, V, mirrored K; block pairs A <= B in the order of the
+// colours only), and this adds up the operator's entries, both of a pair
+// (k, l) by one thread: over the local vertices a of k and b of l with
+// block(a) <= block(b), U(k, l) takes what the tile left at (a, b), and the
+// completion follows, V'(k, l) = U_V(k, l) + U_V(l, k), K'(k, l) = U_K(k, l) +
+// T(l, k).  A vertex's blocks are all of different colours, so walking them in
+// that order adds the tiles as the colour pairs' launches do, and every sum is
+// rounded to the storage as theirs: the two ways give the same bits, and which
+// one is taken may depend on the memory there is.  Two launches instead of one
+// per colour pair (28 to 36, 12-15 us each however few tiles they hold), the
 // completion and the clears: a 642-vertex surface 0.50 -> 0.116 ms (FP64),
 // 0.40 -> 0.074 (FP32); a 320-triangle solve 5.9 -> 5.0 ms, 1 280 triangles
 // mixed 14.5 -> 13.7.
@@ -683,25 +689,23 @@ __global__ void __launch_bounds__(256)
         for (int64_t c = 2 * nv + threadIdx.x; c < ld; c += 256) B[k * ld + c] = MT(0);
     if (l < k || l >= nv) return;
     const MT *K = W, *V = W + S * S, *T = W + 2 * S * S;
-    double v = 0.0, k1 = 0.0, k2 = 0.0;
-    for (int32_t i = occ_ptr[k]; i < occ_ptr[k + 1]; ++i)
-        for (int32_t j = occ_ptr[l]; j < occ_ptr[l + 1]; ++j) {
-            const int64_t a = occ[2 * i], b = occ[2 * j];
-            const int32_t ba = occ[2 * i + 1], bb = occ[2 * j + 1];
-            if (ba <= bb) {
-                v += double(V[a * S + b]);
-                k1 += double(K[a * S + b]);
-                k2 += double(T[a * S + b]);
+    auto tiles = [&](int64_t r, int64_t c, MT (&u)[3]) { // U_V, U_K and T at (r, c)
+        u[0] = u[1] = u[2] = MT(0);
+        for (int32_t i = occ_ptr[r]; i < occ_ptr[r + 1]; ++i)
+            for (int32_t j = occ_ptr[c]; j < occ_ptr[c + 1]; ++j) {
+                if (occ[2 * i + 1] > occ[2 * j + 1]) continue;
+                const int64_t at = occ[2 * i] * S + occ[2 * j];
+                u[0] = MT(double(u[0]) + double(V[at]));
+                u[1] = MT(double(u[1]) + double(K[at]));
+                u[2] = MT(double(u[2]) + double(T[at]));
             }
-            if (bb <= ba) {
-                v += double(V[b * S + a]);
-                k2 += double(K[b * S + a]);
-                k1 += double(T[b * S + a]);
-            }
-        }
-    B[k * ld + nv + l] = B[l * ld + nv + k] = MT(v);
-    B[k * ld + l] = MT(k1);
-    if (l != k) B[l * ld + k] = MT(k2);
+    };
+    MT u[3], w[3];
+    tiles(k, l, u);
+    tiles(l, k, w);
+    B[k * ld + nv + l] = B[l * ld + nv + k] = MT(double(u[0]) + double(w[0]));
+    B[k * ld + l] = MT(double(u[1]) + double(w[2]));
+    if (l != k) B[l * ld + k] = MT(double(w[1]) + double(u[2]));
 }
 
 // ---------------------------------------------------------------------------
@@ -1409,7 +1413,7 @@ static void launch_all_tiles(int shape, bool yuk, bool f32, RegArgs a, const Blo
 // charges them to the request.
 constexpr size_t SLOT_BYTES = size_t(192) << 20;
 constexpr int SLOT_SHAPE = 3;
-static_assert(TILE_SHAPES[SLOT_SHAPE].ta == 16 && TILE_SHAPES[SLOT_SHAPE].tb == 16, "the symmetric 16 x 16 shape");
+static_assert(TILE_SHAPES[SLOT_SHAPE].ta == SLOT_BS && TILE_SHAPES[SLOT_SHAPE].tb == SLOT_BS, "the symmetric 16 x 16 shape");
 static size_t slot_bytes(const BlockSide &H, size_t elem) { return 3 * size_t(H.S) * size_t(H.S) * elem; }
 size_t slot_bytes_bound(int64_t nv, size_t elem)
 {
@@ -1421,12 +1425,11 @@ size_t slot_bytes_bound(int64_t nv, size_t elem)
 }
 static void launch_slots(bool yuk, bool f32, RegArgs a, hipStream_t s)
 {
-    constexpr int TA = TILE_SHAPES[SLOT_SHAPE].ta;
     a.ld = a.A.S;
-    a.listA = a.listB = a.A.col_blk + a.A.nb; // every block in order
+    a.listA = a.listB = a.A.col_blk; // every block, colour by colour
     a.nA = a.nB = a.A.nb;
     a.skip_lower = 1;
-    launch_regular_t<TA, TA, true>(yuk, f32, a, s);
+    launch_regular_t<SLOT_BS, SLOT_BS, true>(yuk, f32, a, s);
 }
 
 // cache key of the tuned shape: precision, kernel and size class (floor log2 of the triangle count)
@@ -1664,16 +1667,17 @@ void ensure_bem(Problem &p, int w, hipStream_t s)
     // square-tile assembly (nv x nv in the storage precision), vertex
     // coordinates and the touching-pair blocks
     // (or, through slots, the three planes over the local vertices)
-    const BlockSide &HS = block_side(T, TILE_SHAPES[SLOT_SHAPE].ta);
-    const bool slots = p.slots && slot_bytes(HS, elem) <= slot_bytes_bound(nv, elem) &&
+    const BlockSide &HS = block_side(T, SLOT_BS);
+    const bool small = slot_bytes(HS, elem) <= slot_bytes_bound(nv, elem) &&
                        (p.tile_fixed < 0 || p.tile_fixed == SLOT_SHAPE);
+    const bool slots = small && p.slots; // else the same shape by colour pairs
     const size_t tbytes = ((slots ? slot_bytes(HS, elem) : size_t(nv) * nv * elem) + 255) / 256 * 256;
     double *ws = wsp->doubles((tbytes + 8 * (3 * size_t(nv) + 18 * size_t(S.ntp))) / 8 + 1);
     void *Tm = ws;
     double *vx = reinterpret_cast<double *>(static_cast<char *>(Tm) + tbytes), *tpv = vx + 3 * nv;
     ra.T = Tm;
     // tile shape: forced, or tuned once per (precision, kernel, size class) and context
-    int shape = slots ? SLOT_SHAPE : p.tile_fixed;
+    int shape = small ? SLOT_SHAPE : p.tile_fixed;
     if (shape < 0) {
         const int key = tile_key(p.precision, yuk, T.nt);
         std::lock_guard<std::mutex> tl(p.ctx->tune_mu);

@@ -107,10 +107,12 @@ struct BlockSide {
     std::vector<int32_t> pref, nvb, seg, cpos, vid;
     int ncolor = 0;
     std::vector<int32_t> col_ptr, col_blk;
-    // operator index -> its local vertices (position pref[b] + k and block b of
-    // each, ascending): occ[2 i], occ[2 i + 1] for occ_ptr[v] <= i < occ_ptr[v + 1]
+    // SLOT_BS: operator index -> its local vertices, by the position r of their
+    // block b in col_blk (position pref[b] + k and r of each): occ[2 i],
+    // occ[2 i + 1] for occ_ptr[v] <= i < occ_ptr[v + 1]
     std::vector<int32_t> occ_ptr, occ;
 };
+constexpr int SLOT_BS = 16; // block size of the assembly through slots (k_bem_gather)
 struct BlockSideDev {
     int bs = 0;
     int64_t nb = 0, S = 0;

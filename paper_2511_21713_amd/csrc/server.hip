@@ -276,7 +276,7 @@ pbfb_status pbfb_server_submit(pbfb_server *sv, pbfb_problem *pp, const pbfb_sol
         size_t steady = 0, extra = 0;
         footprint_estimate(p, O.gmres_restart, true, &steady, &extra);
         // a budget without room for the planes of the slot assembly: colour
-        // pairs, which need the mirrored double layer only (equal to rounding)
+        // pairs, which need the mirrored double layer only (the same bits)
         const bool slots = steady + extra <= sv->s.budget;
         if (!slots) footprint_estimate(p, O.gmres_restart, false, &steady, &extra);
         PB_CHECK(steady + extra <= sv->s.budget, PBFB_ENOMEM, "request exceeds the server's HBM budget");

@@ -88,19 +88,6 @@ const BlockSide &block_side(SurfaceTopo &S, int bs)
         for (int c = 0; c < 3 * bs; ++c) B.cpos[b * bs + c / 3] |= (li[c] < 0 ? next++ : at[li[c]]++) << 8 * (c % 3);
         for (int32_t v : vs) vblocks[v].push_back(int32_t(b));
     }
-    B.occ_ptr.assign(S.nv + 1, 0);
-    for (int32_t v : B.vid) B.occ_ptr[v + 1]++;
-    for (int64_t v = 0; v < S.nv; ++v) B.occ_ptr[v + 1] += B.occ_ptr[v];
-    B.occ.resize(2 * B.S);
-    {
-        std::vector<int32_t> fill(B.occ_ptr.begin(), B.occ_ptr.end() - 1);
-        for (int64_t b = 0; b < B.nb; ++b)
-            for (int32_t k = B.pref[b]; k < B.pref[b + 1]; ++k) {
-                const int32_t i = fill[B.vid[k]]++;
-                B.occ[2 * i] = k;
-                B.occ[2 * i + 1] = int32_t(b);
-            }
-    }
     // greedy colouring in block order: the smallest colour no earlier block
     // sharing a vertex with this one has taken
     std::vector<int32_t> color(B.nb, -1);
@@ -126,6 +113,21 @@ const BlockSide &block_side(SurfaceTopo &S, int bs)
     {
         std::vector<int32_t> fill(B.col_ptr.begin(), B.col_ptr.end() - 1);
         for (int64_t b = 0; b < B.nb; ++b) B.col_blk[fill[color[b]]++] = int32_t(b);
+    }
+    if (bs == SLOT_BS) {
+        B.occ_ptr.assign(S.nv + 1, 0);
+        for (int32_t v : B.vid) B.occ_ptr[v + 1]++;
+        for (int64_t v = 0; v < S.nv; ++v) B.occ_ptr[v + 1] += B.occ_ptr[v];
+        B.occ.resize(2 * B.S);
+        std::vector<int32_t> fill(B.occ_ptr.begin(), B.occ_ptr.end() - 1);
+        for (int64_t r = 0; r < B.nb; ++r) {
+            const int32_t b = B.col_blk[r];
+            for (int32_t k = B.pref[b]; k < B.pref[b + 1]; ++k) {
+                const int32_t i = fill[B.vid[k]]++;
+                B.occ[2 * i] = k;
+                B.occ[2 * i + 1] = int32_t(r);
+            }
+        }
     }
     return S.sides.emplace(bs, std::move(B)).first->second;
 }

@@ -1,0 +1,91 @@
+"""The planes of a small surface's assembly (three square arrays over the
+local vertices of its 16-triangle blocks, instead of one launch per pair of
+block colours): memory that an assembly takes when there is room.  Whether
+there is changes neither a result nor what a server admits."""
+import time
+
+import numpy as np
+import pytest
+
+import pbgen
+from test_gpu_tiles import valence_problem
+
+pytestmark = pytest.mark.gpu
+
+MIB = 1 << 20
+TIGHT = dict(tol_nl=1e-10, tol_gr=1e-11, tol_gr0=1e-11, tol_omega=1e-9, l_e=0.0, max_gmres=20000)
+
+
+def bumpy(n):
+    return pbgen.make_problem(n=n, a=6.0, c=9.0, bump=n > 2, t=3.0, L=1, helix=0, partials=0, kappa=0.2, seed=(9, n),
+                              center_charge=1.0)
+
+
+def colour_pair_bytes(prob, elem):
+    """Assembly workspace without planes: the mirrored double layer, vertex
+    coordinates and touching-pair blocks of the larger surface."""
+    need = 0
+    for tri in (prob.tri_m, prob.tri_s):
+        nv = np.unique(tri).size
+        at = {}
+        for t, c in enumerate(tri):
+            for v in c:
+                at.setdefault(int(v), set()).add(t)
+        ntp = sum(len(set().union(*(at[int(v)] for v in c))) for c in tri)
+        need = max(need, -(-nv * nv * elem // 256) * 256 + 24 * nv + 144 * ntp + 64)
+    return need
+
+
+def drain(srv, tickets, seconds=60):
+    out, end = {}, time.time() + seconds
+    while len(out) < len(tickets) and time.time() < end:
+        for t in tickets:
+            if t not in out:
+                r = srv.poll(t)
+                if r is not None:
+                    out[t] = r
+        time.sleep(0.001)
+    assert len(out) == len(tickets)
+    return [out[t] for t in tickets]
+
+
+# 47 and 119 vertices: an odd count, where the FP32 completion of the colour
+# pairs moves single entries; 92 and 1 002: an even one
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("mesh", ["odd47", "odd119", "n3", "n10"])
+def test_result_is_the_same_with_and_without_planes(mesh, precision):
+    """A server one byte short of the planes assembles by colour pairs: the
+    same result bit for bit, and the planes were not allocated."""
+    import torch
+
+    import paper_2511_21713_amd as pb
+    prob = {"odd47": lambda: valence_problem(9, nlat=6), "odd119": lambda: valence_problem(13, nlat=10),
+            "n3": lambda: bumpy(3), "n10": lambda: bumpy(10)}[mesh]()
+    ctx = pb.Context(0)
+    g = pb.Problem.from_inputs(ctx, prob, precision=precision)
+    phi = torch.zeros(2 * g.n, dtype=torch.float64, device="cuda:0")
+    torch.cuda.synchronize()
+    ref = g.solve(phi_out=phi, **TIGHT)
+    g.close()
+    ctx.close()
+    ctx = pb.Context(0)  # no workspace yet
+    g = pb.Problem.from_inputs(ctx, prob, precision=precision)
+    steady, setup = g.footprint(**TIGHT)
+    need = colour_pair_bytes(prob, 4 if precision else 8)
+    assert setup > need
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    srv = pb.Server(ctx, hbm_budget_bytes=steady + setup - 1, max_slots=1)
+    r, = drain(srv, [srv.submit(g, **TIGHT)])
+    srv.close()
+    torch.cuda.synchronize()
+    kept = free - torch.cuda.mem_get_info()[0]  # the context's workspace
+    print(f"  {mesh} precision {precision}: {r['total']!r} {ref['total']!r}, kept {kept / MIB:.1f} MiB, planes "
+          f"{setup / MIB:.1f}", flush=True)
+    assert r["status"] == 0
+    for k in ("total", "lc", "nc", "dg_omega_i", "gmres_iters", "omega", "e_k"):
+        assert r[k] == ref[k], k
+    if setup - need > 64 * MIB:  # well past what the runtime keeps for itself
+        assert kept < 0.5 * setup
+    g.close()
+    ctx.close()
