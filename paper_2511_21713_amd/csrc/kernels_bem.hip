@@ -1405,8 +1405,8 @@ static void launch_all_tiles(int shape, bool yuk, bool f32, RegArgs a, const Blo
 }
 
 // Square 16 x 16 tiles of a small surface go through slots (k_bem_gather) if
-// the three planes fit in 192 MiB (about 1 200 vertices FP64, 1 700 FP32).
-// Setup of both surfaces, colour pairs -> slots: 1 002 vertices FP64 1.88 ->
+// the three planes fit in 192 MiB (to about 1 250 vertices FP64, 1 750 FP32:
+// some 2.3 local vertices per vertex).  Setup of both surfaces, colour pairs -> slots: 1 002 vertices FP64 1.88 ->
 // 1.10 ms, 1 442 FP32 1.84 -> 1.15; 2 562 vertices would still gain (3.95 ->
 // 3.64 FP64, 2.85 -> 2.44 FP32) and 4 002 nothing, but the planes grow with
 // the square of the surface (0.8 GB FP64 at 2 562 vertices), and a server
@@ -1414,14 +1414,12 @@ static void launch_all_tiles(int shape, bool yuk, bool f32, RegArgs a, const Blo
 constexpr size_t SLOT_BYTES = size_t(192) << 20;
 constexpr int SLOT_SHAPE = 3;
 static_assert(TILE_SHAPES[SLOT_SHAPE].ta == SLOT_BS && TILE_SHAPES[SLOT_SHAPE].tb == SLOT_BS, "the symmetric 16 x 16 shape");
-static size_t slot_bytes(const BlockSide &H, size_t elem) { return 3 * size_t(H.S) * size_t(H.S) * elem; }
-size_t slot_bytes_bound(int64_t nv, size_t elem)
+size_t slot_planes(const Problem &p, int w)
 {
-    // local vertices: about 2.3 per vertex; a surface with more than 2.5 does not take the slots
-    // (S >= nv: past that no plane set fits and none is charged)
-    const size_t S = size_t(2.5 * double(nv)) + 64;
-    if (3 * size_t(nv) * size_t(nv) * elem > SLOT_BYTES) return 0;
-    return std::min(SLOT_BYTES, 3 * S * S * elem);
+    if (p.tile_fixed >= 0 && p.tile_fixed != SLOT_SHAPE) return 0;
+    const size_t S = size_t(p.topo[w].sides.at(SLOT_BS).S);
+    const size_t b = 3 * S * S * (p.precision == PBFB_MIXED ? sizeof(float) : sizeof(double));
+    return b <= SLOT_BYTES ? b : 0;
 }
 static void launch_slots(bool yuk, bool f32, RegArgs a, hipStream_t s)
 {
@@ -1667,11 +1665,9 @@ void ensure_bem(Problem &p, int w, hipStream_t s)
     // square-tile assembly (nv x nv in the storage precision), vertex
     // coordinates and the touching-pair blocks
     // (or, through slots, the three planes over the local vertices)
-    const BlockSide &HS = block_side(T, SLOT_BS);
-    const bool small = slot_bytes(HS, elem) <= slot_bytes_bound(nv, elem) &&
-                       (p.tile_fixed < 0 || p.tile_fixed == SLOT_SHAPE);
-    const bool slots = small && p.slots; // else the same shape by colour pairs
-    const size_t tbytes = ((slots ? slot_bytes(HS, elem) : size_t(nv) * nv * elem) + 255) / 256 * 256;
+    const size_t planes = slot_planes(p, w);
+    const bool small = planes > 0, slots = small && p.slots; // small and no slots: the same shape by colour pairs
+    const size_t tbytes = ((slots ? planes : size_t(nv) * nv * elem) + 255) / 256 * 256;
     double *ws = wsp->doubles((tbytes + 8 * (3 * size_t(nv) + 18 * size_t(S.ntp))) / 8 + 1);
     void *Tm = ws;
     double *vx = reinterpret_cast<double *>(static_cast<char *>(Tm) + tbytes), *tpv = vx + 3 * nv;
@@ -1701,14 +1697,14 @@ void ensure_bem(Problem &p, int w, hipStream_t s)
     if (p.timing) p.timer.begin(T_ASM, s);
     if (slots) {
         ra.U = Tm;
-        ra.T = static_cast<char *>(Tm) + 2 * size_t(HS.S) * HS.S * elem;
+        ra.T = static_cast<char *>(Tm) + planes / 3 * 2;
         launch_slots(yuk, f32, ra, s);
         const dim3 g(nblk(nv, 256), unsigned(nv));
         if (f32)
-            hipLaunchKernelGGL(k_bem_gather<float>, g, dim3(256), 0, s, nv, ld, HS.S, ra.A.occ_ptr, ra.A.occ,
+            hipLaunchKernelGGL(k_bem_gather<float>, g, dim3(256), 0, s, nv, ld, HA.S, ra.A.occ_ptr, ra.A.occ,
                                static_cast<const float *>(Tm), static_cast<float *>(S.B));
         else
-            hipLaunchKernelGGL(k_bem_gather<double>, g, dim3(256), 0, s, nv, ld, HS.S, ra.A.occ_ptr, ra.A.occ,
+            hipLaunchKernelGGL(k_bem_gather<double>, g, dim3(256), 0, s, nv, ld, HA.S, ra.A.occ_ptr, ra.A.occ,
                                static_cast<const double *>(Tm), static_cast<double *>(S.B));
     } else {
         launch_all_tiles(shape, yuk, f32, ra, HA, HB, s);

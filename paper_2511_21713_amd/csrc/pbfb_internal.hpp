@@ -385,6 +385,8 @@ void ensure_geometry(Problem &p, hipStream_t s);
 void ensure_values(Problem &p, hipStream_t s);
 void ensure_rhs(Problem &p, hipStream_t s);
 void ensure_bem(Problem &p, int surf, hipStream_t s);
+// bytes of the planes through which surface w is assembled (0: it is not small, or has another tile shape)
+size_t slot_planes(const Problem &p, int w);
 void ensure_all(Problem &p, hipStream_t s);
 
 // FEM element kernels (row gather over the tets around each node)

@@ -25,7 +25,6 @@
 namespace pbfb {
 
 int64_t bem_ld(int64_t nv);
-size_t slot_bytes_bound(int64_t nv, size_t elem); // kernels_bem.hip: planes of a small surface's assembly
 
 // Device bytes an instance holds while solving, and the assembly workspace it
 // needs while its dense operators are assembled (the mirrored double layer of
@@ -49,7 +48,7 @@ void footprint_estimate(const Problem &p, int restart, bool slots, size_t *stead
         dense += size_t(T.nv) * bem_ld(T.nv) * elem;
         dense += size_t(sym_partials_doubles(T.nv)) * 8 + size_t(T.nv) * 20 * 12; // symmetric use: partials, Delta
         dense += size_t(T.nt) * 18 * 8 * 2 + size_t(T.nv) * (8 * 8 + 16 * 4);  // Morton copies, block tables, rings
-        const size_t plane = std::max(size_t(T.nv) * T.nv * elem, slots ? slot_bytes_bound(T.nv, elem) : 0);
+        const size_t plane = std::max(size_t(T.nv) * T.nv * elem, slots ? slot_planes(p, w) : 0);
         tmp = std::max(tmp, (plane + 255) / 256 * 256 + size_t(T.nv) * 3 * 8 + T.tp_sig.size() * 18 * 8 + 64);
     }
     const size_t n = size_t(p.n());

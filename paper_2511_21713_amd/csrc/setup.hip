@@ -225,6 +225,7 @@ void build_surface_topo_on(SurfaceTopo &S, int64_t nverts, const double *x, int6
     for (int64_t k = 0; k < S.nv; ++k) S.gmv[k] = S.g[S.mvert[k]];
     // blocks of the default tile shape (other block sizes are built when a
     // shape using them is timed or chosen)
+    static_assert(TILE_SHAPES[0].ta == SLOT_BS, "slot_planes reads the blocks built here");
     block_side(S, TILE_SHAPES[0].ta);
     block_side(S, TILE_SHAPES[0].tb);
     // 1-ring of each vertex (itself and every vertex sharing a triangle), ascending

@@ -49,6 +49,31 @@ def drain(srv, tickets, seconds=60):
     return [out[t] for t in tickets]
 
 
+# the first sizes past the planes' 192 MiB (FP64 between n = 11 and 12, FP32
+# between 13 and 14), and well past
+@pytest.mark.parametrize("n,precision", [(12, 0), (14, 1), (16, 0), (20, 1)])
+def test_footprint_holds_planes_only_where_they_are_used(n, precision):
+    import paper_2511_21713_amd as pb
+    prob = bumpy(n)
+    g = pb.Problem.from_inputs(pb.Context(0), prob, precision=precision)
+    _, setup = g.footprint()
+    need = colour_pair_bytes(prob, 4 if precision else 8)
+    print(f"  n {n} precision {precision}: setup {setup}, needed {need}", flush=True)
+    assert setup == need
+    g.close()
+
+
+def test_footprint_of_another_tile_shape_holds_no_planes():
+    import paper_2511_21713_amd as pb
+    prob = bumpy(6)
+    g = pb.Problem.from_inputs(pb.Context(0), prob)
+    _, small = g.footprint()
+    g.set_tile_shape(8, 32)
+    _, pinned = g.footprint()
+    assert pinned == colour_pair_bytes(prob, 8) < small
+    g.close()
+
+
 # 47 and 119 vertices: an odd count, where the FP32 completion of the colour
 # pairs moves single entries; 92 and 1 002: an even one
 @pytest.mark.parametrize("precision", [0, 1])
