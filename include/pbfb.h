@@ -247,7 +247,8 @@ pbfb_status pbfb_solve_batch(pbfb_ctx *ctx, int n, pbfb_problem *const *probs, c
  * not touch it meanwhile and destroys it afterwards); the budget counts a
  * request from admission to completion, plus the context's assembly
  * workspace (shared by the context's problems, grown to the largest
- * assembly it has served and kept).  A completed request's device memory is
+ * assembly it has served and kept; what the requests do not need of it is
+ * given back when one would wait for the room).  A completed request's device memory is
  * released (the problem keeps its mesh, charges and parameters; a later call
  * on it sets it up again), so a finished request holds no budget.  ENOMEM at
  * submit: the request alone exceeds the budget; otherwise a request that does
@@ -255,12 +256,12 @@ pbfb_status pbfb_solve_batch(pbfb_ctx *ctx, int n, pbfb_problem *const *probs, c
 typedef struct pbfb_server pbfb_server;
 pbfb_status pbfb_server_create(pbfb_ctx *ctx, size_t hbm_budget_bytes, int max_slots, pbfb_server **out);
 pbfb_status pbfb_server_submit(pbfb_server *s, pbfb_problem *p, const pbfb_solve_opts *o, uint64_t *ticket);
-/* The device bytes the server charges for a request: steady (held from
- * admission to completion) and setup (the context's assembly workspace the
- * request's setup needs; charged once per context, see above).  A budget of
- * at least steady + setup admits the request; one short of it by no more than
- * a small surface's assembly planes does too, and assembles without them (the
- * same results bit for bit). */
+/* The device bytes of a request: steady (held from admission to completion)
+ * and setup (the context's assembly workspace its setup uses; charged once per
+ * context, see above).  A budget of at least steady + setup admits the request.
+ * The assembly planes of small surfaces (up to 192 MiB of setup) are taken
+ * only where there is room: a budget without room for them admits the request
+ * as well, no request waits for them, and the results are the same bits. */
 pbfb_status pbfb_request_footprint(const pbfb_problem *p, const pbfb_solve_opts *o, size_t *steady_bytes,
                                    size_t *setup_bytes);
 /* done = 1 once the request finished; res (nullable) then receives its result */

@@ -185,6 +185,19 @@ double *Workspace::doubles(size_t n)
     return static_cast<double *>(ptr);
 }
 
+void Ctx::trim_ws(size_t keep)
+{
+    for (int i = N_ASM_WS - 1; i >= 0 && ws_held() > keep; --i) {
+        Workspace &w = asm_ws[i];
+        std::unique_lock<std::mutex> l(w.mu, std::try_to_lock);
+        if (!l.owns_lock() || !w.ptr) continue;
+        (void)hipFree(w.ptr); // after the device has drained
+        w.ptr = nullptr;
+        w.bytes = 0;
+        w.held.store(0);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // event timers
 // ---------------------------------------------------------------------------

@@ -1409,8 +1409,8 @@ static void launch_all_tiles(int shape, bool yuk, bool f32, RegArgs a, const Blo
 // some 2.3 local vertices per vertex).  Setup of both surfaces, colour pairs -> slots: 1 002 vertices FP64 1.88 ->
 // 1.10 ms, 1 442 FP32 1.84 -> 1.15; 2 562 vertices would still gain (3.95 ->
 // 3.64 FP64, 2.85 -> 2.44 FP32) and 4 002 nothing, but the planes grow with
-// the square of the surface (0.8 GB FP64 at 2 562 vertices), and a server
-// charges them to the request.
+// the square of the surface (0.8 GB FP64 at 2 562 vertices), and the context
+// keeps them in its workspaces.
 constexpr size_t SLOT_BYTES = size_t(192) << 20;
 constexpr int SLOT_SHAPE = 3;
 static_assert(TILE_SHAPES[SLOT_SHAPE].ta == SLOT_BS && TILE_SHAPES[SLOT_SHAPE].tb == SLOT_BS, "the symmetric 16 x 16 shape");
@@ -1663,17 +1663,33 @@ void ensure_bem(Problem &p, int w, hipStream_t s)
     ra.sK = sK;
     // the context's assembly workspace: the mirrored double layer T of a
     // square-tile assembly (nv x nv in the storage precision), vertex
-    // coordinates and the touching-pair blocks
-    // (or, through slots, the three planes over the local vertices)
+    // coordinates and the touching-pair blocks.  A small surface has its planes
+    // in T's place if they may be allocated or the workspace has the room
+    // already; by colour pairs of the same tile shape the operator is the same
+    // bits
     const size_t planes = slot_planes(p, w);
-    const bool small = planes > 0, slots = small && p.slots; // small and no slots: the same shape by colour pairs
-    const size_t tbytes = ((slots ? planes : size_t(nv) * nv * elem) + 255) / 256 * 256;
-    double *ws = wsp->doubles((tbytes + 8 * (3 * size_t(nv) + 18 * size_t(S.ntp))) / 8 + 1);
+    size_t tbytes = 0;
+    auto ws_bytes = [&](size_t t) {
+        tbytes = (t + 255) / 256 * 256;
+        return (tbytes + 8 * (3 * size_t(nv) + 18 * size_t(S.ntp))) / 8 * 8 + 8;
+    };
+    bool slots = planes > 0 && (p.planes || wsp->bytes >= ws_bytes(planes));
+    double *ws = nullptr;
+    if (slots) {
+        try {
+            ws = wsp->doubles(ws_bytes(planes) / 8);
+        } catch (const Error &e) {
+            if (e.code != PBFB_ENOMEM) throw;
+            (void)hipGetLastError(); // no room on the device: colour pairs
+            slots = false;
+        }
+    }
+    if (!slots) ws = wsp->doubles(ws_bytes(size_t(nv) * nv * elem) / 8);
     void *Tm = ws;
     double *vx = reinterpret_cast<double *>(static_cast<char *>(Tm) + tbytes), *tpv = vx + 3 * nv;
     ra.T = Tm;
     // tile shape: forced, or tuned once per (precision, kernel, size class) and context
-    int shape = small ? SLOT_SHAPE : p.tile_fixed;
+    int shape = planes > 0 ? SLOT_SHAPE : p.tile_fixed;
     if (shape < 0) {
         const int key = tile_key(p.precision, yuk, T.nt);
         std::lock_guard<std::mutex> tl(p.ctx->tune_mu);

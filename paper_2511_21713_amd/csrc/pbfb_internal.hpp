@@ -200,10 +200,11 @@ struct SurfaceDev {
 };
 
 // Device workspace shared by the problems of a context for their dense
-// assembly (the mirrored double layer of a square-tile assembly, vertex
-// coordinates, touching-pair blocks): grown on demand, never shrunk, freed
-// with the context.  One assembly uses it at a time (the mutex is held until
-// the assembly's stream has drained).
+// assembly (the mirrored double layer of a square-tile assembly or a small
+// surface's planes, vertex coordinates, touching-pair blocks): grown on demand,
+// freed with the context or, idle, when a server needs the room (trim_ws).  One
+// assembly uses it at a time (the mutex is held until the assembly's stream
+// has drained).
 struct Workspace {
     void *ptr = nullptr;
     size_t bytes = 0;
@@ -259,6 +260,7 @@ struct Ctx {
         for (const Workspace &w : asm_ws) b += w.held.load();
         return b;
     }
+    void trim_ws(size_t keep); // frees idle workspaces until at most `keep` bytes are held
     // problems created in this context and not yet destroyed
     std::mutex live_mu;
     std::set<Problem *> live;
@@ -305,7 +307,9 @@ struct Problem {
     bool val_ready = false; // FEM stiffness and coupling values (depend on the permittivities)
     bool bem_topo_ready[NSURF] = {false, false, false};
     int tile_fixed = -1; // tile shape forced by pbfb_set_tile_shape (index), -1: tuned
-    bool slots = true;   // small surfaces assembled through slots; off for a request whose server has no room for the planes
+    // a small surface's assembly may grow the context's workspace for its
+    // planes; off for a request whose server has no room for them
+    bool planes = true;
     bool bem_mf = false; // boundary operators applied matrix-free (no dense storage)
     // host copies
     int64_t nn = 0, ntet = 0, nq = 0;

@@ -10,8 +10,9 @@
 // round advances each running instance to its next linear solve and then runs
 // one batched GMRES over all of them.  Finished requests release their slot
 // and budget.  The per-instance arithmetic (work lists, reduction orders) does
-// not depend on the other members of the batch, so a request's result is the
-// same bit for bit alone or in any mix.
+// not depend on the other members of the batch, nor the operators on whether
+// there was room for assembly planes, so a request's result is the same bit
+// for bit alone or in any mix.
 #include <algorithm>
 #include <chrono>
 #include <condition_variable>
@@ -26,15 +27,15 @@ namespace pbfb {
 
 int64_t bem_ld(int64_t nv);
 
-// Device bytes an instance holds while solving, and the assembly workspace it
-// needs while its dense operators are assembled (the mirrored double layer of
-// a square-tile assembly, nv x nv in the storage precision, or with slots the
-// planes of a small surface's assembly; vertex coordinates and touching-pair
-// blocks).
-void footprint_estimate(const Problem &p, int restart, bool slots, size_t *steady, size_t *setup_extra)
+// Device bytes an instance holds while solving, and the assembly workspace
+// while its dense operators are assembled: what it needs (the mirrored double
+// layer of a square-tile assembly, nv x nv in the storage precision, vertex
+// coordinates and touching-pair blocks) and what it takes where there is room
+// (the planes of a small surface's assembly instead of the mirrored double layer).
+void footprint_estimate(const Problem &p, int restart, size_t *steady, size_t *setup_need, size_t *setup_planes)
 {
     const size_t elem = p.precision == PBFB_MIXED ? 4 : 8;
-    size_t dense = 0, tmp = 0;
+    size_t dense = 0, tmp = 0, tmp_planes = 0;
     for (int w = 0; w < 2 && p.bem_mf; ++w) {
         // matrix-free: touching-pair blocks, the apply's strength buffers and
         // the near-field rows of the preconditioner (~40 per vertex)
@@ -48,8 +49,10 @@ void footprint_estimate(const Problem &p, int restart, bool slots, size_t *stead
         dense += size_t(T.nv) * bem_ld(T.nv) * elem;
         dense += size_t(sym_partials_doubles(T.nv)) * 8 + size_t(T.nv) * 20 * 12; // symmetric use: partials, Delta
         dense += size_t(T.nt) * 18 * 8 * 2 + size_t(T.nv) * (8 * 8 + 16 * 4);  // Morton copies, block tables, rings
-        const size_t plane = std::max(size_t(T.nv) * T.nv * elem, slots ? slot_planes(p, w) : 0);
-        tmp = std::max(tmp, (plane + 255) / 256 * 256 + size_t(T.nv) * 3 * 8 + T.tp_sig.size() * 18 * 8 + 64);
+        const size_t mirror = size_t(T.nv) * T.nv * elem, planes = std::max(mirror, slot_planes(p, w));
+        const size_t rest = size_t(T.nv) * 3 * 8 + T.tp_sig.size() * 18 * 8 + 64;
+        tmp = std::max(tmp, (mirror + 255) / 256 * 256 + rest);
+        tmp_planes = std::max(tmp_planes, (planes + 255) / 256 * 256 + rest);
     }
     const size_t n = size_t(p.n());
     const size_t nnz_est = size_t(p.ntet) * 3 + size_t(p.nn) * 4; // generous: ~14 per row
@@ -57,7 +60,8 @@ void footprint_estimate(const Problem &p, int restart, bool slots, size_t *stead
     const size_t fem = size_t(p.ntet) * (16 * 8 + 16 + 16 * 4) + size_t(p.nn) * 12;
     const size_t vec = n * 8 * (size_t(restart) + 1 + 16);
     *steady = dense + csr + fem + vec + (size_t(64) << 20);
-    *setup_extra = tmp;
+    *setup_need = tmp;
+    *setup_planes = std::max(tmp, tmp_planes);
 }
 
 struct Request {
@@ -65,7 +69,7 @@ struct Request {
     Problem *p;
     pbfb_solve_opts o;
     pbfb_result res{};
-    size_t steady = 0, extra = 0;
+    size_t steady = 0, extra = 0, planes = 0; // planes: the assembly workspace where there is room
     NewtonRun *run = nullptr;
     bool done = false;
     std::string message;
@@ -76,8 +80,10 @@ struct Server {
     Ctx *ctx = nullptr;
     // used: steady footprints of the admitted, unfinished requests; ws_need: the
     // largest assembly workspace any admitted request needs (the context's
-    // workspace grows to it and is kept, so it is charged once, never released)
-    size_t budget = 0, used = 0, ws_need = 0;
+    // workspace grows to it and is kept, so it is charged once, never
+    // released); ws_planes: the largest with planes that one still to be set
+    // up will take (afterwards the context holds it)
+    size_t budget = 0, used = 0, ws_need = 0, ws_planes = 0;
     int max_slots = 1;
     hipStream_t s_solve = nullptr, s_setup = nullptr;
     std::mutex mu;
@@ -93,19 +99,27 @@ struct Server {
     std::thread solve_thread, setup_thread;
     std::string error;
 
-    // device bytes charged for the shared assembly workspace if r were admitted
-    size_t ws_with(const Request *r) const
+    // r fits with `ws` bytes of the shared assembly workspace
+    bool fits(const Request *r, size_t ws) const
     {
-        return std::max(std::max(ws_need, r->extra), ctx->ws_held());
+        return used + r->steady + std::max(std::max(ws_need, ws), std::max(ws_planes, ctx->ws_held())) <= budget;
     }
 
     void admit_locked()
     {
         while (!pending.empty() && in_flight < max_slots) {
             Request *r = pending.front();
-            if (used + r->steady + ws_with(r) > budget && in_flight > 0) break; // wait for memory
+            if (!fits(r, r->extra)) {
+                // workspace past what the requests need (planes, the workspaces
+                // of a batch) is given back; else wait for memory
+                ctx->trim_ws(std::max(ws_need, r->extra));
+                if (!fits(r, r->extra) && in_flight > 0) break;
+            }
             pending.pop_front();
-            ws_need = ws_with(r);
+            // planes where there is room (the operators are the same bits without)
+            r->p->planes = fits(r, r->planes);
+            if (r->p->planes) ws_planes = std::max(ws_planes, r->planes);
+            ws_need = std::max(ws_need, r->extra);
             used += r->steady;
             ++in_flight;
             r->t_admit = std::chrono::steady_clock::now();
@@ -139,6 +153,10 @@ struct Server {
             }
             std::lock_guard<std::mutex> lk(mu);
             ready.push_back(r);
+            if (to_setup.empty()) {
+                ws_planes = 0;
+                admit_locked(); // a request may have waited for that
+            }
             cv.notify_all();
         }
     }
@@ -153,7 +171,7 @@ struct Server {
         } catch (const Error &) {
         }
         release_device_state(*r->p);
-        r->p->slots = true;
+        r->p->planes = true;
         used -= std::min(used, r->steady);
         --in_flight;
         admit_locked();
@@ -272,19 +290,15 @@ pbfb_status pbfb_server_submit(pbfb_server *sv, pbfb_problem *pp, const pbfb_sol
         if (o) O = *o;
         else pbfb_solve_opts_default(&O);
         check_opts(O);
-        size_t steady = 0, extra = 0;
-        footprint_estimate(p, O.gmres_restart, true, &steady, &extra);
-        // a budget without room for the planes of the slot assembly: colour
-        // pairs, which need the mirrored double layer only (the same bits)
-        const bool slots = steady + extra <= sv->s.budget;
-        if (!slots) footprint_estimate(p, O.gmres_restart, false, &steady, &extra);
+        size_t steady = 0, extra = 0, planes = 0;
+        footprint_estimate(p, O.gmres_restart, &steady, &extra, &planes);
         PB_CHECK(steady + extra <= sv->s.budget, PBFB_ENOMEM, "request exceeds the server's HBM budget");
         auto *r = new Request;
         r->o = O;
         r->p = &p;
-        p.slots = slots;
         r->steady = steady;
         r->extra = extra;
+        r->planes = planes;
         r->t_submit = std::chrono::steady_clock::now();
         std::lock_guard<std::mutex> lk(sv->s.mu);
         r->ticket = sv->s.next_ticket++;
@@ -311,7 +325,8 @@ pbfb_status pbfb_request_footprint(const pbfb_problem *pp, const pbfb_solve_opts
         if (o) O = *o;
         else pbfb_solve_opts_default(&O);
         check_opts(O);
-        footprint_estimate(p, O.gmres_restart, true, steady_bytes, setup_bytes);
+        size_t need = 0;
+        footprint_estimate(p, O.gmres_restart, steady_bytes, &need, setup_bytes);
         return PBFB_OK;
     } catch (const Error &e) {
         set_error(e.msg);

@@ -114,3 +114,40 @@ def test_result_is_the_same_with_and_without_planes(mesh, precision):
         assert kept < 0.5 * setup
     g.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("kept,room", [(False, False), (False, True), (True, False)])
+def test_planes_keep_no_request_waiting(kept, room):
+    """A budget for two requests without planes runs two at once, also where
+    the first has room for planes (room) and where an earlier batch has left
+    planes in the context's workspaces (kept): the second waits at most for
+    the first one's setup."""
+    import paper_2511_21713_amd as pb
+    prob = bumpy(11)  # 1 212 vertices: 190 MB of planes
+    ctx = pb.Context(0)
+    gs = [pb.Problem.from_inputs(ctx, prob) for _ in range(4)]
+    if kept:
+        pb.solve_batch(ctx, gs)
+        for g in gs:
+            g.close()
+        gs = [pb.Problem.from_inputs(ctx, prob) for _ in range(2)]
+    else:
+        gs[0].solve()  # code objects loaded
+        for g in gs:
+            g.close()
+        ctx.close()
+        ctx = pb.Context(0)
+        gs = [pb.Problem.from_inputs(ctx, prob) for _ in range(2)]
+    steady, setup = gs[0].footprint(**TIGHT)
+    two = 2 * steady + colour_pair_bytes(prob, 8)
+    assert two < steady + setup
+    srv = pb.Server(ctx, hbm_budget_bytes=steady + setup if room else two, max_slots=2)
+    first, second = drain(srv, [srv.submit(g, **TIGHT) for g in gs])
+    srv.close()
+    print(f"  first: setup {first['t_setup_s']:.3f} s, solve {first['t_solve_s']:.3f}; second waited "
+          f"{second['t_wait_s']:.3f}", flush=True)
+    assert first["status"] == 0 and first["total"] == second["total"]
+    assert second["t_wait_s"] < 0.5 * first["t_solve_s"]
+    for g in gs:
+        g.close()
+    ctx.close()
