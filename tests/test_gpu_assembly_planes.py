@@ -7,8 +7,9 @@ import time
 import numpy as np
 import pytest
 
+import oracle
 import pbgen
-from test_gpu_tiles import valence_problem
+from test_gpu_tiles import rowrel, valence_problem
 
 pytestmark = pytest.mark.gpu
 
@@ -150,4 +151,31 @@ def test_planes_keep_no_request_waiting(kept, room):
     assert second["t_wait_s"] < 0.5 * first["t_solve_s"]
     for g in gs:
         g.close()
+    ctx.close()
+
+
+def test_odd_fp32_surface_past_the_planes_matches_oracle_rows():
+    """1 819 vertices in FP32: the planes pass 192 MiB, so the operator is
+    assembled by colour pairs and completed entry by entry (odd count)."""
+    import paper_2511_21713_amd as pb
+    prob = valence_problem(23, nlat=80)
+    o = oracle.Oracle.from_problem(prob)
+    ctx = pb.Context(0)
+    g = pb.Problem.from_inputs(ctx, prob, precision=pb.MIXED)
+    assert g.n_m == 1819 and g.footprint()[1] == colour_pair_bytes(prob, 4)
+    g.set_tile_shape(16, 16)
+    for surf in (0, 1):
+        rng = np.random.default_rng(surf)
+        nv = o.n_m if surf == 0 else o.n_s
+        rows = np.unique(np.r_[0, nv - 1, rng.choice(nv, size=20, replace=False)])
+        V, K = o.bem_rows(surf, rows)
+        sV, sK = (-1.0, 1.0) if surf == 0 else (1.0, -1.0)
+        x = rng.standard_normal(nv)
+        Mx = o.surface_mass_apply(surf, x)[rows]
+        Vp, Kp = g.export_bem_rows(surf, rows)
+        eV = rowrel(Vp, sV * V)
+        dK = np.abs(Kp @ x - (0.5 * Mx + sK * (K @ x))).max() / (np.abs(Kp) @ np.abs(x)).max()
+        print(f"  surface {surf}: V {eV:.2e} K {dK:.2e}", flush=True)
+        assert eV < 1e-6 and dK < 1e-6
+    g.close()
     ctx.close()

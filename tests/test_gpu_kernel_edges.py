@@ -218,3 +218,44 @@ def test_server_without_room_for_assembly_planes(ctx):
     assert r is not None and r["status"] == 0
     assert abs(r["total"] - ref) < 1e-10 * abs(ref)
     g.close()
+
+
+# 47 and 1 819 vertices: the last wavefront of the full rows holds one row;
+# 3 453: past the full rows' 160 MiB, the symmetric use's last row
+@pytest.mark.parametrize("nlon,nlat,precision", [(9, 6, 0), (9, 6, 1), (23, 80, 0), (23, 80, 1), (29, 120, 0)])
+def test_dense_rows_of_an_odd_vertex_count(ctx, nlon, nlat, precision):
+    """As test_dense_rows_of_either_form_match_the_stored_blocks, for the
+    residual (FP64 FEM values) and the Newton-matrix product."""
+    import paper_2511_21713_amd as pb
+    from test_gpu_tiles import valence_problem
+    prob = valence_problem(nlon, nlat=nlat)
+    g = pb.Problem.from_inputs(ctx, prob, precision=precision)
+    g.set_tile_shape(16, 16)
+    assert g.n_m % 2 == 1
+    rng = np.random.default_rng(nlon)
+    v, phi = rng.standard_normal(g.n), rng.standard_normal(g.n)
+    y = g.apply_jacobian(pb.LIN, phi, v)
+    r = g.residual(pb.LIN, v) + g.export_rhs()
+    nn, nm = g.n_nodes, g.n_m
+    for surf, ids, lo in ((0, np.unique(prob.tri_m), nn), (1, np.unique(prob.tri_s), nn + nm)):
+        V, K = g.export_bem(surf)
+        ref = K @ v[ids] + V @ v[lo:lo + ids.size]
+        for got in (y, r):
+            e = rel2(got[lo:lo + ids.size], ref)
+            print(f"  {ids.size} vertices precision {precision} surface {surf}: {e:.2e}", flush=True)
+            assert e < 1e-13
+    g.close()
+
+
+@pytest.mark.parametrize("precision,bar", [(0, 1e-10), (1, 1e-5)])
+def test_solve_on_an_odd_vertex_count(ctx, precision, bar):
+    """The Krylov step's full rows on 47 vertices: a solve against the oracle's energy."""
+    import paper_2511_21713_amd as pb
+    from test_gpu_tiles import valence_problem
+    prob = valence_problem(9, nlat=6)
+    ref = oracle.Oracle.from_problem(prob).solve(**TIGHT)[0]["total"]
+    g = pb.Problem.from_inputs(ctx, prob, precision=precision)
+    r = g.solve(**(TIGHT if precision == 0 else {}))
+    print(f"  precision {precision}: {abs(r['total'] - ref) / abs(ref):.2e}", flush=True)
+    assert abs(r["total"] - ref) < bar * abs(ref)
+    g.close()
