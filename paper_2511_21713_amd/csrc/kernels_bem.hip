@@ -758,8 +758,9 @@ static double ss_jac(int kind, int r, double xi, double e1, double e2)
 constexpr int SS_STRIDE = 16; // 13 used; one aligned 128-byte line
 constexpr int SS_NPT[3] = {6 * 256, 5 * 256, 2 * 256}, SS_OFF[3] = {0, 6 * 256, 11 * 256}, SS_ALL = 13 * 256;
 
-// device copy of the table, once per context
-static const double *ss_points(Ctx &C)
+// device copy of the table, once per context, uploaded on the stream of the
+// setup that comes first; other streams may use it when this returns
+static const double *ss_points(Ctx &C, hipStream_t s)
 {
     std::lock_guard<std::mutex> lk(C.setup_mu);
     if (C.ss_points) return C.ss_points;
@@ -781,7 +782,8 @@ static const double *ss_points(Ctx &C)
         }
     double *dev = nullptr;
     PB_HIP(hipMalloc(&dev, sizeof(double) * t.size()));
-    const hipError_t e = hipMemcpy(dev, t.data(), sizeof(double) * t.size(), hipMemcpyHostToDevice);
+    hipError_t e = hipMemcpyAsync(dev, t.data(), sizeof(double) * t.size(), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         (void)hipFree(dev);
         PB_HIP(e);
@@ -1502,7 +1504,7 @@ static int tile_tune(Problem &p, int w, RegArgs a, bool yuk, bool f32, hipStream
 static void singular_pairs(Problem &p, const SurfaceDev &S, bool yuk, double kappa, const double *vx, double *tpv,
                            hipStream_t s)
 {
-    const double *pts = ss_points(*p.ctx);
+    const double *pts = ss_points(*p.ctx, s);
     const unsigned g = nblk(S.tp_cnt[0], 64) + nblk(S.tp_cnt[1], 64) + nblk(S.tp_cnt[2], 64);
     if (p.timing) p.timer.begin(T_SING, s);
     if (yuk)
