@@ -1670,23 +1670,32 @@ void ensure_bem(Problem &p, int w, hipStream_t s)
     // already; by colour pairs of the same tile shape the operator is the same
     // bits
     const size_t planes = slot_planes(p, w);
-    size_t tbytes = 0;
-    auto ws_bytes = [&](size_t t) {
-        tbytes = (t + 255) / 256 * 256;
-        return (tbytes + 8 * (3 * size_t(nv) + 18 * size_t(S.ntp))) / 8 * 8 + 8;
+    const size_t mirror = size_t(nv) * nv * elem;
+    auto round256 = [](size_t b) { return (b + 255) / 256 * 256; };
+    // doubles of an assembly with t bytes in T's place
+    auto ws_doubles = [&](size_t t, const SurfaceTopo &V) {
+        return (round256(t) + 8 * (3 * size_t(V.nv) + 18 * V.tp_sig.size())) / 8 + 1;
     };
-    bool slots = planes > 0 && (p.planes || wsp->bytes >= ws_bytes(planes));
+    bool slots = planes > 0 && (p.planes || wsp->bytes >= 8 * ws_doubles(planes, T));
     double *ws = nullptr;
     if (slots) {
+        // room for the planes of all the problem's surfaces, which are not of
+        // one size: a workspace that grows frees its memory first, and that
+        // waits for every stream
+        size_t want = 0;
+        for (int v = 0; v < NSURF; ++v)
+            if (v == w || (!p.bem_ready[v] && (v < 2 || p.gm() == 2) && slot_planes(p, v) > 0))
+                want = std::max(want, ws_doubles(slot_planes(p, v), p.topo[v]));
         try {
-            ws = wsp->doubles(ws_bytes(planes) / 8);
+            ws = wsp->doubles(p.planes ? want : ws_doubles(planes, T));
         } catch (const Error &e) {
             if (e.code != PBFB_ENOMEM) throw;
             (void)hipGetLastError(); // no room on the device: colour pairs
             slots = false;
         }
     }
-    if (!slots) ws = wsp->doubles(ws_bytes(size_t(nv) * nv * elem) / 8);
+    if (!slots) ws = wsp->doubles(ws_doubles(mirror, T));
+    const size_t tbytes = round256(slots ? planes : mirror);
     void *Tm = ws;
     double *vx = reinterpret_cast<double *>(static_cast<char *>(Tm) + tbytes), *tpv = vx + 3 * nv;
     ra.T = Tm;

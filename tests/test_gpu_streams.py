@@ -52,3 +52,13 @@ def test_first_setup_of_a_context_leaves_the_null_stream_alone(bumpy, second):
     g.set_tile_shape(8, 32)  # the same workspace for both surfaces
     assert null_stream_busy_after(g.setup, second)
     g.close()
+
+
+def test_setup_grows_the_workspace_before_it_is_in_use(bumpy, second):
+    """The planes of the two surfaces differ in size: the workspace is made for
+    the larger at once, instead of being freed and made again between them
+    (freeing device memory waits for every stream)."""
+    import paper_2511_21713_amd as pb
+    g = pb.Problem.from_inputs(pb.Context(0), bumpy)
+    assert null_stream_busy_after(g.setup, second)
+    g.close()
