@@ -921,7 +921,7 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
             d.sp_col[w] = p.surf[w].ring;
             d.sp_val[w] = p.surf[w].spai;
             const SurfaceDev &SD = p.surf[w];
-            d.symm[w] = (!p.bem_mf && SD.sym && !gemv_small(SD.nv, d.f32 != 0)) ? 1 : 0;
+            d.symm[w] = (!p.bem_mf && SD.sym) ? 1 : 0;
             d.symP[w] = d.symm[w] ? scratch<double>(p, w == 0 ? SCR_SYMP0 : SCR_SYMP1,
                                                     size_t(sym_partials_doubles(SD.nv)))
                                   : nullptr;

@@ -42,6 +42,7 @@
 #include <type_traits>
 
 #include "bem_quad.hpp"
+#include "gemv_rows.hpp"
 #include "pbfb_internal.hpp"
 
 namespace pbfb {
@@ -1602,10 +1603,12 @@ void ensure_bem(Problem &p, int w, hipStream_t s)
             const int64_t ldt = bem_ld(T.nv);
             if (f32) S.B = A.alloc<float>(T.nv * ldt);
             else S.B = A.alloc<double>(T.nv * ldt);
-            delta_pattern(T);
-            S.d_ptr = A.upload(T.d2_ptr, s);
-            S.d_col = A.upload(T.d2_col, s);
-            S.d_val = A.alloc<double>(std::max<size_t>(T.d2_col.size(), 1));
+            if (!gemv_small(T.nv, f32)) { // small surfaces are applied by full rows
+                delta_pattern(T);
+                S.d_ptr = A.upload(T.d2_ptr, s);
+                S.d_col = A.upload(T.d2_col, s);
+                S.d_val = A.alloc<double>(std::max<size_t>(T.d2_col.size(), 1));
+            }
         }
         PB_HIP(hipStreamSynchronize(s));
         p.bem_topo_ready[w] = true;
@@ -1768,13 +1771,14 @@ void ensure_bem(Problem &p, int w, hipStream_t s)
     // diagonal of V', symmetric storage use (Delta from the stored values),
     // approximate inverse of the single-layer block (from the stored values)
     // symmetric use: the apply reads K' and the lower triangle of V' (square
-    // tiles leave the regular part of V' bitwise symmetric)
-    S.sym = sym;
+    // tiles leave the regular part of V' bitwise symmetric), unless the surface
+    // is small (gemv_small)
+    S.sym = sym && !gemv_small(nv, f32);
     PB_HIP(hipMemsetAsync(p.d_bad, 0, sizeof(int), s));
     if (f32) {
         const float *Bf = static_cast<const float *>(S.B);
         hipLaunchKernelGGL(k_vdiag<float>, dim3(nblk(nv, 256)), dim3(256), 0, s, nv, ld, S.mvert, Bf, S.vdiag);
-        if (sym)
+        if (S.sym)
             hipLaunchKernelGGL(k_sym_delta<float>, dim3(nblk(nv, 256)), dim3(256), 0, s, nv, ld, Bf, S.d_ptr, S.d_col,
                                S.d_val);
         hipLaunchKernelGGL((k_spai_small<float, 4>), dim3(nblk(nv, 4)), dim3(256), 0, s, nv, Bf, ld, S.minv,
@@ -1785,7 +1789,7 @@ void ensure_bem(Problem &p, int w, hipStream_t s)
     } else {
         const double *Bd = static_cast<const double *>(S.B);
         hipLaunchKernelGGL(k_vdiag<double>, dim3(nblk(nv, 256)), dim3(256), 0, s, nv, ld, S.mvert, Bd, S.vdiag);
-        if (sym)
+        if (S.sym)
             hipLaunchKernelGGL(k_sym_delta<double>, dim3(nblk(nv, 256)), dim3(256), 0, s, nv, ld, Bd, S.d_ptr,
                                S.d_col, S.d_val);
         hipLaunchKernelGGL((k_spai_small<double, 2>), dim3(nblk(nv, 4)), dim3(256), 0, s, nv, Bd, ld, S.minv,

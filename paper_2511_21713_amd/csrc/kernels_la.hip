@@ -204,7 +204,7 @@ static GemvSurf gemv_surf(Problem &p, int w, const double *x, double *y, double 
     G.n = D.nv;
     G.ld = bem_ld(D.nv);
     G.small = gemv_small(D.nv, p.precision == PBFB_MIXED) ? 1 : 0;
-    G.sym = D.sym && !G.small ? 1 : 0;
+    G.sym = D.sym ? 1 : 0;
     G.f32 = p.precision == PBFB_MIXED ? 1 : 0;
     G.P = G.sym ? P : nullptr;
     G.dptr = D.d_ptr;

@@ -189,7 +189,8 @@ struct SurfaceDev {
     // mvert[k]) = [K'_k (nv) | V'_k (nv)], columns in the same order, FP64 or FP32
     void *B = nullptr;
     double *vdiag = nullptr; // diagonal of the signed single-layer block V' (ascending vertex order)
-    // symmetric storage use: the regular part of V' is bitwise symmetric, and
+    // symmetric use of the stored operator (sym; not of small surfaces, which
+    // are applied by full rows): the regular part of V' is bitwise symmetric, and
     // Delta_kl = V'_kl - V'_lk (l > k in the Morton order, two-ring pattern) carries the rest
     bool sym = false;
     int32_t *d_ptr = nullptr, *d_col = nullptr;

@@ -259,3 +259,23 @@ def test_solve_on_an_odd_vertex_count(ctx, precision, bar):
     print(f"  precision {precision}: {abs(r['total'] - ref) / abs(ref):.2e}", flush=True)
     assert abs(r["total"] - ref) < bar * abs(ref)
     g.close()
+
+
+@pytest.mark.parametrize("n,precision", [(14, 0), (16, 1)])
+def test_full_rows_hold_nothing_of_the_symmetric_use(ctx, n, precision):
+    """A surface applied by full rows holds neither the column partials nor
+    the two-ring differences of the symmetric use: after a product, square
+    tiles hold no more than rectangular ones do beyond their block tables."""
+    import paper_2511_21713_amd as pb
+    prob = pbgen.make_problem(n=n, a=6.0, c=9.0, bump=True, t=3.0, L=1, helix=0, partials=0, kappa=0.2, seed=(9, n),
+                              center_charge=1.0)
+    held = {}
+    for shape in ((16, 16), (8, 16)):  # the second's tables hold the first's
+        g = pb.Problem.from_inputs(ctx, prob, precision=precision)
+        g.set_tile_shape(*shape)
+        g.apply_jacobian(pb.LIN, np.zeros(g.n), np.ones(g.n))
+        held[shape] = g.hbm()
+        g.close()
+    nv = np.unique(prob.tri_m).size
+    print(f"  n {n} precision {precision}: {held}, partials {8 * (nv * (-(-nv // 64)) + nv)}", flush=True)
+    assert held[(16, 16)] <= held[(8, 16)]
