@@ -56,7 +56,6 @@ struct GDesc {
     int64_t ldm, lds, nm, ns;
     int f32;  // operator values in FP32
     int vf32; // Krylov basis stored in FP32
-    int mf;   // boundary operators applied matrix-free (no dense GEMV)
     int two_field; // lambda_m is not an unknown (two-field form): identity row, no Gamma_m GEMV
     // symmetric use of the stored single layer, per surface: column partials, Delta rows
     int symm[2];
@@ -92,7 +91,7 @@ struct GDesc {
 
 struct GState {
     int st, j, total, code, napply;
-    double beta, target, hn;
+    double beta, target;
 };
 
 struct WItem {
@@ -676,7 +675,6 @@ __global__ void __launch_bounds__(64) k_bcontrol(const GDesc *__restrict__ D, GS
             ss.j = j + 1;
             ss.total += 1;
             ss.napply += 1;
-            ss.hn = nr;
             const double res = fabs(d.g[j + 1]);
             if (!(res == res)) {
                 ss.st = G_FAIL;
@@ -899,7 +897,6 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
         d.ldm = bem_ld(d.nm);
         d.lds = bem_ld(d.ns);
         d.f32 = p.precision == PBFB_MIXED;
-        d.mf = p.bem_mf ? 1 : 0;
         d.two_field = p.two_field() ? 1 : 0;
         d.mvm = p.bem_mf ? nullptr : p.surf[0].mvert;
         d.mvs = p.bem_mf ? nullptr : p.surf[1].mvert;
@@ -959,7 +956,7 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
         d.tol = J.tol;
         d.m = m;
         d.maxit = J.maxit;
-        st[q] = GState{G_INIT, 0, 0, 0, 0, 0.0, 0.0, 0.0};
+        st[q] = GState{G_INIT, 0, 0, 0, 0, 0.0, 0.0};
         nmax = std::max(nmax, n);
         for (int64_t k = 0; k < n; k += CH) wl_vec.push_back(WItem{q, 0, k});
         for (int64_t c = 0; c < d.nchb; ++c) wl_dot.push_back(WItem{q, int(c), c * d.chb});

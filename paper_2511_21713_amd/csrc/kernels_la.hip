@@ -147,12 +147,9 @@ struct PtrTab {
     const double *b[8];
 };
 
-// partial dot products of k <= 8 vector pairs; partial[b * k + j] (skip:
-// optional device flag, nonzero = nothing to do)
-__global__ void __launch_bounds__(256) k_dots_partial(int64_t n, int k, PtrTab T, double *__restrict__ partial,
-                                                      const int *__restrict__ skip)
+// partial dot products of k <= 8 vector pairs; partial[b * k + j]
+__global__ void __launch_bounds__(256) k_dots_partial(int64_t n, int k, PtrTab T, double *__restrict__ partial)
 {
-    if (skip && *skip) return;
     const double *const *A = T.a;
     const double *const *Bv = T.b;
     __shared__ double red[8][256];
@@ -170,10 +167,8 @@ __global__ void __launch_bounds__(256) k_dots_partial(int64_t n, int k, PtrTab T
     if (threadIdx.x < k) partial[blockIdx.x * k + threadIdx.x] = red[threadIdx.x][0];
 }
 
-__global__ void k_reduce_partial(int nb, int k, const double *__restrict__ partial, double *__restrict__ out,
-                                 const int *__restrict__ skip)
+__global__ void k_reduce_partial(int nb, int k, const double *__restrict__ partial, double *__restrict__ out)
 {
-    if (skip && *skip) return;
     __shared__ double red[256];
     const int j = blockIdx.x;
     double s = 0.0;
@@ -430,9 +425,8 @@ void lambda_m_recover(Problem &p, const double *phi, bool with_load, double *lam
         T.b[0] = b0;
         T.a[1] = a1;
         T.b[1] = b1;
-        hipLaunchKernelGGL(k_dots_partial, dim3(RED_BLOCKS), dim3(256), 0, s, nm, k, T, part, (const int *)nullptr);
-        hipLaunchKernelGGL(k_reduce_partial, dim3(k), dim3(256), 0, s, RED_BLOCKS, k, part, red,
-                           (const int *)nullptr);
+        hipLaunchKernelGGL(k_dots_partial, dim3(RED_BLOCKS), dim3(256), 0, s, nm, k, T, part);
+        hipLaunchKernelGGL(k_reduce_partial, dim3(k), dim3(256), 0, s, RED_BLOCKS, k, part, red);
     };
     if (M.iw)
         hipLaunchKernelGGL(k_pack_trace, dim3(g), dim3(256), 0, s, nm, ldm, M.mvert, M.iw, p.d_tet, phi, xm);

@@ -42,8 +42,11 @@ static void *noalloc_base(int device)
 
 static size_t round256(size_t b) { return (b + 255) / 256 * 256; }
 
-// Work bytes of one residual: 4 element terms per tet, the packed surface inputs, and (when a surface is stored symmetric, which
-// is assumed here so that the bound holds before setup) its column partials.
+// Work bytes that a residual may have, the limit in pbfb.h: 8 bytes per FEM
+// node, 4 element terms per tet, the packed surface inputs, and the column
+// partials of the symmetric use (assumed here, so that the bound holds before
+// setup).  The node terms are added up in the pass that writes F and take no
+// memory any more; the limit is kept, so that what is refused does not change.
 size_t noalloc_residual_bytes(const Problem &p)
 {
     size_t b = round256(sizeof(double) * size_t(p.nn)) + round256(sizeof(double) * 4 * size_t(p.ntet));

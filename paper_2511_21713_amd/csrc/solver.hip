@@ -201,7 +201,7 @@ struct OmegaSearch {
     double tol, wmin, wmax, omega0;
     double pp; // p.p of this step
     // state
-    int phase, ev, done, fb, si;
+    int phase, ev, done, si;
     double w; // the point of the next evaluation (the element kernel reads it)
     double lo, hi, flo, wstart;
     double w0, f0, w1, f1;
@@ -210,16 +210,15 @@ struct OmegaSearch {
 };
 
 __device__ inline double om_clamp(const OmegaSearch &S, double w) { return fmin(S.wmax, fmax(S.wmin, w)); }
-__device__ inline void om_finish(OmegaSearch &S, double w, bool fallback)
+__device__ inline void om_finish(OmegaSearch &S, double w)
 {
     S.result = w;
-    S.fb = fallback ? 1 : S.fb;
     S.done = 1;
 }
 // Newton from w (the while condition of the iteration is checked first)
 __device__ inline void om_newton_start(OmegaSearch &S, double w)
 {
-    if (S.ev >= S.max_it) return om_finish(S, w, false);
+    if (S.ev >= S.max_it) return om_finish(S, w);
     S.phase = OM_NEWTON;
     S.w = w;
 }
@@ -376,20 +375,20 @@ __device__ inline void om_next(OmegaSearch &S, const double (&v)[6])
         dfd = -(-v[2] + v[3] - v[4]) / beta + a * (-v[5]) / (beta * beta) - 1.0;
     }
     ++S.ev;
-    if (!ok) return om_finish(S, 1.0, true);
+    if (!ok) return om_finish(S, 1.0);
     switch (S.phase) {
     case OM_NEWTON:
-        if (fabs(fd) < S.tol) om_finish(S, w, false);
-        else if (dfd == 0.0 || !isfinite(dfd)) om_finish(S, 1.0, true);
+        if (fabs(fd) < S.tol) om_finish(S, w);
+        else if (dfd == 0.0 || !isfinite(dfd)) om_finish(S, 1.0);
         else {
             const double wn = om_clamp(S, w - fd / dfd);
-            if (S.ev >= S.max_it) om_finish(S, wn, false);
+            if (S.ev >= S.max_it) om_finish(S, wn);
             else S.w = wn;
         }
         break;
     case OM_SEC_A:
         if (fabs(fd) < S.tol) {
-            om_finish(S, w, false);
+            om_finish(S, w);
         } else {
             S.f0 = fd;
             S.phase = OM_SEC_B;
@@ -401,7 +400,7 @@ __device__ inline void om_next(OmegaSearch &S, const double (&v)[6])
         if (fabs(S.f1) >= S.tol && S.ev < S.max_it) {
             const double slope = S.f0 - S.f1;
             if (slope == 0.0 || !isfinite(slope)) {
-                om_finish(S, 1.0, true);
+                om_finish(S, 1.0);
             } else {
                 const double w2 = om_clamp(S, S.w0 - (S.w0 - S.w1) * S.f0 / slope);
                 S.w0 = S.w1;
@@ -410,12 +409,12 @@ __device__ inline void om_next(OmegaSearch &S, const double (&v)[6])
                 S.w = w2;
             }
         } else {
-            om_finish(S, S.w1, false);
+            om_finish(S, S.w1);
         }
         break;
     case OM_BIS_LO:
         if (fabs(fd) < S.tol) {
-            om_finish(S, S.lo, false);
+            om_finish(S, S.lo);
         } else {
             S.flo = fd;
             S.phase = OM_BIS_HI;
@@ -423,9 +422,9 @@ __device__ inline void om_next(OmegaSearch &S, const double (&v)[6])
         }
         break;
     case OM_BIS_HI:
-        if (fabs(fd) < S.tol) om_finish(S, S.hi, false);
+        if (fabs(fd) < S.tol) om_finish(S, S.hi);
         else if ((S.flo > 0.0) == (fd > 0.0)) om_newton_start(S, S.wstart); // no sign change over the interval
-        else if (S.ev >= S.max_it) om_finish(S, 0.5 * (S.lo + S.hi), false);
+        else if (S.ev >= S.max_it) om_finish(S, 0.5 * (S.lo + S.hi));
         else {
             S.phase = OM_BIS_MID;
             S.w = 0.5 * (S.lo + S.hi);
@@ -433,7 +432,7 @@ __device__ inline void om_next(OmegaSearch &S, const double (&v)[6])
         break;
     case OM_BIS_MID:
         if (fabs(fd) < S.tol) {
-            om_finish(S, w, false);
+            om_finish(S, w);
         } else {
             if ((fd > 0.0) == (S.flo > 0.0)) {
                 S.lo = w;
@@ -442,7 +441,7 @@ __device__ inline void om_next(OmegaSearch &S, const double (&v)[6])
                 S.hi = w;
             }
             if (S.ev < S.max_it) S.w = 0.5 * (S.lo + S.hi);
-            else om_finish(S, w, false);
+            else om_finish(S, w);
         }
         break;
     case OM_BS_START:
@@ -466,10 +465,10 @@ __device__ inline void om_next(OmegaSearch &S, const double (&v)[6])
         om_bs_loop(S);
         break;
     case OM_DF:
-        if (fd == 1.0 || !isfinite(fd)) om_finish(S, 1.0, true);
-        else om_finish(S, om_clamp(S, 0.125 / (1.0 - fd)), false);
+        if (fd == 1.0 || !isfinite(fd)) om_finish(S, 1.0);
+        else om_finish(S, om_clamp(S, 0.125 / (1.0 - fd)));
         break;
-    default: om_finish(S, 1.0, true); break;
+    default: om_finish(S, 1.0); break;
     }
 }
 
@@ -632,7 +631,7 @@ static bool advance_impl(NewtonRun &r, hipStream_t s)
         r.d = scratch<double>(p, SCR_G7, n);
         r.D = scratch<double>(p, SCR_G8, n);
         r.pv = scratch<double>(p, SCR_G9, n);
-            double *t3 = scratch<double>(p, SCR_G11, 3 * nn);
+        double *t3 = scratch<double>(p, SCR_G11, 3 * nn);
         r.rN = t3;
         r.rJ = t3 + nn;
         r.rH = t3 + 2 * nn;
