@@ -43,6 +43,7 @@
 #include <cstring>
 #include <initializer_list>
 #include <thread>
+#include <utility>
 
 #include "gemv_rows.hpp"
 #include "pbfb_internal.hpp"
@@ -1031,11 +1032,14 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
     } drain{s};
     size_t cur = 0;
     bool same = true; // the lists are those of the previous call
+    // until the copy is enqueued the device copy holds none: an exception on
+    // the way leaves new lists in the stage alone
+    const size_t listed = std::exchange(BB.listed, 0);
     auto put = [&](const void *src, size_t b, bool list) {
         char *to = static_cast<char *>(BB.stage) + cur;
         if (!list) {
             std::memcpy(to, src, b);
-        } else if (!same || cur + b > BB.listed || std::memcmp(to, src, b)) {
+        } else if (!same || cur + b > listed || std::memcmp(to, src, b)) {
             same = false;
             std::memcpy(to, src, b);
         }
@@ -1060,8 +1064,7 @@ void batched_gmres(std::vector<GmresJob *> &jobs, hipStream_t s)
     WItem *dfirst = put_items({&wl_cheb, &wl_surf});
     WItem *dtiny = put_items({&wl_tiny});
     WItem *ddot = put_items({&wl_dot});
-    if (BB.listed != cur || BB.head != head) same = false;
-    BB.listed = 0; // until the copy is enqueued
+    if (listed != cur || BB.head != head) same = false;
     PB_HIP(hipMemcpyAsync(BB.dev, BB.stage, same ? head : cur, hipMemcpyHostToDevice, s));
     BB.listed = cur;
     BB.head = head;
