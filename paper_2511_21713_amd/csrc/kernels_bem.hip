@@ -20,7 +20,10 @@
 //     entries, and the launches run one after the other, so every entry
 //     receives its contributions in a fixed order.  Square shapes evaluate
 //     each unordered pair once and also add the double layer of the
-//     mirrored pair to an nv x nv matrix T (the only workspace);
+//     mirrored pair to an nv x nv matrix T in the context's workspace.  Small
+//     surfaces run every tile in one launch, each into entries of its own in
+//     planes over the blocks' local vertices, and a second one adds them up in
+//     the colour pairs' order (k_bem_gather; the same bits);
 //  2. square shapes: a transpose pass completes V' = U + U^T and K' += T^T
 //     (the regular part of V' bitwise symmetric);
 //  3. touching pairs (identical, common edge, common vertex) are integrated
@@ -668,45 +671,61 @@ __global__ void __launch_bounds__(256) k_bem_symm2(int64_t nv, int64_t ld, MT *_
 // Small surfaces (launch_slots): one launch holds every tile, each storing its
 // folded values to its own entries of three S x S planes over the blocks'
 // local vertices (K, V, mirrored K; block pairs A <= B in the order of the
-// colours only), and this adds up the operator's entries, both of a pair
-// (k, l) by one thread: over the local vertices a of k and b of l with
-// block(a) <= block(b), U(k, l) takes what the tile left at (a, b), and the
-// completion follows, V'(k, l) = U_V(k, l) + U_V(l, k), K'(k, l) = U_K(k, l) +
-// T(l, k).  A vertex's blocks are all of different colours, so walking them in
-// that order adds the tiles as the colour pairs' launches do, and every sum is
-// rounded to the storage as theirs: the two ways give the same bits, and which
-// one is taken may depend on the memory there is.  Two launches instead of one
-// per colour pair (28 to 36, 12-15 us each however few tiles they hold), the
-// completion and the clears: a 642-vertex surface 0.50 -> 0.116 ms (FP64),
-// 0.40 -> 0.074 (FP32); a 320-triangle solve 5.9 -> 5.0 ms, 1 280 triangles
-// mixed 14.5 -> 13.7.
+// colours only), and this adds them up for the completion above: U(k, l) and
+// T(k, l) take, over the local vertices a of k and b of l with block(a) <=
+// block(b), what the tile left at (a, b).  A vertex's blocks are all of
+// different colours, so walking them in that order adds the tiles as the colour
+// pairs' launches do, rounded to the storage after each: the two ways give the
+// same bits, and which one is taken may depend on the memory there is.  Three
+// launches instead of one per colour pair (28 to 36, 12-15 us each however few
+// tiles they hold), the completion and the clears: a 642-vertex surface 0.50 ->
+// 0.105 ms (FP64), 0.40 -> 0.067 (FP32); a 320-triangle solve 5.9 -> 5.0 ms,
+// 1 280 triangles mixed 14.5 -> 13.7.
+//
+// Bound by the latency of the plane reads and of the lists before them.  A
+// workgroup takes 256 columns of one row, so that its reads are rows of the
+// planes, whose lines the lanes share (1 212 vertices FP64 67 us and 15 of
+// completion, 1 692 FP32 82 and 17); a thread that adds up both entries of a
+// pair and completes them itself reads every second block by columns (137 and
+// 216 us).
 template <typename MT>
 __global__ void __launch_bounds__(256)
     k_bem_gather(int64_t nv, int64_t ld, int64_t S, const int32_t *__restrict__ occ_ptr,
-                 const int32_t *__restrict__ occ, const MT *__restrict__ W, MT *__restrict__ B)
+                 const int32_t *__restrict__ occ, const MT *__restrict__ W, MT *__restrict__ U, MT *__restrict__ T)
 {
+    struct Occ { // a local vertex and the place of its block in the order of the colours
+        int32_t at, rank;
+    };
+    const Occ *O = reinterpret_cast<const Occ *>(occ);
     const int64_t k = blockIdx.y, l = blockIdx.x * int64_t(256) + threadIdx.x;
     if (blockIdx.x == 0) // the row padding, read by the dense apply against zero inputs
-        for (int64_t c = 2 * nv + threadIdx.x; c < ld; c += 256) B[k * ld + c] = MT(0);
-    if (l < k || l >= nv) return;
-    const MT *K = W, *V = W + S * S, *T = W + 2 * S * S;
-    auto tiles = [&](int64_t r, int64_t c, MT (&u)[3]) { // U_V, U_K and T at (r, c)
-        u[0] = u[1] = u[2] = MT(0);
-        for (int32_t i = occ_ptr[r]; i < occ_ptr[r + 1]; ++i)
-            for (int32_t j = occ_ptr[c]; j < occ_ptr[c + 1]; ++j) {
-                if (occ[2 * i + 1] > occ[2 * j + 1]) continue;
-                const int64_t at = occ[2 * i] * S + occ[2 * j];
-                u[0] = MT(double(u[0]) + double(V[at]));
-                u[1] = MT(double(u[1]) + double(K[at]));
-                u[2] = MT(double(u[2]) + double(T[at]));
+        for (int64_t c = 2 * nv + threadIdx.x; c < ld; c += 256) U[k * ld + c] = MT(0);
+    if (l >= nv) return;
+    const int32_t j0 = occ_ptr[l], j1 = occ_ptr[l + 1];
+    MT u[3] = {}; // K, V, mirrored K
+    constexpr int N = 4; // local vertices of l read at a time
+    for (int32_t i = occ_ptr[k]; i < occ_ptr[k + 1]; ++i) {
+        const Occ a = O[i];
+        const MT *row = W + a.at * S;
+        for (int32_t j = j0; j < j1; j += N) {
+            bool take[N];
+            MT d[N][3];
+#pragma unroll
+            for (int t = 0; t < N; ++t) { // unconditional reads; past the end the last again
+                const Occ b = O[min(j + t, j1 - 1)];
+                take[t] = j + t < j1 && a.rank <= b.rank;
+#pragma unroll
+                for (int q = 0; q < 3; ++q) d[t][q] = row[q * S * S + b.at];
             }
-    };
-    MT u[3], w[3];
-    tiles(k, l, u);
-    tiles(l, k, w);
-    B[k * ld + nv + l] = B[l * ld + nv + k] = MT(double(u[0]) + double(w[0]));
-    B[k * ld + l] = MT(double(u[1]) + double(w[2]));
-    if (l != k) B[l * ld + k] = MT(double(w[1]) + double(u[2]));
+#pragma unroll
+            for (int t = 0; t < N; ++t)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) u[q] = take[t] ? MT(double(u[q]) + double(d[t][q])) : u[q];
+        }
+    }
+    U[k * ld + l] = u[0];
+    U[k * ld + nv + l] = u[1];
+    T[k * nv + l] = u[2];
 }
 
 // ---------------------------------------------------------------------------
@@ -1409,8 +1428,8 @@ static void launch_all_tiles(int shape, bool yuk, bool f32, RegArgs a, const Blo
 
 // Square 16 x 16 tiles of a small surface go through slots (k_bem_gather) if
 // the three planes fit in 192 MiB (to about 1 250 vertices FP64, 1 750 FP32:
-// some 2.3 local vertices per vertex).  Setup of both surfaces, colour pairs -> slots: 1 002 vertices FP64 1.88 ->
-// 1.10 ms, 1 442 FP32 1.84 -> 1.15; 2 562 vertices would still gain (3.95 ->
+// some 2.3 local vertices per vertex).  Setup of both surfaces, colour pairs ->
+// slots: 1 002 vertices FP64 1.88 -> 1.10 ms, 1 442 FP32 1.84 -> 1.15; 2 562 vertices would still gain (3.95 ->
 // 3.64 FP64, 2.85 -> 2.44 FP32) and 4 002 nothing, but the planes grow with
 // the square of the surface (0.8 GB FP64 at 2 562 vertices), and the context
 // keeps them in its workspaces.
@@ -1668,39 +1687,38 @@ void ensure_bem(Problem &p, int w, hipStream_t s)
     ra.sK = sK;
     // the context's assembly workspace: the mirrored double layer T of a
     // square-tile assembly (nv x nv in the storage precision), vertex
-    // coordinates and the touching-pair blocks.  A small surface has its planes
-    // in T's place if they may be allocated or the workspace has the room
-    // already; by colour pairs of the same tile shape the operator is the same
-    // bits
+    // coordinates and the touching-pair blocks; behind them the planes of a
+    // small surface if they may be allocated or the workspace has the room
+    // already (by colour pairs of the same tile shape the operator is the same
+    // bits)
     const size_t planes = slot_planes(p, w);
-    const size_t mirror = size_t(nv) * nv * elem;
     auto round256 = [](size_t b) { return (b + 255) / 256 * 256; };
-    // doubles of an assembly with t bytes in T's place
-    auto ws_doubles = [&](size_t t, const SurfaceTopo &V) {
-        return (round256(t) + 8 * (3 * size_t(V.nv) + 18 * V.tp_sig.size())) / 8 + 1;
+    // bytes of an assembly without planes
+    auto ws_pairs = [&](const SurfaceTopo &V) {
+        return round256(round256(size_t(V.nv) * V.nv * elem) + 8 * (3 * size_t(V.nv) + 18 * V.tp_sig.size()));
     };
-    bool slots = planes > 0 && (p.planes || wsp->bytes >= 8 * ws_doubles(planes, T));
+    bool slots = planes > 0 && (p.planes || wsp->bytes >= ws_pairs(T) + planes);
     double *ws = nullptr;
     if (slots) {
         // room for the planes of all the problem's surfaces, which are not of
         // one size: a workspace that grows frees its memory first, and that
         // waits for every stream
-        size_t want = 0;
-        for (int v = 0; v < NSURF; ++v)
-            if (v == w || (!p.bem_ready[v] && (v < 2 || p.gm() == 2) && slot_planes(p, v) > 0))
-                want = std::max(want, ws_doubles(slot_planes(p, v), p.topo[v]));
+        size_t want = ws_pairs(T) + planes;
+        for (int v = 0; v < NSURF && p.planes; ++v)
+            if (!p.bem_ready[v] && (v < 2 || p.gm() == 2) && slot_planes(p, v) > 0)
+                want = std::max(want, ws_pairs(p.topo[v]) + slot_planes(p, v));
         try {
-            ws = wsp->doubles(p.planes ? want : ws_doubles(planes, T));
+            ws = wsp->doubles(want / 8);
         } catch (const Error &e) {
             if (e.code != PBFB_ENOMEM) throw;
             (void)hipGetLastError(); // no room on the device: colour pairs
             slots = false;
         }
     }
-    if (!slots) ws = wsp->doubles(ws_doubles(mirror, T));
-    const size_t tbytes = round256(slots ? planes : mirror);
+    if (!slots) ws = wsp->doubles(ws_pairs(T) / 8);
     void *Tm = ws;
-    double *vx = reinterpret_cast<double *>(static_cast<char *>(Tm) + tbytes), *tpv = vx + 3 * nv;
+    double *vx = ws + round256(size_t(nv) * nv * elem) / 8, *tpv = vx + 3 * nv;
+    void *Wp = ws + ws_pairs(T) / 8; // the planes
     ra.T = Tm;
     // tile shape: forced, or tuned once per (precision, kernel, size class) and context
     int shape = planes > 0 ? SLOT_SHAPE : p.tile_fixed;
@@ -1726,22 +1744,23 @@ void ensure_bem(Problem &p, int w, hipStream_t s)
     if (sym && !slots) PB_HIP(hipMemsetAsync(Tm, 0, size_t(nv) * nv * elem, s));
     if (p.timing) p.timer.begin(T_ASM, s);
     if (slots) {
-        ra.U = Tm;
-        ra.T = static_cast<char *>(Tm) + planes / 3 * 2;
+        ra.U = Wp;
+        ra.T = static_cast<char *>(Wp) + planes / 3 * 2;
         launch_slots(yuk, f32, ra, s);
         const dim3 g(nblk(nv, 256), unsigned(nv));
         if (f32)
             hipLaunchKernelGGL(k_bem_gather<float>, g, dim3(256), 0, s, nv, ld, HA.S, ra.A.occ_ptr, ra.A.occ,
-                               static_cast<const float *>(Tm), static_cast<float *>(S.B));
+                               static_cast<const float *>(Wp), static_cast<float *>(S.B), static_cast<float *>(Tm));
         else
             hipLaunchKernelGGL(k_bem_gather<double>, g, dim3(256), 0, s, nv, ld, HA.S, ra.A.occ_ptr, ra.A.occ,
-                               static_cast<const double *>(Tm), static_cast<double *>(S.B));
+                               static_cast<const double *>(Wp), static_cast<double *>(S.B),
+                               static_cast<double *>(Tm));
     } else {
         launch_all_tiles(shape, yuk, f32, ra, HA, HB, s);
     }
     if (p.timing) p.timer.end(s);
     PB_HIP(hipGetLastError());
-    if (sym && !slots) {
+    if (sym) {
         const unsigned nbt = unsigned((nv + SYMT - 1) / SYMT);
         // FP32 storage with an even nv: pairs of entries, upper tile pairs only
         // (11.3 -> 7.7 ms per 80k-triangle interface); the same form ran FP64

@@ -31,7 +31,7 @@ int64_t bem_ld(int64_t nv);
 // while its dense operators are assembled: what it needs (the mirrored double
 // layer of a square-tile assembly, nv x nv in the storage precision, vertex
 // coordinates and touching-pair blocks) and what it takes where there is room
-// (the planes of a small surface's assembly instead of the mirrored double layer).
+// (also the planes of a small surface's assembly).
 void footprint_estimate(const Problem &p, int restart, size_t *steady, size_t *setup_need, size_t *setup_planes)
 {
     const size_t elem = p.precision == PBFB_MIXED ? 4 : 8;
@@ -49,10 +49,10 @@ void footprint_estimate(const Problem &p, int restart, size_t *steady, size_t *s
         dense += size_t(T.nv) * bem_ld(T.nv) * elem;
         dense += size_t(sym_partials_doubles(T.nv)) * 8 + size_t(T.nv) * 20 * 12; // symmetric use: partials, Delta
         dense += size_t(T.nt) * 18 * 8 * 2 + size_t(T.nv) * (8 * 8 + 16 * 4);  // Morton copies, block tables, rings
-        const size_t mirror = size_t(T.nv) * T.nv * elem, planes = std::max(mirror, slot_planes(p, w));
-        const size_t rest = size_t(T.nv) * 3 * 8 + T.tp_sig.size() * 18 * 8 + 64;
-        tmp = std::max(tmp, (mirror + 255) / 256 * 256 + rest);
-        tmp_planes = std::max(tmp_planes, (planes + 255) / 256 * 256 + rest);
+        const size_t need = (size_t(T.nv) * T.nv * elem + 255) / 256 * 256 + size_t(T.nv) * 3 * 8 +
+                            T.tp_sig.size() * 18 * 8 + 64;
+        tmp = std::max(tmp, need);
+        if (const size_t planes = slot_planes(p, w)) tmp_planes = std::max(tmp_planes, need + 256 + planes);
     }
     const size_t n = size_t(p.n());
     const size_t nnz_est = size_t(p.ntet) * 3 + size_t(p.nn) * 4; // generous: ~14 per row
