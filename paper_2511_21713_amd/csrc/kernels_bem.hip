@@ -1429,10 +1429,10 @@ static void launch_all_tiles(int shape, bool yuk, bool f32, RegArgs a, const Blo
 // Square 16 x 16 tiles of a small surface go through slots (k_bem_gather) if
 // the three planes fit in 192 MiB (to about 1 250 vertices FP64, 1 750 FP32:
 // some 2.3 local vertices per vertex).  Setup of both surfaces, colour pairs ->
-// slots: 1 002 vertices FP64 1.88 -> 1.10 ms, 1 442 FP32 1.84 -> 1.15; 2 562 vertices would still gain (3.95 ->
-// 3.64 FP64, 2.85 -> 2.44 FP32) and 4 002 nothing, but the planes grow with
-// the square of the surface (0.8 GB FP64 at 2 562 vertices), and the context
-// keeps them in its workspaces.
+// slots: 1 002 vertices FP64 1.88 -> 1.10 ms, 1 442 FP32 1.84 -> 1.15; 2 562
+// vertices would still gain (3.95 -> 3.64 FP64, 2.85 -> 2.44 FP32) and 4 002
+// nothing, but the planes grow with the square of the surface (0.8 GB FP64 at
+// 2 562 vertices), and the context keeps them in its workspaces.
 constexpr size_t SLOT_BYTES = size_t(192) << 20;
 constexpr int SLOT_SHAPE = 3;
 static_assert(TILE_SHAPES[SLOT_SHAPE].ta == SLOT_BS && TILE_SHAPES[SLOT_SHAPE].tb == SLOT_BS, "the symmetric 16 x 16 shape");
@@ -1697,16 +1697,16 @@ void ensure_bem(Problem &p, int w, hipStream_t s)
     auto ws_pairs = [&](const SurfaceTopo &V) {
         return round256(round256(size_t(V.nv) * V.nv * elem) + 8 * (3 * size_t(V.nv) + 18 * V.tp_sig.size()));
     };
-    bool slots = planes > 0 && (p.planes || wsp->bytes >= ws_pairs(T) + planes);
+    auto ws_slots = [&](int v) { return ws_pairs(p.topo[v]) + round256(slot_planes(p, v)); };
+    bool slots = planes > 0 && (p.planes || wsp->bytes >= ws_slots(w));
     double *ws = nullptr;
     if (slots) {
         // room for the planes of all the problem's surfaces, which are not of
         // one size: a workspace that grows frees its memory first, and that
         // waits for every stream
-        size_t want = ws_pairs(T) + planes;
+        size_t want = ws_slots(w);
         for (int v = 0; v < NSURF && p.planes; ++v)
-            if (!p.bem_ready[v] && (v < 2 || p.gm() == 2) && slot_planes(p, v) > 0)
-                want = std::max(want, ws_pairs(p.topo[v]) + slot_planes(p, v));
+            if (!p.bem_ready[v] && (v < 2 || p.gm() == 2) && slot_planes(p, v) > 0) want = std::max(want, ws_slots(v));
         try {
             ws = wsp->doubles(want / 8);
         } catch (const Error &e) {

@@ -52,7 +52,7 @@ void footprint_estimate(const Problem &p, int restart, size_t *steady, size_t *s
         const size_t need = (size_t(T.nv) * T.nv * elem + 255) / 256 * 256 + size_t(T.nv) * 3 * 8 +
                             T.tp_sig.size() * 18 * 8 + 64;
         tmp = std::max(tmp, need);
-        if (const size_t planes = slot_planes(p, w)) tmp_planes = std::max(tmp_planes, need + 256 + planes);
+        if (const size_t planes = slot_planes(p, w)) tmp_planes = std::max(tmp_planes, need + 512 + planes);
     }
     const size_t n = size_t(p.n());
     const size_t nnz_est = size_t(p.ntet) * 3 + size_t(p.nn) * 4; // generous: ~14 per row
