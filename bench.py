@@ -32,17 +32,17 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 
-# HBM bytes per dense apply (k_bgemv, and the second stage measured while it
-# was a launch of its own; both interfaces) at the
+# HBM bytes per dense apply (k_bgemv and the second stage in k_btail, which
+# kernel timing launches by itself; both interfaces) at the
 # 80k-triangle size from two rocprofv3 --pmc runs (FETCH_SIZE x 2: the
 # counter reads 0.5 x the bytes of a plain device copy; WRITE_SIZE x 1), valid
 # for the row routines whose source hash is recorded with them; see
 # profiles/gemv_rna80k_hbm_counters.md.
 GEMV_TRAFFIC = {
     "rna80k_f32": {"src_sha256_16": "63b4d5ac2bbe4a09",
-                   "bytes": 9868495.89 * 2048 + 207680.13 * 1024 + 157896.09 * 2048 + 1235.06 * 1024},
+                   "bytes": 9868515.03 * 2048 + 207676.37 * 1024 + 157901.60 * 2048 + 1234.80 * 1024},
     "rna80k_f64": {"src_sha256_16": "63b4d5ac2bbe4a09",
-                   "bytes": 19708652.32 * 2048 + 210785.92 * 1024 + 157896.09 * 2048 + 1235.06 * 1024},
+                   "bytes": 19708653.76 * 2048 + 210765.34 * 1024 + 157925.30 * 2048 + 1236.30 * 1024},
 }
 
 

@@ -76,9 +76,9 @@ const char *pbfb_last_error(void);
 /* precision PBFB_FP64: every operator evaluated, stored and applied in FP64.
  * PBFB_MIXED: the regular (non-touching) boundary-element quadrature is
  * evaluated in FP32 (point offsets from FP64 triangle centroids, FP32 kernel
- * values and per-pair sums over the 36 quadrature pairs), folded onto the
- * vertices in FP64; dense
- * boundary operators and FEM matrix values are stored in FP32 (rounded once
+ * values, per-pair sums over the 36 quadrature pairs and corner sums onto a
+ * tile's vertices), each tile's sums added to the stored entries in FP64;
+ * dense boundary operators and FEM matrix values are stored in FP32 (rounded
  * from their FP64 sums) and every product is accumulated in FP64.  Krylov
  * vectors (unless krylov_fp32), Newton update, relaxation search,
  * orthogonalisation and touching-panel integrals stay FP64. */
@@ -295,8 +295,8 @@ pbfb_status pbfb_get_tile_shape(const pbfb_problem *p, int surf, int *ta, int *t
 /* PBFB_BEM_DENSE (default): the four Galerkin blocks are assembled once per
  * setup and stored (n x 2n per interface, FP64 or FP32), every apply is a
  * dense GEMV.  PBFB_BEM_MATRIX_FREE: nothing dense is stored; every apply
- * evaluates the regular quadrature-point pairs on the fly (about 36 N_t^2
- * kernel evaluations per interface) and adds the touching-pair blocks and
+ * evaluates the regular quadrature-point pairs on the fly (each unordered
+ * pair once, about 18 N_t^2 kernel evaluations per interface) and adds the touching-pair blocks and
  * 1/2 M kept from setup: for instances whose dense blocks would not fit
  * (the paper switches to a fast multipole method above 90k vertices for the
  * same reason).  The 1-ring approximate inverse of the single layers (the

@@ -6,9 +6,9 @@
 // kernel below takes a packed work list that covers every instance, so one
 // launch per step serves the whole batch whatever the mesh sizes.  The Krylov
 // scalars (Hessenberg column, rotations, residual estimate, restart and
-// convergence decisions, triangular solve) live on the device in one thread
-// per instance, so the host only enqueues iterations and polls a completion
-// counter asynchronously; nothing waits on the host between iterations.
+// convergence decisions, triangular solve) live on the device in one wavefront
+// per instance, so the host only enqueues steps, two ahead of a progress word
+// in pinned memory; nothing waits on the host between steps.
 //
 // Per-instance state machine (P^-1 the right preconditioner):
 //   INIT  -> w = b, V_0 = b/|b|, target = tol |b|              -> ARN (or DONE if b = 0)
