@@ -248,7 +248,8 @@ pbfb_status pbfb_solve_batch(pbfb_ctx *ctx, int n, pbfb_problem *const *probs, c
  * request from admission to completion, plus the context's assembly
  * workspace (shared by the context's problems, grown to the largest
  * assembly it has served and kept; what the requests do not need of it is
- * given back when one would wait for the room).  A completed request's device memory is
+ * given back when one would wait for the room).  A completed request's
+ * device memory is
  * released (the problem keeps its mesh, charges and parameters; a later call
  * on it sets it up again), so a finished request holds no budget.  ENOMEM at
  * submit: the request alone exceeds the budget; otherwise a request that does
@@ -296,7 +297,8 @@ pbfb_status pbfb_get_tile_shape(const pbfb_problem *p, int surf, int *ta, int *t
  * setup and stored (n x 2n per interface, FP64 or FP32), every apply is a
  * dense GEMV.  PBFB_BEM_MATRIX_FREE: nothing dense is stored; every apply
  * evaluates the regular quadrature-point pairs on the fly (each unordered
- * pair once, about 18 N_t^2 kernel evaluations per interface) and adds the touching-pair blocks and
+ * pair once, about 18 N_t^2 kernel evaluations per interface) and adds the
+ * touching-pair blocks and
  * 1/2 M kept from setup: for instances whose dense blocks would not fit
  * (the paper switches to a fast multipole method above 90k vertices for the
  * same reason).  The 1-ring approximate inverse of the single layers (the

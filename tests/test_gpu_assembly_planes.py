@@ -148,7 +148,7 @@ def test_planes_keep_no_request_waiting(kept, room):
     print(f"  first: setup {first['t_setup_s']:.3f} s, solve {first['t_solve_s']:.3f}; second waited "
           f"{second['t_wait_s']:.3f}", flush=True)
     assert first["status"] == 0 and first["total"] == second["total"]
-    assert second["t_wait_s"] < 0.5 * first["t_solve_s"]
+    assert second["t_wait_s"] < first["t_setup_s"] + 0.5 * first["t_solve_s"]
     for g in gs:
         g.close()
     ctx.close()
